@@ -223,9 +223,9 @@ int finish_partition(pop_layer *L, int T, int n_ret, int n_cand, float *scores, 
     PartitionExtra ex;
     const bool from_partials = !scores_ready && partition_takes_partials(m);
     if (!scores_ready && !from_partials)
-        POP_HIP(launch_scores_from_partials(L->s2_part, prefill_rows_used(T, L->is_bf16, m, L->n_cu), m, L->nrm, L->scores, s));
+        POP_HIP(launch_scores_from_partials(L->s2_part, prefill_rows_used(T, L->is_bf16, L->d, m, L->n_cu), m, L->nrm, L->scores, s));
     if (from_partials) {
-        ex.s2_part = L->s2_part, ex.n_tiles = prefill_rows_used(T, L->is_bf16, m, L->n_cu), ex.nrm = L->nrm;
+        ex.s2_part = L->s2_part, ex.n_tiles = prefill_rows_used(T, L->is_bf16, L->d, m, L->n_cu), ex.nrm = L->nrm;
         ex.scores_out = L->scores;
     }
     ex.sync = L->sync, ex.n_sync = 16;
@@ -489,7 +489,7 @@ int pop_prefill_partition(pop_layer_t *L, const void *x, int T, int n_ret, int n
         POP_HIP(launch_prefill_gateup(L->w, L->is_bf16, L->d, m, x, T, L->s2_part, L->n_cu, s, &fin));
     }
     return finish_partition(L, T, n_ret, n_cand, scores, region, ret_idx, cand_idx, s,
-                            T == 0 || L->input_side || prefill_forms_scores(L->is_bf16, T, m, L->n_cu));
+                            T == 0 || L->input_side || prefill_forms_scores(L->is_bf16, T, L->d, m, L->n_cu));
 }
 
 int pop_prefill_forward(pop_layer_t *L, const void *x, int T, int n_ret, int n_cand, int k0, void *y, pop_dtype_t ydtype,
@@ -544,7 +544,7 @@ int pop_prefill_forward(pop_layer_t *L, const void *x, int T, int n_ret, int n_c
     }
     {
         int rc = finish_partition(L, T, n_ret, n_cand, scores, region, ret_idx, cand_idx, s,
-                                  T == 0 || L->input_side || prefill_forms_scores(L->is_bf16, T, m, L->n_cu), n_ret + k0, mask || !keep, keep ? &gather : nullptr);
+                                  T == 0 || L->input_side || prefill_forms_scores(L->is_bf16, T, L->d, m, L->n_cu), n_ret + k0, mask || !keep, keep ? &gather : nullptr);
         if (rc != POP_OK) return rc;
     }
     unsigned char *pm = L->ffn_any;

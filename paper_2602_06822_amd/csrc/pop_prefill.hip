@@ -2,24 +2,19 @@
 // importance reduction  s2[j] = sum_t H[t][j]^2  (Sec. 3.3 "Prefilling Stage"; Eq. 3: activation norm over
 // tokens and samples).  In its plain form H is never written to memory.
 //
-// bf16: MFMA 32x32x16 tiles.  A workgroup owns BM tokens (256 with 8 waves, 4 along the tokens x 2 along the B rows;
-// 128 with 4 waves for short prompts) and a chunk of up to 96 channels, i.e. up to 192 rows of the B operand (gate
-// and up rows of the channel-major blocks w[j] = [gate row | up row | down column]); a wave owns 64 tokens x 48
-// channels = 96 B rows.  The 96 B rows of a wave are three fragments: gate of its channels 0..31, up of the same
-// channels (same lane and register slot in the two accumulators, so silu(g)*u needs no exchange), and a mixed
-// fragment [gate 32..47 | up 32..47] whose halves meet through one cross-lane move in the epilogue.  A second
-// tile form drops the mixed fragment (64 channels per chunk, 64 B rows per wave).  The chunk size is chosen so
-// that the tiles divide evenly over the compute units (one or a whole number of tiles each).  Each accumulator
-// lane holds 16 token rows of one channel column, so the token reduction is in-register adds, one cross-half
-// shuffle and an LDS combine of the token waves.  Token tiles write separate partial rows that are summed in
-// tile order.  Operand rows that are whole k-steps long (d a multiple of 64) go from global memory straight into LDS
-// (global_load_lds, 1 KB = 8 unpadded rows per wave instruction, 16-byte units XOR-swizzled by row pair so that the
-// fragment reads stay conflict-free); fetching them through registers costs a quarter more time even when every load
-// hits the cache, and remains the path for other row lengths.  On the direct path every wave issues the same loads
-// in every k-step (rows that do not exist are pointed at one that does and left out by the epilogue), so a step waits
-// with an exact count for its own rows only, and the 128-token tile runs a ring of three LDS buffers: short prompts
-// are bound by the weight stream from memory, where two k-steps in flight carry twice the bytes of one.
-// Two more forms of the same kernel serve the forward pass of a whole prompt under the pruning structure
+// bf16: matrix-core tiles.  Rows that are whole k-steps long (d a multiple of 64) run prefill_mma_kernel, described
+// there; other row lengths are staged through registers (prefill_bf16_kernel): a workgroup owns BM tokens (256 with 8
+// waves, 4 along the tokens x 2 along the B rows; 128 with 4 waves for short prompts) and a chunk of up to 96 channels,
+// i.e. up to 192 rows of the B operand (gate and up rows of the channel-major blocks w[j] = [gate row | up row | down
+// column]); a wave owns 64 tokens x 48 channels = 96 B rows.  The 96 B rows of a wave are three fragments of 32x32x16
+// products: gate of its channels 0..31, up of the same channels (same lane and register slot in the two accumulators,
+// so silu(g)*u needs no exchange), and a mixed fragment [gate 32..47 | up 32..47] whose halves meet through one
+// cross-lane move in the epilogue.  A second tile form drops the mixed fragment (64 channels per chunk, 64 B rows per
+// wave).  The chunk size is chosen so that the tiles divide evenly over the compute units (one or a whole number of
+// tiles each).  Either way an accumulator lane holds several token rows of one channel column, so the token reduction
+// is in-register adds, cross-lane adds and an LDS combine of the token waves.  Token tiles write separate partial rows
+// that are summed in tile order.
+// Two more forms of the same kernels serve the forward pass of a whole prompt under the pruning structure
 // (Sec. 3.4): one also writes H (rounded to bf16) as [T][m]; one runs its chunks over a device-resident list of
 // active channels instead of all m and writes H (optionally times a per-token mask) in compact form
 // [T][list position] for the down projection instead of reducing its squares.
@@ -33,7 +28,7 @@ namespace pop {
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 
-constexpr int kPfBMmin = 128;     // smallest token tile (sizes the partial-row buffer)
+constexpr int kPfBMmin = 64;      // smallest token tile (sizes the partial-row buffer)
 constexpr int kPfChunk = 96;      // channels per workgroup tile at most
 constexpr int kPfBK = 64;         // k elements per stage
 constexpr int kPfLd = kPfBK + 8;  // padded LDS row stride in elements (144 B): conflict-free 16-byte reads
@@ -122,9 +117,47 @@ struct PfStore {
     float *scores = nullptr;    // [m]
 };
 
+// The tile's partial row from its waves' column sums and, where asked for, the chunk's scores.
+template <int TW>
+__device__ __forceinline__ void pf_chunk_scores(const float (&colsum)[TW][kPfChunk], int m, int n_ttiles, int ttile,
+                                                int ctile, int c0, int cn, float *__restrict__ s2_part, const PfStore &st)
+{
+    const int tid = threadIdx.x;
+    __syncthreads();
+    if (tid < cn) {
+        float tot = 0.f;
+#pragma unroll
+        for (int q = 0; q < TW; ++q) tot += colsum[q][tid];
+        if (st.fin_ctr)
+            coherent_store(&s2_part[(size_t)ttile * m + c0 + tid], tot);
+        else
+            s2_part[(size_t)ttile * m + c0 + tid] = tot;
+    }
+    if (st.fin_ctr) {
+        // Scores of this chunk's channels (Eq. 3): I_j = n_j * sqrt(sum over the token tiles, in tile order and in
+        // double, of the partial sums).  The partial rows are written through and read with device-coherent loads;
+        // a tile counts itself in once its own row has been acknowledged, and the tile that completes the count does
+        // the sum and puts the counter back to zero for the next launch.  Nobody waits for anybody.
+        __shared__ int fin_last;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        if (tid == 0) {
+            const bool last = atomicAdd(&st.fin_ctr[ctile], 1) == n_ttiles - 1;
+            if (last) coherent_store(&st.fin_ctr[ctile], 0);
+            fin_last = last;
+        }
+        __syncthreads();
+        if (fin_last && tid < cn) {
+            double acc = 0.0;
+            for (int t = 0; t < n_ttiles; ++t) acc += (double)coherent_load(&s2_part[(size_t)t * m + c0 + tid]);
+            st.scores[c0 + tid] = (float)((double)st.nrm[c0 + tid] * sqrt(acc));
+        }
+    }
+}
+
 // kMode 0: scores only (s2_part).  1: channels from st.list, H stored compact (no s2_part).  2: all m channels,
 // s2_part and H stored as [T][m padded].
-template <int BM, int NW, int NF, int kMode, bool kDma = false, int NS = 2>
+template <int BM, int NW, int NF, int kMode>
 __global__ __launch_bounds__(NW * 64) void prefill_bf16_kernel(const uint16_t *__restrict__ w,
                                                            const uint16_t *__restrict__ x, int T, int d, int m,
                                                            int n_ttiles, int chunk, int n_items, int per_xcd,
@@ -135,13 +168,10 @@ __global__ __launch_bounds__(NW * 64) void prefill_bf16_kernel(const uint16_t *_
     constexpr int RP = NW * 8;          // rows one staging pass of the workgroup covers
     constexpr int BR = NF * 64;         // B rows of the workgroup tile
     constexpr int WC = NF * 16;         // channels per wave
-    // LDS rows: 64 elements padded to 72 (register staging), or exactly 64 with the 16-byte units of row r stored
-    // at unit ^ ((r / 2) % 8) (direct global -> LDS loads, which fill 1 KB = 8 whole rows per wave instruction)
-    constexpr int LD = kDma ? kPfBK : kPfLd;
+    constexpr int LD = kPfLd;           // LDS rows: 64 elements padded to 72
     extern __shared__ __attribute__((aligned(16))) uint16_t pf_lds[];
-    static_assert(kDma || NS == 2, "the register-staged path has two LDS buffers");
-    uint16_t *As = pf_lds;                    // [NS][BM * LD]
-    uint16_t *Bs = pf_lds + NS * BM * LD;     // [NS][BR * LD]
+    uint16_t *As = pf_lds;                    // [2][BM * LD]
+    uint16_t *Bs = pf_lds + 2 * BM * LD;      // [2][BR * LD]
     __shared__ float colsum[TW][kPfChunk];
 
     constexpr bool kList = kMode == 1, kStore = kMode != 0;
@@ -167,25 +197,21 @@ __global__ __launch_bounds__(NW * 64) void prefill_bf16_kernel(const uint16_t *_
     constexpr int PA = BM / RP, PB = BR / RP;
     static_assert(BM % RP == 0 && BR % RP == 0, "whole staging passes");
     uint4 ra[PA], rb[PB];
-    // Row starts.  Register-staged path: null for a row of zeros (tokens beyond T, channels beyond the chunk).  Direct
-    // path: such rows are pointed at a row that exists instead, so that every wave issues the same number of loads per
-    // k-step (its waits count them); what they produce is left out by the epilogue.
+    // row starts; null for a row of zeros (tokens beyond T, channels beyond the chunk)
     const uint16_t *pa[PA], *pb[PB];
 #pragma unroll
     for (int p = 0; p < PA; ++p) {
         const int t = t0 + ld_row + p * RP;
-        pa[p] = kDma ? x + (size_t)min(t, T - 1) * d : (t < T ? x + (size_t)t * d : nullptr);
+        pa[p] = t < T ? x + (size_t)t * d : nullptr;
     }
 #pragma unroll
     for (int p = 0; p < PB; ++p) {
         int ch, which;
         pf_row_channel<NF>(ld_row + p * RP, ch, which);
-        if (ch < cn || kDma) {
-            const int cc = min(ch, cn - 1);
-            const int j = kList ? st.list[c0 + cc] : c0 + cc;
+        pb[p] = nullptr;
+        if (ch < cn) {
+            const int j = kList ? st.list[c0 + ch] : c0 + ch;
             pb[p] = w + ((size_t)j * 3 + which) * d;
-        } else {
-            pb[p] = nullptr;
         }
     }
     auto load_global = [&](int k0) {
@@ -206,23 +232,6 @@ __global__ __launch_bounds__(NW * 64) void prefill_bf16_kernel(const uint16_t *_
         for (int p = 0; p < PB; ++p)
             *reinterpret_cast<uint4 *>(&Bs[(buf * BR + ld_row + p * RP) * LD + ld_kv * 8]) = rb[p];
     };
-    // direct loads: this lane's 16 bytes land at LDS unit ld_kv of row ld_row of the pass, so it fetches the k-vector
-    // that belongs there under the swizzle
-    const int wave_u = __builtin_amdgcn_readfirstlane(wave);
-    const int src_kv = (ld_kv ^ ((ld_row / 2) % 8)) * 8;  // (passes are RP rows apart, a multiple of 16: same swizzle term)
-    auto dma_load = [&](int buf, int k0) {
-        typedef __attribute__((address_space(3))) void lds_t;
-        typedef __attribute__((address_space(1))) const void glb_t;
-#pragma unroll
-        for (int p = 0; p < PA; ++p)
-            __builtin_amdgcn_global_load_lds((glb_t *)(pa[p] + k0 + src_kv),
-                                             (lds_t *)(As + (buf * BM + p * RP + wave_u * 8) * LD), 16, 0, 0);
-#pragma unroll
-        for (int p = 0; p < PB; ++p)
-            __builtin_amdgcn_global_load_lds((glb_t *)(pb[p] + k0 + src_kv),
-                                             (lds_t *)(Bs + (buf * BR + p * RP + wave_u * 8) * LD), 16, 0, 0);
-    };
-
     f32x16_t acc[MT][NF];  // [token fragment][0 = gate 0..31, 1 = up 0..31, 2 = gate 32..47 | up 32..47]
 #pragma unroll
     for (int a = 0; a < MT; ++a)
@@ -233,21 +242,17 @@ __global__ __launch_bounds__(NW * 64) void prefill_bf16_kernel(const uint16_t *_
 
     const int n_k = (d + kPfBK - 1) / kPfBK;
     const int arow = wm * (BM / TW) + (lane % 32), brow = wn * (NF * 32) + (lane % 32), koff = (lane / 32) * 8;
-    const int a_sw = (arow / 2) % 8, b_sw = (brow / 2) % 8;  // (fragments are 32 rows apart: same swizzle term)
     auto multiply = [&](int buf) {
-        const uint16_t *Ab = As + (buf * BM + arow) * LD + (kDma ? 0 : koff);
-        const uint16_t *Bb = Bs + (buf * BR + brow) * LD + (kDma ? 0 : koff);
+        const uint16_t *Ab = As + (buf * BM + arow) * LD + koff;
+        const uint16_t *Bb = Bs + (buf * BR + brow) * LD + koff;
         // the fragments of k-slice q + 1 are requested before the products of slice q are issued (two register
         // sets), so that their LDS latency runs under the matrix pipe
         bf16x8_t bf[2][NF], af[2][MT];
         auto fetch = [&](int q, int set) {
-            // element offset of this lane's 8 k-values within its row
-            const int ka = kDma ? (((q * 2 + lane / 32) ^ a_sw) * 8) : q * 16;
-            const int kb = kDma ? (((q * 2 + lane / 32) ^ b_sw) * 8) : q * 16;
 #pragma unroll
-            for (int f = 0; f < NF; ++f) bf[set][f] = *reinterpret_cast<const bf16x8_t *>(Bb + f * 32 * LD + kb);
+            for (int f = 0; f < NF; ++f) bf[set][f] = *reinterpret_cast<const bf16x8_t *>(Bb + f * 32 * LD + q * 16);
 #pragma unroll
-            for (int a = 0; a < MT; ++a) af[set][a] = *reinterpret_cast<const bf16x8_t *>(Ab + a * 32 * LD + ka);
+            for (int a = 0; a < MT; ++a) af[set][a] = *reinterpret_cast<const bf16x8_t *>(Ab + a * 32 * LD + q * 16);
         };
         fetch(0, 0);
 #pragma unroll
@@ -262,43 +267,20 @@ __global__ __launch_bounds__(NW * 64) void prefill_bf16_kernel(const uint16_t *_
             __builtin_amdgcn_sched_barrier(0);
         }
     };
-    if (kDma) {
-        // (needs d % 64 == 0.)  A ring of NS LDS buffers: step ks multiplies buffer ks % NS while the rows of steps
-        // ks + 1 .. ks + NS - 1 are landing in or on their way to the others.  Per step: wait until this wave's loads
-        // of step ks have landed (all but the (NS - 2) (PA + PB) younger ones), meet the other waves (now everybody's
-        // have, and everybody is done reading the buffer of step ks - 1), request step ks + NS - 1 into that buffer,
-        // multiply.  Steps beyond the last are requested again from the last step's columns, so the count holds.
-        constexpr int kYounger = (NS - 2) * (PA + PB);
-        static_assert(kYounger < 64, "vmcnt is a 6-bit counter");
-        // s_waitcnt with only the vector-memory counter set: vmcnt[3:0] | expcnt 7 << 4 | lgkmcnt 15 << 8 | vmcnt[5:4] << 14
-        constexpr int kWaitImm = (kYounger & 15) | (7 << 4) | (15 << 8) | ((kYounger >> 4) << 14);
-#pragma unroll
-        for (int q = 0; q < NS - 1; ++q) dma_load(q, min(q, n_k - 1) * kPfBK);
-        for (int ks = 0; ks < n_k; ++ks) {
-            __builtin_amdgcn_s_waitcnt(kWaitImm);
-            asm volatile("s_barrier" ::: "memory");  // (no fence: a fence would wait for the younger loads too)
-            dma_load((ks + NS - 1) % NS, min(ks + NS - 1, n_k - 1) * kPfBK);
-            multiply(ks % NS);
-        }
-        __builtin_amdgcn_s_waitcnt((0 & 15) | (7 << 4) | (15 << 8));  // the surplus requests, before LDS is reused
+    // step ks multiplies LDS buffer ks % 2 while the rows of step ks + 1 are on their way through registers
+    load_global(0);
+    store_lds(0);
+    __syncthreads();
+    for (int ks = 0; ks < n_k; ++ks) {
+        const int buf = ks & 1;
+        if (ks + 1 < n_k) load_global((ks + 1) * kPfBK);
+        multiply(buf);
+        if (ks + 1 < n_k) store_lds(buf ^ 1);
         __syncthreads();
-    } else {
-        // step ks multiplies LDS buffer ks % 2 while the rows of step ks + 1 are on their way through registers
-        load_global(0);
-        store_lds(0);
-        __syncthreads();
-        for (int ks = 0; ks < n_k; ++ks) {
-            const int buf = ks & 1;
-            if (ks + 1 < n_k) load_global((ks + 1) * kPfBK);
-            multiply(buf);
-            if (ks + 1 < n_k) store_lds(buf ^ 1);
-            __syncthreads();
-        }
     }
 
-    // epilogue: lane holds 16 * MT token rows of column (lane % 32) of each fragment.  Register-staged path: rows of
-    // padded tokens and columns of padded channels are exactly 0.  Direct path: they hold products of the rows their
-    // loads were pointed at; padded tokens are left out of the sums below, padded channels are never written.
+    // epilogue: lane holds 16 * MT token rows of column (lane % 32) of each fragment; rows of padded tokens and columns
+    // of padded channels are exactly 0
     // H of the tile (modes 1 and 2), written after the partial sums have gone out: the tile's arrival is counted once
     // its partial row is acknowledged, and that wait should not take in the much larger H.
     auto store_h = [&]() {
@@ -338,57 +320,347 @@ __global__ __launch_bounds__(NW * 64) void prefill_bf16_kernel(const uint16_t *_
         return;
     }
     float ss01 = 0.f, ss2 = 0.f;
-    const int t_left = T - (t0 + wm * (BM / TW) + (lane / 32) * 4);  // this lane's rows below t_left are tokens
 #pragma unroll
     for (int a = 0; a < MT; ++a)
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
-            const bool live = !kDma || a * 32 + (v / 4) * 8 + v % 4 < t_left;
             const float hv = silu_mul_tile(acc[a][0][v], acc[a][1][v]);
-            ss01 = fmaf(hv, live ? hv : 0.f, ss01);
+            ss01 = fmaf(hv, hv, ss01);
             if (NF == 3) {
                 // mixed fragment: the up value of column c < 16 sits in lane c + 16, same register
                 const float g2 = acc[a][NF - 1][v];
                 const float u2 = __shfl_xor(g2, 16, kWave);
                 const float h2 = silu_mul_tile(g2, u2);
-                ss2 = fmaf(h2, live ? h2 : 0.f, ss2);
+                ss2 = fmaf(h2, h2, ss2);
             }
         }
     ss01 += __shfl_xor(ss01, 32, kWave);
     ss2 += __shfl_xor(ss2, 32, kWave);
     if (lane < 32) colsum[wm][wn * WC + lane] = ss01;
     if (NF == 3 && lane < 16) colsum[wm][wn * WC + 32 + lane] = ss2;
-    __syncthreads();
-    if (tid < cn) {
-        float tot = 0.f;
-#pragma unroll
-        for (int q = 0; q < TW; ++q) tot += colsum[q][tid];
-        if (st.fin_ctr)
-            coherent_store(&s2_part[(size_t)ttile * m + c0 + tid], tot);
-        else
-            s2_part[(size_t)ttile * m + c0 + tid] = tot;
-    }
-    if (st.fin_ctr) {
-        // Scores of this chunk's channels (Eq. 3): I_j = n_j * sqrt(sum over the token tiles, in tile order and in
-        // double, of the partial sums).  The partial rows are written through and read with device-coherent loads;
-        // a tile counts itself in once its own row has been acknowledged, and the tile that completes the count does
-        // the sum and puts the counter back to zero for the next launch.  Nobody waits for anybody.
-        __shared__ int fin_last;
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();
-        if (tid == 0) {
-            const bool last = atomicAdd(&st.fin_ctr[ctile], 1) == n_ttiles - 1;
-            if (last) coherent_store(&st.fin_ctr[ctile], 0);
-            fin_last = last;
-        }
-        __syncthreads();
-        if (fin_last && tid < cn) {
-            double acc = 0.0;
-            for (int t = 0; t < n_ttiles; ++t) acc += (double)coherent_load(&s2_part[(size_t)t * m + c0 + tid]);
-            st.scores[c0 + tid] = (float)((double)st.nrm[c0 + tid] * sqrt(acc));
-        }
-    }
+    pf_chunk_scores<TW>(colsum, m, n_ttiles, ttile, ctile, c0, cn, s2_part, st);
     if (kStore) store_h();
+}
+
+// ---- rows that are whole k-steps long (d a multiple of 64): the direct-load kernel
+//
+// A tile is 64 MF tokens x 8 F channels (16 F rows of the B operand); four waves, 16 MF tokens each.  F comes from a
+// short ladder and MF is 1..5, so that ragged prompts and channel counts waste little: a tile's last rows are padding.
+constexpr int kPmThreads = 256;
+constexpr int kPmMaxMF = 5;
+constexpr int kPmMaxF = 12;
+// LDS ring depths (k-steps of 64 elements): token rows, which mostly come from L2, and weight rows, which come from
+// memory; as deep as 160 KB allow with F = 12.
+template <int MF>
+struct PmRing {
+    static constexpr int NA = MF >= 4 ? 2 : (MF >= 2 ? 3 : 4);
+    static constexpr int NB = MF >= 3 ? 3 : (MF == 2 ? 4 : 5);
+    static constexpr size_t kBytes = (size_t)(NA * 64 * MF + NB * 16 * kPmMaxF) * kPfBK * sizeof(uint16_t);
+};
+
+// Channel (relative to the chunk) and matrix (0 gate, 1 up) of B row r: fragments of 16 rows go in pairs, the gate rows
+// of 16 channels and the up rows of the same; an odd last fragment is [gate of 8 channels | up of the same 8].
+template <int F>
+__device__ __forceinline__ void pm_row_channel(int r, int &ch, int &which)
+{
+    const int f = r / 16, c = r % 16;
+    if (F % 2 && f >= F - 1) {
+        ch = 8 * (F - 1) + c % 8, which = c / 8;
+    } else {
+        ch = f / 2 * 16 + c, which = f % 2;
+    }
+}
+
+// Tiles of one launch: F and the counts that follow.  Shared by host and device (the list form learns its channel
+// count on the device).
+struct PmTiles {
+    int f, n_ct, total, per_xcd;
+};
+// Relative time of a tile on its compute unit, per 32 elements of the contraction, in cycles: its products (16 cycles
+// each on one matrix pipe) and the LDS and L2 traffic next to them, or the memory time of its weight rows where few
+// token tiles share them.
+__host__ __device__ inline int pm_tile_cost(int mf, int f, int n_tt)
+{
+    const int work = 16 * mf * f + 8 * (4 * mf + f) + 60, mem = 100 * f / n_tt;
+    return work > mem ? work : mem;
+}
+__host__ __device__ inline PmTiles pm_tiles(int n_ch, int n_tt, int mf, int n_cu, int *cost = nullptr)
+{
+    PmTiles best{kPmMaxF, 0, 0, 0};
+    int best_cost = 0;
+    const int ladder[7] = {12, 11, 10, 8, 7, 6, 4};
+    for (int i = 0; i < 7; ++i) {
+        const int f = ladder[i], n_ct = (n_ch + 8 * f - 1) / (8 * f), total = n_ct * n_tt;
+        const int c = (total + n_cu - 1) / n_cu * pm_tile_cost(mf, f, n_tt);
+        if (i == 0 || c < best_cost) best_cost = c, best = PmTiles{f, n_ct, total, (total + 7) / 8};
+    }
+    if (cost) *cost = best_cost;
+    return best;
+}
+
+// Bound by the matrix pipe, the LDS and the chip's power together: with random operands the clock falls from 2.4 to
+// about 1.6 GHz, so what counts is work per product.  16x16x32 products move fewer accumulator bytes per flop than
+// 32x32x16 ones (7 % faster here at equal cycles), a wave keeps all 16 F rows against its 16 MF tokens (MF + F
+// fragment reads of 1 KB for MF * F products of 16 cycles: 60 KB = 480 LDS cycles for 704 cycles of products at
+// MF = 4, F = 11), and F follows the channel count in eights instead of padding it to 96.
+// One wave per SIMD has nobody to hide behind, so the stream is pipelined by hand: while the products of one 32-element
+// slice issue, the fragments of the next are read, and direct loads go out a few products apart (bunched together they
+// hold up the wave's issue).  A k-step is two slices: the first carries the requests for weight rows, then this wave's
+// reads of the step's buffers are over (the second slice's fragments are in registers), the barrier makes the next
+// step's rows visible, and the second slice carries the requests for token rows and the reads of the next step's first
+// slice.
+// Operand rows go straight from global memory into LDS (global_load_lds: 1 KB = 8 unpadded 128-byte rows per wave
+// instruction, the 16-byte units of row r stored at unit ^ ((r / 2) % 8): conflict-free fragment reads).  Every wave
+// issues the same loads in every k-step (rows beyond T or beyond the chunk are pointed at a row that exists, steps
+// beyond the last at the last step), so each wait counts exactly.
+// Measured, d 4096, m 11008 (before: eight waves of 64 tokens x 96 rows, 32x32x16 products, reads and products of all
+// waves in lockstep): 512 tokens 102 -> 80 us (1.16 PFLOP/s), 2048 tokens 380 -> 292 us (1.26), 256 tokens 54 us.  Without
+// the products it takes 65 us, without the direct loads 63: neither alone is the bound, and at 2.4 GHz the loop would be
+// a third faster.
+template <int MF, int F, int kMode>
+__device__ __forceinline__ void pm_tile(const uint16_t *__restrict__ w, const uint16_t *__restrict__ x, int T, int d,
+                                        int m, int n_ch, int n_tt, int logical, float *__restrict__ s2_part,
+                                        const PfStore &st, uint16_t *lds, float (&colsum)[4][kPfChunk])
+{
+    typedef __attribute__((address_space(3))) void lds_t;
+    typedef __attribute__((address_space(1))) const void glb_t;
+    typedef float f32x4_t __attribute__((ext_vector_type(4)));
+    constexpr int NA = PmRing<MF>::NA, NB = PmRing<MF>::NB;
+    constexpr bool kList = kMode == 1;
+    constexpr int BM = 64 * MF, BC = 8 * F;             // tokens and channels of the tile
+    constexpr int PA = BM / 32, PB = (F + 1) / 2;       // direct loads per wave and k-step (32 rows a pass)
+    constexpr int AT = BM * kPfBK, BT = PB * 32 * kPfBK;  // elements of one buffer
+    uint16_t *As = lds;            // [NA][BM * 64]
+    uint16_t *Bs = lds + NA * AT;  // [NB][PB * 32 * 64]
+
+    const int ctile = logical / n_tt, ttile = logical % n_tt;
+    const int t0 = ttile * BM, c0 = ctile * BC, cn = min(BC, n_ch - c0);
+    const int tid = threadIdx.x, lane = tid % kWave;
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+
+    // direct loads: this lane's 16 bytes land at LDS unit lane % 8 of row ld_row of the pass, so it fetches the
+    // k-vector that belongs there under the swizzle (passes are 32 rows apart: same swizzle term)
+    const int ld_row = tid / 8, src_kv = ((tid % 8) ^ ((ld_row / 2) % 8)) * 8;
+    const uint16_t *pa[PA], *pb[PB];
+#pragma unroll
+    for (int p = 0; p < PA; ++p) pa[p] = x + (size_t)min(t0 + ld_row + p * 32, T - 1) * d + src_kv;
+#pragma unroll
+    for (int p = 0; p < PB; ++p) {
+        int ch, which;
+        pm_row_channel<F>(ld_row + p * 32, ch, which);
+        const int cc = min(ch, cn - 1);
+        const int j = kList ? st.list[c0 + cc] : c0 + cc;
+        pb[p] = w + ((size_t)j * 3 + which) * d + src_kv;
+    }
+    const int n_k = d / kPfBK;
+    // k-step s of this tile is columns kof(s) (steps beyond the last repeat it).  With one token tile nobody shares this
+    // tile's weight rows, and every chunk starts at a column of its own: rows are a power of two apart in most models, so
+    // workgroups in step with each other would keep asking the same few memory channels (256 tokens: 58.7 -> 54.4 us).
+    // Where token tiles share weight rows through the L2 it gained nothing, and they start at column 0.
+    const int rot = n_tt == 1 ? ctile % n_k : 0;
+    auto kof = [&](int step) {
+        const int q = min(step, n_k - 1) + rot;
+        return (q >= n_k ? q - n_k : q) * kPfBK;
+    };
+    auto load_a = [&](int p, int buf, int k0) {
+        __builtin_amdgcn_global_load_lds((glb_t *)(pa[p] + k0), (lds_t *)(As + buf * AT + (p * 32 + wave * 8) * kPfBK), 16,
+                                         0, 0);
+    };
+    auto load_b = [&](int p, int buf, int k0) {
+        __builtin_amdgcn_global_load_lds((glb_t *)(pb[p] + k0), (lds_t *)(Bs + buf * BT + (p * 32 + wave * 8) * kPfBK), 16,
+                                         0, 0);
+    };
+
+    f32x4_t acc[MF][F];
+#pragma unroll
+    for (int a = 0; a < MF; ++a)
+#pragma unroll
+        for (int f = 0; f < F; ++f)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) acc[a][f][v] = 0.f;
+
+    // fragment reads: row lane % 16 of the fragment, unit 4 q + lane / 16 under the row's swizzle (fragments are 16 rows
+    // apart: same term); the order is the one their products need
+    int koff[2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) koff[q] = ((q * 4 + lane / 16) ^ ((lane % 16) / 2)) * 8;
+    const uint16_t *Al = As + (wave * MF * 16 + lane % 16) * kPfBK, *Bl = Bs + (lane % 16) * kPfBK;
+    bf16x8_t af[2][MF], bf[2][F];
+    auto fetch = [&](const uint16_t *Ab, const uint16_t *Bb, int i, int q, int set) {
+        if (i == 0)
+            af[set][0] = *reinterpret_cast<const bf16x8_t *>(Ab + koff[q]);
+        else if (i <= F)
+            bf[set][i - 1] = *reinterpret_cast<const bf16x8_t *>(Bb + (i - 1) * 16 * kPfBK + koff[q]);
+        else
+            af[set][i - F] = *reinterpret_cast<const bf16x8_t *>(Ab + (i - F) * 16 * kPfBK + koff[q]);
+    };
+    // (inline assembly ties the accumulator to itself: left to choose, the compiler gives products of this size other
+    // destinations and copies them back, which costs more than the products)
+    auto product = [&](int i, int set) {
+        asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0"
+                     : "+a"(acc[i / F][i % F])
+                     : "v"(af[set][i / F]), "v"(bf[set][i % F]));
+    };
+
+    // Requests in program order: ... A(s + NA - 1) | B(s + NB - 1) [wait for step s + 1] A(s + NA) | B(s + NB) [...: the
+    // wait may leave in flight what was issued after both A(s + 1) and B(s + 1).
+    constexpr int kAfterA = (NA - 1) * PB + (NA - 2) * PA, kAfterB = (NB - 2) * (PA + PB);
+    constexpr int kYounger = kAfterA < kAfterB ? kAfterA : kAfterB;
+    static_assert(kYounger + PA < 64, "vmcnt is a 6-bit counter");
+    constexpr int kFirst = NA > NB - 1 ? NA : NB - 1;
+#pragma unroll
+    for (int j = -kFirst; j < 0; ++j) {  // what steps j < 0 would have requested
+        if (j - 1 + NB >= 0) {
+#pragma unroll
+            for (int p = 0; p < PB; ++p) load_b(p, j - 1 + NB, kof(j - 1 + NB));
+        }
+        if (j + NA >= 0) {
+#pragma unroll
+            for (int p = 0; p < PA; ++p) load_a(p, j + NA, kof(j + NA));
+        }
+    }
+    // the wait "before step 0", with the token rows requested behind it in flight as well
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(kYounger + PA) : "memory");
+    constexpr int NP = MF * F, NR = MF + F;    // products and fragment reads of a slice
+    constexpr int kSpread = NP > 8 ? NP * 3 / 4 : NP;  // products the reads are spread over: the last have time to arrive
+#pragma unroll
+    for (int i = 0; i < NR; ++i) fetch(Al, Bl, i, 0, 0);
+    int abuf = 0, bbuf = 0, bprev = NB - 1;
+    for (int ks = 0; ks < n_k; ++ks) {
+        const uint16_t *Ab = Al + abuf * AT, *Bb = Bl + bbuf * BT;
+        const int kb = kof(ks + NB - 1), ka = kof(ks + NA);
+#pragma unroll
+        for (int i = 0; i < NP; ++i) {
+            product(i, 0);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int r = min(i, kSpread) * NR / kSpread; r < min(i + 1, kSpread) * NR / kSpread; ++r) fetch(Ab, Bb, r, 1, 1);
+#pragma unroll
+            for (int p = i * PB / NP; p < (i + 1) * PB / NP; ++p) load_b(p, bprev, kb);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(kYounger) : "memory");
+        const int a_free = abuf;
+        bprev = bbuf;
+        abuf = abuf + 1 == NA ? 0 : abuf + 1;
+        bbuf = bbuf + 1 == NB ? 0 : bbuf + 1;
+        Ab = Al + abuf * AT, Bb = Bl + bbuf * BT;
+#pragma unroll
+        for (int i = 0; i < NP; ++i) {
+            product(i, 1);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int r = min(i, kSpread) * NR / kSpread; r < min(i + 1, kSpread) * NR / kSpread; ++r) fetch(Ab, Bb, r, 0, 0);
+#pragma unroll
+            for (int p = i * PA / NP; p < (i + 1) * PA / NP; ++p) load_a(p, a_free, ka);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    // the surplus requests, before the LDS is used for something else; the products' results before they are read (the
+    // compiler does not see the products, so it adds no wait states for them)
+    asm volatile("s_waitcnt vmcnt(0)\n\ts_nop 15\n\ts_nop 15" ::: "memory");
+    __syncthreads();
+
+    // Accumulator register v of a lane: token 4 (lane / 16) + v of the fragment, B row lane % 16 of the fragment.  An odd
+    // last fragment holds gate values in lanes 0..7 of each 16 and up values of the same channels in lanes 8..15: the
+    // halves trade two registers each, so that every lane forms two of the four.
+    uint16_t *hs = lds;                 // [BM][BC + 8] bf16: H of the tile on its way out
+    constexpr int HS = BC + 8;
+    const int col = lane % 16, row0 = wave * MF * 16 + lane / 16 * 4;  // first token row of this lane
+    const bool upper = col >= 8;
+    const int c_odd = 8 * (F - 1) + col % 8, r_odd = upper ? 2 : 0;
+    float ss[(F + 1) / 2];
+#pragma unroll
+    for (int p = 0; p < F / 2; ++p) {
+        const int c = 16 * p + col;
+        const bool live_c = c < cn;
+        const int j = (kList && st.tmask && live_c) ? st.list[c0 + c] : 0;
+        ss[p] = 0.f;
+#pragma unroll
+        for (int a = 0; a < MF; ++a)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int t = t0 + row0 + a * 16 + v;
+                float h = silu_mul_tile(acc[a][2 * p][v], acc[a][2 * p + 1][v]);
+                h = (t < T && live_c) ? h : 0.f;  // (padding holds products of the rows its loads were pointed at)
+                ss[p] = fmaf(h, h, ss[p]);
+                if (kMode != 0) {
+                    if (kList && st.tmask && t < T && live_c && !st.tmask[(size_t)t * m + j]) h = 0.f;
+                    hs[(row0 + a * 16 + v) * HS + c] = f32_to_bf16(h);
+                }
+            }
+    }
+    if (F % 2) {
+        const bool live_c = c_odd < cn;
+        const int j = (kList && st.tmask && live_c) ? st.list[c0 + c_odd] : 0;
+        ss[F / 2] = 0.f;
+#pragma unroll
+        for (int a = 0; a < MF; ++a)
+#pragma unroll
+            for (int v = 0; v < 2; ++v) {
+                const float mine = upper ? acc[a][F - 1][v + 2] : acc[a][F - 1][v];
+                const float give = upper ? acc[a][F - 1][v] : acc[a][F - 1][v + 2];
+                const float got = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(give), 0x128, 0xf, 0xf, true));  // row_ror:8
+                const int t = t0 + row0 + a * 16 + r_odd + v;
+                float h = silu_mul_tile(upper ? got : mine, upper ? mine : got);
+                h = (t < T && live_c) ? h : 0.f;
+                ss[F / 2] = fmaf(h, h, ss[F / 2]);
+                if (kMode != 0) {
+                    if (kList && st.tmask && t < T && live_c && !st.tmask[(size_t)t * m + j]) h = 0.f;
+                    hs[(row0 + a * 16 + r_odd + v) * HS + c_odd] = f32_to_bf16(h);
+                }
+            }
+    }
+    if (!kList) {
+#pragma unroll
+        for (int p = 0; p < (F + 1) / 2; ++p) {
+            float s = ss[p];
+            if (p == F / 2) s += __shfl_xor(s, 8, kWave);
+            s += __shfl_xor(s, 16, kWave);
+            s += __shfl_xor(s, 32, kWave);
+            if (lane < 16 && (p < F / 2 || lane < 8)) colsum[wave][16 * p + lane] = s;
+        }
+        pf_chunk_scores<4>(colsum, m, n_tt, ttile, ctile, c0, cn, s2_part, st);
+    }
+    if (kMode != 0) {
+        __syncthreads();
+        for (int i = tid; i < BM * F; i += kPmThreads) {
+            const int r = i / F, v = i % F;
+            if (t0 + r < T && c0 + v * 8 < st.ldh)
+                *reinterpret_cast<uint4 *>(st.hc + (size_t)(t0 + r) * st.ldh + c0 + v * 8) =
+                    *reinterpret_cast<const uint4 *>(hs + r * HS + v * 8);
+        }
+    }
+}
+
+// One workgroup per compute unit; each walks its share of the tiles of its XCD (the token tiles of a channel chunk are
+// neighbours there and meet in its L2).
+template <int MF, int kMode>
+__global__ __launch_bounds__(kPmThreads, 1) void prefill_mma_kernel(const uint16_t *__restrict__ w,
+                                                                    const uint16_t *__restrict__ x, int T, int d, int m,
+                                                                    int n_tt, PmTiles g, float *__restrict__ s2_part,
+                                                                    PfStore st)
+{
+    extern __shared__ __attribute__((aligned(16))) uint16_t pf_lds[];
+    __shared__ float colsum[4][kPfChunk];
+    int n_ch = m;  // channels the chunks run over
+    if (kMode == 1) {
+        n_ch = *st.n_list;
+        g = pm_tiles(n_ch, n_tt, MF, st.n_cu);
+    }
+    for (int i = blockIdx.x / 8; i < g.per_xcd; i += gridDim.x / 8) {
+        const int logical = (blockIdx.x % 8) * g.per_xcd + i;
+        if (logical >= g.total) break;
+        switch (g.f) {
+#define POP_PM(FF)                                                                               \
+    case FF:                                                                                     \
+        pm_tile<MF, FF, kMode>(w, x, T, d, m, n_ch, n_tt, logical, s2_part, st, pf_lds, colsum); \
+        break;
+            POP_PM(12) POP_PM(11) POP_PM(10) POP_PM(8) POP_PM(7) POP_PM(6) POP_PM(4)
+#undef POP_PM
+        }
+        __syncthreads();  // the next tile's direct loads overwrite the LDS
+    }
 }
 
 // float32: 64 tokens x 32 channels per workgroup; thread (tx = channel, ty = group of 8 tokens).
@@ -444,14 +716,11 @@ __global__ __launch_bounds__(256) void prefill_f32_kernel(const float *__restric
     }
 }
 
-// Token tile: 256 or 128 tokens, whichever gives the cheaper schedule: tiles per compute unit on the busiest one
-// (after the chunks are evened out) times a tile's measured relative cost - 1 for 256 tokens x three fragments, 0.8
-// with two fragments, and 0.6 of either for the 128-token form (half the products, a ring of three LDS buffers).
-// At config 2 this picks 128 up to 256 tokens and 256 from there on.  POP_PF_BM=128 / 256 overrides (tuning).
+// Token tile of the register-staged kernel: 256 or 128 tokens, whichever gives the cheaper schedule: tiles per compute
+// unit on the busiest one (after the chunks are evened out) times a tile's measured relative cost - 1 for 256 tokens x
+// three fragments, 0.8 with two fragments, and 0.6 of either for the 128-token form.
 static int prefill_token_tile(int T, int n_ch, int n_cu)
 {
-    static const int forced = getenv("POP_PF_BM") ? atoi(getenv("POP_PF_BM")) : 0;
-    if (forced == 128 || forced == 256) return forced;
     int best_bm = 256;
     long best = -1;
     for (int bm = 256; bm >= 128; bm -= 128) {
@@ -463,9 +732,29 @@ static int prefill_token_tile(int T, int n_ch, int n_cu)
     return best_bm;
 }
 
-int prefill_rows_used(int T, int is_bf16, int m, int n_cu)
+// Rows that are whole k-steps long take the direct-load kernel.
+static bool prefill_direct(int d) { return d % kPfBK == 0; }
+
+// Token fragments per wave of the direct-load kernel: the cheapest schedule over the tile heights.
+static int pm_token_fragments(int T, int n_ch, int n_cu, PmTiles *tiles)
+{
+    int best = 1, best_cost = 0;
+    for (int mf = 1; mf <= kPmMaxMF; ++mf) {
+        int cost = 0;
+        const PmTiles g = pm_tiles(n_ch, (T + 64 * mf - 1) / (64 * mf), mf, n_cu, &cost);
+        if (mf == 1 || cost < best_cost) best_cost = cost, best = mf, *tiles = g;
+    }
+    return best;
+}
+
+int prefill_rows_used(int T, int is_bf16, int d, int m, int n_cu)
 {
     if (!is_bf16) return (T + kPf32BM - 1) / kPf32BM;
+    if (prefill_direct(d)) {
+        PmTiles g;
+        const int bm = 64 * pm_token_fragments(T, m, n_cu, &g);
+        return (T + bm - 1) / bm;
+    }
     const int bm = prefill_token_tile(T, m, n_cu);
     return (T + bm - 1) / bm;
 }
@@ -474,23 +763,6 @@ template <int BM, int NW, int NF, int kMode>
 static hipError_t launch_pf_bf16(int blocks, hipStream_t s, const void *w, const void *x, int T, int d, int m, int n_tt,
                                  const PfGeom &g, float *s2_part, const PfStore &st)
 {
-    // rows that are whole k-steps long go from global memory straight into LDS (POP_PF_DMA=0 keeps them on the
-    // register-staged path, for comparison).  The 128-token tile is small enough for a ring of three LDS buffers:
-    // short prompts are bound by the weight stream from memory, and two k-steps in flight per compute unit carry
-    // twice the bytes of one.
-    static const int use_dma = getenv("POP_PF_DMA") ? atoi(getenv("POP_PF_DMA")) : 1;
-    if (use_dma && d % kPfBK == 0) {
-        constexpr int NS = BM <= 128 ? 3 : 2;
-        const size_t lds_d = (size_t)NS * (BM + NF * 64) * kPfBK * sizeof(uint16_t);
-        hipError_t e =
-            hipFuncSetAttribute(reinterpret_cast<const void *>(&prefill_bf16_kernel<BM, NW, NF, kMode, true, NS>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_d);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((prefill_bf16_kernel<BM, NW, NF, kMode, true, NS>), dim3(blocks), dim3(NW * 64), lds_d, s,
-                           (const uint16_t *)w, (const uint16_t *)x, T, d, m, n_tt, g.chunk, g.total, g.per_xcd, s2_part,
-                           st);
-        return hipGetLastError();
-    }
     const size_t lds = (size_t)2 * (BM + NF * 64) * kPfLd * sizeof(uint16_t);
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&prefill_bf16_kernel<BM, NW, NF, kMode>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -500,13 +772,46 @@ static hipError_t launch_pf_bf16(int blocks, hipStream_t s, const void *w, const
     return hipGetLastError();
 }
 
+template <int MF, int kMode>
+static hipError_t launch_pm(const void *w, int d, int m, const void *x, int T, const PmTiles &g, float *s2_part, int n_cu,
+                            const PfStore &st, hipStream_t s)
+{
+    const size_t lds = PmRing<MF>::kBytes;
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&prefill_mma_kernel<MF, kMode>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    const int n_tt = (T + 64 * MF - 1) / (64 * MF), all = kMode == 1 ? n_cu : (g.total < n_cu ? g.total : n_cu);
+    hipLaunchKernelGGL((prefill_mma_kernel<MF, kMode>), dim3((all + 7) / 8 * 8), dim3(kPmThreads), lds, s,
+                       (const uint16_t *)w, (const uint16_t *)x, T, d, m, n_tt, g, s2_part, st);
+    return hipGetLastError();
+}
+
+template <int kMode>
+static hipError_t launch_pm_all(const void *w, int d, int m, const void *x, int T, float *s2_part, int n_cu,
+                                const PfStore &st, hipStream_t s)
+{
+    PmTiles g;
+    switch (pm_token_fragments(T, m, n_cu, &g)) {  // (list form: priced as all m channels, cut up on the device)
+    case 1: return launch_pm<1, kMode>(w, d, m, x, T, g, s2_part, n_cu, st, s);
+    case 2: return launch_pm<2, kMode>(w, d, m, x, T, g, s2_part, n_cu, st, s);
+    case 3: return launch_pm<3, kMode>(w, d, m, x, T, g, s2_part, n_cu, st, s);
+    case 4: return launch_pm<4, kMode>(w, d, m, x, T, g, s2_part, n_cu, st, s);
+    default: return launch_pm<5, kMode>(w, d, m, x, T, g, s2_part, n_cu, st, s);
+    }
+}
+
 // Whether the contraction's launch forms the scores itself: when every compute unit runs one tile at most.  The tile
 // that completes a chunk learns so through a write-through store, its acknowledgement and a counted arrival, a few
 // microseconds that nothing hides at the end of a launch with one tile per compute unit anyway, but that would stand
 // between the tiles a compute unit runs back to back on a long prompt (measured: +14 us at 2048 tokens).
-static bool prefill_scores_in_launch(int is_bf16, int T, int m, int n_cu)
+bool prefill_forms_scores(int is_bf16, int T, int d, int m, int n_cu)
 {
     if (!is_bf16 || T < 1) return false;
+    if (prefill_direct(d)) {
+        PmTiles g;
+        pm_token_fragments(T, m, n_cu, &g);
+        return g.total <= n_cu;
+    }
     const int bm = prefill_token_tile(T, m, n_cu);
     return prefill_geometry(m, (T + bm - 1) / bm, n_cu).total <= n_cu;
 }
@@ -515,11 +820,12 @@ template <int kMode>
 static hipError_t launch_pf_bf16_all(const void *w, int d, int m, const void *x, int T, float *s2_part, int n_cu,
                                      PfStore st, hipStream_t s)
 {
+    if (!prefill_forms_scores(1, T, d, m, n_cu)) st.fin_ctr = nullptr;
+    if (prefill_direct(d)) return launch_pm_all<kMode>(w, d, m, x, T, s2_part, n_cu, st, s);
     const int bm = prefill_token_tile(T, m, n_cu);
     const int n_tt = (T + bm - 1) / bm;
     const PfGeom g = prefill_geometry(m, n_tt, n_cu);
     const int blocks = g.per_xcd * 8;
-    if (!prefill_scores_in_launch(1, T, m, n_cu)) st.fin_ctr = nullptr;
     // 256-token tiles run with 8 waves (two per SIMD: one wave's waits for staging loads, LDS writes and the
     // k-step barrier are covered by the other's products), 128-token tiles with 4
     if (bm == 256 && g.nf == 3) return launch_pf_bf16<256, 8, 3, kMode>(blocks, s, w, x, T, d, m, n_tt, g, s2_part, st);
@@ -537,8 +843,6 @@ hipError_t launch_prefill_gateup_keep_bf16(const void *w, int d, int m, const vo
     return launch_pf_bf16_all<2>(w, d, m, x, T, s2_part, n_cu, st, s);
 }
 
-bool prefill_forms_scores(int is_bf16, int T, int m, int n_cu) { return prefill_scores_in_launch(is_bf16, T, m, n_cu); }
-
 hipError_t launch_prefill_gateup(const void *w, int is_bf16, int d, int m, const void *x, int T, float *s2_part,
                                  int n_cu, hipStream_t s, const PrefillScores *fin)
 {
@@ -553,15 +857,16 @@ hipError_t launch_prefill_gateup(const void *w, int is_bf16, int d, int m, const
 }
 
 // bf16 only.  Gate/up over the channels of a device-resident list; hc[t][c] = bf16(H[t][list[c]]) (times
-// tmask[t][list[c]] if tmask is given).  The list's length is known on the device only: both tile forms are
-// launched, each sized for the longest possible list (m channels), and the one the length does not call for exits
-// at once.
+// tmask[t][list[c]] if tmask is given).  The list's length is known on the device only.  Direct-load kernel: every
+// workgroup cuts the list up for itself.  Register-staged kernel: both tile forms are launched, each sized for the
+// longest possible list (m channels), and the one the length does not call for exits at once.
 hipError_t launch_gateup_list_bf16(const void *w, int d, int m, const void *x, int T, const int *list, const int *n_list,
                                    const unsigned char *tmask, uint16_t *hc, int ldh, int n_cu, hipStream_t s)
 {
+    PfStore st{list, n_list, hc, ldh, tmask, n_cu};
+    if (prefill_direct(d)) return launch_pm_all<1>(w, d, m, x, T, nullptr, n_cu, st, s);
     const int bm = prefill_token_tile(T, m, n_cu);  // (the list's length is not known here: priced as all m channels)
     const int n_tt = (T + bm - 1) / bm;
-    PfStore st{list, n_list, hc, ldh, tmask, n_cu};
     PfGeom g{};
     hipError_t e = hipSuccess;
     for (int nf = 3; nf >= 2 && e == hipSuccess; --nf) {

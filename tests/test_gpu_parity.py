@@ -515,6 +515,22 @@ def test_prefill_rows_of_whole_k_steps(pop, oracle, d, m, T):
         _check_decode(oracle, G, L, region, cand, xt, k)
 
 
+@pytest.mark.parametrize("mf,f,d", [(1, 4, 64), (1, 12, 128), (2, 11, 192), (3, 7, 64), (4, 6, 128), (4, 11, 64), (5, 8, 64),
+                                    (5, 10, 128), (5, 12, 64)])
+def test_prefill_direct_load_tiles(pop, oracle, mf, f, d):
+    """Every tile height (64 mf tokens) and a spread of chunk widths (8 f channels, odd f with its shared fragment) of
+    the direct-load contraction, a few rows and channels short of whole tiles and with row lengths shorter than the LDS
+    ring: scores of all channels against the oracle, then the kept-H form through the prompt's output."""
+    T, m = 64 * mf - 5, 2048 * f - 3
+    L = synth.make_layer(synth.small_config("direct_tiles", d, m, BF16))
+    x = synth.make_activations(L, T, "prompt")
+    n_ret, n_cand, k = m // 2, m // 8, m // 16
+    rows = np.array([0, T // 2, T - 1])
+    with GpuLayer(pop, L, max_tokens=T, max_batch=1) as G:
+        _check_prefill(oracle, G, L, x, n_ret, n_cand)
+        _check_prefill_forward(oracle, G, L, x, n_ret, n_cand, k, F32, FFN_MFMA_TOL_F32, rows=rows)
+
+
 def test_prefill_forward_full_size(pop, oracle):
     """Llama-2-7B-shaped layer, prompt 512: prefill scores on a sample of channels, partition and prefill mask
     on all channels, the prompt's output on a sample of tokens, then a decode step on the partition."""
