@@ -209,45 +209,27 @@ int pruned_ffn_mfma(pop_layer *L, const void *x, int T, const unsigned char *mas
 }
 
 // Scores, partition and partition-constant step state from s2_part (the second half of the prefilling stage).
-// n_top >= 0: the same launch also leaves the n_top best channels as an ascending list with its length in top_list
-// and, with top_mask, as a byte mask in ffn_any; compact: a column gather that the state launch takes along.
+// n_top: size of the prompt's own mask; `o` says what the caller wants of it.
 int finish_partition(pop_layer *L, int T, int n_ret, int n_cand, float *scores, unsigned char *region, int *ret_idx,
-                     int *cand_idx, hipStream_t s, bool scores_ready, int n_top = -1, bool top_mask = true,
-                     const CompactJob *compact = nullptr)
+                     int *cand_idx, hipStream_t s, bool scores_ready, int n_top = 0,
+                     PartitionOutputs o = PartitionOutputs{})
 {
     const int m = L->m;
-    // the partition launch also forms the scores from the contraction's partial rows (the input-side scores are
-    // already in place) and clears the step counters; one more launch writes everything that is constant per
-    // partition (retained bytes of every mask row, retained prefix of every active list and of the union list, the
-    // candidate-then-retained list)
-    PartitionExtra ex;
-    const bool from_partials = !scores_ready && partition_takes_partials(m);
-    if (!scores_ready && !from_partials)
-        POP_HIP(launch_scores_from_partials(L->s2_part, prefill_rows_used(T, L->is_bf16, L->d, m, L->n_cu), m, L->nrm, L->scores, s));
-    if (from_partials) {
-        ex.s2_part = L->s2_part, ex.n_tiles = prefill_rows_used(T, L->is_bf16, L->d, m, L->n_cu), ex.nrm = L->nrm;
-        ex.scores_out = L->scores;
-    }
-    ex.sync = L->sync, ex.n_sync = 16;
-#ifdef POP_TRACE
-    ex.trace = g_trace ? g_trace + 1000 * 8 : nullptr;
-#endif
-    if (n_top >= 0) {
-        ex.n_top = n_top, ex.top_list = L->top_list, ex.top_count = L->top_list + m;
-        ex.top_mask = top_mask ? L->ffn_any : nullptr;
-    }
-    POP_HIP(launch_partition(L->scores, m, n_ret, n_cand, L->region, L->ret_idx, L->cand_idx, s, &ex));
-    POP_HIP(launch_step_state_init(L->region, m, L->ret_idx, n_ret, L->max_batch, m, L->mask, L->active_idx, s,
-                                   L->cand_idx, n_cand, L->rc_idx, L->ulist, nullptr, compact));
+    if (!scores_ready)
+        POP_HIP(launch_scores_from_partials(L->s2_part, prefill_rows_used(T, L->is_bf16, L->d, m, L->n_cu), m, L->nrm,
+                                            L->scores, s));
+    o.scores = L->scores, o.scores_copy = scores;
+    o.region[0] = L->region, o.region[1] = region;
+    o.ret_idx[0] = L->ret_idx, o.ret_idx[1] = ret_idx;
+    o.cand_idx[0] = L->cand_idx, o.cand_idx[1] = cand_idx;
+    o.rows = L->max_batch, o.act_stride = m, o.mask = L->mask, o.active_idx = L->active_idx;
+    o.rc_idx = L->rc_idx, o.ulist = L->ulist;
+    o.sync = L->sync, o.n_sync = 16;
+    POP_HIP(launch_partition(L->scores, m, n_ret, n_cand, n_top, o, s));
     L->ulist_prefix_ok = true;
     L->n_ret = n_ret;
     L->n_cand = n_cand;
     { int rc = plan_fused_step(L); if (rc != POP_OK) return rc; }
-    if (scores) POP_HIP(hipMemcpyAsync(scores, L->scores, (size_t)m * 4, hipMemcpyDeviceToDevice, s));
-    if (region) POP_HIP(hipMemcpyAsync(region, L->region, (size_t)m, hipMemcpyDeviceToDevice, s));
-    if (ret_idx && n_ret) POP_HIP(hipMemcpyAsync(ret_idx, L->ret_idx, (size_t)n_ret * 4, hipMemcpyDeviceToDevice, s));
-    if (cand_idx && n_cand)
-        POP_HIP(hipMemcpyAsync(cand_idx, L->cand_idx, (size_t)n_cand * 4, hipMemcpyDeviceToDevice, s));
     L->has_partition = true;
     return POP_OK;
 }
@@ -535,27 +517,23 @@ int pop_prefill_forward(pop_layer_t *L, const void *x, int T, int n_ret, int n_c
     // prefill mask: retained channels plus the best k0 candidates by prefill score, i.e. the n_ret + k0 best channels
     // of the partition's own order: the partition launch emits them as well (mask bytes and ascending list)
     if (!L->top_list && !dev_alloc((void **)&L->top_list, ((size_t)m + 1) * sizeof(int))) return POP_ENOMEM;
-    // (the byte mask only where somebody reads it: the caller, or the path below that works from a mask; the gather of
-    // the active columns of H into compact form rides along with the partition's state launch)
-    CompactJob gather;
-    if (keep) {
-        gather.h_all = L->ffn_hall, gather.ldh = ldh, gather.T = T, gather.list = L->top_list;
-        gather.n_list = L->top_list + m, gather.hc = L->ffn_hc, gather.ldhc = ldh;
-    }
+    // (the byte mask only where somebody reads it: the caller, or the path below that works from a mask)
+    PartitionOutputs o;
+    o.top_list = L->top_list, o.top_count = L->top_list + m;
+    o.top_mask[0] = keep ? nullptr : L->ffn_any, o.top_mask[1] = mask;
     {
         int rc = finish_partition(L, T, n_ret, n_cand, scores, region, ret_idx, cand_idx, s,
-                                  T == 0 || L->input_side || prefill_forms_scores(L->is_bf16, T, L->d, m, L->n_cu), n_ret + k0, mask || !keep, keep ? &gather : nullptr);
+                                  T == 0 || L->input_side || prefill_forms_scores(L->is_bf16, T, L->d, m, L->n_cu), n_ret + k0, o);
         if (rc != POP_OK) return rc;
     }
-    unsigned char *pm = L->ffn_any;
-    if (mask) POP_HIP(hipMemcpyAsync(mask, pm, (size_t)m, hipMemcpyDeviceToDevice, s));
     if (T == 0) return POP_OK;  // no token rows to produce
     if (keep) {
+        POP_HIP(launch_compact_hidden(L->ffn_hall, ldh, T, L->top_list, L->top_list + m, n_ret + k0, L->ffn_hc, ldh, s));
         POP_HIP(launch_down_gemm_bf16(L->w, d, L->top_list, L->top_list + m, L->ffn_hc, ldh, T, n_split, L->ffn_part, y,
                                       ydtype == POP_BF16, s, L->zero_row));
         return POP_OK;
     }
-    const int rc = pop_pruned_ffn(L, x, T, pm, 1, y, ydtype, stream);
+    const int rc = pop_pruned_ffn(L, x, T, L->ffn_any, 1, y, ydtype, stream);
     return rc;
 }
 
@@ -708,7 +686,9 @@ int pop_partition_from_scores(const float *scores, int m, int n_ret, int n_cand,
 {
     if (!scores) return POP_EINVAL;
     if (m <= 0 || n_ret < 0 || n_cand < 0 || (long long)n_ret + n_cand > m) return POP_ESHAPE;
-    POP_HIP(launch_partition(scores, m, n_ret, n_cand, region, ret_idx, cand_idx, as_stream(stream)));
+    PartitionOutputs o;
+    o.region[0] = region, o.ret_idx[0] = ret_idx, o.cand_idx[0] = cand_idx;
+    POP_HIP(launch_partition(scores, m, n_ret, n_cand, 0, o, as_stream(stream)));
     return POP_OK;
 }
 
@@ -718,9 +698,10 @@ int pop_partition_top_from_scores(const float *scores, int m, int n_ret, int n_c
     if (!scores || !top_list) return POP_EINVAL;
     if (m <= 0 || n_ret < 0 || n_cand < 0 || (long long)n_ret + n_cand > m) return POP_ESHAPE;
     if (n_top < 0 || n_top > m) return POP_ESHAPE;
-    PartitionExtra ex;
-    ex.n_top = n_top, ex.top_mask = top_mask, ex.top_list = top_list;
-    POP_HIP(launch_partition(scores, m, n_ret, n_cand, region, ret_idx, cand_idx, as_stream(stream), &ex));
+    PartitionOutputs o;
+    o.region[0] = region, o.ret_idx[0] = ret_idx, o.cand_idx[0] = cand_idx;
+    o.top_mask[0] = top_mask, o.top_list = top_list;
+    POP_HIP(launch_partition(scores, m, n_ret, n_cand, n_top, o, as_stream(stream)));
     return POP_OK;
 }
 
@@ -732,7 +713,7 @@ int pop_topk_from_scores(const float *cand_scores, const int *cand_idx, int n_ca
     if (mask && !region) return POP_EINVAL;
     BatchK kk = {};
     kk.k[0] = k;
-    if (mask) POP_HIP(launch_step_state_init(region, m, nullptr, 0, 1, 0, mask, nullptr, as_stream(stream)));
+    if (mask) POP_HIP(launch_retained_mask(region, m, mask, as_stream(stream)));
     POP_HIP(launch_topk(cand_scores, n_cand, cand_idx, n_cand, 0, m, 1, kk, 0, mask, nullptr, nullptr, sel_idx,
                         nullptr, nullptr, nullptr, nullptr, as_stream(stream)));
     return POP_OK;

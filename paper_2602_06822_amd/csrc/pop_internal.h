@@ -88,30 +88,32 @@ hipError_t launch_repack(const void *w_gate, const void *w_up, const void *w_dow
                          void *w, float *nrm, int is_bf16, hipStream_t s);
 
 // ---- selection (pop_select.hip) ----
-// Regions by rank of scores[m]; outputs may be null.  Two things the prefill call needs can ride in the same
-// launch: the scores themselves from the prefill kernel's partial rows (scores[j] = nrm[j] * sqrt(sum over tiles,
-// in order, of s2_part[tile][j]), written to scores_out and used instead of the scores argument; only when
-// partition_takes_partials(m)), and n_sync <= 1024 counters to clear.
-struct PartitionExtra {
-    const float *s2_part = nullptr;
-    int n_tiles = 0;
-    const float *nrm = nullptr;
-    float *scores_out = nullptr;
-    int *sync = nullptr;
+// What the partition of scores[m] writes; every pointer may be null.  Two destinations where a layer keeps its own copy.
+struct PartitionOutputs {
+    const float *scores = nullptr;  // read for scores_copy
+    float *scores_copy = nullptr;
+    unsigned char *region[2] = {nullptr, nullptr};
+    int *ret_idx[2] = {nullptr, nullptr}, *cand_idx[2] = {nullptr, nullptr};
+    // the n_top best channels of the same order (the prompt's own mask, Sec. 3.4: the retained channels plus the best
+    // candidates by prefill score are the n_top best overall): bytes, ascending list, its length
+    unsigned char *top_mask[2] = {nullptr, nullptr};
+    int *top_list = nullptr, *top_count = nullptr;
+    // partition-constant step state: mask[b][j] = (region[j] == retained), active_idx[b][0..n_ret) = ret_idx for b < rows,
+    // rc_idx = cand_idx ++ ret_idx, ulist[0..n_ret) = ret_idx
+    int rows = 0, act_stride = 0;
+    unsigned char *mask = nullptr;
+    int *active_idx = nullptr, *rc_idx = nullptr, *ulist = nullptr;
+    int *sync = nullptr;  // n_sync <= 1024 counters to clear
     int n_sync = 0;
-    // with top_list given: the n_top best channels of the same order as well (the prompt's own mask, Sec. 3.4: the
-    // retained channels plus the best candidates by prefill score are the n_top best overall) - top_mask[m] bytes
-    // (optional), their ascending list, *top_count = n_top
-    int n_top = 0;
-    unsigned char *top_mask = nullptr;
-    int *top_list = nullptr;
-    int *top_count = nullptr;
-    unsigned long long *trace = nullptr;  // profiling builds only: timestamps of the kernel's phases, else null
 };
-bool partition_takes_partials(int m);
 void set_select_trace(unsigned long long *p);  // profiling builds: phase stamps of topk_kernel (8 words), or null
-hipError_t launch_partition(const float *scores, int m, int n_ret, int n_cand, unsigned char *region, int *ret_idx,
-                            int *cand_idx, hipStream_t s, const PartitionExtra *extra = nullptr);
+// Regions by rank of scores[m]: the best n_ret channels, the next n_cand, the rest; and the n_top best.
+hipError_t launch_partition(const float *scores, int m, int n_ret, int n_cand, int n_top, const PartitionOutputs &o,
+                            hipStream_t s);
+// hc[t][c] = h_all[t][list[c]] for c < *n_list <= max_list, t < T (bf16 bits), and zero columns up to the next multiple
+// of 64.  ldhc even.
+hipError_t launch_compact_hidden(const uint16_t *h_all, int ldh, int T, const int *list, const int *n_list, int max_list,
+                                 uint16_t *hc, int ldhc, hipStream_t s);
 // Per sequence b (grid = B): select k.k[b] of n_cand candidates by cscore[b*cs_stride + i]; writes the candidate
 // bytes of mask[b][m], active_idx[b*act_stride + n_ret .. n_ret+k), n_active[b], sel_idx (sequence 0, only when
 // active_idx is null), each if non-null.  With union_list non-null also: selflag [B][n_cand] (scratch), and the
@@ -121,48 +123,8 @@ hipError_t launch_partition(const float *scores, int m, int n_ret, int n_cand, u
 hipError_t launch_topk(const float *cscore, int cs_stride, const int *cand_idx, int n_cand, int n_ret, int m, int B,
                        BatchK k, int act_stride, unsigned char *mask, int *active_idx, int *n_active, int *sel_idx,
                        unsigned char *selflag, int *union_ctr, int *union_list, int *n_union, hipStream_t s);
-// Partition-constant step state: mask[b][j] = (region[j] == retained), active_idx[b][0..n_ret) = ret_idx.
-// With cand_idx / rc_idx / ulist given it also writes rc_idx = cand_idx ++ ret_idx and ulist[0..n_ret) = ret_idx.
-// With `clear` given the same launch zeroes that buffer's words.
-struct StridedClear {
-    int *p = nullptr;  // n slots of `words` ints (<= 256), `stride` ints apart
-    int n = 0, stride = 0, words = 0;
-};
-// hc[t][c] = h_all[t][list[c]] for c < *n_list, t < T (bf16 bits): the columns of the listed channels moved next to
-// each other.  With `compact` given the same launch does this as well (the list must be final when it starts).
-struct CompactJob {
-    const uint16_t *h_all = nullptr;
-    int ldh = 0, T = 0;
-    const int *list = nullptr, *n_list = nullptr;
-    uint16_t *hc = nullptr;
-    int ldhc = 0;  // even
-};
-constexpr int kCompactRows = 8;  // tokens a workgroup of the compaction walks
-// The compaction's workgroup (bx, by) of 256 threads: positions 512 bx .. + 511, tokens kCompactRows by .. + 7.
-__device__ __forceinline__ void compact_hidden_block(const CompactJob &job, int bx, int by)
-{
-    const int a = *job.n_list;
-    const int c = (bx * 256 + (int)threadIdx.x) * 2;  // a thread owns two adjacent positions (one 32-bit store)
-    const int t0 = by * kCompactRows, t1 = min(job.T, t0 + kCompactRows);
-    if (c >= a) {
-        // the columns between the list's end and the end of its last 64-channel k-step are read by the direct-load
-        // GEMM (against rows of zeros): they must not keep what an earlier, longer list left there
-        if (c < min((a + 63) / 64 * 64, job.ldhc))
-            for (int t = t0; t < t1; ++t) *reinterpret_cast<uint32_t *>(job.hc + (size_t)t * job.ldhc + c) = 0u;
-        return;
-    }
-    const int j0 = job.list[c], j1 = c + 1 < a ? job.list[c + 1] : -1;
-    for (int t = t0; t < t1; ++t) {
-        const uint16_t *row = job.h_all + (size_t)t * job.ldh;
-        const uint32_t v = (uint32_t)row[j0] | (j1 >= 0 ? (uint32_t)row[j1] << 16 : 0u);
-        *reinterpret_cast<uint32_t *>(job.hc + (size_t)t * job.ldhc + c) = v;
-    }
-}
-hipError_t launch_step_state_init(const unsigned char *region, int m, const int *ret_idx, int n_ret, int rows,
-                                  int act_stride, unsigned char *mask, int *active_idx, hipStream_t s,
-                                  const int *cand_idx = nullptr, int n_cand = 0, int *rc_idx = nullptr,
-                                  int *ulist = nullptr, const StridedClear *clear = nullptr,
-                                  const CompactJob *compact = nullptr);
+// mask[j] = (region[j] == retained)
+hipError_t launch_retained_mask(const unsigned char *region, int m, unsigned char *mask, hipStream_t s);
 // mask rows -> ascending list of channels active in any row.  With pad_hc given ([pad_T][pad_ld] bf16, pad_ld a
 // multiple of 64) the launch also zeroes its columns from the list's length up to the next multiple of 64 (what the
 // direct-load GEMM reads beyond a compact H's last column).

@@ -2,201 +2,348 @@
 // per-step candidate top-k (Sec. 3.3 "Decoding Stage") and the index-list compactions around them.
 //
 // All selections use one strict total order on channels: higher score first, equal scores by lower channel
-// index.  Scores are mapped to order-preserving 32-bit keys; an MSB-first radix select over four 8-bit digits
-// finds the key of the n-th best element, and a block scan in index order admits elements equal to that key
-// until the count is exact.  One workgroup handles one selection, so the result is deterministic.
+// index.  Scores are mapped to order-preserving 32-bit keys; a digit-wise select from the most significant bits down
+// finds the n-th best element, so the result is deterministic.
 #include "pop_select_dev.h"
 
 namespace pop {
 
 // ---------------------------------------------------------------- three-region partition
-// The keys are staged in LDS once (eight independent loads in flight per thread), so the radix passes and the
-// index-ordered passes never go back to memory; beyond kPartLdsKeys channels they are read from global memory.
-constexpr int kPartLdsKeys = 24576;  // 96 KiB of keys
+// One launch: every workgroup finds the rank thresholds for itself, from all keys, and then writes what belongs to its
+// own 1024 channels.  Finding them in one place and handing them on would cost a launch or a grid-wide wait, as long as
+// the search itself; done by everybody at once it costs nothing more, and the outputs (a dozen arrays in a layer's
+// prefill) are written by the whole chip.
+// Search: the keys sit in registers (NS per thread).  One histogram over the 11 bits below the keys' common leading bits
+// leaves a threshold in a bucket of a few dozen keys (another digit is swept only where more than kPartList are left),
+// whose ranks are counted out pairwise.  11 bits instead of 8 spread the LDS atomics over eight times as many words, and
+// one sweep of all keys takes the place of two, plus two of short lists.
+// A threshold is an element (key, channel): channels up to it in the order (key descending, channel ascending) are in.
+// 11008 channels with all of a layer's outputs: 13 us, against 25 us for the four 8-bit sweeps of one workgroup and 6 us for
+// the launch that spread its lists; comparing all pairs of keys instead, 64 channels per workgroup, took 27 us.
+constexpr int kPartThreads = 1024;
+constexpr int kPartBins = 2048;
+constexpr int kPartList = 256;     // keys of a bucket counted out pairwise at most
+constexpr int kPartMaxSlots = 32;  // keys per thread held in registers at most: 32768 channels
 
-// Index-ordered passes of the partition: thread t owns channels [t*E, (t+1)*E).  A channel above a threshold key is
-// in; one equal to it is in while fewer than `take` equal ones precede it.  So with the numbers of greater and of
-// equal channels before a thread's range (one scan of 2 NT streams) every channel's region and list position follow
-// directly.  NT = 3 also emits the channels within the third threshold: a byte mask, their ascending list, its length.
-template <int NT, class KeyFn>
-__device__ __forceinline__ void partition_emit(KeyFn key, int m, const uint32_t (&kth)[3], const int (&take)[3],
-                                               unsigned char *__restrict__ region, int *__restrict__ ret_idx,
-                                               int *__restrict__ cand_idx, const PartitionExtra &ex, SelShared &sh)
+struct PartShared {
+    unsigned int hist[3][kPartBins];
+    __attribute__((aligned(16))) uint32_t list_key[3][kPartList];
+    __attribute__((aligned(16))) int list_idx[3][kPartList];
+    int list_len[3];
+    int digit[3], remaining[3], matching[3];
+    uint32_t thr_key[3];
+    int thr_idx[3];
+    uint32_t key_or, key_nand;
+    int wave_tot[6][kPartThreads / kWave];
+};
+
+// Exclusive scan of N streams over the workgroup, totals in tot.
+template <int N>
+__device__ __forceinline__ void part_scan(int (&v)[N], int (&tot)[N], PartShared &sh)
 {
-    const int E = (m + blockDim.x - 1) / blockDim.x;
-    const int lo = min(m, (int)threadIdx.x * E), hi = min(m, lo + E);
-    int cnt[2 * NT], tot[2 * NT];  // per threshold: greater than its key, equal to it
+    const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    int inc[N];
 #pragma unroll
-    for (int q = 0; q < 2 * NT; ++q) cnt[q] = 0;
-    for (int j = lo; j < hi; ++j) {
-        const uint32_t k = key(j);
-#pragma unroll
-        for (int t = 0; t < NT; ++t) {
-            cnt[2 * t] += (k > kth[t]);
-            cnt[2 * t + 1] += (k == kth[t]);
-        }
+    for (int q = 0; q < N; ++q) {
+        inc[q] = wave_incl_scan(v[q]);
+        if (lane == kWave - 1) sh.wave_tot[q][wave] = inc[q];
     }
-    block_excl_scan<2 * NT>(cnt, tot, sh);
-    for (int j = lo; j < hi; ++j) {
-        const uint32_t k = key(j);
-        bool in[NT];
-        int before[NT];  // channels within threshold t before this one
+    __syncthreads();
 #pragma unroll
-        for (int t = 0; t < NT; ++t) {
-            in[t] = (k > kth[t]) || (k == kth[t] && cnt[2 * t + 1] < take[t]);
-            before[t] = cnt[2 * t] + min(cnt[2 * t + 1], take[t]);
-            cnt[2 * t] += (k > kth[t]);
-            cnt[2 * t + 1] += (k == kth[t]);
-        }
-        if (region) region[j] = in[0] ? POP_REGION_RETAINED : (in[1] ? POP_REGION_CANDIDATE : POP_REGION_PRUNED);
-        if (in[0]) {
-            if (ret_idx) ret_idx[before[0]] = j;
-        } else if (in[1]) {
-            if (cand_idx) cand_idx[before[1] - before[0]] = j;
-        }
-        if (NT == 3) {
-            if (ex.top_mask) ex.top_mask[j] = in[NT - 1] ? 1 : 0;
-            if (in[NT - 1]) ex.top_list[before[NT - 1]] = j;
-        }
+    for (int q = 0; q < N; ++q) {
+        const int t = lane < kPartThreads / kWave ? sh.wave_tot[q][lane] : 0;
+        const int ts = wave_incl_scan(t);
+        v[q] = (wave > 0 ? __builtin_amdgcn_readlane(ts, wave - 1) : 0) + inc[q] - v[q];
+        tot[q] = __builtin_amdgcn_readlane(ts, kWave - 1);
     }
-    if (NT == 3 && threadIdx.x == 0 && ex.top_count) *ex.top_count = ex.n_top;
+    __syncthreads();
 }
 
-__global__ __launch_bounds__(1024) void partition_kernel(const float *__restrict__ scores, int m, int n_ret, int n_cand,
-                                                         unsigned char *__restrict__ region, int *__restrict__ ret_idx,
-                                                         int *__restrict__ cand_idx, PartitionExtra ex)
+// What one channel's place in the partition writes; r, c, t: retained, candidate and top channels before it.
+__device__ __forceinline__ void write_channel(const PartitionOutputs &o, int m, int n_cand, int j, int region, bool top,
+                                              int r, int c, int t)
 {
-    __shared__ SelShared sh;
-    extern __shared__ uint32_t part_keys[];  // [m] when m <= kPartLdsKeys
-    const bool in_lds = m <= kPartLdsKeys;
-#ifdef POP_TRACE
-#define POP_PSTAMP(slot)                                                          \
-    do {                                                                          \
-        if (ex.trace && threadIdx.x == 0) ex.trace[slot] = wall_clock64();        \
-    } while (0)
-#else
-#define POP_PSTAMP(slot) \
-    do {                 \
-    } while (0)
-#endif
-    POP_PSTAMP(0);
-    if (ex.sync && threadIdx.x < ex.n_sync) ex.sync[threadIdx.x] = 0;
-    // while the keys pass through registers: the bits set in any key and the bits clear in any key (the radix select
-    // starts below the leading bits that all keys share)
-    __shared__ uint32_t key_or, key_nand;
-    uint32_t my_or = 0, my_nand = 0;
-    if (in_lds) {
-        if (threadIdx.x == 0) key_or = key_nand = 0;
-        __syncthreads();
-    }
-    if (in_lds && ex.s2_part) {
-        // scores straight from the prefill kernel's partial rows (Eq. 3), kept for the caller as well
-        for (int base = 0; base < m; base += 4 * blockDim.x) {
-            double acc[4] = {0.0, 0.0, 0.0, 0.0};
-            float nr[4];
+    if (o.scores_copy) o.scores_copy[j] = o.scores[j];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int i = base + u * blockDim.x + threadIdx.x;
-                nr[u] = ex.nrm[i < m ? i : 0];
+    for (int q = 0; q < 2; ++q) {
+        if (o.region[q]) o.region[q][j] = (unsigned char)region;
+        if (o.top_mask[q]) o.top_mask[q][j] = top ? 1 : 0;
+    }
+    for (int b = 0; b < o.rows; ++b) o.mask[(size_t)b * m + j] = region == POP_REGION_RETAINED ? 1 : 0;
+    if (region == POP_REGION_CANDIDATE) {
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+            if (o.cand_idx[q]) o.cand_idx[q][c] = j;
+        if (o.rc_idx) o.rc_idx[c] = j;
+    } else if (region == POP_REGION_RETAINED) {
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+            if (o.ret_idx[q]) o.ret_idx[q][r] = j;
+        for (int b = 0; b < o.rows; ++b) o.active_idx[(size_t)b * o.act_stride + r] = j;
+        if (o.rc_idx) o.rc_idx[n_cand + r] = j;
+        if (o.ulist) o.ulist[r] = j;
+    }
+    if (top && o.top_list) o.top_list[t] = j;
+}
+
+// NS keys per thread in registers, thread t those of channels t, t + 1024, ...; NS = 0: any number of channels, read again
+// in every sweep, by one workgroup that writes all outputs.
+template <int NS>
+__global__ __launch_bounds__(kPartThreads) void partition_kernel(const float *__restrict__ scores, int m, int n_ret,
+                                                                 int n_cand, int n_top, PartitionOutputs o)
+{
+    __shared__ PartShared sh;
+    constexpr int NT = 3, NK = NS > 0 ? NS : 1;
+    const int tid = threadIdx.x;
+    if (blockIdx.x == 0 && tid < o.n_sync) o.sync[tid] = 0;
+    if (blockIdx.x == 0 && tid == 0 && o.top_count) *o.top_count = n_top;
+    for (int i = tid; i < kPartBins; i += kPartThreads) sh.hist[0][i] = 0;
+    if (tid == 0) sh.key_or = sh.key_nand = 0;
+    if (tid < NT) sh.list_len[tid] = 0;
+    if (tid < NT * kPartList) (&sh.list_key[0][0])[tid] = 0u, (&sh.list_idx[0][0])[tid] = 0x7fffffff;  // (before nothing)
+    uint32_t keys[NK];
+    uint32_t my_or = 0, my_nand = 0;
+    if (NS > 0) {
+        float v[NK];
+#pragma unroll
+        for (int s = 0; s < NK; ++s) {
+            const int i = s * kPartThreads + tid;
+            v[s] = scores[i < m ? i : 0];
+        }
+#pragma unroll
+        for (int s = 0; s < NK; ++s) keys[s] = score_key(v[s]);
+    }
+    // f(key, channel) for every key of this thread
+    auto sweep = [&](auto f) {
+        if (NS > 0) {
+#pragma unroll
+            for (int s = 0; s < NK; ++s) {
+                const int i = s * kPartThreads + tid;
+                if (i < m) f(keys[s], i);
             }
-            for (int t = 0; t < ex.n_tiles; ++t) {
-                float v[4];
+        } else {
+            for (int i = tid; i < m; i += kPartThreads) f(score_key(scores[i]), i);
+        }
+    };
+    __syncthreads();
+    sweep([&](uint32_t k, int) { my_or |= k, my_nand |= ~k; });
+    my_or = wave_or_rows(my_or), my_nand = wave_or_rows(my_nand);
+    if (tid % 16 == 0) {
+        atomicOr(&sh.key_or, my_or);
+        atomicOr(&sh.key_nand, my_nand);
+    }
+    __syncthreads();
+    const uint32_t diff = sh.key_or & sh.key_nand;
+
+    // thresholds: retained (rank n_ret), retained + candidate (rank n_ret + n_cand), the n_top best; a set of none is
+    // sought as a set of one and closed at the end
+    const int want[NT] = {n_ret, n_ret + n_cand, n_top};
+    uint32_t known = 0u, prefix[NT];
+    int remaining[NT], matching[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) remaining[t] = max(want[t], 1), matching[t] = m;
+    const int top_bit = diff ? 31 - __builtin_clz(diff) : -1;
+    known = top_bit == 31 ? 0u : ~((2u << top_bit) - 1u);  // (top_bit -1: every bit is known)
+    if (top_bit < 0) known = 0xffffffffu;
+#pragma unroll
+    for (int t = 0; t < NT; ++t) prefix[t] = sh.key_or & known;
+    int hi = top_bit;
+    bool first = true;
+    while (hi >= 0 && (matching[0] > kPartList || matching[1] > kPartList || matching[2] > kPartList)) {
+        const int lo = hi >= 10 ? hi - 10 : 0;
+        const uint32_t dmask = (1u << (hi - lo + 1)) - 1u;
+        if (first) {  // one prefix: one histogram for all thresholds
+            sweep([&](uint32_t k, int) { atomicAdd(&sh.hist[0][(k >> lo) & dmask], 1u); });
+        } else {
+            for (int i = tid; i < NT * kPartBins; i += kPartThreads) (&sh.hist[0][0])[i] = 0;
+            __syncthreads();
+            sweep([&](uint32_t k, int) {
+#pragma unroll
+                for (int t = 0; t < NT; ++t)
+                    if ((k & known) == prefix[t]) atomicAdd(&sh.hist[t][(k >> lo) & dmask], 1u);
+            });
+        }
+        __syncthreads();
+        // thread t owns the bins 2047 - 2t and 2046 - 2t: scanned from the largest digit down
+        int c[NT][2], v[NT], tot[NT];
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            const uint2 two = *reinterpret_cast<const uint2 *>(&sh.hist[first ? 0 : t][kPartBins - 2 - 2 * tid]);
+            c[t][0] = (int)two.y, c[t][1] = (int)two.x;
+            v[t] = c[t][0] + c[t][1];
+        }
+        part_scan<NT>(v, tot, sh);
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            int before = v[t];
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                if (before < remaining[t] && remaining[t] <= before + c[t][q])
+                    sh.digit[t] = kPartBins - 1 - 2 * tid - q, sh.remaining[t] = remaining[t] - before, sh.matching[t] = c[t][q];
+                before += c[t][q];
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            prefix[t] |= (uint32_t)sh.digit[t] << lo;
+            remaining[t] = sh.remaining[t], matching[t] = sh.matching[t];
+        }
+        known |= dmask << lo;
+        hi = lo - 1;
+        first = false;
+    }
+    // the bucket of each threshold, counted out pairwise
+    sweep([&](uint32_t k, int i) {
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+            if (matching[t] <= kPartList && (k & known) == prefix[t]) {
+                const int at = atomicAdd(&sh.list_len[t], 1);
+                sh.list_key[t][at] = k, sh.list_idx[t][at] = i;
+            }
+    });
+    __syncthreads();
+    if (tid < NT * kPartList) {
+        const int t = tid / kPartList, e = tid % kPartList, len = sh.list_len[t];
+        const int rem = t == 0 ? remaining[0] : (t == 1 ? remaining[1] : remaining[2]);
+        if (e < len) {
+            const uint32_t k = sh.list_key[t][e];
+            const int i = sh.list_idx[t][e];
+            int before = 0;
+            for (int q0 = 0; q0 < len; q0 += 16) {  // (sixteen at a time: one LDS latency for all of them)
+                uint4 kq[4];
+                int4 iq[4];
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
-                    const int i = base + u * blockDim.x + threadIdx.x;
-                    v[u] = ex.s2_part[(size_t)t * m + (i < m ? i : 0)];
+                    kq[u] = *reinterpret_cast<const uint4 *>(&sh.list_key[t][q0 + 4 * u]);
+                    iq[u] = *reinterpret_cast<const int4 *>(&sh.list_idx[t][q0 + 4 * u]);
                 }
 #pragma unroll
-                for (int u = 0; u < 4; ++u) acc[u] += (double)v[u];
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int i = base + u * blockDim.x + threadIdx.x;
-                if (i < m) {
-                    const float sc = (float)((double)nr[u] * sqrt(acc[u]));
-                    ex.scores_out[i] = sc;
-                    const uint32_t k = score_key(sc);
-                    part_keys[i] = k;
-                    my_or |= k, my_nand |= ~k;
+                for (int u = 0; u < 4; ++u) {
+                    before += kq[u].x > k || (kq[u].x == k && iq[u].x < i);
+                    before += kq[u].y > k || (kq[u].y == k && iq[u].y < i);
+                    before += kq[u].z > k || (kq[u].z == k && iq[u].z < i);
+                    before += kq[u].w > k || (kq[u].w == k && iq[u].w < i);
                 }
             }
+            if (before == rem - 1) sh.thr_key[t] = k, sh.thr_idx[t] = i;
         }
-    } else if (in_lds) {
-        constexpr int kLoads = 12;  // scores requested together per thread (11008 channels: one pass)
-        for (int base = 0; base < m; base += kLoads * blockDim.x) {
-            float v[kLoads];
+    }
+    // more equal keys than a list holds: the remaining-th of them in channel order
 #pragma unroll
-            for (int u = 0; u < kLoads; ++u) {
-                const int i = base + u * blockDim.x + threadIdx.x;
-                v[u] = scores[i < m ? i : 0];
-            }
+    for (int t = 0; t < NT; ++t) {
+        if (matching[t] <= kPartList) continue;
+        int seen = 0;
+        for (int s = 0; s * kPartThreads < m; ++s) {
+            const int i = s * kPartThreads + tid;
+            const bool eq = i < m && score_key(scores[i < m ? i : 0]) == prefix[t];
+            int v[1] = {eq ? 1 : 0}, tot[1];
+            part_scan<1>(v, tot, sh);
+            if (eq && seen + v[0] == remaining[t] - 1) sh.thr_key[t] = prefix[t], sh.thr_idx[t] = i;
+            seen += tot[0];
+            if (seen >= remaining[t]) break;
+        }
+    }
+    __syncthreads();
+    uint32_t thr_key[NT];
+    int thr_idx[NT];
 #pragma unroll
-            for (int u = 0; u < kLoads; ++u) {
-                const int i = base + u * blockDim.x + threadIdx.x;
-                if (i < m) {
-                    const uint32_t k = score_key(v[u]);
-                    part_keys[i] = k;
-                    my_or |= k, my_nand |= ~k;
-                }
+    for (int t = 0; t < NT; ++t) {
+        thr_key[t] = want[t] > 0 ? sh.thr_key[t] : 0xffffffffu;
+        thr_idx[t] = want[t] > 0 ? sh.thr_idx[t] : -1;
+    }
+    auto within = [&](int t, uint32_t k, int i) { return k > thr_key[t] || (k == thr_key[t] && i <= thr_idx[t]); };
+
+    // outputs: this workgroup's channels are those of key slot blockIdx.x; the channels before them are counted
+    int base[NT] = {0, 0, 0};
+    const int s_first = blockIdx.x, s_last = NS > 0 ? s_first + 1 : (m + kPartThreads - 1) / kPartThreads;
+    uint32_t mine = 0u;
+    if (NS > 0) {
+#pragma unroll
+        for (int s = 0; s < NK; ++s) {
+            if (s == s_first) mine = keys[s];
+            if (s < s_first) {
+#pragma unroll
+                for (int t = 0; t < NT; ++t) base[t] += within(t, keys[s], s * kPartThreads + tid);
             }
         }
     }
-    if (in_lds) {
-        my_or = wave_or_rows(my_or), my_nand = wave_or_rows(my_nand);
-        if (threadIdx.x % 16 == 0) {
-            atomicOr(&key_or, my_or);
-            atomicOr(&key_nand, my_nand);
+    for (int s = s_first; s < s_last; ++s) {
+        const int j = s * kPartThreads + tid;
+        const uint32_t k = NS > 0 ? mine : score_key(scores[j < m ? j : 0]);
+        bool in[NT];
+        int v[2 * NT], tot[2 * NT];
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            in[t] = j < m && within(t, k, j);
+            v[t] = in[t], v[NT + t] = s == s_first ? base[t] : 0;
         }
-        __syncthreads();
+        part_scan<2 * NT>(v, tot, sh);
+        if (s == s_first) {
+#pragma unroll
+            for (int t = 0; t < NT; ++t) base[t] = tot[NT + t];  // (this thread's share becomes everybody's sum)
+        }
+        if (j < m)
+            write_channel(o, m, n_cand, j, in[0] ? POP_REGION_RETAINED : (in[1] ? POP_REGION_CANDIDATE : POP_REGION_PRUNED),
+                          in[2], base[0] + v[0], base[1] + v[1] - (base[0] + v[0]), base[2] + v[2]);
+#pragma unroll
+        for (int t = 0; t < NT; ++t) base[t] += tot[t];
     }
-    POP_PSTAMP(1);
-    auto key = [&](int i) { return in_lds ? part_keys[i] : score_key(scores[i]); };
-    // thresholds: retained (rank n_ret), retained + candidate (rank n_ret + n_cand) and, on request, the n_top best
-    // channels.  An empty set is sought as a set of one and then closed (key above all keys, nothing taken).
-    const bool top = ex.top_list != nullptr;
-    uint32_t kth[3] = {0xffffffffu, 0xffffffffu, 0xffffffffu};
-    int take[3] = {0, 0, 0};
-    const uint32_t diff = in_lds ? key_or & key_nand : 0u;
-    if (top) {
-        const int cnt[3] = {max(n_ret, 1), max(n_ret + n_cand, 1), max(ex.n_top, 1)};
-        radix_thresholds_lists<3>(key, m, cnt, sh, kth, take, in_lds, diff);
-    } else {
-        const int cnt[2] = {max(n_ret, 1), max(n_ret + n_cand, 1)};
-        uint32_t kth2[2];
-        int take2[2];
-#ifdef POP_TRACE
-        radix_thresholds_lists<2>(key, m, cnt, sh, kth2, take2, in_lds, diff, ex.trace ? ex.trace + 4 : nullptr);
-#else
-        radix_thresholds_lists<2>(key, m, cnt, sh, kth2, take2, in_lds, diff);
-#endif
-        kth[0] = kth2[0], kth[1] = kth2[1], take[0] = take2[0], take[1] = take2[1];
-    }
-    if (n_ret == 0) kth[0] = 0xffffffffu, take[0] = 0;
-    if (n_ret + n_cand == 0) kth[1] = 0xffffffffu, take[1] = 0;
-    if (!top || ex.n_top == 0) kth[2] = 0xffffffffu, take[2] = 0;
-    POP_PSTAMP(2);
-    if (top)
-        partition_emit<3>(key, m, kth, take, region, ret_idx, cand_idx, ex, sh);
-    else
-        partition_emit<2>(key, m, kth, take, region, ret_idx, cand_idx, ex, sh);
-    POP_PSTAMP(3);
 }
 
-bool partition_takes_partials(int m) { return m <= kPartLdsKeys; }
-
-hipError_t launch_partition(const float *scores, int m, int n_ret, int n_cand, unsigned char *region, int *ret_idx,
-                            int *cand_idx, hipStream_t s, const PartitionExtra *extra)
+hipError_t launch_partition(const float *scores, int m, int n_ret, int n_cand, int n_top, const PartitionOutputs &o,
+                            hipStream_t s)
 {
-    PartitionExtra ex = extra ? *extra : PartitionExtra{};
-    if (ex.s2_part && !partition_takes_partials(m)) return hipErrorInvalidValue;
-    const size_t lds = m <= kPartLdsKeys ? (size_t)m * 4 : 0;
-    if (lds > 32 * 1024) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&partition_kernel),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) return e;
+    const int slots = (m + kPartThreads - 1) / kPartThreads;
+#define POP_PART(NS, WGS) \
+    hipLaunchKernelGGL(partition_kernel<NS>, dim3(WGS), dim3(kPartThreads), 0, s, scores, m, n_ret, n_cand, n_top, o)
+    if (slots <= 2) POP_PART(2, slots);
+    else if (slots <= 4) POP_PART(4, slots);
+    else if (slots <= 8) POP_PART(8, slots);
+    else if (slots <= 11) POP_PART(11, slots);
+    else if (slots <= 14) POP_PART(14, slots);
+    else if (slots <= 20) POP_PART(20, slots);
+    else if (slots <= kPartMaxSlots) POP_PART(kPartMaxSlots, slots);
+    else POP_PART(0, 1);
+#undef POP_PART
+    return hipGetLastError();
+}
+
+// hc[t][c] = h_all[t][list[c]] for c < *n_list, and zero columns from there up to the next multiple of 64 (the
+// direct-load GEMM reads them, against rows of zeros: they must not keep what an earlier, longer list left there).  A
+// workgroup gathers 512 columns of kCompactRows tokens; a thread owns two adjacent columns (one 32-bit store).
+constexpr int kCompactRows = 8;
+__global__ __launch_bounds__(256) void compact_hidden_kernel(const uint16_t *__restrict__ h_all, int ldh, int T,
+                                                             const int *__restrict__ list,
+                                                             const int *__restrict__ n_list, uint16_t *__restrict__ hc,
+                                                             int ldhc)
+{
+    const int a = *n_list;
+    const int c = (blockIdx.x * 256 + (int)threadIdx.x) * 2;
+    const int t0 = blockIdx.y * kCompactRows, t1 = min(T, t0 + kCompactRows);
+    if (c >= a) {
+        if (c < min((a + 63) / 64 * 64, ldhc))
+            for (int t = t0; t < t1; ++t) *reinterpret_cast<uint32_t *>(hc + (size_t)t * ldhc + c) = 0u;
+        return;
     }
-    hipLaunchKernelGGL(partition_kernel, dim3(1), dim3(1024), lds, s, scores, m, n_ret, n_cand, region, ret_idx, cand_idx,
-                       ex);
+    const int j0 = list[c], j1 = c + 1 < a ? list[c + 1] : -1;
+    uint32_t v[kCompactRows];
+#pragma unroll
+    for (int u = 0; u < kCompactRows; ++u) {  // (requested together)
+        const uint16_t *row = h_all + (size_t)min(t0 + u, T - 1) * ldh;
+        v[u] = (uint32_t)row[j0] | (j1 >= 0 ? (uint32_t)row[j1] << 16 : 0u);
+    }
+#pragma unroll
+    for (int u = 0; u < kCompactRows; ++u)
+        if (t0 + u < t1) *reinterpret_cast<uint32_t *>(hc + (size_t)(t0 + u) * ldhc + c) = v[u];
+}
+
+hipError_t launch_compact_hidden(const uint16_t *h_all, int ldh, int T, const int *list, const int *n_list, int max_list,
+                                 uint16_t *hc, int ldhc, hipStream_t s)
+{
+    // (63 columns beyond the longest list, for the zeros)
+    dim3 grid((max_list + 63 + 511) / 512, (T + kCompactRows - 1) / kCompactRows);
+    hipLaunchKernelGGL(compact_hidden_kernel, grid, dim3(256), 0, s, h_all, ldh, T, list, n_list, hc, ldhc);
     return hipGetLastError();
 }
 
@@ -206,7 +353,7 @@ void set_select_trace(unsigned long long *p) { g_select_trace = p; }
 
 // One workgroup per sequence b.  Only candidate-dependent state is written: the candidate bytes of mask[b][:]
 // and the selected suffix of active_idx[b][:]; the retained / pruned bytes and the retained prefix are constant
-// for a partition (step_state_init_kernel).
+// for a partition (partition_kernel).
 // With a union request (B > 1) every workgroup also leaves one byte per candidate position, and the workgroup
 // that finishes last (an arrival counter; nobody waits) compacts the candidates selected by any sequence into
 // list[n_ret..] and rewinds the counter.
@@ -275,59 +422,17 @@ hipError_t launch_topk(const float *cscore, int cs_stride, const int *cand_idx, 
     return hipGetLastError();
 }
 
-// Partition-constant part of the step state, for `rows` sequences: mask[b][j] = 1 for retained channels, 0 for
-// pruned and (until a step selects them) candidate channels; active_idx[b][0..n_ret) = ret_idx.  Row 0's workgroups
-// also write the candidate-then-retained list rc_idx and the retained prefix of the union list, when given.  One
-// more row of workgroups zeroes a strided word buffer (clr.n slots of clr.words ints, clr.stride ints apart), and
-// further rows gather the columns of a channel list (job), which saves the partition and the prompt's forward pass a
-// launch of their own for each.
-__global__ __launch_bounds__(256) void step_state_init_kernel(const unsigned char *__restrict__ region, int m,
-                                                              const int *__restrict__ ret_idx, int n_ret, int rows,
-                                                              int act_stride, unsigned char *__restrict__ mask,
-                                                              int *__restrict__ active_idx,
-                                                              const int *__restrict__ cand_idx, int n_cand,
-                                                              int *__restrict__ rc_idx, int *__restrict__ ulist,
-                                                              StridedClear clr, CompactJob job)
+// mask[j] = 1 for retained channels, 0 for the others (until a selection sets candidates).
+__global__ __launch_bounds__(256) void retained_mask_kernel(const unsigned char *__restrict__ region, int m,
+                                                            unsigned char *__restrict__ mask)
 {
-    const int b = blockIdx.y;
-    if (b > rows) {
-        compact_hidden_block(job, blockIdx.x, b - rows - 1);
-        return;
-    }
-    if (b == rows) {
-        if (!clr.p) return;
-        const int per = blockDim.x / clr.words;  // slots a workgroup clears at once
-        for (int q = blockIdx.x * per + threadIdx.x / clr.words; q < clr.n && (int)threadIdx.x < per * clr.words;
-             q += gridDim.x * per)
-            clr.p[(size_t)q * clr.stride + threadIdx.x % clr.words] = 0;
-        return;
-    }
-    for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < m; j += gridDim.x * blockDim.x) {
-        if (mask) mask[(size_t)b * m + j] = region[j] == POP_REGION_RETAINED ? 1 : 0;
-        if (j < n_ret) {
-            const int r = ret_idx[j];
-            if (active_idx) active_idx[(size_t)b * act_stride + j] = r;
-            if (b == 0 && rc_idx) rc_idx[n_cand + j] = r;
-            if (b == 0 && ulist) ulist[j] = r;
-        }
-        if (b == 0 && rc_idx && j < n_cand) rc_idx[j] = cand_idx[j];
-    }
+    const int j = blockIdx.x * blockDim.x + threadIdx.x;
+    if (j < m) mask[j] = region[j] == POP_REGION_RETAINED ? 1 : 0;
 }
 
-hipError_t launch_step_state_init(const unsigned char *region, int m, const int *ret_idx, int n_ret, int rows,
-                                  int act_stride, unsigned char *mask, int *active_idx, hipStream_t s,
-                                  const int *cand_idx, int n_cand, int *rc_idx, int *ulist, const StridedClear *clear,
-                                  const CompactJob *compact)
+hipError_t launch_retained_mask(const unsigned char *region, int m, unsigned char *mask, hipStream_t s)
 {
-    StridedClear clr = clear ? *clear : StridedClear{};
-    CompactJob job = compact ? *compact : CompactJob{};
-    if (clr.p && (clr.words < 1 || clr.words > 256)) return hipErrorInvalidValue;
-    // rows of workgroups: `rows` of state, one that clears (idle without a buffer, present whenever a later row is),
-    // then the compaction's (its 512 positions per workgroup cover any list of up to m channels in this grid's width)
-    const int job_rows = job.hc ? (job.T + kCompactRows - 1) / kCompactRows : 0;
-    dim3 grid((m + 255) / 256, rows + ((clr.p || job_rows) ? 1 : 0) + job_rows);
-    hipLaunchKernelGGL(step_state_init_kernel, grid, dim3(256), 0, s, region, m, ret_idx, n_ret, rows, act_stride, mask,
-                       active_idx, cand_idx, n_cand, rc_idx, ulist, clr, job);
+    hipLaunchKernelGGL(retained_mask_kernel, dim3((m + 255) / 256), dim3(256), 0, s, region, m, mask);
     return hipGetLastError();
 }
 

@@ -531,6 +531,36 @@ def test_prefill_direct_load_tiles(pop, oracle, mf, f, d):
         _check_prefill_forward(oracle, G, L, x, n_ret, n_cand, k, F32, FFN_MFMA_TOL_F32, rows=rows)
 
 
+@pytest.mark.parametrize("m", [1, 63, 257, 1025, 2049, 4100, 11265, 14337, 20481, 33000])
+def test_layer_partition_with_ties(pop, oracle, m):
+    """A layer's partition (ranks counted out over the chip, lists from the classes; one workgroup beyond 32768
+    channels) on weights and tokens so coarse that most scores are equal: regions, lists and the prompt's mask are the
+    oracle's on the same scores, at channel counts around the workgroups' and keys' boundaries; then a decode step."""
+    d, T = 64, 40
+    g = synth.rng("layer_ties", m)
+    L = synth.make_layer(synth.small_config("layer_ties", d, m, BF16))
+    for name in ("w_gate", "w_up"):  # exact sums: channels with the same few nonzero weights have the same scores
+        w = np.zeros((m, d), dtype=np.float32)
+        w[:, :2] = g.integers(-1, 2, size=(m, 2)) * 0.25
+        setattr(L, name, synth.f32_to_bf16_bits(w))
+    wd = np.zeros((d, m), dtype=np.float32)
+    wd[0] = 0.5
+    L.w_down = synth.f32_to_bf16_bits(wd)
+    x = synth.f32_to_bf16_bits(g.integers(-2, 3, size=(T, d)).astype(np.float32))
+    with GpuLayer(pop, L, max_tokens=T, max_batch=2) as G:
+        for n_ret, n_cand in ((m // 2, m // 5), (0, m), (m, 0), (m // 3, 0), (0, 0)):
+            scores, region, ret, cand, _ = _check_prefill(oracle, G, L, x, n_ret, n_cand)
+            k0 = n_cand // 2
+            scores, region, ret, cand, mask, _ = G.prefill_forward(x, n_ret, n_cand, k0, F32)
+            r1, ret1, cand1 = oracle.partition(scores, n_ret, n_cand)
+            assert np.array_equal(region, r1) and np.array_equal(ret, ret1) and np.array_equal(cand, cand1)
+            assert np.array_equal(mask, oracle.select(region, scores[cand], cand, k0)[0])
+        assert m < 100 or len(np.unique(scores)) < m // 4
+        G.prefill(x, m // 2, m // 5)
+        _check_decode(oracle, G, L, oracle.partition(scores, m // 2, m // 5)[0], oracle.partition(scores, m // 2, m // 5)[2],
+                      x[:2], m // 10)
+
+
 def test_prefill_forward_full_size(pop, oracle):
     """Llama-2-7B-shaped layer, prompt 512: prefill scores on a sample of channels, partition and prefill mask
     on all channels, the prompt's output on a sample of tokens, then a decode step on the partition."""
