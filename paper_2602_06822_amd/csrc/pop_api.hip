@@ -91,8 +91,11 @@ struct pop_layer {
     size_t ffn_hall_cap = 0;           // elements
     float *ffn_part = nullptr;         // [splits][tokens][d]: partial outputs of the split contraction
     size_t ffn_part_cap = 0;           // elements
-    unsigned char *ffn_any = nullptr;  // [m]: channels active in any row of a per-token mask
+    unsigned char *ffn_any = nullptr;  // [m]: the prompt's mask, or channels active in any row of a per-token mask
     int *top_list = nullptr;           // [m] + 1: the prompt's own active channels (ascending), then their number
+    // pruned FFN of a few tokens
+    int chunk = 0;                     // tokens the decode kernels take at a time
+    float *hs = nullptr;               // [kPreciseMaxTokens][m] float32 (bf16 layers with d % 64 == 0)
     uint16_t *zero_row = nullptr;      // 256 bytes of zeros: stands in for weight rows beyond a channel list
 };
 
@@ -133,6 +136,11 @@ int copy_step_outputs(pop_layer *L, int B, float *cand_scores, unsigned char *ma
 // From this many tokens on a bf16 layer's stand-alone pruned FFN runs on the matrix cores (below it, the decode
 // kernels take the tokens eight at a time).
 constexpr int kFfnMfmaMinTokens = 32;
+
+// From this many sequences on a bf16 layer's batched step takes the matrix cores for its down projection: the vector
+// kernel's multiply-adds grow with the batch (13B shape: 22.2 us at 4 sequences, 27.8 at 8), the matrix-core kernel's time
+// does not (22 us).
+constexpr int kSkinnyMinBatch = 5;
 
 // hipMalloc that leaves no pending error behind when it fails (a later launch check would report it as its own).
 bool dev_alloc(void **p, size_t bytes)
@@ -181,8 +189,6 @@ int ffn_scratch(pop_layer *L, int T, bool keep_all, int *ldh, int *n_split, hipS
     if (rc == POP_OK && part_rows)
         rc = grow((void **)&L->ffn_part, &L->ffn_part_cap, part_rows * L->d, sizeof(float));
     if (rc == POP_OK && keep_all) rc = grow((void **)&L->ffn_hall, &L->ffn_hall_cap, (size_t)T * *ldh, sizeof(uint16_t));
-    if (rc == POP_OK && !L->ffn_any && !dev_alloc((void **)&L->ffn_any, ((size_t)L->m + 3) / 4 * 4))
-        rc = POP_ENOMEM;
     return rc;
 }
 
@@ -345,7 +351,7 @@ int pop_layer_destroy(pop_layer_t *L)
     if (!L) return POP_EINVAL;
     void *ptrs[] = {L->w,      L->nrm, L->scores, L->s2_part, L->region,     L->ret_idx,  L->cand_idx, L->rc_idx,
                     L->h,      L->cscore, L->mask, L->selflag, L->active_idx, L->n_active, L->ulist, L->n_ulist,  L->partial,
-                    L->sync,   L->hc, L->selw, L->fctr, L->pf_ctr, L->ffn_hc, L->ffn_part, L->ffn_any, L->ffn_hall, L->in_s2, L->in_part, L->top_list, L->zero_row};
+                    L->sync,   L->hc, L->selw, L->fctr, L->pf_ctr, L->ffn_hc, L->ffn_part, L->ffn_any, L->ffn_hall, L->in_s2, L->in_part, L->top_list, L->zero_row, L->hs};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
     delete L;
@@ -391,7 +397,16 @@ int pop_layer_create(pop_layer_t **out, int d, int m, pop_dtype_t wdtype, const 
     if (L->wg_target > fused_max_workgroups()) L->wg_target = fused_max_workgroups();
     if (const char *e = getenv("POP_WAIT_LIMIT")) L->spin_limit = atoi(e) < 0 ? 0 : atoi(e);  // (tuning, tests)
 
-    const size_t mm = (size_t)m, B = (size_t)max_batch;
+    // tokens of a stand-alone FFN that the decode kernels take at a time: as many as they can, whatever the batch
+    L->chunk = max_batch;
+    while (L->chunk < POP_MAX_BATCH && (long long)(L->chunk + 1) * d * esize <= lds_max) ++L->chunk;
+    const bool precise = precise_gateup_takes(is_bf16, d, 1);
+
+    const size_t mm = (size_t)m, B = (size_t)max_batch, C = (size_t)L->chunk;
+    size_t partial_rows = (size_t)L->n_slabs * C;
+    if (partial_rows < (size_t)fused_max_workgroups()) partial_rows = (size_t)fused_max_workgroups();
+    if (is_bf16 && partial_rows < (size_t)skinny_down_slabs(d, n_cu) * kSkMaxTokens)
+        partial_rows = (size_t)skinny_down_slabs(d, n_cu) * kSkMaxTokens;
     struct Req { void **p; size_t bytes; };
     Req reqs[] = {
         {&L->w, mm * 3 * d * esize},
@@ -402,7 +417,7 @@ int pop_layer_create(pop_layer_t **out, int d, int m, pop_dtype_t wdtype, const 
         {(void **)&L->ret_idx, mm * 4},
         {(void **)&L->cand_idx, mm * 4},
         {(void **)&L->rc_idx, mm * 4},
-        {(void **)&L->h, B * mm * 4},
+        {(void **)&L->h, C * mm * 4},
         {(void **)&L->cscore, B * mm * 4},
         {(void **)&L->mask, B * mm},
         {(void **)&L->selflag, (size_t)POP_MAX_BATCH * mm},
@@ -410,15 +425,18 @@ int pop_layer_create(pop_layer_t **out, int d, int m, pop_dtype_t wdtype, const 
         {(void **)&L->n_active, B * 4},
         {(void **)&L->ulist, mm * 4},
         {(void **)&L->n_ulist, 4},
-        {(void **)&L->partial, ((size_t)L->n_slabs * B > (size_t)fused_max_workgroups() ? (size_t)L->n_slabs * B
-                                                                                        : (size_t)fused_max_workgroups()) * d * 4},
+        {(void **)&L->partial, partial_rows * d * 4},
         {(void **)&L->sync, 64},
         {(void **)&L->hc, mm * 8},
         {(void **)&L->selw, fused_selw_words() * 8},
         {(void **)&L->fctr, 64},
         {(void **)&L->pf_ctr, mm * 4},
+        {(void **)&L->ffn_any, (mm + 3) / 4 * 4},
+        {(void **)&L->top_list, (mm + 1) * 4},
+        {(void **)&L->hs, precise ? (size_t)kPreciseMaxTokens * mm * 4 : 0},
     };
     for (const Req &r : reqs) {
+        if (r.bytes == 0) continue;
         hipError_t e = hipMalloc(r.p, r.bytes);
         if (e != hipSuccess) {
             (void)hipGetLastError();
@@ -458,6 +476,7 @@ int pop_prefill_partition(pop_layer_t *L, const void *x, int T, int n_ret, int n
     if (n_ret < 0 || n_cand < 0 || (long long)n_ret + n_cand > L->m) return POP_ESHAPE;
     hipStream_t s = as_stream(stream);
     const int m = L->m;
+    const bool few = !L->input_side && precise_gateup_takes(L->is_bf16, L->d, T);
     L->has_partition = false;
     L->has_step = false;
     if (T == 0) {
@@ -468,10 +487,13 @@ int pop_prefill_partition(pop_layer_t *L, const void *x, int T, int n_ret, int n
         POP_HIP(launch_input_side_scores(L->w, L->is_bf16, L->d, L->in_s2, 1, nullptr, m, L->scores, m, s));
     } else {
         const PrefillScores fin{L->pf_ctr, L->nrm, L->scores};
-        POP_HIP(launch_prefill_gateup(L->w, L->is_bf16, L->d, m, x, T, L->s2_part, L->n_cu, s, &fin));
+        if (few)  // (the same launch as pop_prefill_forward's: the same scores, bit for bit)
+            POP_HIP(launch_precise_gateup(L->w, L->d, m, x, T, nullptr, nullptr, L->hs, L->s2_part, &fin, L->n_cu, s));
+        else
+            POP_HIP(launch_prefill_gateup(L->w, L->is_bf16, L->d, m, x, T, L->s2_part, L->n_cu, s, &fin));
     }
     return finish_partition(L, T, n_ret, n_cand, scores, region, ret_idx, cand_idx, s,
-                            T == 0 || L->input_side || prefill_forms_scores(L->is_bf16, T, L->d, m, L->n_cu));
+                            T == 0 || L->input_side || few || prefill_forms_scores(L->is_bf16, T, L->d, m, L->n_cu));
 }
 
 int pop_prefill_forward(pop_layer_t *L, const void *x, int T, int n_ret, int n_cand, int k0, void *y, pop_dtype_t ydtype,
@@ -494,6 +516,8 @@ int pop_prefill_forward(pop_layer_t *L, const void *x, int T, int n_ret, int n_c
     // H of the importance contraction is kept and the output runs on the matrix cores (the input-side importance
     // has no such contraction: partition first, then the masked FFN)
     const bool keep = L->is_bf16 && T >= kFfnMfmaMinTokens && !L->input_side;
+    // a short prompt: H of all channels in float32 from the same pass that scores them
+    const bool few = !L->input_side && precise_gateup_takes(L->is_bf16, d, T);
     L->has_partition = false;
     L->has_step = false;
     int ldh = 0, n_split = 1;
@@ -503,12 +527,14 @@ int pop_prefill_forward(pop_layer_t *L, const void *x, int T, int n_ret, int n_c
         const PrefillScores fin{L->pf_ctr, L->nrm, L->scores};
         POP_HIP(launch_prefill_gateup_keep_bf16(L->w, d, m, x, T, L->s2_part, L->ffn_hall, ldh, L->n_cu, s, &fin));
     } else {
-        if (!L->ffn_any && !dev_alloc((void **)&L->ffn_any, ((size_t)m + 3) / 4 * 4)) return POP_ENOMEM;
         if (T == 0) {
             POP_HIP(launch_fill_int((int *)L->scores, m, 0, s));  // no tokens: all importances zero
         } else if (L->input_side) {
             POP_HIP(launch_input_norms(x, L->is_bf16, T, d, L->in_part, L->in_s2, s));
             POP_HIP(launch_input_side_scores(L->w, L->is_bf16, d, L->in_s2, 1, nullptr, m, L->scores, m, s));
+        } else if (few) {
+            const PrefillScores fin{L->pf_ctr, L->nrm, L->scores};
+            POP_HIP(launch_precise_gateup(L->w, d, m, x, T, nullptr, nullptr, L->hs, L->s2_part, &fin, L->n_cu, s));
         } else {
             const PrefillScores fin{L->pf_ctr, L->nrm, L->scores};
             POP_HIP(launch_prefill_gateup(L->w, L->is_bf16, d, m, x, T, L->s2_part, L->n_cu, s, &fin));
@@ -516,14 +542,14 @@ int pop_prefill_forward(pop_layer_t *L, const void *x, int T, int n_ret, int n_c
     }
     // prefill mask: retained channels plus the best k0 candidates by prefill score, i.e. the n_ret + k0 best channels
     // of the partition's own order: the partition launch emits them as well (mask bytes and ascending list)
-    if (!L->top_list && !dev_alloc((void **)&L->top_list, ((size_t)m + 1) * sizeof(int))) return POP_ENOMEM;
     // (the byte mask only where somebody reads it: the caller, or the path below that works from a mask)
     PartitionOutputs o;
     o.top_list = L->top_list, o.top_count = L->top_list + m;
-    o.top_mask[0] = keep ? nullptr : L->ffn_any, o.top_mask[1] = mask;
+    o.top_mask[0] = keep || few ? nullptr : L->ffn_any, o.top_mask[1] = mask;
     {
         int rc = finish_partition(L, T, n_ret, n_cand, scores, region, ret_idx, cand_idx, s,
-                                  T == 0 || L->input_side || prefill_forms_scores(L->is_bf16, T, L->d, m, L->n_cu), n_ret + k0, o);
+                                  T == 0 || L->input_side || few || prefill_forms_scores(L->is_bf16, T, L->d, m, L->n_cu),
+                                  n_ret + k0, o);
         if (rc != POP_OK) return rc;
     }
     if (T == 0) return POP_OK;  // no token rows to produce
@@ -531,6 +557,11 @@ int pop_prefill_forward(pop_layer_t *L, const void *x, int T, int n_ret, int n_c
         POP_HIP(launch_compact_hidden(L->ffn_hall, ldh, T, L->top_list, L->top_list + m, n_ret + k0, L->ffn_hc, ldh, s));
         POP_HIP(launch_down_gemm_bf16(L->w, d, L->top_list, L->top_list + m, L->ffn_hc, ldh, T, n_split, L->ffn_part, y,
                                       ydtype == POP_BF16, s, L->zero_row));
+        return POP_OK;
+    }
+    if (few) {
+        POP_HIP(launch_skinny_down(L->w, d, m, L->top_list, L->top_list + m, L->hs, nullptr, 0, T, L->partial,
+                                   skinny_down_slabs(d, L->n_cu), y, ydtype == POP_BF16, s));
         return POP_OK;
     }
     const int rc = pop_pruned_ffn(L, x, T, L->ffn_any, 1, y, ydtype, stream);
@@ -656,6 +687,9 @@ int pop_pruned_ffn(pop_layer_t *L, const void *x, int T, const unsigned char *ma
         else if (T == 1)
             POP_HIP(launch_down(L->w, L->is_bf16, d, m, L->active_idx, nullptr, L->n_ret + L->step_k.k[0], L->h,
                                 nullptr, 0, 1, L->partial, L->n_slabs, y, y_bf16, s));
+        else if (L->is_bf16 && T >= kSkinnyMinBatch)
+            POP_HIP(launch_skinny_down(L->w, d, m, L->ulist, L->n_ulist, L->h, L->mask, m, T, L->partial,
+                                       skinny_down_slabs(d, L->n_cu), y, y_bf16, s));
         else
             POP_HIP(launch_down(L->w, L->is_bf16, d, m, L->ulist, L->n_ulist, 0, L->h, L->mask, m, T, L->partial,
                                 L->n_slabs, y, y_bf16, s));
@@ -667,9 +701,22 @@ int pop_pruned_ffn(pop_layer_t *L, const void *x, int T, const unsigned char *ma
     L->has_step = false;  // the step scratch is reused below
     L->ulist_prefix_ok = false;
     if (L->is_bf16 && T >= kFfnMfmaMinTokens) return pruned_ffn_mfma(L, x, T, mask, mask_rows, y, y_bf16, s);
+    if (T > 1 && precise_gateup_takes(L->is_bf16, d, T)) {
+        // a few tokens in one pass over the weights
+        const unsigned char *rows = mask;
+        if (mask_rows > 1) {
+            POP_HIP(launch_mask_any(mask, T, m, L->ffn_any, s));
+            rows = L->ffn_any;
+        }
+        POP_HIP(launch_mask_to_list(rows, 1, m, L->ulist, L->n_ulist, s));
+        POP_HIP(launch_precise_gateup(L->w, d, m, x, T, L->ulist, L->n_ulist, L->hs, nullptr, nullptr, L->n_cu, s));
+        POP_HIP(launch_skinny_down(L->w, d, m, L->ulist, L->n_ulist, L->hs, mask_rows > 1 ? mask : nullptr, m, T, L->partial,
+                                   skinny_down_slabs(d, L->n_cu), y, y_bf16, s));
+        return POP_OK;
+    }
     if (mask_rows == 1) POP_HIP(launch_mask_to_list(mask, 1, m, L->ulist, L->n_ulist, s));
-    for (int t0 = 0; t0 < T; t0 += L->max_batch) {
-        const int Bc = (T - t0 < L->max_batch) ? T - t0 : L->max_batch;
+    for (int t0 = 0; t0 < T; t0 += L->chunk) {
+        const int Bc = (T - t0 < L->chunk) ? T - t0 : L->chunk;
         const unsigned char *mk = mask_rows == 1 ? nullptr : mask + (size_t)t0 * m;
         if (mk) POP_HIP(launch_mask_to_list(mk, Bc, m, L->ulist, L->n_ulist, s));
         const char *xc = (const char *)x + (size_t)t0 * d * L->esize;
@@ -747,7 +794,6 @@ int pop_layer_reserve_prompt(pop_layer_t *L, int T, void *stream)
     if (!L->is_bf16 || T < kFfnMfmaMinTokens) return POP_OK;  // those forward passes use the layer's fixed scratch
     int ldh = 0, n_split = 1;
     { int rc = ffn_scratch(L, T, true, &ldh, &n_split, as_stream(stream), true); if (rc != POP_OK) return rc; }
-    if (!L->top_list && !dev_alloc((void **)&L->top_list, ((size_t)L->m + 1) * sizeof(int))) return POP_ENOMEM;
     return POP_OK;
 }
 

@@ -428,15 +428,16 @@ __global__ __launch_bounds__(256) void down_kernel(const typename V::vec_t *__re
 
 // y[b][o] = sum over slabs of partial[slab][b][o]; total = B*d outputs.  A workgroup owns 64 outputs; its 4
 // waves each sum a contiguous quarter of the slabs (independent loads, added in slab order) and are combined in
-// wave order, so the result does not depend on scheduling.
+// wave order, so the result does not depend on scheduling.  Sums in double: the slabs' partial sums are of the size of
+// the result, so a float32 chain over them would cost more than everything before it.
 __global__ __launch_bounds__(256) void down_reduce_kernel(const float *__restrict__ partial, int n_slabs, int total,
                                                           void *__restrict__ y, int y_bf16)
 {
-    __shared__ float part[4][kWave];
+    __shared__ double part[4][kWave];
     const int lane = threadIdx.x % kWave, q = threadIdx.x / kWave;
     const int i = blockIdx.x * kWave + lane;
     const int per = (n_slabs + 3) / 4, s0 = min(n_slabs, q * per), s1 = min(n_slabs, s0 + per);
-    float acc = 0.f;
+    double acc = 0.0;
     if (i < total) {
         int s = s0;
         for (; s + 8 <= s1; s += 8) {
@@ -444,14 +445,14 @@ __global__ __launch_bounds__(256) void down_reduce_kernel(const float *__restric
 #pragma unroll
             for (int u = 0; u < 8; ++u) v[u] = partial[(size_t)(s + u) * total + i];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) acc += v[u];
+            for (int u = 0; u < 8; ++u) acc += (double)v[u];
         }
-        for (; s < s1; ++s) acc += partial[(size_t)s * total + i];
+        for (; s < s1; ++s) acc += (double)partial[(size_t)s * total + i];
     }
     part[q][lane] = acc;
     __syncthreads();
     if (q == 0 && i < total) {
-        float v = ((part[0][lane] + part[1][lane]) + part[2][lane]) + part[3][lane];
+        const float v = (float)(((part[0][lane] + part[1][lane]) + part[2][lane]) + part[3][lane]);
         if (y_bf16)
             ((uint16_t *)y)[i] = f32_to_bf16(v);
         else
@@ -501,6 +502,194 @@ hipError_t launch_down(const void *w, int is_bf16, int d, int m, const int *list
                                       y, y_bf16, s);
     return down_dispatch<VecF32>(w, d / 4, d, m, list, n_dev, n_host, h, mask, mask_stride, B, partial, n_slabs, y,
                                  y_bf16, s);
+}
+
+// ---------------------------------------------------------------- down projection of up to 31 tokens on the matrix cores
+// y[t][:] = sum over listed j of h[t][j] * W_down[:, j], h in float32.  Bound by the weight stream: the vector kernel above
+// spends a fused multiply-add per token and weight (eight sequences: 27 us where the rows take 15), and takes eight tokens
+// at a time.  Here a float32 h is the exact sum of three bf16 values, so three 16x16x32 products per 16 tokens give what
+// float32 multiplies would: products are exact, sums are float32.
+// A workgroup owns 128 columns and a slab of the list, its eight waves 32 channels each of every 256.  Lane (c, g) =
+// (lane % 16, lane / 16) loads 16 bytes of the rows of channels 8 g .. 8 g + 7 at columns 8 c .. 8 c + 7 (256 contiguous
+// bytes per row), which is a transposed operand: one byte permute per register pairs the values of two channels, and
+// product e takes column 8 c + e of every lane.
+// 24 tokens, d 4096, 7155 channels: 19 us (3.0 TB/s); requesting rows or h further ahead took 25 to 80 us, for registers.
+constexpr int kSkThreads = 512;
+constexpr int kSkChunk = 256;      // channels staged at a time
+constexpr int kSkCols = 128;       // columns per workgroup
+constexpr int kSkLd = kSkChunk + 8;  // LDS row stride of the staged h planes (16-byte aligned, rows four banks apart)
+
+// f = hi + mid + lo exactly (24 significant bits in three bf16 values of 8; the rests are exact differences)
+__device__ __forceinline__ void split3(float f, uint16_t &hi, uint16_t &mid, uint16_t &lo)
+{
+    const uint32_t b0 = __float_as_uint(f) & 0xffff0000u;
+    const float r1 = f - __uint_as_float(b0);
+    const uint32_t b1 = __float_as_uint(r1) & 0xffff0000u;
+    const float r2 = r1 - __uint_as_float(b1);
+    hi = (uint16_t)(b0 >> 16), mid = (uint16_t)(b1 >> 16), lo = (uint16_t)(__float_as_uint(r2) >> 16);
+}
+
+// TG groups of 16 tokens; kMask: masks per token (else none)
+template <int TG, bool kMask>
+__global__ __launch_bounds__(kSkThreads) void skinny_down_kernel(const uint4 *__restrict__ w, int nvec,
+                                                                 const int *__restrict__ list, const int *__restrict__ n_dev,
+                                                                 const float *__restrict__ h, int m,
+                                                                 const unsigned char *__restrict__ mask, int mask_stride,
+                                                                 int T, float *__restrict__ partial, int d)
+{
+    typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+    typedef float f32x4_t __attribute__((ext_vector_type(4)));
+    extern __shared__ __attribute__((aligned(16))) unsigned char sk_lds[];
+    constexpr int kPlanes = 3 * 16 * TG * kSkLd * 2;        // bytes
+    uint16_t *hp = reinterpret_cast<uint16_t *>(sk_lds);  // [3][16 TG][kSkLd]: planes of h, rows by token
+    const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int c = lane % 16, g = lane / 16;
+    const int n = *n_dev;
+    const int n_slabs = gridDim.y, per_slab = (n + n_slabs - 1) / n_slabs;
+    const int s0 = min(n, (int)blockIdx.y * per_slab), s1 = min(n, s0 + per_slab);
+    const int vcol = blockIdx.x * (kSkCols / 8) + c;  // this lane's vector column
+    const bool col_ok = vcol < nvec;
+    const uint4 *wc = w + (col_ok ? vcol : 0);
+
+    f32x4_t acc[TG][8];
+#pragma unroll
+    for (int t = 0; t < TG; ++t)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) acc[t][e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+
+    // channels of two chunks behind the planes: chunk q's in js[q % 2], loaded two chunks ahead
+    int *js = reinterpret_cast<int *>(sk_lds + kPlanes);  // [2][kSkChunk]
+    const int li = threadIdx.x % kSkChunk, half = threadIdx.x / kSkChunk;
+    auto channel = [&](int at) { return list[min(at + li, s1 - 1)]; };  // beyond the slab: its last channel (h is 0 there)
+    uint4 rows[2][8];
+    auto request = [&](int set) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) rows[set][i] = wc[((size_t)js[set * kSkChunk + 32 * wave + 8 * g + i] * 3 + 2) * nvec];
+    };
+    // h of the 256 channels at `at` as three planes; zero beyond the slab, beyond T and where a mask says so
+    auto stage = [&](int set, int at) {
+        const int j = js[set * kSkChunk + li];
+        float v[8 * TG];
+        unsigned char mk[8 * TG];
+#pragma unroll
+        for (int q = 0; q < 8 * TG; ++q) {
+            const int t = min(2 * q + half, T - 1);
+            v[q] = h[(size_t)t * m + j];
+            if (kMask) mk[q] = mask[(size_t)t * mask_stride + j];
+        }
+#pragma unroll
+        for (int q = 0; q < 8 * TG; ++q) {
+            const int t = 2 * q + half;
+            uint16_t a, b, e;
+            split3(t < T && at + li < s1 && (!kMask || mk[q]) ? v[q] : 0.f, a, b, e);
+            hp[(0 * 16 * TG + t) * kSkLd + li] = a;
+            hp[(1 * 16 * TG + t) * kSkLd + li] = b;
+            hp[(2 * 16 * TG + t) * kSkLd + li] = e;
+        }
+    };
+    auto multiply = [&](int set) {
+        bf16x8_t bw[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            uint32_t v[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const uint4 &r0 = rows[set][2 * q], &r1 = rows[set][2 * q + 1];
+                const uint32_t a0 = e / 2 == 0 ? r0.x : (e / 2 == 1 ? r0.y : (e / 2 == 2 ? r0.z : r0.w));
+                const uint32_t a1 = e / 2 == 0 ? r1.x : (e / 2 == 1 ? r1.y : (e / 2 == 2 ? r1.z : r1.w));
+                v[q] = __builtin_amdgcn_perm(a1, a0, e % 2 ? 0x07060302u : 0x05040100u);
+            }
+            bw[e] = __builtin_bit_cast(bf16x8_t, make_uint4(v[0], v[1], v[2], v[3]));
+        }
+#pragma unroll
+        for (int t = 0; t < TG; ++t)
+#pragma unroll
+            for (int part = 2; part >= 0; --part) {  // (small parts first)
+                const bf16x8_t ha = *reinterpret_cast<const bf16x8_t *>(
+                    &hp[((part * TG + t) * 16 + c) * kSkLd + 32 * wave + 8 * g]);
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    acc[t][e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ha, bw[e], acc[t][e], 0, 0, 0);
+            }
+    };
+    if (s0 < s1) {
+        if (half == 0) js[li] = channel(s0), js[kSkChunk + li] = channel(s0 + kSkChunk);
+        __syncthreads();
+        request(0);
+        auto step = [&](int set, int at) {
+            const int next = channel(at + 2 * kSkChunk);
+            stage(set, at);
+            if (at + kSkChunk < s1) request(set ^ 1);
+            __syncthreads();
+            if (half == 0) js[set * kSkChunk + li] = next;
+            multiply(set);
+            __syncthreads();  // the planes' readers are done, the channels are there
+        };
+        for (int at = s0; at < s1; at += 2 * kSkChunk) {
+            step(0, at);
+            if (at + kSkChunk < s1) step(1, at + kSkChunk);
+        }
+    }
+    // the eight waves' sums in wave order, 16 tokens at a time; register v of product e is token 4 g + v, column 8 c + e
+    float *red = reinterpret_cast<float *>(sk_lds);  // [8 waves][16 tokens][128 columns]
+#pragma unroll
+    for (int t = 0; t < TG; ++t) {
+        __syncthreads();
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            float4 *dst = reinterpret_cast<float4 *>(red + ((size_t)(wave * 16 + 4 * g + v)) * kSkCols + 8 * c);
+            dst[0] = make_float4(acc[t][0][v], acc[t][1][v], acc[t][2][v], acc[t][3][v]);
+            dst[1] = make_float4(acc[t][4][v], acc[t][5][v], acc[t][6][v], acc[t][7][v]);
+        }
+        __syncthreads();
+        for (int i = threadIdx.x; i < 16 * kSkCols; i += kSkThreads) {
+            const int tok = 16 * t + i / kSkCols, col = blockIdx.x * kSkCols + i % kSkCols;
+            if (tok < T && col < d) {
+                double s = 0.0;
+#pragma unroll
+                for (int q = 0; q < kSkThreads / kWave; ++q) s += (double)red[q * 16 * kSkCols + i];
+                partial[((size_t)blockIdx.y * T + tok) * d + col] = (float)s;
+            }
+        }
+    }
+}
+
+// Slabs of the list so that the column blocks fill the chip once.
+int skinny_down_slabs(int d, int n_cu)
+{
+    const int cols = (d + kSkCols - 1) / kSkCols;
+    const int slabs = n_cu / cols;
+    return slabs < 1 ? 1 : (slabs > 64 ? 64 : slabs);
+}
+
+hipError_t launch_skinny_down(const void *w, int d, int m, const int *list, const int *n_dev, const float *h,
+                              const unsigned char *mask, int mask_stride, int T, float *partial, int n_slabs, void *y,
+                              int y_bf16, hipStream_t s)
+{
+    if (T < 1 || T > kSkMaxTokens) return hipErrorInvalidValue;
+    const dim3 grid((d + kSkCols - 1) / kSkCols, n_slabs);
+    const int tg = (T + 15) / 16;
+    const size_t stage = (size_t)3 * 16 * tg * kSkLd * 2 + 2 * kSkChunk * 4, red = (size_t)8 * 16 * kSkCols * 4, lds = stage > red ? stage : red;
+    hipError_t e = hipSuccess;
+#define POP_SK(TG, MK)                                                                                                    \
+    do {                                                                                                                  \
+        e = hipFuncSetAttribute(reinterpret_cast<const void *>(&skinny_down_kernel<TG, MK>),                              \
+                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);                                    \
+        if (e != hipSuccess) return e;                                                                                    \
+        hipLaunchKernelGGL((skinny_down_kernel<TG, MK>), grid, dim3(kSkThreads), lds, s, (const uint4 *)w, d / 8, list,   \
+                           n_dev, h, m, mask, mask_stride, T, partial, d);                                                \
+    } while (0)
+    if (tg == 1 && mask) POP_SK(1, true);
+    else if (tg == 1) POP_SK(1, false);
+    else if (mask) POP_SK(2, true);
+    else POP_SK(2, false);
+#undef POP_SK
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    const int total = T * d;
+    hipLaunchKernelGGL(down_reduce_kernel, dim3((total + kWave - 1) / kWave), dim3(256), 0, s, partial, n_slabs, total, y,
+                       y_bf16);
+    return hipGetLastError();
 }
 
 }  // namespace pop

@@ -143,6 +143,13 @@ hipError_t launch_down(const void *w, int is_bf16, int d, int m, const int *list
                        const float *h, const unsigned char *mask, int mask_stride, int B, float *partial, int n_slabs,
                        void *y, int y_bf16, hipStream_t s);
 int down_num_slabs(int d, int is_bf16);
+// The same for up to kSkMaxTokens rows of h ([T][m] float32, by channel) on bf16 layers, on the matrix cores; masks one row
+// per token (mask_stride) or null.  partial: [n_slabs][T][d] float32.
+constexpr int kSkMaxTokens = 32;
+int skinny_down_slabs(int d, int n_cu);
+hipError_t launch_skinny_down(const void *w, int d, int m, const int *list, const int *n_dev, const float *h,
+                              const unsigned char *mask, int mask_stride, int T, float *partial, int n_slabs, void *y,
+                              int y_bf16, hipStream_t s);
 // Batched decode (2 <= B <= POP_MAX_BATCH) with the per-sequence selection inside the gate/up kernel: the listed
 // rows are the n_cand candidates followed by the n_ret retained channels; all workgroups evaluate the candidates
 // first, then the last B workgroups wait (bounded) for everybody's candidate scores and select for one sequence
@@ -234,6 +241,13 @@ hipError_t launch_down_gemm_bf16(const void *w, int d, const int *list, const in
 hipError_t launch_prefill_gateup_keep_bf16(const void *w, int d, int m, const void *x, int T, float *s2_part,
                                            uint16_t *h_all, int ldh, int n_cu, hipStream_t s,
                                            const PrefillScores *fin = nullptr);
+// bf16 layers with d % 64 == 0, T <= kPreciseMaxTokens: gate/up with the contraction's partial sums added up in double,
+// h[t][j] in float32 ([T][m], by channel).  Without a list: all channels, and their scores as fin says (chunk_ctr zero
+// before and after).  With one (n_list: its length, on the device): the listed channels, no scores.
+constexpr int kPreciseMaxTokens = 31;
+bool precise_gateup_takes(int is_bf16, int d, int T);
+hipError_t launch_precise_gateup(const void *w, int d, int m, const void *x, int T, const int *list, const int *n_list,
+                                 float *h, float *s2_part, const PrefillScores *fin, int n_cu, hipStream_t s);
 // ---- input-side importance (pop_input_side.hip) ----
 int input_side_groups(int T);  // row groups of a T-token prompt (sizes part below: [groups][d] doubles)
 // s2[k] = sum_t x[t][k]^2 over the T rows (fixed summation order)

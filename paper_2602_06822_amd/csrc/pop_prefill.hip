@@ -110,6 +110,7 @@ struct PfStore {
     int ldh;
     const unsigned char *tmask; // per-token masks [T][m], or null
     int n_cu;
+    float *h32 = nullptr;       // [T][m] float32, by channel (precise modes)
     // scores formed in the same launch (modes 0 and 2; null = leave that to the caller): the token tile of a
     // channel chunk that finishes last sums the chunk's partial rows
     int *fin_ctr = nullptr;     // one arrival counter per channel chunk; zero between launches
@@ -156,7 +157,8 @@ __device__ __forceinline__ void pf_chunk_scores(const float (&colsum)[TW][kPfChu
 }
 
 // kMode 0: scores only (s2_part).  1: channels from st.list, H stored compact (no s2_part).  2: all m channels,
-// s2_part and H stored as [T][m padded].
+// s2_part and H stored as [T][m padded].  Of the direct-load kernel also 3 and 4, for prompts too short for H in bf16: all
+// channels with s2_part, or those of st.list without, sums in double and H in float32 by channel.
 template <int BM, int NW, int NF, int kMode>
 __global__ __launch_bounds__(NW * 64) void prefill_bf16_kernel(const uint16_t *__restrict__ w,
                                                            const uint16_t *__restrict__ x, int T, int d, int m,
@@ -426,7 +428,7 @@ __device__ __forceinline__ void pm_tile(const uint16_t *__restrict__ w, const ui
     typedef __attribute__((address_space(1))) const void glb_t;
     typedef float f32x4_t __attribute__((ext_vector_type(4)));
     constexpr int NA = PmRing<MF>::NA, NB = PmRing<MF>::NB;
-    constexpr bool kList = kMode == 1;
+    constexpr bool kList = kMode == 1 || kMode == 4, kPrecise = kMode >= 3;
     constexpr int BM = 64 * MF, BC = 8 * F;             // tokens and channels of the tile
     constexpr int PA = BM / 32, PB = (F + 1) / 2;       // direct loads per wave and k-step (32 rows a pass)
     constexpr int AT = BM * kPfBK, BT = PB * 32 * kPfBK;  // elements of one buffer
@@ -496,10 +498,26 @@ __device__ __forceinline__ void pm_tile(const uint16_t *__restrict__ w, const ui
     };
     // (inline assembly ties the accumulator to itself: left to choose, the compiler gives products of this size other
     // destinations and copies them back, which costs more than the products)
+    // Precise modes: a k-step's two products run from zero and their sums are added up in double, one step later.
+    double sum[kPrecise ? MF : 1][kPrecise ? F : 1][4] = {};
     auto product = [&](int i, int set) {
-        asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0"
-                     : "+a"(acc[i / F][i % F])
-                     : "v"(af[set][i / F]), "v"(bf[set][i % F]));
+        if constexpr (kPrecise) {
+            const f32x4_t from = set == 0 ? f32x4_t{0.f, 0.f, 0.f, 0.f} : acc[i / F][i % F];
+            acc[i / F][i % F] =
+                __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[set][i / F], bf[set][i % F], from, 0, 0, 0);
+        } else {
+            asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0"
+                         : "+a"(acc[i / F][i % F])
+                         : "v"(af[set][i / F]), "v"(bf[set][i % F]));
+        }
+    };
+    auto add_up = [&]() {
+        if constexpr (kPrecise) {
+#pragma unroll
+            for (int i = 0; i < MF * F; ++i)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) sum[i / F][i % F][v] += (double)acc[i / F][i % F][v];
+        }
     };
 
     // Requests in program order: ... A(s + NA - 1) | B(s + NB - 1) [wait for step s + 1] A(s + NA) | B(s + NB) [...: the
@@ -529,6 +547,7 @@ __device__ __forceinline__ void pm_tile(const uint16_t *__restrict__ w, const ui
     for (int ks = 0; ks < n_k; ++ks) {
         const uint16_t *Ab = Al + abuf * AT, *Bb = Bl + bbuf * BT;
         const int kb = kof(ks + NB - 1), ka = kof(ks + NA);
+        add_up();  // (the step before; zeroes first)
 #pragma unroll
         for (int i = 0; i < NP; ++i) {
             product(i, 0);
@@ -560,6 +579,13 @@ __device__ __forceinline__ void pm_tile(const uint16_t *__restrict__ w, const ui
     // compiler does not see the products, so it adds no wait states for them)
     asm volatile("s_waitcnt vmcnt(0)\n\ts_nop 15\n\ts_nop 15" ::: "memory");
     __syncthreads();
+    if constexpr (kPrecise) {
+        add_up();
+#pragma unroll
+        for (int i = 0; i < MF * F; ++i)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) acc[i / F][i % F][v] = (float)sum[i / F][i % F][v];
+    }
 
     // Accumulator register v of a lane: token 4 (lane / 16) + v of the fragment, B row lane % 16 of the fragment.  An odd
     // last fragment holds gate values in lanes 0..7 of each 16 and up values of the same channels in lanes 8..15: the
@@ -574,17 +600,20 @@ __device__ __forceinline__ void pm_tile(const uint16_t *__restrict__ w, const ui
     for (int p = 0; p < F / 2; ++p) {
         const int c = 16 * p + col;
         const bool live_c = c < cn;
-        const int j = (kList && st.tmask && live_c) ? st.list[c0 + c] : 0;
+        const int j = (kList && (kPrecise || st.tmask) && live_c) ? st.list[c0 + c] : c0 + c;
         ss[p] = 0.f;
 #pragma unroll
         for (int a = 0; a < MF; ++a)
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 const int t = t0 + row0 + a * 16 + v;
-                float h = silu_mul_tile(acc[a][2 * p][v], acc[a][2 * p + 1][v]);
+                float h = kPrecise ? silu_mul(acc[a][2 * p][v], acc[a][2 * p + 1][v])
+                                   : silu_mul_tile(acc[a][2 * p][v], acc[a][2 * p + 1][v]);
                 h = (t < T && live_c) ? h : 0.f;  // (padding holds products of the rows its loads were pointed at)
                 ss[p] = fmaf(h, h, ss[p]);
-                if (kMode != 0) {
+                if (kPrecise) {
+                    if (t < T && live_c) st.h32[(size_t)t * m + j] = h;
+                } else if (kMode != 0) {
                     if (kList && st.tmask && t < T && live_c && !st.tmask[(size_t)t * m + j]) h = 0.f;
                     hs[(row0 + a * 16 + v) * HS + c] = f32_to_bf16(h);
                 }
@@ -592,7 +621,7 @@ __device__ __forceinline__ void pm_tile(const uint16_t *__restrict__ w, const ui
     }
     if (F % 2) {
         const bool live_c = c_odd < cn;
-        const int j = (kList && st.tmask && live_c) ? st.list[c0 + c_odd] : 0;
+        const int j = (kList && (kPrecise || st.tmask) && live_c) ? st.list[c0 + c_odd] : c0 + c_odd;
         ss[F / 2] = 0.f;
 #pragma unroll
         for (int a = 0; a < MF; ++a)
@@ -602,10 +631,13 @@ __device__ __forceinline__ void pm_tile(const uint16_t *__restrict__ w, const ui
                 const float give = upper ? acc[a][F - 1][v] : acc[a][F - 1][v + 2];
                 const float got = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(give), 0x128, 0xf, 0xf, true));  // row_ror:8
                 const int t = t0 + row0 + a * 16 + r_odd + v;
-                float h = silu_mul_tile(upper ? got : mine, upper ? mine : got);
+                const float gate = upper ? got : mine, up = upper ? mine : got;
+                float h = kPrecise ? silu_mul(gate, up) : silu_mul_tile(gate, up);
                 h = (t < T && live_c) ? h : 0.f;
                 ss[F / 2] = fmaf(h, h, ss[F / 2]);
-                if (kMode != 0) {
+                if (kPrecise) {
+                    if (t < T && live_c) st.h32[(size_t)t * m + j] = h;
+                } else if (kMode != 0) {
                     if (kList && st.tmask && t < T && live_c && !st.tmask[(size_t)t * m + j]) h = 0.f;
                     hs[(row0 + a * 16 + r_odd + v) * HS + c_odd] = f32_to_bf16(h);
                 }
@@ -622,7 +654,7 @@ __device__ __forceinline__ void pm_tile(const uint16_t *__restrict__ w, const ui
         }
         pf_chunk_scores<4>(colsum, m, n_tt, ttile, ctile, c0, cn, s2_part, st);
     }
-    if (kMode != 0) {
+    if (kMode == 1 || kMode == 2) {
         __syncthreads();
         for (int i = tid; i < BM * F; i += kPmThreads) {
             const int r = i / F, v = i % F;
@@ -644,7 +676,7 @@ __global__ __launch_bounds__(kPmThreads, 1) void prefill_mma_kernel(const uint16
     extern __shared__ __attribute__((aligned(16))) uint16_t pf_lds[];
     __shared__ float colsum[4][kPfChunk];
     int n_ch = m;  // channels the chunks run over
-    if (kMode == 1) {
+    if (kMode == 1 || kMode == 4) {
         n_ch = *st.n_list;
         g = pm_tiles(n_ch, n_tt, MF, st.n_cu);
     }
@@ -780,7 +812,7 @@ static hipError_t launch_pm(const void *w, int d, int m, const void *x, int T, c
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&prefill_mma_kernel<MF, kMode>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
-    const int n_tt = (T + 64 * MF - 1) / (64 * MF), all = kMode == 1 ? n_cu : (g.total < n_cu ? g.total : n_cu);
+    const int n_tt = (T + 64 * MF - 1) / (64 * MF), all = kMode == 1 || kMode == 4 ? n_cu : (g.total < n_cu ? g.total : n_cu);
     hipLaunchKernelGGL((prefill_mma_kernel<MF, kMode>), dim3((all + 7) / 8 * 8), dim3(kPmThreads), lds, s,
                        (const uint16_t *)w, (const uint16_t *)x, T, d, m, n_tt, g, s2_part, st);
     return hipGetLastError();
@@ -882,6 +914,20 @@ hipError_t launch_gateup_list_bf16(const void *w, int d, int m, const void *x, i
         else e = launch_pf_bf16<128, 4, 2, 1>(blocks, s, w, x, T, d, m, n_tt, g, nullptr, st);
     }
     return e;
+}
+
+bool precise_gateup_takes(int is_bf16, int d, int T) { return is_bf16 && prefill_direct(d) && T >= 1 && T <= kPreciseMaxTokens; }
+
+// (One token tile, bound by the weight stream, so the sums in double are free: 24 tokens, d 4096, m 11008
+// take 43 us, the same as without.)
+hipError_t launch_precise_gateup(const void *w, int d, int m, const void *x, int T, const int *list, const int *n_list,
+                                 float *h, float *s2_part, const PrefillScores *fin, int n_cu, hipStream_t s)
+{
+    PfStore st{list, n_list, nullptr, 0, nullptr, n_cu};
+    st.h32 = h;
+    if (list) return launch_pm<1, 4>(w, d, m, x, T, PmTiles{}, nullptr, n_cu, st, s);
+    if (fin) st.fin_ctr = fin->chunk_ctr, st.nrm = fin->nrm, st.scores = fin->scores;
+    return launch_pm<1, 3>(w, d, m, x, T, pm_tiles(m, 1, 1, n_cu), s2_part, n_cu, st, s);
 }
 
 // scores[j] = nrm[j] * sqrt(sum over token tiles, in tile order, of s2_part[tile][j])   (Eq. 3)

@@ -561,6 +561,38 @@ def test_layer_partition_with_ties(pop, oracle, m):
                       x[:2], m // 10)
 
 
+# float32 outputs of a short prompt: hidden activations good to a few 2^-24, products exact, float32 sums of at most a few
+# thousand terms in chains of a few dozen: well below 1e-5 of the largest output
+SHORT_PROMPT_TOL = 1e-5
+
+
+@pytest.mark.parametrize("d,m", [(64, 300), (192, 1100), (640, 2900), (136, 300)])
+@pytest.mark.parametrize("T", [2, 15, 16, 17, 31])
+def test_short_prompts_in_one_pass(pop, oracle, T, d, m):
+    """bf16 prompts below 32 tokens (one pass over the weights, hidden activations in float32, down projection on the
+    matrix cores in three exact parts): stand-alone FFN under shared and per-token masks whose lists are empty, one
+    channel, whole and ragged chunks, and the prompt's own forward pass with its scores; a row length that is no whole
+    k-step takes the decode kernels."""
+    L = synth.make_layer(synth.small_config("short_prompt", d, m, BF16, heavy_tail=True))
+    x = synth.make_activations(L, T, "prompt")
+    g = synth.rng("short_prompt_mask", d, m, T)
+    with GpuLayer(pop, L, max_tokens=T, max_batch=1) as G:
+        for n in (0, 1, min(256, m), min(257, m), m):
+            mask = np.zeros(m, dtype=np.uint8)
+            mask[g.choice(m, size=n, replace=False)] = 1
+            y = G.ffn(x, mask, F32)
+            y_ref = oracle.pruned_ffn(x, L.w_gate, L.w_up, L.w_down, BF16, mask)
+            assert (not y.any()) if n == 0 else max_abs_rel(y, y_ref) <= SHORT_PROMPT_TOL, n
+        masks = (g.random((T, m)) < 0.4).astype(np.uint8)
+        masks[0] = 0
+        y = G.ffn(x, masks, F32)
+        y_ref = np.stack([oracle.pruned_ffn(x[t:t + 1], L.w_gate, L.w_up, L.w_down, BF16, masks[t])[0] for t in range(T)])
+        assert max_abs_rel(y, y_ref) <= SHORT_PROMPT_TOL
+        n_ret, n_cand, k = m // 2, m // 4, m // 8
+        _check_prefill(oracle, G, L, x, n_ret, n_cand)
+        _check_prefill_forward(oracle, G, L, x, n_ret, n_cand, k, F32, SHORT_PROMPT_TOL)
+
+
 def test_prefill_forward_full_size(pop, oracle):
     """Llama-2-7B-shaped layer, prompt 512: prefill scores on a sample of channels, partition and prefill mask
     on all channels, the prompt's output on a sample of tokens, then a decode step on the partition."""
