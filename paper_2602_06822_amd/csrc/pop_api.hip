@@ -772,10 +772,15 @@ int pop_importance_reduce(const void *h, pop_dtype_t hdtype, int T, int m, const
     if (!h || !nrm || !scores) return POP_EINVAL;
     if (hdtype != POP_F32 && hdtype != POP_BF16) return POP_EINVAL;
     if (T < 1 || m < 1) return POP_ESHAPE;
-    // the per-chunk partial sums live in stream-ordered scratch: allocated and freed on the caller's stream
     hipStream_t s = as_stream(stream);
+    const size_t bytes = importance_reduce_scratch_bytes(T, m);
+    if (bytes == 0) {
+        POP_HIP(launch_importance_reduce(h, hdtype == POP_BF16, T, m, nrm, scores, nullptr, s));
+        return POP_OK;
+    }
+    // long prompts of few channels: the per-chunk partial sums live in stream-ordered scratch
     void *scratch = nullptr;
-    hipError_t e = hipMallocAsync(&scratch, importance_reduce_scratch_bytes(T, m), s);
+    hipError_t e = hipMallocAsync(&scratch, bytes, s);
     if (e != hipSuccess) {
         (void)hipGetLastError();
         return e == hipErrorOutOfMemory ? POP_ENOMEM : hip_fail(e, "hipMallocAsync");

@@ -1,15 +1,20 @@
 // Column-wise importance reduction over materialised activations (Sec. 3.4 Eq. 3):
 //     scores[j] = nrm[j] * sqrt( sum over tokens t of H[t][j]^2 ),   H: [T][m] float32 or bf16.
 //
-// HBM-bound: every element of H is read once.  The tokens are split into chunks so that a prompt-sized H fills
-// the chip (a column block alone gives only m/256 workgroups); a workgroup owns 256 adjacent columns of one token
-// chunk, a lane one column of each 64-column group (coalesced row segments), eight rows in flight per lane.
-//   stage 1  part[chunk][j] = sum over the chunk's tokens of H[t][j]^2, in double (a float32 running sum over a
-//            long prompt would lose more than the 1e-5 the scores are held to); the four waves take the chunk's
-//            rows round robin and meet through LDS in wave order.
-//   stage 2  scores[j] = nrm[j] * sqrt(sum over chunks, in chunk order, of part[chunk][j]).
-// The summation order is fixed by (T, m) alone, so the result is bit-reproducible.
-// `part` is scratch: [n_chunks][m] doubles beyond the inputs and outputs.
+// HBM-bound: every element of H is read once, sums in double (a float32 running sum over a long prompt would lose more
+// than the 1e-5 the scores are held to), the summation order fixed by (T, m, the alignment) alone, so the result is
+// bit-reproducible.  Two forms:
+//  * importance_columns_kernel: one workgroup takes 64 columns and all tokens, so nothing is left to add up afterwards and
+//    no scratch is needed.  A row segment is one or two cache lines; 16 waves x 8 loads of 16 bytes per lane keep 128 KB on
+//    their way per compute unit, so a 1024-token prompt is a single round trip.  1024 x 13824 bf16: 7 us, against 20 + 6 us
+//    for the two launches below and the allocation of their scratch around them.
+//  * long prompts of few columns (fewer than kIrMinGroups workgroups, more than kIrLongPrompt tokens) would leave most
+//    of the chip idle for many rounds: tokens split into chunks, per-chunk partial sums in scratch.
+//      stage 1  part[chunk][j] = sum over the chunk's tokens of H[t][j]^2; 256 adjacent columns of one token chunk per
+//               workgroup, a lane one column of each 64-column group, eight rows in flight per lane; the four waves take
+//               the chunk's rows round robin and meet through LDS in wave order.
+//      stage 2  scores[j] = nrm[j] * sqrt(sum over chunks, in chunk order, of part[chunk][j]).
+//    `part` is scratch: [n_chunks][m] doubles beyond the inputs and outputs.
 #include <mutex>
 
 #include "pop_internal.h"
@@ -25,6 +30,76 @@ template <bool BF16>
 __device__ __forceinline__ float ir_load(const void *h, size_t i)
 {
     return BF16 ? __uint_as_float(((uint32_t)((const uint16_t *)h)[i]) << 16) : ((const float *)h)[i];
+}
+
+constexpr int kIcCols = 64;        // columns per workgroup
+constexpr int kIcWaves = 16;
+constexpr int kIcRows = 8;         // loads in flight per lane
+constexpr int kIrMinGroups = 128;
+constexpr int kIrLongPrompt = 8192;
+
+// E columns per lane: 16-byte loads (8 bf16, 4 float32; rows and base 16-byte aligned) or, E = 1, one element.
+template <bool BF16, int E>
+__global__ __launch_bounds__(kIcWaves * kWave) void importance_columns_kernel(const void *__restrict__ h, int T, int m,
+                                                                              const float *__restrict__ nrm,
+                                                                              float *__restrict__ scores)
+{
+    __shared__ double red[kIcWaves][kIcCols];
+    constexpr int LPR = kIcCols / E;        // lanes per row
+    constexpr int RPW = kWave / LPR;        // rows a wave's load covers
+    constexpr int step = kIcWaves * RPW;
+    const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+    const int col = blockIdx.x * kIcCols + lane % LPR * E, r0 = wave * RPW + lane / LPR;
+    const bool ok = col < m;                // (E columns at once: m is a multiple of E there)
+    double acc[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) acc[e] = 0.0;
+    for (int t = r0; t < T; t += step * kIcRows) {
+        if constexpr (E == 1) {
+            float v[kIcRows];
+#pragma unroll
+            for (int u = 0; u < kIcRows; ++u) {
+                const int tr = t + u * step;
+                v[u] = ir_load<BF16>(h, (size_t)min(tr, T - 1) * m + (ok ? col : 0));
+                v[u] = tr < T ? v[u] : 0.f;
+            }
+#pragma unroll
+            for (int u = 0; u < kIcRows; ++u) acc[0] = fma((double)v[u], (double)v[u], acc[0]);
+        } else {
+            uint4 v[kIcRows];
+#pragma unroll
+            for (int u = 0; u < kIcRows; ++u) {
+                const size_t at = (size_t)min(t + u * step, T - 1) * m + (ok ? col : 0);
+                v[u] = *reinterpret_cast<const uint4 *>((const unsigned char *)h + at * (BF16 ? 2 : 4));
+            }
+#pragma unroll
+            for (int u = 0; u < kIcRows; ++u) {
+                const uint32_t q[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
+                const bool live = t + u * step < T;
+#pragma unroll
+                for (int e = 0; e < E; ++e) {
+                    const float f = BF16 ? (e % 2 ? bf16_hi(q[e / 2]) : bf16_lo(q[e / 2])) : __uint_as_float(q[e % 4]);
+                    const double d = live ? (double)f : 0.0;
+                    acc[e] = fma(d, d, acc[e]);
+                }
+            }
+        }
+    }
+    // rows of the wave's lanes, then the waves in order
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+#pragma unroll
+        for (int off = LPR; off < kWave; off <<= 1) acc[e] += __shfl_xor(acc[e], off, kWave);
+        if (lane < LPR) red[wave][lane * E + e] = acc[e];
+    }
+    __syncthreads();
+    const int j = blockIdx.x * kIcCols + (int)threadIdx.x;
+    if (threadIdx.x < kIcCols && j < m) {
+        double tot = 0.0;
+#pragma unroll
+        for (int w = 0; w < kIcWaves; ++w) tot += red[w][threadIdx.x];
+        scores[j] = (float)((double)nrm[j] * sqrt(tot));
+    }
 }
 
 template <bool BF16>
@@ -93,11 +168,29 @@ static int importance_chunks(int T, int m)
     return n < 1 ? 1 : n;
 }
 
-size_t importance_reduce_scratch_bytes(int T, int m) { return (size_t)importance_chunks(T, m) * m * sizeof(double); }
+static bool importance_in_chunks(int T, int m) { return T > kIrLongPrompt && (m + kIcCols - 1) / kIcCols < kIrMinGroups; }
+
+size_t importance_reduce_scratch_bytes(int T, int m)
+{
+    return importance_in_chunks(T, m) ? (size_t)importance_chunks(T, m) * m * sizeof(double) : 0;
+}
 
 hipError_t launch_importance_reduce(const void *h, int is_bf16, int T, int m, const float *nrm, float *scores,
                                     void *scratch, hipStream_t s)
 {
+    if (!importance_in_chunks(T, m)) {
+        const dim3 grid((m + kIcCols - 1) / kIcCols), block(kIcWaves * kWave);
+        const bool vec = (reinterpret_cast<uintptr_t>(h) & 15u) == 0 && m % (is_bf16 ? 8 : 4) == 0;
+        if (is_bf16 && vec)
+            hipLaunchKernelGGL((importance_columns_kernel<true, 8>), grid, block, 0, s, h, T, m, nrm, scores);
+        else if (is_bf16)
+            hipLaunchKernelGGL((importance_columns_kernel<true, 1>), grid, block, 0, s, h, T, m, nrm, scores);
+        else if (vec)
+            hipLaunchKernelGGL((importance_columns_kernel<false, 4>), grid, block, 0, s, h, T, m, nrm, scores);
+        else
+            hipLaunchKernelGGL((importance_columns_kernel<false, 1>), grid, block, 0, s, h, T, m, nrm, scores);
+        return hipGetLastError();
+    }
     const int n_chunks = importance_chunks(T, m);
     const int rows_per_chunk = (T + n_chunks - 1) / n_chunks;
     double *part = (double *)scratch;
@@ -160,7 +253,7 @@ extern "C" int pop_importance_reduce_static(const void *h, pop_dtype_t hdtype, i
     if (m > kStaticMaxChannels || pop::importance_reduce_scratch_bytes(T, m) > kStaticScratchBytes)
         return POP_EUNSUPPORTED;  // beyond the static scratch: use pop_importance_reduce
     void *ptr = nullptr;
-    if (static_scratch(&ptr) != hipSuccess) {
+    if (pop::importance_reduce_scratch_bytes(T, m) > 0 && static_scratch(&ptr) != hipSuccess) {
         (void)hipGetLastError();
         return POP_EHIP;
     }

@@ -593,6 +593,28 @@ def test_short_prompts_in_one_pass(pop, oracle, T, d, m):
         _check_prefill_forward(oracle, G, L, x, n_ret, n_cand, k, F32, SHORT_PROMPT_TOL)
 
 
+@pytest.mark.parametrize("dtype", [F32, BF16])
+@pytest.mark.parametrize("T,m,shift", [(1, 1, 0), (7, 63, 0), (8, 64, 0), (129, 72, 0), (1025, 200, 0), (2047, 1000, 0),
+                                       (130, 72, 1), (9000, 40, 0), (8193, 8200, 0)])
+def test_importance_reduce_forms(pop, T, m, shift, dtype):
+    """The stand-alone reduction at the edges of its forms: 16-byte loads, single elements (row lengths or a base
+    address that are no multiples of 16 bytes), rows beyond T in a round of loads, chunks for a long prompt of few
+    columns; both entry points bit for bit.  The sums are in double and rounded once: 2^-23 relative."""
+    H = synth.rng("importance_forms", T, m).standard_normal((T, m), dtype=np.float32)
+    nrm = np.abs(synth.rng("importance_forms_nrm", m).standard_normal(m, dtype=np.float32)) + np.float32(0.1)
+    st = H if dtype == F32 else synth.f32_to_bf16_bits(H)
+    flat = torch.zeros(T * m + shift, dtype=torch.float32 if dtype == F32 else torch.int16, device="cuda")
+    flat[shift:] = dev(st).reshape(-1)
+    h, nd = flat[shift:], dev(nrm)
+    a = torch.full((m,), -1.0, device="cuda")
+    b = torch.full((m,), -2.0, device="cuda")
+    pop.pop_importance_reduce(h, dtype, T, m, nd, a)
+    pop.pop_importance_reduce_static(h, dtype, T, m, nd, b)
+    ref = nrm.astype(np.float64) * np.sqrt((synth.storage_to_f64(st, dtype) ** 2).sum(0))
+    assert np.max(np.abs(host(a) - ref) / ref) <= 2.0 ** -23
+    assert np.array_equal(host(a), host(b))
+
+
 def test_prefill_forward_full_size(pop, oracle):
     """Llama-2-7B-shaped layer, prompt 512: prefill scores on a sample of channels, partition and prefill mask
     on all channels, the prompt's output on a sample of tokens, then a decode step on the partition."""
