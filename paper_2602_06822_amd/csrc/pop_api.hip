@@ -95,7 +95,7 @@ struct pop_layer {
     int *top_list = nullptr;           // [m] + 1: the prompt's own active channels (ascending), then their number
     // pruned FFN of a few tokens
     int chunk = 0;                     // tokens the decode kernels take at a time
-    float *hs = nullptr;               // [kPreciseMaxTokens][m] float32 (bf16 layers with d % 64 == 0)
+    float *hs = nullptr;               // [precise_max_tokens][m] float32
     uint16_t *zero_row = nullptr;      // 256 bytes of zeros: stands in for weight rows beyond a channel list
 };
 
@@ -222,7 +222,7 @@ int finish_partition(pop_layer *L, int T, int n_ret, int n_cand, float *scores, 
 {
     const int m = L->m;
     if (!scores_ready)
-        POP_HIP(launch_scores_from_partials(L->s2_part, prefill_rows_used(T, L->is_bf16, L->d, m, L->n_cu), m, L->nrm,
+        POP_HIP(launch_scores_from_partials(L->s2_part, prefill_rows_used(T, L->d, m, L->n_cu), m, L->nrm,
                                             L->scores, s));
     o.scores = L->scores, o.scores_copy = scores;
     o.region[0] = L->region, o.region[1] = region;
@@ -400,13 +400,13 @@ int pop_layer_create(pop_layer_t **out, int d, int m, pop_dtype_t wdtype, const 
     // tokens of a stand-alone FFN that the decode kernels take at a time: as many as they can, whatever the batch
     L->chunk = max_batch;
     while (L->chunk < POP_MAX_BATCH && (long long)(L->chunk + 1) * d * esize <= lds_max) ++L->chunk;
-    const bool precise = precise_gateup_takes(is_bf16, d, 1);
+    const int few_tokens = precise_max_tokens(is_bf16, d);
 
     const size_t mm = (size_t)m, B = (size_t)max_batch, C = (size_t)L->chunk;
     size_t partial_rows = (size_t)L->n_slabs * C;
     if (partial_rows < (size_t)fused_max_workgroups()) partial_rows = (size_t)fused_max_workgroups();
-    if (is_bf16 && partial_rows < (size_t)skinny_down_slabs(d, n_cu) * kSkMaxTokens)
-        partial_rows = (size_t)skinny_down_slabs(d, n_cu) * kSkMaxTokens;
+    const size_t skinny_rows = (size_t)skinny_down_slabs(is_bf16, d, m, n_cu) * (is_bf16 ? kSkMaxTokens : kF32MaxTokens);
+    if (partial_rows < skinny_rows) partial_rows = skinny_rows;
     struct Req { void **p; size_t bytes; };
     Req reqs[] = {
         {&L->w, mm * 3 * d * esize},
@@ -433,7 +433,7 @@ int pop_layer_create(pop_layer_t **out, int d, int m, pop_dtype_t wdtype, const 
         {(void **)&L->pf_ctr, mm * 4},
         {(void **)&L->ffn_any, (mm + 3) / 4 * 4},
         {(void **)&L->top_list, (mm + 1) * 4},
-        {(void **)&L->hs, precise ? (size_t)kPreciseMaxTokens * mm * 4 : 0},
+        {(void **)&L->hs, (size_t)few_tokens * mm * 4},
     };
     for (const Req &r : reqs) {
         if (r.bytes == 0) continue;
@@ -476,7 +476,7 @@ int pop_prefill_partition(pop_layer_t *L, const void *x, int T, int n_ret, int n
     if (n_ret < 0 || n_cand < 0 || (long long)n_ret + n_cand > L->m) return POP_ESHAPE;
     hipStream_t s = as_stream(stream);
     const int m = L->m;
-    const bool few = !L->input_side && precise_gateup_takes(L->is_bf16, L->d, T);
+    const bool few = !L->input_side && T <= precise_max_tokens(L->is_bf16, L->d);
     L->has_partition = false;
     L->has_step = false;
     if (T == 0) {
@@ -488,7 +488,7 @@ int pop_prefill_partition(pop_layer_t *L, const void *x, int T, int n_ret, int n
     } else {
         const PrefillScores fin{L->pf_ctr, L->nrm, L->scores};
         if (few)  // (the same launch as pop_prefill_forward's: the same scores, bit for bit)
-            POP_HIP(launch_precise_gateup(L->w, L->d, m, x, T, nullptr, nullptr, L->hs, L->s2_part, &fin, L->n_cu, s));
+            POP_HIP(launch_precise_gateup(L->w, L->is_bf16, L->d, m, x, T, nullptr, nullptr, L->hs, L->s2_part, &fin, L->n_cu, s));
         else
             POP_HIP(launch_prefill_gateup(L->w, L->is_bf16, L->d, m, x, T, L->s2_part, L->n_cu, s, &fin));
     }
@@ -517,7 +517,7 @@ int pop_prefill_forward(pop_layer_t *L, const void *x, int T, int n_ret, int n_c
     // has no such contraction: partition first, then the masked FFN)
     const bool keep = L->is_bf16 && T >= kFfnMfmaMinTokens && !L->input_side;
     // a short prompt: H of all channels in float32 from the same pass that scores them
-    const bool few = !L->input_side && precise_gateup_takes(L->is_bf16, d, T);
+    const bool few = !L->input_side && T > 0 && T <= precise_max_tokens(L->is_bf16, d);
     L->has_partition = false;
     L->has_step = false;
     int ldh = 0, n_split = 1;
@@ -534,7 +534,7 @@ int pop_prefill_forward(pop_layer_t *L, const void *x, int T, int n_ret, int n_c
             POP_HIP(launch_input_side_scores(L->w, L->is_bf16, d, L->in_s2, 1, nullptr, m, L->scores, m, s));
         } else if (few) {
             const PrefillScores fin{L->pf_ctr, L->nrm, L->scores};
-            POP_HIP(launch_precise_gateup(L->w, d, m, x, T, nullptr, nullptr, L->hs, L->s2_part, &fin, L->n_cu, s));
+            POP_HIP(launch_precise_gateup(L->w, L->is_bf16, d, m, x, T, nullptr, nullptr, L->hs, L->s2_part, &fin, L->n_cu, s));
         } else {
             const PrefillScores fin{L->pf_ctr, L->nrm, L->scores};
             POP_HIP(launch_prefill_gateup(L->w, L->is_bf16, d, m, x, T, L->s2_part, L->n_cu, s, &fin));
@@ -560,8 +560,8 @@ int pop_prefill_forward(pop_layer_t *L, const void *x, int T, int n_ret, int n_c
         return POP_OK;
     }
     if (few) {
-        POP_HIP(launch_skinny_down(L->w, d, m, L->top_list, L->top_list + m, L->hs, nullptr, 0, T, L->partial,
-                                   skinny_down_slabs(d, L->n_cu), y, ydtype == POP_BF16, s));
+        POP_HIP(launch_skinny_down(L->w, L->is_bf16, d, m, L->top_list, L->top_list + m, L->hs, nullptr, 0, T, L->partial,
+                                   skinny_down_slabs(L->is_bf16, d, m, L->n_cu), y, ydtype == POP_BF16, s));
         return POP_OK;
     }
     const int rc = pop_pruned_ffn(L, x, T, L->ffn_any, 1, y, ydtype, stream);
@@ -688,8 +688,8 @@ int pop_pruned_ffn(pop_layer_t *L, const void *x, int T, const unsigned char *ma
             POP_HIP(launch_down(L->w, L->is_bf16, d, m, L->active_idx, nullptr, L->n_ret + L->step_k.k[0], L->h,
                                 nullptr, 0, 1, L->partial, L->n_slabs, y, y_bf16, s));
         else if (L->is_bf16 && T >= kSkinnyMinBatch)
-            POP_HIP(launch_skinny_down(L->w, d, m, L->ulist, L->n_ulist, L->h, L->mask, m, T, L->partial,
-                                       skinny_down_slabs(d, L->n_cu), y, y_bf16, s));
+            POP_HIP(launch_skinny_down(L->w, L->is_bf16, d, m, L->ulist, L->n_ulist, L->h, L->mask, m, T, L->partial,
+                                       skinny_down_slabs(L->is_bf16, d, m, L->n_cu), y, y_bf16, s));
         else
             POP_HIP(launch_down(L->w, L->is_bf16, d, m, L->ulist, L->n_ulist, 0, L->h, L->mask, m, T, L->partial,
                                 L->n_slabs, y, y_bf16, s));
@@ -701,17 +701,23 @@ int pop_pruned_ffn(pop_layer_t *L, const void *x, int T, const unsigned char *ma
     L->has_step = false;  // the step scratch is reused below
     L->ulist_prefix_ok = false;
     if (L->is_bf16 && T >= kFfnMfmaMinTokens) return pruned_ffn_mfma(L, x, T, mask, mask_rows, y, y_bf16, s);
-    if (T > 1 && precise_gateup_takes(L->is_bf16, d, T)) {
-        // a few tokens in one pass over the weights
+    if (const int few = precise_max_tokens(L->is_bf16, d); T > 1 && few > 0) {
+        // a few tokens (bf16 layers: all of them) per pass over the weights
         const unsigned char *rows = mask;
         if (mask_rows > 1) {
             POP_HIP(launch_mask_any(mask, T, m, L->ffn_any, s));
             rows = L->ffn_any;
         }
         POP_HIP(launch_mask_to_list(rows, 1, m, L->ulist, L->n_ulist, s));
-        POP_HIP(launch_precise_gateup(L->w, d, m, x, T, L->ulist, L->n_ulist, L->hs, nullptr, nullptr, L->n_cu, s));
-        POP_HIP(launch_skinny_down(L->w, d, m, L->ulist, L->n_ulist, L->hs, mask_rows > 1 ? mask : nullptr, m, T, L->partial,
-                                   skinny_down_slabs(d, L->n_cu), y, y_bf16, s));
+        for (int t0 = 0; t0 < T; t0 += few) {
+            const int n = T - t0 < few ? T - t0 : few;
+            POP_HIP(launch_precise_gateup(L->w, L->is_bf16, d, m, (const char *)x + (size_t)t0 * d * L->esize, n, L->ulist,
+                                          L->n_ulist, L->hs, nullptr, nullptr, L->n_cu, s));
+            POP_HIP(launch_skinny_down(L->w, L->is_bf16, d, m, L->ulist, L->n_ulist, L->hs,
+                                       mask_rows > 1 ? mask + (size_t)t0 * m : nullptr, m, n, L->partial,
+                                       skinny_down_slabs(L->is_bf16, d, m, L->n_cu),
+                                       (char *)y + (size_t)t0 * d * ysize, y_bf16, s));
+        }
         return POP_OK;
     }
     if (mask_rows == 1) POP_HIP(launch_mask_to_list(mask, 1, m, L->ulist, L->n_ulist, s));

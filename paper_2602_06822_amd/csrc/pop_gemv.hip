@@ -655,16 +655,17 @@ __global__ __launch_bounds__(kSkThreads) void skinny_down_kernel(const uint4 *__
 }
 
 // Slabs of the list so that the column blocks fill the chip once.
-int skinny_down_slabs(int d, int n_cu)
+int skinny_down_slabs(int is_bf16, int d, int m, int n_cu)
 {
+    if (!is_bf16) return f32_down_slabs(d, m, n_cu);
     const int cols = (d + kSkCols - 1) / kSkCols;
     const int slabs = n_cu / cols;
     return slabs < 1 ? 1 : (slabs > 64 ? 64 : slabs);
 }
 
-hipError_t launch_skinny_down(const void *w, int d, int m, const int *list, const int *n_dev, const float *h,
-                              const unsigned char *mask, int mask_stride, int T, float *partial, int n_slabs, void *y,
-                              int y_bf16, hipStream_t s)
+static hipError_t launch_skinny_down_partials(const void *w, int d, int m, const int *list, const int *n_dev,
+                                              const float *h, const unsigned char *mask, int mask_stride, int T,
+                                              float *partial, int n_slabs, hipStream_t s)
 {
     if (T < 1 || T > kSkMaxTokens) return hipErrorInvalidValue;
     const dim3 grid((d + kSkCols - 1) / kSkCols, n_slabs);
@@ -684,7 +685,15 @@ hipError_t launch_skinny_down(const void *w, int d, int m, const int *list, cons
     else if (mask) POP_SK(2, true);
     else POP_SK(2, false);
 #undef POP_SK
-    e = hipGetLastError();
+    return hipGetLastError();
+}
+
+hipError_t launch_skinny_down(const void *w, int is_bf16, int d, int m, const int *list, const int *n_dev, const float *h,
+                              const unsigned char *mask, int mask_stride, int T, float *partial, int n_slabs, void *y,
+                              int y_bf16, hipStream_t s)
+{
+    hipError_t e = is_bf16 ? launch_skinny_down_partials(w, d, m, list, n_dev, h, mask, mask_stride, T, partial, n_slabs, s)
+                           : launch_down_f32_partials(w, d, m, list, n_dev, h, mask, mask_stride, T, partial, n_slabs, s);
     if (e != hipSuccess) return e;
     const int total = T * d;
     hipLaunchKernelGGL(down_reduce_kernel, dim3((total + kWave - 1) / kWave), dim3(256), 0, s, partial, n_slabs, total, y,

@@ -143,11 +143,11 @@ hipError_t launch_down(const void *w, int is_bf16, int d, int m, const int *list
                        const float *h, const unsigned char *mask, int mask_stride, int B, float *partial, int n_slabs,
                        void *y, int y_bf16, hipStream_t s);
 int down_num_slabs(int d, int is_bf16);
-// The same for up to kSkMaxTokens rows of h ([T][m] float32, by channel) on bf16 layers, on the matrix cores; masks one row
-// per token (mask_stride) or null.  partial: [n_slabs][T][d] float32.
-constexpr int kSkMaxTokens = 32;
-int skinny_down_slabs(int d, int n_cu);
-hipError_t launch_skinny_down(const void *w, int d, int m, const int *list, const int *n_dev, const float *h,
+// The same for up to kSkMaxTokens (bf16 layers) or kF32MaxTokens rows of h ([T][m] float32, by channel) on the matrix cores; masks one row per token
+// (mask_stride) or null.  partial: [n_slabs][T][d] float32.
+constexpr int kSkMaxTokens = 32;  // (bf16)
+int skinny_down_slabs(int is_bf16, int d, int m, int n_cu);
+hipError_t launch_skinny_down(const void *w, int is_bf16, int d, int m, const int *list, const int *n_dev, const float *h,
                               const unsigned char *mask, int mask_stride, int T, float *partial, int n_slabs, void *y,
                               int y_bf16, hipStream_t s);
 // Batched decode (2 <= B <= POP_MAX_BATCH) with the per-sequence selection inside the gate/up kernel: the listed
@@ -212,8 +212,8 @@ hipError_t launch_probe_step_read(const void *w, int nvec, const int *gu_list, i
 // ---- prefill (pop_prefill.hip) ----
 // s2_part[tile][j] = sum over the tile's tokens of H[t][j]^2, one row per token tile.
 int prefill_num_tiles(int T, int is_bf16);  // upper bound on the rows used, for sizing s2_part
-int prefill_rows_used(int T, int is_bf16, int d, int m, int n_cu);  // rows the launch below writes for this T
-// With `fin`, launches for which prefill_forms_scores holds (bf16 layers, one tile per compute unit at most) also leave scores[j] = nrm[j] * sqrt(sum over the token tiles, in tile
+int prefill_rows_used(int T, int d, int m, int n_cu);  // rows the launch below writes for this T (bf16)
+// With `fin`, launches for which prefill_forms_scores holds (float32 layers; bf16 ones with one tile per compute unit at most) also leave scores[j] = nrm[j] * sqrt(sum over the token tiles, in tile
 // order and in double, of s2_part[tile][j]) (Eq. 3): the token tile of a channel chunk that finishes last does the sum.
 // chunk_ctr: one int per channel chunk (m of them suffice), zero before the launch and zero again after it.
 struct PrefillScores {
@@ -241,13 +241,19 @@ hipError_t launch_down_gemm_bf16(const void *w, int d, const int *list, const in
 hipError_t launch_prefill_gateup_keep_bf16(const void *w, int d, int m, const void *x, int T, float *s2_part,
                                            uint16_t *h_all, int ldh, int n_cu, hipStream_t s,
                                            const PrefillScores *fin = nullptr);
-// bf16 layers with d % 64 == 0, T <= kPreciseMaxTokens: gate/up with the contraction's partial sums added up in double,
-// h[t][j] in float32 ([T][m], by channel).  Without a list: all channels, and their scores as fin says (chunk_ctr zero
-// before and after).  With one (n_list: its length, on the device): the listed channels, no scores.
-constexpr int kPreciseMaxTokens = 31;
-bool precise_gateup_takes(int is_bf16, int d, int T);
-hipError_t launch_precise_gateup(const void *w, int d, int m, const void *x, int T, const int *list, const int *n_list,
-                                 float *h, float *s2_part, const PrefillScores *fin, int n_cu, hipStream_t s);
+// Gate/up of up to precise_max_tokens tokens (0: not for such layers) with sums in double and h[t][j] in float32 ([T][m],
+// by channel).  Without a list: all channels, and their scores as fin says (chunk_ctr zero before and after).  With one
+// (n_list: its length, on the device): the listed channels, no scores.
+constexpr int kF32MaxTokens = 64;
+int precise_max_tokens(int is_bf16, int d);
+hipError_t launch_precise_gateup(const void *w, int is_bf16, int d, int m, const void *x, int T, const int *list,
+                                 const int *n_list, float *h, float *s2_part, const PrefillScores *fin, int n_cu,
+                                 hipStream_t s);
+// float32 layers, T <= kF32MaxTokens: the slab partials of the down projection (summed by launch_skinny_down)
+int f32_down_slabs(int d, int m, int n_cu);
+hipError_t launch_down_f32_partials(const void *w, int d, int m, const int *list, const int *n_dev, const float *h,
+                                    const unsigned char *mask, int mask_stride, int T, float *partial, int n_slabs,
+                                    hipStream_t s);
 // ---- input-side importance (pop_input_side.hip) ----
 int input_side_groups(int T);  // row groups of a T-token prompt (sizes part below: [groups][d] doubles)
 // s2[k] = sum_t x[t][k]^2 over the T rows (fixed summation order)

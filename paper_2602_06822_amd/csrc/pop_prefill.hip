@@ -18,7 +18,7 @@
 // (Sec. 3.4): one also writes H (rounded to bf16) as [T][m]; one runs its chunks over a device-resident list of
 // active channels instead of all m and writes H (optionally times a per-token mask) in compact form
 // [T][list position] for the down projection instead of reducing its squares.
-// float32: plain FMA tiles with the same structure (64 tokens x 32 channels per workgroup).
+// float32: FP64 matrix-core tiles (gateup_f32_kernel), described there.
 #include <stdlib.h>
 
 #include "pop_internal.h"
@@ -33,9 +33,7 @@ constexpr int kPfChunk = 96;      // channels per workgroup tile at most
 constexpr int kPfBK = 64;         // k elements per stage
 constexpr int kPfLd = kPfBK + 8;  // padded LDS row stride in elements (144 B): conflict-free 16-byte reads
 
-constexpr int kPf32BM = 64;
-constexpr int kPf32BC = 32;
-constexpr int kPf32BK = 16;
+constexpr int kPf32BM = 16;       // smallest token tile of the float32 form
 
 int prefill_num_tiles(int T, int is_bf16)
 {
@@ -695,57 +693,228 @@ __global__ __launch_bounds__(kPmThreads, 1) void prefill_mma_kernel(const uint16
     }
 }
 
-// float32: 64 tokens x 32 channels per workgroup; thread (tx = channel, ty = group of 8 tokens).
-__global__ __launch_bounds__(256) void prefill_f32_kernel(const float *__restrict__ w, const float *__restrict__ x,
-                                                          int T, int d, int m, float *__restrict__ s2_part)
+// ---- float32 layers: both projections of a few tokens on the FP64 matrix cores
+//
+// Products of float32 values are exact in double, so the sums are good to double whatever their order, and the decode
+// steps' float64 dot products lose nothing to these.  16x16x4 products (64 cycles; lane (c, g) = (lane % 16, lane / 16)
+// holds row c, k = g of either operand; register v of the result is row 4 v + g, column c).  The contraction index may be
+// taken in any order as long as both operands agree, so a lane loads 16 bytes along k and feeds four products.
+// Small layers are bound by latency: the four waves of a workgroup split the contraction and meet through LDS, and the
+// tile (16 TA tokens x 8 NB channels) is small where that takes to fill the chip.  64 tokens, d 512, m 1376: 12 us
+// with the scores, against 62 + 5 us for a float32 multiply-add tile on 43 workgroups and the launch that summed its rows.
+typedef double f64x4_t __attribute__((ext_vector_type(4)));
+constexpr int kF32Waves = 4;
+constexpr int kF32Steps = 4;  // k-steps of 16 elements whose loads are in flight per lane
+
+// B rows of a fragment: gate rows of 8 channels, then the up rows of the same.  list: channels (null: all m), n_list on
+// the device.  h32 [T][m] by channel and s2_part / scores as asked for.
+template <int TA, int NB>
+__global__ __launch_bounds__(kF32Waves * 64) void gateup_f32_kernel(const float *__restrict__ w, const float *__restrict__ x,
+                                                                    int T, int d, int m, int n_tt,
+                                                                    float *__restrict__ s2_part, PfStore st)
 {
-    __shared__ float As[kPf32BM][kPf32BK + 1];
-    __shared__ float Bg[kPf32BC][kPf32BK + 1];
-    __shared__ float Bu[kPf32BC][kPf32BK + 1];
-    __shared__ float colsum[8][kPf32BC];
-    const int c0 = blockIdx.x * kPf32BC, ttile = blockIdx.y, t0 = ttile * kPf32BM;
-    const int tid = threadIdx.x, tx = tid % 32, ty = tid / 32;
-    float g[8], u[8];
+    constexpr int BM = 16 * TA, BC = 8 * NB;
+    extern __shared__ __attribute__((aligned(16))) double f32_lds[];  // [4 waves][BM][16 NB], then h [BM][BC] floats
+    __shared__ float colsum[1][kPfChunk];
+    const int n_ch = st.list ? *st.n_list : m;
+    const int c0 = blockIdx.x * BC, ttile = blockIdx.y, t0 = ttile * BM;
+    if (c0 >= n_ch) return;
+    const int cn = min(BC, n_ch - c0);
+    const int tid = threadIdx.x, lane = tid % kWave, wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int c = lane % 16, g = lane / 16;
+
+    const float *pa[TA], *pb[NB];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) g[i] = u[i] = 0.f;
-    for (int k0 = 0; k0 < d; k0 += kPf32BK) {
-        for (int i = tid; i < kPf32BM * kPf32BK; i += 256) {
-            int r = i / kPf32BK, k = i % kPf32BK;
-            As[r][k] = (t0 + r < T && k0 + k < d) ? x[(size_t)(t0 + r) * d + k0 + k] : 0.f;
+    for (int a = 0; a < TA; ++a) pa[a] = x + (size_t)min(t0 + 16 * a + c, T - 1) * d;
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+        const int cc = c0 + min(8 * b + c % 8, cn - 1);
+        const int j = st.list ? st.list[cc] : cc;
+        pb[b] = w + ((size_t)j * 3 + c / 8) * d;
+    }
+    f64x4_t acc[TA][NB];
+#pragma unroll
+    for (int a = 0; a < TA; ++a)
+#pragma unroll
+        for (int b = 0; b < NB; ++b) acc[a][b] = f64x4_t{0.0, 0.0, 0.0, 0.0};
+    for (int s = wave; s * 16 < d; s += kF32Waves * kF32Steps) {
+        float4 va[kF32Steps][TA], vb[kF32Steps][NB];
+#pragma unroll
+        for (int u = 0; u < kF32Steps; ++u) {
+            const int k = (s + u * kF32Waves) * 16 + 4 * g, kk = k < d ? k : 0;
+#pragma unroll
+            for (int a = 0; a < TA; ++a) va[u][a] = *reinterpret_cast<const float4 *>(pa[a] + kk);
+#pragma unroll
+            for (int b = 0; b < NB; ++b) vb[u][b] = *reinterpret_cast<const float4 *>(pb[b] + kk);
         }
-        for (int i = tid; i < kPf32BC * kPf32BK; i += 256) {
-            int r = i / kPf32BK, k = i % kPf32BK;
-            bool ok = c0 + r < m && k0 + k < d;
-            Bg[r][k] = ok ? w[((size_t)(c0 + r) * 3) * d + k0 + k] : 0.f;
-            Bu[r][k] = ok ? w[((size_t)(c0 + r) * 3 + 1) * d + k0 + k] : 0.f;
+#pragma unroll
+        for (int u = 0; u < kF32Steps; ++u) {
+            const bool live = (s + u * kF32Waves) * 16 + 4 * g < d;  // (beyond the row: zero times the row's start)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int a = 0; a < TA; ++a) {
+                    const float4 &q = va[u][a];
+                    const float f = e == 0 ? q.x : (e == 1 ? q.y : (e == 2 ? q.z : q.w));
+                    const double fa = live ? (double)f : 0.0;
+#pragma unroll
+                    for (int b = 0; b < NB; ++b) {
+                        const float4 &r = vb[u][b];
+                        const double fb = (double)(e == 0 ? r.x : (e == 1 ? r.y : (e == 2 ? r.z : r.w)));
+                        acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa, fb, acc[a][b], 0, 0, 0);
+                    }
+                }
         }
-        __syncthreads();
+    }
+    constexpr int RW = 16 * NB;
+    double *mine = f32_lds + (size_t)wave * BM * RW;
 #pragma unroll
-        for (int k = 0; k < kPf32BK; ++k) {
-            float wg = Bg[tx][k], wu = Bu[tx][k];
+    for (int a = 0; a < TA; ++a)
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                float a = As[ty * 8 + i][k];
-                g[i] = fmaf(a, wg, g[i]);
-                u[i] = fmaf(a, wu, u[i]);
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) mine[(16 * a + 4 * v + g) * RW + 16 * b + c] = acc[a][b][v];
+    __syncthreads();
+    float *hs = reinterpret_cast<float *>(f32_lds + (size_t)kF32Waves * BM * RW);  // [BM][BC]
+    for (int i = tid; i < BM * BC; i += kF32Waves * kWave) {
+        const int r = i / BC, ch = i % BC, at = r * RW + 16 * (ch / 8) + ch % 8;
+        double gs = 0.0, us = 0.0;
+#pragma unroll
+        for (int q = 0; q < kF32Waves; ++q) {
+            gs += f32_lds[(size_t)q * BM * RW + at];
+            us += f32_lds[(size_t)q * BM * RW + at + 8];
+        }
+        const bool live = t0 + r < T && ch < cn;
+        const float h = live ? silu_mul((float)gs, (float)us) : 0.f;
+        hs[i] = h;
+        if (live && st.h32) st.h32[(size_t)(t0 + r) * m + (st.list ? st.list[c0 + ch] : c0 + ch)] = h;
+    }
+    if (!s2_part) return;
+    __syncthreads();
+    if (tid < BC) {
+        double tot = 0.0;
+        for (int r = 0; r < BM; ++r) tot += (double)hs[r * BC + tid] * (double)hs[r * BC + tid];
+        colsum[0][tid] = (float)tot;
+    }
+    pf_chunk_scores<1>(colsum, m, n_tt, ttile, blockIdx.x, c0, cn, s2_part, st);
+}
+
+template <int TA, int NB>
+static hipError_t launch_gateup_f32(const void *w, int d, int m, const void *x, int T, float *s2_part, const PfStore &st,
+                                    hipStream_t s)
+{
+    const size_t lds = (size_t)kF32Waves * 16 * TA * 16 * NB * sizeof(double) + (size_t)16 * TA * 8 * NB * sizeof(float);
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&gateup_f32_kernel<TA, NB>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    const int n_tt = (T + 16 * TA - 1) / (16 * TA);
+    hipLaunchKernelGGL((gateup_f32_kernel<TA, NB>), dim3((m + 8 * NB - 1) / (8 * NB), n_tt), dim3(kF32Waves * kWave), lds, s,
+                       (const float *)w, (const float *)x, T, d, m, n_tt, s2_part, st);
+    return hipGetLastError();
+}
+
+// Tile of a float32 contraction: 64 tokens x 16 channels where that still gives every compute unit two workgroups, else
+// 16 tokens x 8 channels.
+static bool f32_large_tile(int T, int m, int n_cu) { return (T + 63) / 64 * ((m + 15) / 16) >= 2 * n_cu; }
+
+static hipError_t launch_gateup_f32_any(const void *w, int d, int m, const void *x, int T, float *s2_part, int n_cu,
+                                        const PfStore &st, hipStream_t s)
+{
+    return f32_large_tile(T, m, n_cu) ? launch_gateup_f32<4, 2>(w, d, m, x, T, s2_part, st, s)
+                                      : launch_gateup_f32<1, 1>(w, d, m, x, T, s2_part, st, s);
+}
+
+// partial[slab][t][:] = sum over the slab's list positions of h[t][j] * w[j][2][:], t < T <= 16 TA.  A workgroup owns 64
+// columns and a slab, its waves every fourth group of four channels; lane (c, g) loads 16 bytes of channel g's row at
+// columns 4 c, product e takes column 4 c + e of every lane.
+template <int TA>
+__global__ __launch_bounds__(kF32Waves * 64) void down_f32_kernel(const float4 *__restrict__ w, int nvec,
+                                                                  const int *__restrict__ list,
+                                                                  const int *__restrict__ n_dev,
+                                                                  const float *__restrict__ h, int m,
+                                                                  const unsigned char *__restrict__ mask, int mask_stride,
+                                                                  int T, float *__restrict__ partial, int d)
+{
+    __shared__ double red[kF32Waves][16 * 64];
+    const int tid = threadIdx.x, lane = tid % kWave, wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int c = lane % 16, g = lane / 16;
+    const int n = *n_dev, n_slabs = gridDim.y, per_slab = (n + n_slabs - 1) / n_slabs;
+    const int s0 = min(n, (int)blockIdx.y * per_slab), s1 = min(n, s0 + per_slab);
+    const int vcol = blockIdx.x * 16 + c;
+    const float4 *wc = w + (vcol < nvec ? vcol : 0);
+    f64x4_t acc[TA][4];
+#pragma unroll
+    for (int a = 0; a < TA; ++a)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[a][e] = f64x4_t{0.0, 0.0, 0.0, 0.0};
+    constexpr int U = 4;
+    for (int p0 = s0 + 4 * wave; p0 < s1; p0 += 4 * kF32Waves * U) {
+        float4 vw[U];
+        float va[U][TA];
+        unsigned char mk[U][TA];
+        int js[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) js[u] = list[min(p0 + 4 * kF32Waves * u + g, s1 - 1)];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            vw[u] = wc[((size_t)js[u] * 3 + 2) * nvec];
+#pragma unroll
+            for (int a = 0; a < TA; ++a) {
+                const int t = min(16 * a + c, T - 1);
+                va[u][a] = h[(size_t)t * m + js[u]];
+                mk[u][a] = mask ? mask[(size_t)t * mask_stride + js[u]] : (unsigned char)1;
             }
         }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const bool live = p0 + 4 * kF32Waves * u + g < s1;
+            const double fw[4] = {(double)vw[u].x, (double)vw[u].y, (double)vw[u].z, (double)vw[u].w};
+#pragma unroll
+            for (int a = 0; a < TA; ++a) {
+                const double fa = live && mk[u][a] ? (double)va[u][a] : 0.0;
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    acc[a][e] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa, fw[e], acc[a][e], 0, 0, 0);
+            }
+        }
+    }
+#pragma unroll
+    for (int a = 0; a < TA; ++a) {
         __syncthreads();
-    }
-    float ss = 0.f;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        float hv = silu_mul(g[i], u[i]);
-        ss = fmaf(hv, hv, ss);
-    }
-    colsum[ty][tx] = ss;
-    __syncthreads();
-    if (tid < kPf32BC && c0 + tid < m) {
-        float tot = 0.f;
+        for (int e = 0; e < 4; ++e)
 #pragma unroll
-        for (int q = 0; q < 8; ++q) tot += colsum[q][tid];
-        s2_part[(size_t)ttile * m + c0 + tid] = tot;
+            for (int v = 0; v < 4; ++v) red[wave][(4 * v + g) * 64 + 4 * c + e] = acc[a][e][v];
+        __syncthreads();
+        for (int i = tid; i < 16 * 64; i += kF32Waves * kWave) {
+            const int t = 16 * a + i / 64, col = blockIdx.x * 64 + i % 64;
+            if (t < T && col < d)
+                partial[((size_t)blockIdx.y * T + t) * d + col] = (float)((red[0][i] + red[1][i]) + (red[2][i] + red[3][i]));
+        }
     }
+}
+
+int f32_down_slabs(int d, int m, int n_cu)
+{
+    const int cols = (d + 63) / 64;
+    int slabs = 2 * n_cu / cols;
+    if (slabs > (m + 31) / 32) slabs = (m + 31) / 32;  // (a few channels per wave at least)
+    return slabs < 1 ? 1 : (slabs > 64 ? 64 : slabs);
+}
+
+hipError_t launch_down_f32_partials(const void *w, int d, int m, const int *list, const int *n_dev, const float *h,
+                                    const unsigned char *mask, int mask_stride, int T, float *partial, int n_slabs,
+                                    hipStream_t s)
+{
+    if (T < 1 || T > kF32MaxTokens) return hipErrorInvalidValue;
+    const dim3 grid((d + 63) / 64, n_slabs);
+    if (T <= 16)
+        hipLaunchKernelGGL(down_f32_kernel<1>, grid, dim3(kF32Waves * kWave), 0, s, (const float4 *)w, d / 4, list, n_dev, h,
+                           m, mask, mask_stride, T, partial, d);
+    else
+        hipLaunchKernelGGL(down_f32_kernel<4>, grid, dim3(kF32Waves * kWave), 0, s, (const float4 *)w, d / 4, list, n_dev, h,
+                           m, mask, mask_stride, T, partial, d);
+    return hipGetLastError();
 }
 
 // Token tile of the register-staged kernel: 256 or 128 tokens, whichever gives the cheaper schedule: tiles per compute
@@ -779,9 +948,8 @@ static int pm_token_fragments(int T, int n_ch, int n_cu, PmTiles *tiles)
     return best;
 }
 
-int prefill_rows_used(int T, int is_bf16, int d, int m, int n_cu)
+int prefill_rows_used(int T, int d, int m, int n_cu)
 {
-    if (!is_bf16) return (T + kPf32BM - 1) / kPf32BM;
     if (prefill_direct(d)) {
         PmTiles g;
         const int bm = 64 * pm_token_fragments(T, m, n_cu, &g);
@@ -838,7 +1006,8 @@ static hipError_t launch_pm_all(const void *w, int d, int m, const void *x, int 
 // between the tiles a compute unit runs back to back on a long prompt (measured: +14 us at 2048 tokens).
 bool prefill_forms_scores(int is_bf16, int T, int d, int m, int n_cu)
 {
-    if (!is_bf16 || T < 1) return false;
+    if (T < 1) return false;
+    if (!is_bf16) return true;  // (small tiles, many per compute unit: one's wait hides behind the others)
     if (prefill_direct(d)) {
         PmTiles g;
         pm_token_fragments(T, m, n_cu, &g);
@@ -883,9 +1052,9 @@ hipError_t launch_prefill_gateup(const void *w, int is_bf16, int d, int m, const
         if (fin) st.fin_ctr = fin->chunk_ctr, st.nrm = fin->nrm, st.scores = fin->scores;
         return launch_pf_bf16_all<0>(w, d, m, x, T, s2_part, n_cu, st, s);
     }
-    dim3 grid((m + kPf32BC - 1) / kPf32BC, (T + kPf32BM - 1) / kPf32BM);
-    hipLaunchKernelGGL(prefill_f32_kernel, grid, dim3(256), 0, s, (const float *)w, (const float *)x, T, d, m, s2_part);
-    return hipGetLastError();
+    PfStore st{};
+    if (fin) st.fin_ctr = fin->chunk_ctr, st.nrm = fin->nrm, st.scores = fin->scores;
+    return launch_gateup_f32_any(w, d, m, x, T, s2_part, n_cu, st, s);
 }
 
 // bf16 only.  Gate/up over the channels of a device-resident list; hc[t][c] = bf16(H[t][list[c]]) (times
@@ -916,17 +1085,19 @@ hipError_t launch_gateup_list_bf16(const void *w, int d, int m, const void *x, i
     return e;
 }
 
-bool precise_gateup_takes(int is_bf16, int d, int T) { return is_bf16 && prefill_direct(d) && T >= 1 && T <= kPreciseMaxTokens; }
+int precise_max_tokens(int is_bf16, int d) { return is_bf16 ? (prefill_direct(d) ? 31 : 0) : kF32MaxTokens; }
 
-// (One token tile, bound by the weight stream, so the sums in double are free: 24 tokens, d 4096, m 11008
-// take 43 us, the same as without.)
-hipError_t launch_precise_gateup(const void *w, int d, int m, const void *x, int T, const int *list, const int *n_list,
-                                 float *h, float *s2_part, const PrefillScores *fin, int n_cu, hipStream_t s)
+// (bf16: one token tile, bound by the weight stream, so the sums in double are free: 24 tokens, d 4096, m 11008 take 43 us,
+// the same as without.)
+hipError_t launch_precise_gateup(const void *w, int is_bf16, int d, int m, const void *x, int T, const int *list,
+                                 const int *n_list, float *h, float *s2_part, const PrefillScores *fin, int n_cu,
+                                 hipStream_t s)
 {
     PfStore st{list, n_list, nullptr, 0, nullptr, n_cu};
     st.h32 = h;
+    if (fin && !list) st.fin_ctr = fin->chunk_ctr, st.nrm = fin->nrm, st.scores = fin->scores;
+    if (!is_bf16) return launch_gateup_f32_any(w, d, m, x, T, list ? nullptr : s2_part, n_cu, st, s);
     if (list) return launch_pm<1, 4>(w, d, m, x, T, PmTiles{}, nullptr, n_cu, st, s);
-    if (fin) st.fin_ctr = fin->chunk_ctr, st.nrm = fin->nrm, st.scores = fin->scores;
     return launch_pm<1, 3>(w, d, m, x, T, pm_tiles(m, 1, 1, n_cu), s2_part, n_cu, st, s);
 }
 

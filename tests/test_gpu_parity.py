@@ -566,14 +566,16 @@ def test_layer_partition_with_ties(pop, oracle, m):
 SHORT_PROMPT_TOL = 1e-5
 
 
-@pytest.mark.parametrize("d,m", [(64, 300), (192, 1100), (640, 2900), (136, 300)])
-@pytest.mark.parametrize("T", [2, 15, 16, 17, 31])
-def test_short_prompts_in_one_pass(pop, oracle, T, d, m):
-    """bf16 prompts below 32 tokens (one pass over the weights, hidden activations in float32, down projection on the
-    matrix cores in three exact parts): stand-alone FFN under shared and per-token masks whose lists are empty, one
+@pytest.mark.parametrize("T,dtype,d,m", [(T, BF16, d, m) for T in (2, 15, 16, 17, 31)
+                                         for d, m in ((64, 300), (192, 1100), (640, 2900), (136, 300))] +
+                         [(T, F32, d, m) for T in (2, 15, 16, 17, 31, 64, 70, 129)
+                          for d, m in ((4, 9), (260, 333), (512, 1376), (72, 4200))])
+def test_short_prompts_in_one_pass(pop, oracle, T, dtype, d, m):
+    """bf16 prompts below 32 tokens, float32 prompts of any length (one pass over the weights, hidden activations in float32, down projection on the
+    matrix cores in exact parts or in double): stand-alone FFN under shared and per-token masks whose lists are empty, one
     channel, whole and ragged chunks, and the prompt's own forward pass with its scores; a row length that is no whole
     k-step takes the decode kernels."""
-    L = synth.make_layer(synth.small_config("short_prompt", d, m, BF16, heavy_tail=True))
+    L = synth.make_layer(synth.small_config("short_prompt", d, m, dtype, heavy_tail=dtype == BF16))
     x = synth.make_activations(L, T, "prompt")
     g = synth.rng("short_prompt_mask", d, m, T)
     with GpuLayer(pop, L, max_tokens=T, max_batch=1) as G:
@@ -581,12 +583,12 @@ def test_short_prompts_in_one_pass(pop, oracle, T, d, m):
             mask = np.zeros(m, dtype=np.uint8)
             mask[g.choice(m, size=n, replace=False)] = 1
             y = G.ffn(x, mask, F32)
-            y_ref = oracle.pruned_ffn(x, L.w_gate, L.w_up, L.w_down, BF16, mask)
+            y_ref = oracle.pruned_ffn(x, L.w_gate, L.w_up, L.w_down, dtype, mask)
             assert (not y.any()) if n == 0 else max_abs_rel(y, y_ref) <= SHORT_PROMPT_TOL, n
         masks = (g.random((T, m)) < 0.4).astype(np.uint8)
         masks[0] = 0
         y = G.ffn(x, masks, F32)
-        y_ref = np.stack([oracle.pruned_ffn(x[t:t + 1], L.w_gate, L.w_up, L.w_down, BF16, masks[t])[0] for t in range(T)])
+        y_ref = np.stack([oracle.pruned_ffn(x[t:t + 1], L.w_gate, L.w_up, L.w_down, dtype, masks[t])[0] for t in range(T)])
         assert max_abs_rel(y, y_ref) <= SHORT_PROMPT_TOL
         n_ret, n_cand, k = m // 2, m // 4, m // 8
         _check_prefill(oracle, G, L, x, n_ret, n_cand)
