@@ -209,7 +209,7 @@ int pruned_ffn_mfma(pop_layer *L, const void *x, int T, const unsigned char *mas
         tmask = mask;
     }
     POP_HIP(launch_gateup_list_bf16(L->w, d, m, x, T, L->ulist, L->n_ulist, tmask, L->ffn_hc, ldh, L->n_cu, s));
-    POP_HIP(launch_down_gemm_bf16(L->w, d, L->ulist, L->n_ulist, L->ffn_hc, ldh, T, n_split, L->ffn_part, y, y_bf16, s,
+    POP_HIP(launch_down_gemm_bf16(L->w, d, L->ulist, L->n_ulist, L->ffn_hc, ldh, T, n_split, L->n_cu, L->ffn_part, y, y_bf16, s,
                                   L->zero_row));
     return POP_OK;
 }
@@ -555,7 +555,7 @@ int pop_prefill_forward(pop_layer_t *L, const void *x, int T, int n_ret, int n_c
     if (T == 0) return POP_OK;  // no token rows to produce
     if (keep) {
         POP_HIP(launch_compact_hidden(L->ffn_hall, ldh, T, L->top_list, L->top_list + m, n_ret + k0, L->ffn_hc, ldh, s));
-        POP_HIP(launch_down_gemm_bf16(L->w, d, L->top_list, L->top_list + m, L->ffn_hc, ldh, T, n_split, L->ffn_part, y,
+        POP_HIP(launch_down_gemm_bf16(L->w, d, L->top_list, L->top_list + m, L->ffn_hc, ldh, T, n_split, L->n_cu, L->ffn_part, y,
                                       ydtype == POP_BF16, s, L->zero_row));
         return POP_OK;
     }

@@ -9,24 +9,22 @@
 // 16 lanes points at a 4 (k) x 16 (n) patch, lane i at the 4 values of row i / 4 starting at column 4 (i % 4), and
 // receives it transposed, lane j the 4 k-values of column j.  Two such reads make the 8 values of one B fragment.
 //
-// Workgroup: 256 tokens x 128 columns, 8 waves (4 along the tokens x 2 along n), wave tile 64 x 64 = 2 x 2 MFMA
-// tiles, k-steps of 64 channels.  Short prompts do not give enough tiles to fill the chip, so the contraction is
-// split into n_split ranges whose float32 partial results are summed, in split order, by a second kernel
-// (deterministic).  Two kernels share this tile:
-//  * down_gemm_dma_kernel (d a multiple of 128): both operands go from global memory straight into a ring of three
-//    unpadded, swizzled LDS buffers, with one exact wait per k-step (described at the kernel);
-//  * down_gemm_bf16_kernel (any d): an LDS double buffer filled through registers with the rows of two k-steps in
-//    flight; channel numbers are fetched a step further ahead so the weight loads never wait for them.  Its weight
-//    tile has a row stride of 160 elements, which puts the 4 rows of a patch, and the two patches a read instruction's
-//    half-wave touches, into disjoint banks.
-#include <stdlib.h>
-
+// Short prompts do not give enough tiles to fill the chip, so the contraction is split into n_split ranges whose float32
+// partial results are summed, in split order, by a second kernel (deterministic).  Two kernels:
+//  * down_gemm_dma_kernel (d a multiple of 128): both operands go from global memory straight into rings of unpadded,
+//    swizzled LDS buffers, with one exact wait per k-step (described at the kernel);
+//  * down_gemm_bf16_kernel (other d): 256 tokens x 128 columns per workgroup, 8 waves (4 along the tokens x 2 along n), wave
+//    tile 64 x 64 = 2 x 2 products of 32x32x16, k-steps of 64 channels; an LDS double buffer filled through registers with
+//    the rows of two k-steps in flight; channel numbers are fetched a step further ahead so the weight loads never wait for
+//    them.  Its weight tile has a row stride of 160 elements, which puts the 4 rows of a patch, and the two patches a read
+//    instruction's half-wave touches, into disjoint banks.
 #include "pop_internal.h"
 
 namespace pop {
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 typedef short s16x4_t __attribute__((ext_vector_type(4)));
 typedef short s16x8_t __attribute__((ext_vector_type(8)));
 
@@ -212,209 +210,245 @@ __global__ __launch_bounds__(512) void down_gemm_bf16_kernel(const uint16_t *__r
         }
 }
 
-// The same tile with both operands loaded straight into LDS (global_load_lds) through a ring of three buffers.
-// Hc tile: 256 rows x 128 bytes, unpadded, the 16-byte units of row r stored at unit ^ ((r / 2) % 8) (conflict-free
-// 16-byte fragment reads).  Weight tile: 64 rows x 256 bytes, unpadded, the units of row k stored at
-// unit ^ (4 (k % 4)): the four rows of a transposing read's patch, and the two patches side by side that a half-wave
-// touches, then fall into eight different 32-byte bank groups.  Every wave issues the same loads in every k-step (2
-// for its weight rows' channel numbers, two steps ahead; 4 + 2 direct loads), so a step waits with an exact count for
-// its own rows only.  Nothing is masked: token rows beyond T are pointed at the last token and never stored, list
-// positions beyond the a channels are pointed at a row of zeros (zero_row, 256 bytes), which makes it irrelevant what
-// the Hc columns beyond a hold, as long as it is finite (the buffer is cleared when it is allocated and only ever
-// holds H values).  Needs d % 128 == 0 and ldh >= a rounded up to 64.
-constexpr int kDdStages = 3;
-constexpr int kDdPerStep = 8;  // vector-memory instructions a wave issues per k-step: 2 channel loads + 6 direct loads
+// Both operands loaded straight into LDS (global_load_lds).  A tile is 64 MF tokens x 128 columns; four waves of 16 MF
+// tokens x 128 columns each, 16x16x32 products.  Hc tile: rows of 128 bytes, unpadded, the 16-byte units of row r stored at
+// unit ^ ((r / 2) % 8) (conflict-free 16-byte fragment reads).  Weight tile: 64 rows x 256 bytes as they come: a quarter
+// wave reads one whole row.  The weight fragments are transposed in registers (two 16-byte rows, one byte permute per
+// register), which measured the same as the transposing LDS read and leaves all reads to the compiler's own counting.
+// One wave per SIMD, pipelined by hand like the prefill contraction (and as bound by power: 16x16x32 products move fewer
+// accumulator bytes, four waves read 48 KB of fragments per 32-element slice where eight of 64 x 64 read 64 KB): while the
+// products of one slice issue, the fragments of the next are read; a k-step is two slices, the first with the requests for
+// weight rows and channel numbers, then the barrier, the second with the requests for Hc rows.
+// Every wave issues the same loads in every k-step, so a step waits with an exact count for its own rows only.  Nothing is
+// masked: token rows beyond T are pointed at the last token and never stored, list positions beyond the a channels are
+// pointed at a row of zeros (zero_row, 256 bytes), which makes it irrelevant what the Hc columns beyond a hold, as long as
+// it is finite (the buffer is cleared when it is allocated and only ever holds H values).  Needs d % 128 == 0 and
+// ldh >= a rounded up to 64.
+// d 4096, 7155 channels: 512 tokens 45 us (the kernel of eight waves and 32x32x16 products it replaced: 42), 2048 tokens 122
+// us (123 to 136); 13B shape, 333 tokens, 6912 channels 43 us (47); 270 tokens, 9318 channels 41 us (48).
+constexpr int kDdThreads = 256;
+constexpr int kDdMaxMF = 5;
+constexpr int kDdSlots = 8;  // k-steps whose channel numbers are kept
+template <int MF>
+struct DdRing {
+    static constexpr int NA = MF >= 5 ? 2 : (MF >= 3 ? 3 : 4);
+    static constexpr int NB = MF == 4 ? 3 : 4;
+    static constexpr size_t kBytes = (size_t)(NA * 64 * MF * kDgBK + NB * kDgBK * kDgBN) * sizeof(uint16_t) + kDdSlots * kDgBK * 4;
+};
 
-__global__ __launch_bounds__(512) void down_gemm_dma_kernel(const uint16_t *__restrict__ w, int d,
-                                                            const int *__restrict__ list,
-                                                            const int *__restrict__ n_list,
-                                                            const uint16_t *__restrict__ hc, int ldh, int T, int n_tt,
-                                                            int n_nt, int n_split, int per_xcd,
-                                                            const uint16_t *__restrict__ zero_row,
-                                                            float *__restrict__ part, void *__restrict__ y, int y_bf16)
+template <int MF>
+__global__ __launch_bounds__(kDdThreads, 1) void down_gemm_dma_kernel(const uint16_t *__restrict__ w, int d,
+                                                                      const int *__restrict__ list,
+                                                                      const int *__restrict__ n_list,
+                                                                      const uint16_t *__restrict__ hc, int ldh, int T,
+                                                                      int n_tt, int n_nt, int n_split, int per_xcd,
+                                                                      const uint16_t *__restrict__ zero_row,
+                                                                      float *__restrict__ part, void *__restrict__ y,
+                                                                      int y_bf16)
 {
     typedef __attribute__((address_space(3))) void lds_t;
     typedef __attribute__((address_space(1))) const void glb_t;
-    constexpr int NS = kDdStages;
-    constexpr int kATile = kDgBM * kDgBK, kBTile = kDgBK * kDgBN;  // elements per stage
+    typedef float f32x4_t __attribute__((ext_vector_type(4)));
+    constexpr int NA = DdRing<MF>::NA, NB = DdRing<MF>::NB, F = kDgBN / 16;
+    constexpr int BM = 64 * MF, AT = BM * kDgBK, BT = kDgBK * kDgBN;  // elements per stage
+    constexpr int PA = BM / 32, PB = 4;  // direct loads per wave and k-step (and one of channel numbers)
     extern __shared__ __attribute__((aligned(16))) uint16_t dg_lds[];
-    uint16_t *As = dg_lds;                 // [NS][256 * 64]
-    uint16_t *Bs = dg_lds + NS * kATile;   // [NS][64 * 128]
+    uint16_t *As = dg_lds;            // [NA][64 MF * 64]
+    uint16_t *Bs = dg_lds + NA * AT;  // [NB][64 * 128]
+    int *Cs = reinterpret_cast<int *>(Bs + NB * BT);  // [8][64]
 
     const int logical = dg_xcd_logical_block(blockIdx.x, per_xcd);
     if (logical >= n_tt * n_nt * n_split) return;
+    // token tiles of one (split, column tile) are neighbours: they share its weight rows in the XCD's L2
     const int ttile = logical % n_tt, ntile = (logical / n_tt) % n_nt, split = logical / (n_tt * n_nt);
-    const int t0 = ttile * kDgBM, n0 = ntile * kDgBN;
+    const int t0 = ttile * BM, n0 = ntile * kDgBN;
 
     const int a = *n_list;
     const int steps_all = (a + kDgBK - 1) / kDgBK, steps_per = (steps_all + n_split - 1) / n_split;
     const int ks0 = min(split * steps_per, steps_all), ks1 = min(ks0 + steps_per, steps_all);
     const int n_steps = ks1 - ks0;
 
-    const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
-    const int wave_u = __builtin_amdgcn_readfirstlane(wave);
-    const int wm = wave / 2, wn = wave % 2;
+    const int tid = threadIdx.x, lane = tid % kWave;
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
 
-    f32x16_t acc[2][2];
+    f32x4_t acc[MF][F];
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < MF; ++i)
 #pragma unroll
-        for (int f = 0; f < 2; ++f)
+        for (int f = 0; f < F; ++f)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][f][v] = 0.f;
+            for (int v = 0; v < 4; ++v) acc[i][f][v] = 0.f;
 
     if (n_steps > 0) {
-        // direct loads.  Hc: pass p of wave w covers rows 64 p + 8 w + lane / 8, this lane the unit that belongs at
-        // position lane % 8 of its row.  Weights: pass p covers rows 32 p + 4 w + lane / 16, position lane % 16.
+        // direct loads.  Hc: pass p of wave w covers rows 32 p + 8 w + lane / 8, this lane the unit that belongs at
+        // position lane % 8 of its row.  Weights: pass p covers rows 16 p + 4 w + lane / 16, unit lane % 16.
         const int a_row = wave * 8 + lane / 8;
-        const int a_src = ((lane % 8) ^ ((a_row / 2) % 8)) * 8;   // (passes are 64 rows apart: same swizzle term)
-        const uint16_t *pa[4];
+        const int a_src = ((lane % 8) ^ ((a_row / 2) % 8)) * 8;  // (passes are 32 rows apart: same swizzle term)
+        const uint16_t *pa[PA];
 #pragma unroll
-        for (int p = 0; p < 4; ++p) pa[p] = hc + (size_t)min(t0 + a_row + p * 64, T - 1) * ldh + a_src;
-        const int b_row = wave * 4 + lane / 16;
-        const int b_src = n0 + ((lane % 16) ^ (4 * (b_row % 4))) * 8;  // (passes are 32 rows apart: same swizzle term)
-        // Channel numbers of this lane's two weight rows, for three k-steps (set = step % 3).  They are loaded with
-        // inline assembly, two steps before the direct loads that need them: the compiler does not see these loads, so
-        // it adds no waits of its own for them (across the loop's back edge those come out as waits for everything);
-        // the step's one explicit wait covers them, and passes the registers through so that no use moves above it.
-        int chn[3][2];
-        auto load_channels = [&](int set, int ks) {
-#pragma unroll
-            for (int p = 0; p < 2; ++p) {
-                const int *src = list + min(min(ks, ks1 - 1) * kDgBK + b_row + p * 32, a - 1);
-                asm volatile("global_load_dword %0, %1, off" : "=v"(chn[set][p]) : "v"(src) : "memory");
-            }
+        for (int p = 0; p < PA; ++p) pa[p] = hc + (size_t)min(t0 + a_row + p * 32, T - 1) * ldh + a_src;
+        const int b_row = wave * 4 + lane / 16, b_src = n0 + (lane % 16) * 8;
+        // Channel numbers of a k-step: one direct load of 64 of them into slot step % 8 of a small ring, two steps before
+        // they are needed (every wave loads the same, so that its own waits cover it).
+        auto load_channels = [&](int step) {
+            const int *src = list + min(min(ks0 + step, ks1 - 1) * kDgBK + lane, a - 1);
+            __builtin_amdgcn_global_load_lds((glb_t *)src, (lds_t *)(Cs + step % kDdSlots * kDgBK), 4, 0, 0);
         };
-        auto dma_load = [&](int buf, int set, int ks) {
-            const int kc = min(ks, ks1 - 1);
-#pragma unroll
-            for (int p = 0; p < 4; ++p)
-                __builtin_amdgcn_global_load_lds((glb_t *)(pa[p] + kc * kDgBK),
-                                                 (lds_t *)(As + buf * kATile + (p * 64 + wave_u * 8) * kDgBK), 16, 0, 0);
-#pragma unroll
-            for (int p = 0; p < 2; ++p) {
-                // (selected with a mask: a conditional would put the load under a branch and make its wait inexact)
-                const uintptr_t live = -(uintptr_t)(ks < ks1 && ks * kDgBK + b_row + p * 32 < a);
-                const uintptr_t p_row = (uintptr_t)(w + ((size_t)chn[set][p] * 3 + 2) * d + b_src);
-                const uintptr_t p_zero = (uintptr_t)(zero_row + (lane % 16) * 8);
-                const uint16_t *row = (const uint16_t *)(p_zero ^ ((p_row ^ p_zero) & live));
-                __builtin_amdgcn_global_load_lds((glb_t *)row,
-                                                 (lds_t *)(Bs + buf * kBTile + (p * 32 + wave_u * 4) * kDgBN), 16, 0, 0);
-            }
+        // (read with their own wait: seen as an ordinary read it would be taken to alias the direct loads in flight and wait
+        // for all of them)
+        auto channels = [&](int (&c)[PB], int step) {
+            const uint32_t at = (uint32_t)(uintptr_t)(Cs + step % kDdSlots * kDgBK + b_row);
+            asm volatile("ds_read_b32 %0, %4\n\tds_read_b32 %1, %4 offset:64\n\tds_read_b32 %2, %4 offset:128\n\t"
+                         "ds_read_b32 %3, %4 offset:192\n\ts_waitcnt lgkmcnt(0)"
+                         : "=&v"(c[0]), "=&v"(c[1]), "=&v"(c[2]), "=&v"(c[3])
+                         : "v"(at)
+                         : "memory");
         };
-        // fragment addresses.  A: row lane % 32 of the token fragment, unit kk / 8 + lane / 32 under the row's swizzle.
-        // B, read r: this lane points at row kk + 8 (lane / 32) + 4 r + (lane % 16) / 4, columns
-        // 16 ((lane / 16) % 2) + 4 (lane % 4) .. + 3 of the fragment, and receives column lane % 32.
-        const int arow = wm * 64 + lane % 32, a_sw = (arow / 2) % 8;  // (fragments are 32 rows apart: same term)
-        const int b_k = (lane / 32) * 8 + (lane % 16) / 4, b_sw = 4 * (b_k % 4);
-        const int b_col = wn * 64 + 16 * ((lane / 16) % 2) + 4 * (lane % 4);
-        // The fragment reads are issued as inline assembly: as an intrinsic the compiler takes the transposing read to
-        // alias the direct loads in flight and waits for all of those first.  It therefore does not count these reads
-        // either; the explicit waits below do: the reads of k-slice q + 1 are issued before the products of slice q,
-        // which wait for all reads but those six.
-        auto tr_read = [&](s16x4_t &v, const uint16_t *q) {
-            asm volatile("ds_read_b64_tr_b16 %0, %1" : "=v"(v) : "v"((uint32_t)(uintptr_t)q));
+        auto load_a = [&](int p, int buf, int step) {
+            __builtin_amdgcn_global_load_lds((glb_t *)(pa[p] + min(ks0 + step, ks1 - 1) * kDgBK),
+                                             (lds_t *)(As + buf * AT + (p * 32 + wave * 8) * kDgBK), 16, 0, 0);
         };
-        auto a_read = [&](bf16x8_t &v, const uint16_t *q) {
-            asm volatile("ds_read_b128 %0, %1" : "=v"(v) : "v"((uint32_t)(uintptr_t)q));
+        auto load_b = [&](int c, int p, int buf, int step) {
+            // (selected with a mask: a conditional would put the load under a branch and make its wait inexact)
+            const int ks = ks0 + step;
+            const uintptr_t live = -(uintptr_t)(ks < ks1 && ks * kDgBK + b_row + p * 16 < a);
+            const uintptr_t p_row = (uintptr_t)(w + ((size_t)c * 3 + 2) * d + b_src);
+            const uintptr_t p_zero = (uintptr_t)(zero_row + (lane % 16) * 8);
+            const uint16_t *row = (const uint16_t *)(p_zero ^ ((p_row ^ p_zero) & live));
+            __builtin_amdgcn_global_load_lds((glb_t *)row, (lds_t *)(Bs + buf * BT + (p * 16 + wave * 4) * kDgBN), 16, 0, 0);
         };
-        auto multiply = [&](int buf) {
-            const uint16_t *Ab = As + buf * kATile + arow * kDgBK;
-            const uint16_t *Bb = Bs + buf * kBTile + b_k * kDgBN;
-            bf16x8_t af[2][2];
-            s16x4_t lo[2][2], hi[2][2];
-            auto fetch = [&](int q, int set) {
+        // Fragment reads.  A: row lane % 16 of the token fragment, unit 4 q + lane / 16 under the row's swizzle.  Weights: lane
+        // (c, g) = (lane % 16, lane / 16) reads columns 8 c .. 8 c + 7 of rows 32 q + 8 g .. + 7, which is a transposed
+        // operand: one byte permute per register pairs the values of two rows, and product e takes column 8 c + e of every
+        // lane.
+        const uint16_t *Al = As + (wave * MF * 16 + lane % 16) * kDgBK;
+        const uint16_t *Bl = Bs + (lane / 16) * 8 * kDgBN + (lane % 16) * 8;
+        int koff[2];
 #pragma unroll
-                for (int f = 0; f < 2; ++f) {
-                    const int col = b_col + f * 32;
-                    const uint16_t *p = Bb + q * 16 * kDgBN + (((col / 8) ^ b_sw) * 8) + col % 8;
-                    tr_read(lo[set][f], p);
-                    tr_read(hi[set][f], p + 4 * kDgBN);
+        for (int q = 0; q < 2; ++q) koff[q] = ((q * 4 + lane / 16) ^ ((lane % 16) / 2)) * 8;
+        bf16x8_t af[2][MF];
+        bf16x8_t rows[2][8];
+        constexpr int NR = 8 + MF, NP = MF * F;
+        auto fetch = [&](const uint16_t *Ab, const uint16_t *Bb, int i, int q, int set) {
+            if (i < 8)
+                rows[set][i] = *reinterpret_cast<const bf16x8_t *>(Bb + (q * 32 + i) * kDgBN);
+            else
+                af[set][i - 8] = *reinterpret_cast<const bf16x8_t *>(Ab + (i - 8) * 16 * kDgBK + koff[q]);
+        };
+        // product i: fragment i / MF of the columns, i % MF of the tokens
+        bf16x8_t bw;
+        auto product = [&](int i, int set) {
+            const int e = i / MF, m_ = i % MF;
+            if (m_ == 0) {
+                uint32_t v[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const u32x4_t r0 = __builtin_bit_cast(u32x4_t, rows[set][2 * q]);
+                    const u32x4_t r1 = __builtin_bit_cast(u32x4_t, rows[set][2 * q + 1]);
+                    v[q] = __builtin_amdgcn_perm(r1[e / 2], r0[e / 2], e % 2 ? 0x07060302u : 0x05040100u);
                 }
-#pragma unroll
-                for (int i = 0; i < 2; ++i)
-                    a_read(af[set][i], Ab + i * 32 * kDgBK + (((q * 2 + lane / 32) ^ a_sw) * 8));
-            };
-            fetch(0, 0);
-#pragma unroll
-            for (int q = 0; q < kDgBK / 16; ++q) {
-                const int c = q & 1;
-                if (q + 1 < kDgBK / 16) {
-                    fetch(q + 1, c ^ 1);
-                    asm volatile("s_waitcnt lgkmcnt(6)"
-                                 : "+v"(lo[c][0]), "+v"(hi[c][0]), "+v"(lo[c][1]), "+v"(hi[c][1]), "+v"(af[c][0]), "+v"(af[c][1])
-                                 :
-                                 : "memory");
-                } else {
-                    asm volatile("s_waitcnt lgkmcnt(0)"
-                                 : "+v"(lo[c][0]), "+v"(hi[c][0]), "+v"(lo[c][1]), "+v"(hi[c][1]), "+v"(af[c][0]), "+v"(af[c][1])
-                                 :
-                                 : "memory");
-                }
-#pragma unroll
-                for (int i = 0; i < 2; ++i)
-#pragma unroll
-                    for (int f = 0; f < 2; ++f) {
-                        const bf16x8_t bf = __builtin_bit_cast(
-                            bf16x8_t, __builtin_shufflevector(lo[c][f], hi[c][f], 0, 1, 2, 3, 4, 5, 6, 7));
-                        acc[i][f] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[c][i], bf, acc[i][f], 0, 0, 0);
-                    }
+                bw = __builtin_bit_cast(bf16x8_t, u32x4_t{v[0], v[1], v[2], v[3]});
             }
+            // (two wait states: the compiler does not see that a product reads what a permute has just written)
+            if (m_ == 0)
+                asm volatile("s_nop 1\n\tv_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc[m_][e]) : "v"(af[set][m_]), "v"(bw));
+            else
+                asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc[m_][e]) : "v"(af[set][m_]), "v"(bw));
         };
-
-        // Step ks0 + i multiplies buffer i % 3.  Per step: wait until this wave's direct loads of the step have landed
-        // (all but the kDdPerStep instructions of the step after it), meet the other waves (now everybody's have, and
-        // everybody is done reading the buffer of the step before), request the channel numbers of the step four
-        // ahead and the rows of the step two ahead (into that buffer; its channel numbers were requested before the
-        // rows of this step, so they have arrived too), multiply.  Steps beyond the last are requested as rows of
-        // zeros (weights) and again from the last step (Hc), so the count holds.
-        static_assert((NS - 2) * kDdPerStep == 8, "the wait below allows the 8 instructions of the next step");
-#define POP_DD_CHN "+v"(chn[0][0]), "+v"(chn[0][1]), "+v"(chn[1][0]), "+v"(chn[1][1]), "+v"(chn[2][0]), "+v"(chn[2][1])
-        load_channels(0, ks0);
-        load_channels(1, ks0 + 1);
-        load_channels(2, ks0 + 2);
-        asm volatile("s_waitcnt vmcnt(0)" : POP_DD_CHN : : "memory");
-        dma_load(0, 0, ks0);
-        dma_load(1, 1, ks0 + 1);
-        load_channels(0, ks0 + 3);
-        // step i (buffer and channel set b = i % 3, fixed by unrolling three steps per trip)
-        auto step = [&](int i, int b) {
-            asm volatile("s_waitcnt vmcnt(8)\n\ts_barrier" : POP_DD_CHN : : "memory");  // (no fence: it would wait for all)
-            load_channels((b + 1) % 3, ks0 + i + 4);
-            dma_load((b + 2) % 3, (b + 2) % 3, ks0 + i + 2);
-            __builtin_amdgcn_sched_barrier(0);
-            multiply(b);
-        };
-        int i = 0;
-        for (; i + 3 <= n_steps; i += 3) {
-            step(i, 0);
-            step(i + 1, 1);
-            step(i + 2, 2);
+        // Requests in program order: ... A(s + NA - 1) | C(s + NB + 1), B(s + NB - 1) [wait for step s + 1] A(s + NA) | ...: the
+        // wait may leave in flight what was issued after A(s + 1), B(s + 1) and the C that the next B requests use
+        constexpr int kAfterA = (NA - 1) * (PB + 1) + (NA - 2) * PA, kAfterB = (NB - 2) * (PA + PB + 1);
+        constexpr int kAfterC = PA + 2 * PB + 1;
+        constexpr int kRows = kAfterA < kAfterB ? kAfterA : kAfterB, kYounger = kRows < kAfterC ? kRows : kAfterC;
+        static_assert(kYounger < 64 && (NB - 2) * PB + (NA - 1) * PA < 64, "vmcnt is a 6-bit counter");
+        // What steps before the first would have requested: channel numbers up to step NB, then the first NB - 1 steps of
+        // weight rows and the first NA of token rows, step by step; the first two waits leave what comes after their step.
+        static_assert(NB + 2 <= kDdSlots && NA >= 2 && NB >= 3, "rings");
+        static_assert(kYounger <= (NB - 3) * PB + (NA - 2) * PA + PB + 1, "the wait of the first step");
+        for (int q = 0; q <= NB; ++q) load_channels(q);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        int chn[PB];
+        constexpr int kDeep = NA > NB - 1 ? NA : NB - 1;
+#pragma unroll
+        for (int q = 0; q < kDeep; ++q) {
+            if (q < NB - 1) {
+                channels(chn, q);
+#pragma unroll
+                for (int p = 0; p < PB; ++p) load_b(chn[p], p, q, q);
+            }
+            if (q < NA) {
+#pragma unroll
+                for (int p = 0; p < PA; ++p) load_a(p, q, q);
+            }
         }
-        if (i < n_steps) step(i, 0);
-        if (i + 1 < n_steps) step(i + 1, 1);
-        // the surplus requests, before the LDS is given up; the channel registers are operands so that they stay
-        // allocated until the loads into them have landed (the last ones are never used)
-        asm volatile("s_waitcnt vmcnt(0)" : POP_DD_CHN : : "memory");
-#undef POP_DD_CHN
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((NB - 2) * PB + (NA - 1) * PA) : "memory");
+        int abuf = 0, bbuf = 0, bprev = NB - 1;
+        constexpr int kSpread = NP > 8 ? NP * 3 / 4 : NP;  // products the reads are spread over: the last have time to arrive
+#pragma unroll
+        for (int i = 0; i < NR; ++i) fetch(Al, Bl, i, 0, 0);
+        auto k_step = [&](int s) {
+            const uint16_t *Ab = Al + abuf * AT, *Bb = Bl + bbuf * BT;
+            load_channels(s + NB + 1);
+            channels(chn, s + NB - 1);
+#pragma unroll
+            for (int i = 0; i < NP; ++i) {
+                product(i, 0);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int r = min(i, kSpread) * NR / kSpread; r < min(i + 1, kSpread) * NR / kSpread; ++r) fetch(Ab, Bb, r, 1, 1);
+#pragma unroll
+                for (int p = i * PB / NP; p < (i + 1) * PB / NP; ++p) load_b(chn[p], p, bprev, s + NB - 1);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            // this wave's reads of the buffers are over and its rows of the next step have landed; after the barrier so are
+            // everybody's and have everybody's
+            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(kYounger) : "memory");
+            const int a_free = abuf;
+            bprev = bbuf;
+            abuf = abuf + 1 == NA ? 0 : abuf + 1;
+            bbuf = bbuf + 1 == NB ? 0 : bbuf + 1;
+            Ab = Al + abuf * AT, Bb = Bl + bbuf * BT;
+#pragma unroll
+            for (int i = 0; i < NP; ++i) {
+                product(i, 1);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int r = min(i, kSpread) * NR / kSpread; r < min(i + 1, kSpread) * NR / kSpread; ++r) fetch(Ab, Bb, r, 0, 0);
+#pragma unroll
+                for (int p = i * PA / NP; p < (i + 1) * PA / NP; ++p) load_a(p, a_free, s + NA);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        int s = 0;
+        for (; s + 2 <= n_steps; s += 2) {
+            k_step(s);
+            k_step(s + 1);
+        }
+        if (s < n_steps) k_step(s);
+        // the surplus requests, before the LDS is given up; the products' results before they are read (the compiler does
+        // not see the products, so it adds no wait states for them)
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_nop 15\n\ts_nop 15" ::: "memory");
     }
 
-    // register v of a fragment is token row (v / 4) * 8 + (lane / 32) * 4 + v % 4, column lane % 32
-    float *yp = part ? part + (size_t)split * T * d : nullptr;
+    // register v of product e is token 4 (lane / 16) + v of the fragment, column 8 (lane % 16) + e
+    const int row0 = t0 + wave * MF * 16 + lane / 16 * 4;
+    const size_t col = n0 + lane % 16 * 8;
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < MF; ++i)
 #pragma unroll
-        for (int f = 0; f < 2; ++f) {
-            const int n = n0 + wn * 64 + f * 32 + lane % 32;
+        for (int v = 0; v < 4; ++v) {
+            const int t = row0 + i * 16 + v;
+            if (t >= T) continue;
+            if (part || !y_bf16) {
+                float4 *dst = reinterpret_cast<float4 *>((part ? part + (size_t)split * T * d : (float *)y) + (size_t)t * d + col);
+                dst[0] = make_float4(acc[i][0][v], acc[i][1][v], acc[i][2][v], acc[i][3][v]);
+                dst[1] = make_float4(acc[i][4][v], acc[i][5][v], acc[i][6][v], acc[i][7][v]);
+            } else {
+                uint32_t q[4];
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int t = t0 + wm * 64 + i * 32 + (v / 4) * 8 + (lane / 32) * 4 + v % 4;
-                if (t < T && n < d) {
-                    const size_t o = (size_t)t * d + n;
-                    if (yp) yp[o] = acc[i][f][v];
-                    else if (y_bf16) ((uint16_t *)y)[o] = f32_to_bf16(acc[i][f][v]);
-                    else ((float *)y)[o] = acc[i][f][v];
-                }
+                for (int e = 0; e < 4; ++e)
+                    q[e] = (uint32_t)f32_to_bf16(acc[i][2 * e][v]) | ((uint32_t)f32_to_bf16(acc[i][2 * e + 1][v]) << 16);
+                *reinterpret_cast<uint4 *>((uint16_t *)y + (size_t)t * d + col) = make_uint4(q[0], q[1], q[2], q[3]);
             }
         }
 }
@@ -440,42 +474,80 @@ __global__ __launch_bounds__(256) void down_gemm_reduce_kernel(const float4 *__r
     }
 }
 
-// Ranges the contraction is split into so that the tiles fill the compute units.
+// Token fragments per wave (tiles of 64 MF tokens) and ranges the contraction is split into so that the tiles fill the
+// compute units.  A tile's time per k-slice: its products (16 cycles each on one matrix pipe) and what the LDS and the loads
+// add; splits shorten it, tiles beyond one per compute unit lengthen it.
+static int dd_shape(int T, int d, int n_cu, int *n_split)
+{
+    int best = 4;
+    long best_cost = -1;
+    for (int mf = kDdMaxMF; mf >= 1; --mf) {
+        const long tiles = (long)((T + 64 * mf - 1) / (64 * mf)) * ((d + kDgBN - 1) / kDgBN);
+        long split = n_cu / tiles;
+        if (split < 1) split = 1;
+        if (split > kDgMaxSplit) split = kDgMaxSplit;
+        const long cost = (tiles * split + n_cu - 1) / n_cu * (144 * mf + 100) * 840 / split;
+        if (best_cost < 0 || cost < best_cost) best_cost = cost, best = mf, *n_split = (int)split;
+    }
+    return best;
+}
+
 int down_gemm_splits(int T, int d, int n_cu)
 {
+    int n_split = 1;
+    if (d % kDgBN == 0) {
+        dd_shape(T, d, n_cu, &n_split);
+        return n_split;
+    }
     const int tiles = ((T + kDgBM - 1) / kDgBM) * ((d + kDgBN - 1) / kDgBN);
-    int n_split = n_cu / tiles;
+    n_split = n_cu / tiles;
     if (n_split < 1) n_split = 1;
     if (n_split > kDgMaxSplit) n_split = kDgMaxSplit;
     return n_split;
 }
 
+template <int MF>
+static hipError_t launch_dd(const void *w, int d, const int *list, const int *n_list, const uint16_t *hc, int ldh, int T,
+                            int n_split, float *part, void *y, int y_bf16, hipStream_t s, const uint16_t *zero_row)
+{
+    const size_t lds = DdRing<MF>::kBytes;
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&down_gemm_dma_kernel<MF>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    const int n_tt = (T + 64 * MF - 1) / (64 * MF), n_nt = d / kDgBN, per_xcd = (n_tt * n_nt * n_split + 7) / 8;
+    hipLaunchKernelGGL(down_gemm_dma_kernel<MF>, dim3(per_xcd * 8), dim3(kDdThreads), lds, s, (const uint16_t *)w, d, list,
+                       n_list, hc, ldh, T, n_tt, n_nt, n_split, per_xcd, zero_row, part, y, y_bf16);
+    return hipGetLastError();
+}
+
 // bf16 only; d % 8 == 0, ldh % 8 == 0.  part: float32 [n_split][T][d], needed when n_split > 1.  zero_row: 256 bytes
-// of zeros (optional); with it, d % 128 == 0 and ldh % 64 == 0 the direct-load kernel runs (POP_DG_DMA=0 keeps the
-// register-staged one, for comparison), which reads Hc columns up to the list length rounded up to 64.
+// of zeros (optional); with it, d % 128 == 0 and ldh % 64 == 0 the direct-load kernel runs, which reads Hc columns up to
+// the list length rounded up to 64.
 hipError_t launch_down_gemm_bf16(const void *w, int d, const int *list, const int *n_list, const uint16_t *hc, int ldh,
-                                 int T, int n_split, float *part, void *y, int y_bf16, hipStream_t s,
+                                 int T, int n_split, int n_cu, float *part, void *y, int y_bf16, hipStream_t s,
                                  const uint16_t *zero_row)
 {
-    static const int use_dma = getenv("POP_DG_DMA") ? atoi(getenv("POP_DG_DMA")) : 1;
-    const int n_tt = (T + kDgBM - 1) / kDgBM, n_nt = (d + kDgBN - 1) / kDgBN;
-    const int total = n_tt * n_nt * n_split, per_xcd = (total + 7) / 8;
-    hipError_t e;
-    if (use_dma && zero_row && d % kDgBN == 0 && ldh % kDgBK == 0) {
-        const size_t lds = (size_t)kDdStages * (kDgBM * kDgBK + kDgBK * kDgBN) * sizeof(uint16_t);
-        e = hipFuncSetAttribute(reinterpret_cast<const void *>(&down_gemm_dma_kernel),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    float *parts = n_split > 1 ? part : nullptr;
+    hipError_t e = hipSuccess;
+    if (zero_row && d % kDgBN == 0 && ldh % kDgBK == 0) {
+        int split = 1;
+#define POP_DD(MF) \
+    case MF: e = launch_dd<MF>(w, d, list, n_list, hc, ldh, T, n_split, parts, y, y_bf16, s, zero_row); break;
+        switch (dd_shape(T, d, n_cu, &split)) {
+            POP_DD(5) POP_DD(4) POP_DD(3) POP_DD(2) POP_DD(1)
+            default: return hipErrorInvalidValue;
+        }
+#undef POP_DD
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(down_gemm_dma_kernel, dim3(per_xcd * 8), dim3(512), lds, s, (const uint16_t *)w, d, list,
-                           n_list, hc, ldh, T, n_tt, n_nt, n_split, per_xcd, zero_row, n_split > 1 ? part : nullptr, y,
-                           y_bf16);
     } else {
+        const int n_tt = (T + kDgBM - 1) / kDgBM, n_nt = (d + kDgBN - 1) / kDgBN;
+        const int per_xcd = (n_tt * n_nt * n_split + 7) / 8;
         const size_t lds = (size_t)2 * (kDgBM * kDgLdA + kDgBK * kDgLdB) * sizeof(uint16_t);
         e = hipFuncSetAttribute(reinterpret_cast<const void *>(&down_gemm_bf16_kernel),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL(down_gemm_bf16_kernel, dim3(per_xcd * 8), dim3(512), lds, s, (const uint16_t *)w, d, list,
-                           n_list, hc, ldh, T, n_tt, n_nt, n_split, per_xcd, n_split > 1 ? part : nullptr, y, y_bf16);
+                           n_list, hc, ldh, T, n_tt, n_nt, n_split, per_xcd, parts, y, y_bf16);
     }
     e = hipGetLastError();
     if (e != hipSuccess || n_split <= 1) return e;

@@ -234,7 +234,7 @@ hipError_t launch_gateup_list_bf16(const void *w, int d, int m, const void *x, i
 // finite values.
 int down_gemm_splits(int T, int d, int n_cu);
 hipError_t launch_down_gemm_bf16(const void *w, int d, const int *list, const int *n_list, const uint16_t *hc, int ldh,
-                                 int T, int n_split, float *part, void *y, int y_bf16, hipStream_t s,
+                                 int T, int n_split, int n_cu, float *part, void *y, int y_bf16, hipStream_t s,
                                  const uint16_t *zero_row = nullptr);
 // bf16 layers: the prefill contraction (s2_part as in launch_prefill_gateup) that also keeps H:
 // h_all[t][j] = bf16(H[t][j]), row stride ldh.
