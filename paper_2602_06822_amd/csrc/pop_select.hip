@@ -14,15 +14,15 @@ namespace pop {
 // the search itself; done by everybody at once it costs nothing more, and the outputs (a dozen arrays in a layer's
 // prefill) are written by the whole chip.
 // Search: the keys sit in registers (NS per thread).  One histogram over the 11 bits below the keys' common leading bits
-// leaves a threshold in a bucket of a few dozen keys (another digit is swept only where more than kPartList are left),
-// whose ranks are counted out pairwise.  11 bits instead of 8 spread the LDS atomics over eight times as many words, and
-// one sweep of all keys takes the place of two, plus two of short lists.
+// leaves a threshold in a bucket of a few dozen to a few hundred keys, a second one (few keys take part) in one of a few,
+// whose ranks are counted out pairwise.  11 bits instead of 8 spread the LDS atomics over eight times as many words.
 // A threshold is an element (key, channel): channels up to it in the order (key descending, channel ascending) are in.
 // 11008 channels with all of a layer's outputs: 13 us, against 25 us for the four 8-bit sweeps of one workgroup and 6 us for
 // the launch that spread its lists; comparing all pairs of keys instead, 64 channels per workgroup, took 27 us.
 constexpr int kPartThreads = 1024;
 constexpr int kPartBins = 2048;
 constexpr int kPartList = 256;     // keys of a bucket counted out pairwise at most
+constexpr int kPartSmall = 32;     // another digit is swept while a bucket holds more: that is cheaper than the pairs
 constexpr int kPartMaxSlots = 32;  // keys per thread held in registers at most: 32768 channels
 
 struct PartShared {
@@ -149,7 +149,7 @@ __global__ __launch_bounds__(kPartThreads) void partition_kernel(const float *__
     for (int t = 0; t < NT; ++t) prefix[t] = sh.key_or & known;
     int hi = top_bit;
     bool first = true;
-    while (hi >= 0 && (matching[0] > kPartList || matching[1] > kPartList || matching[2] > kPartList)) {
+    while (hi >= 0 && (matching[0] > kPartSmall || matching[1] > kPartSmall || matching[2] > kPartSmall)) {
         const int lo = hi >= 10 ? hi - 10 : 0;
         const uint32_t dmask = (1u << (hi - lo + 1)) - 1u;
         if (first) {  // one prefix: one histogram for all thresholds
