@@ -39,6 +39,7 @@ constexpr int kIrMinGroups = 128;
 constexpr int kIrLongPrompt = 8192;
 
 // E columns per lane: 16-byte loads (8 bf16, 4 float32; rows and base 16-byte aligned) or, E = 1, one element.
+// nrm == nullptr: the sums themselves.
 template <bool BF16, int E>
 __global__ __launch_bounds__(kIcWaves * kWave) void importance_columns_kernel(const void *__restrict__ h, int T, int m,
                                                                               const float *__restrict__ nrm,
@@ -98,7 +99,7 @@ __global__ __launch_bounds__(kIcWaves * kWave) void importance_columns_kernel(co
         double tot = 0.0;
 #pragma unroll
         for (int w = 0; w < kIcWaves; ++w) tot += red[w][threadIdx.x];
-        scores[j] = (float)((double)nrm[j] * sqrt(tot));
+        scores[j] = nrm ? (float)((double)nrm[j] * sqrt(tot)) : (float)tot;
     }
 }
 
@@ -175,22 +176,26 @@ size_t importance_reduce_scratch_bytes(int T, int m)
     return importance_in_chunks(T, m) ? (size_t)importance_chunks(T, m) * m * sizeof(double) : 0;
 }
 
+static hipError_t launch_importance_columns(const void *h, int is_bf16, int T, int m, const float *nrm, float *scores,
+                                            hipStream_t s)
+{
+    const dim3 grid((m + kIcCols - 1) / kIcCols), block(kIcWaves * kWave);
+    const bool vec = (reinterpret_cast<uintptr_t>(h) & 15u) == 0 && m % (is_bf16 ? 8 : 4) == 0;
+    if (is_bf16 && vec)
+        hipLaunchKernelGGL((importance_columns_kernel<true, 8>), grid, block, 0, s, h, T, m, nrm, scores);
+    else if (is_bf16)
+        hipLaunchKernelGGL((importance_columns_kernel<true, 1>), grid, block, 0, s, h, T, m, nrm, scores);
+    else if (vec)
+        hipLaunchKernelGGL((importance_columns_kernel<false, 4>), grid, block, 0, s, h, T, m, nrm, scores);
+    else
+        hipLaunchKernelGGL((importance_columns_kernel<false, 1>), grid, block, 0, s, h, T, m, nrm, scores);
+    return hipGetLastError();
+}
+
 hipError_t launch_importance_reduce(const void *h, int is_bf16, int T, int m, const float *nrm, float *scores,
                                     void *scratch, hipStream_t s)
 {
-    if (!importance_in_chunks(T, m)) {
-        const dim3 grid((m + kIcCols - 1) / kIcCols), block(kIcWaves * kWave);
-        const bool vec = (reinterpret_cast<uintptr_t>(h) & 15u) == 0 && m % (is_bf16 ? 8 : 4) == 0;
-        if (is_bf16 && vec)
-            hipLaunchKernelGGL((importance_columns_kernel<true, 8>), grid, block, 0, s, h, T, m, nrm, scores);
-        else if (is_bf16)
-            hipLaunchKernelGGL((importance_columns_kernel<true, 1>), grid, block, 0, s, h, T, m, nrm, scores);
-        else if (vec)
-            hipLaunchKernelGGL((importance_columns_kernel<false, 4>), grid, block, 0, s, h, T, m, nrm, scores);
-        else
-            hipLaunchKernelGGL((importance_columns_kernel<false, 1>), grid, block, 0, s, h, T, m, nrm, scores);
-        return hipGetLastError();
-    }
+    if (!importance_in_chunks(T, m)) return launch_importance_columns(h, is_bf16, T, m, nrm, scores, s);
     const int n_chunks = importance_chunks(T, m);
     const int rows_per_chunk = (T + n_chunks - 1) / n_chunks;
     double *part = (double *)scratch;
@@ -205,6 +210,13 @@ hipError_t launch_importance_reduce(const void *h, int is_bf16, int T, int m, co
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(importance_finish_kernel, dim3((m + 255) / 256), dim3(256), 0, s, part, n_chunks, m, nrm, scores);
     return hipGetLastError();
+}
+
+bool column_squares_takes(int T) { return T <= kIrLongPrompt; }
+
+hipError_t launch_column_squares(const void *x, int is_bf16, int T, int d, float *s2, hipStream_t s)
+{
+    return launch_importance_columns(x, is_bf16, T, d, nullptr, s2, s);
 }
 
 }  // namespace pop

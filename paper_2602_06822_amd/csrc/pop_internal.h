@@ -276,4 +276,8 @@ size_t importance_reduce_scratch_bytes(int T, int m);
 hipError_t launch_importance_reduce(const void *h, int is_bf16, int T, int m, const float *nrm, float *scores,
                                     void *scratch, hipStream_t s);
 
+// s2[k] = sum_t x[t][k]^2 in one launch (not for very long prompts)
+bool column_squares_takes(int T);
+hipError_t launch_column_squares(const void *x, int is_bf16, int T, int d, float *s2, hipStream_t s);
+
 }  // namespace pop
