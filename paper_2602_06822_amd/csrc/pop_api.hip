@@ -117,20 +117,14 @@ int plan_fused_step(pop_layer *L)
     return POP_OK;
 }
 
-// Copies the step's selection results from the layer's state to the caller's buffers (each may be null).
-int copy_step_outputs(pop_layer *L, int B, float *cand_scores, unsigned char *mask, int *active_idx, int *n_active,
-                      hipStream_t s)
+// What the caller takes of the step's selection results, from the layer's state (each destination may be null).
+StepCopy step_copy(const pop_layer *L, int B, float *cand_scores, unsigned char *mask, int *active_idx, int *n_active)
 {
-    const int m = L->m, n_ret = L->n_ret, n_cand = L->n_cand;
-    if (cand_scores && n_cand)
-        POP_HIP(hipMemcpy2DAsync(cand_scores, (size_t)n_cand * 4, L->cscore, (size_t)m * 4, (size_t)n_cand * 4, B,
-                                 hipMemcpyDeviceToDevice, s));
-    if (mask) POP_HIP(hipMemcpyAsync(mask, L->mask, (size_t)B * m, hipMemcpyDeviceToDevice, s));
-    if (active_idx && n_ret + n_cand)
-        POP_HIP(hipMemcpy2DAsync(active_idx, (size_t)(n_ret + n_cand) * 4, L->active_idx, (size_t)m * 4,
-                                 (size_t)(n_ret + n_cand) * 4, B, hipMemcpyDeviceToDevice, s));
-    if (n_active) POP_HIP(hipMemcpyAsync(n_active, L->n_active, (size_t)B * 4, hipMemcpyDeviceToDevice, s));
-    return POP_OK;
+    StepCopy c;
+    c.B = B, c.m = L->m, c.n_cand = L->n_cand, c.n_list = L->n_ret + L->n_cand;
+    c.cscore = L->cscore, c.mask_src = L->mask, c.act_src = L->active_idx, c.n_act_src = L->n_active;
+    c.cand_scores = cand_scores, c.mask = mask, c.active_idx = active_idx, c.n_active = n_active;
+    return c;
 }
 
 // From this many tokens on a bf16 layer's stand-alone pruned FFN runs on the matrix cores (below it, the decode
@@ -568,8 +562,8 @@ int pop_prefill_forward(pop_layer_t *L, const void *x, int T, int n_ret, int n_c
     return rc;
 }
 
-int pop_decode_mask(pop_layer_t *L, const void *x_t, int B, const int *k, float *cand_scores, unsigned char *mask,
-                    int *active_idx, int *n_active, void *stream)
+// Pass 1 and the selection of a decode step; the results stay in the layer's state.
+static int decode_select(pop_layer_t *L, const void *x_t, int B, const int *k, void *stream)
 {
     if (!L || !x_t || !aligned16(x_t)) return POP_EINVAL;
     if (!L->has_partition) return POP_ESTATE;
@@ -617,7 +611,6 @@ int pop_decode_mask(pop_layer_t *L, const void *x_t, int B, const int *k, float 
                 POP_HIP(launch_gateup(L->w, L->is_bf16, L->d, m, x_t, B, L->ulist, m, L->n_ulist, L->h, nullptr, nullptr,
                                       0, 0, L->n_cu, s));
             L->step_fused = false;
-            { int rc = copy_step_outputs(L, B, cand_scores, mask, active_idx, n_active, s); if (rc != POP_OK) return rc; }
             L->step_B = B;
             L->step_k = kk;
             L->has_step = true;
@@ -646,10 +639,38 @@ int pop_decode_mask(pop_layer_t *L, const void *x_t, int B, const int *k, float 
         }
         L->step_fused = false;
     }
-    { int rc = copy_step_outputs(L, B, cand_scores, mask, active_idx, n_active, s); if (rc != POP_OK) return rc; }
     L->step_B = B;
     L->step_k = kk;
     L->has_step = true;
+    return POP_OK;
+}
+
+// The output of the decode step in the layer's state; `copy` rides along with its last launch.
+static int decode_output(pop_layer_t *L, int T, void *y, pop_dtype_t ydtype, const StepCopy *copy, hipStream_t s)
+{
+    const int m = L->m, d = L->d, y_bf16 = ydtype == POP_BF16;
+    if (!L->has_step) return POP_ESTATE;
+    if (T != L->step_B) return POP_ESHAPE;
+    if (L->step_fused)
+        POP_HIP(launch_decode_tail(L->partial, L->plan.n_wg, d, y, y_bf16, s, copy));
+    else if (T == 1)
+        POP_HIP(launch_down(L->w, L->is_bf16, d, m, L->active_idx, nullptr, L->n_ret + L->step_k.k[0], L->h, nullptr, 0, 1,
+                            L->partial, L->n_slabs, y, y_bf16, s, copy));
+    else if (L->is_bf16 && T >= kSkinnyMinBatch)
+        POP_HIP(launch_skinny_down(L->w, L->is_bf16, d, m, L->ulist, L->n_ulist, L->h, L->mask, m, T, L->partial,
+                                   skinny_down_slabs(L->is_bf16, d, m, L->n_cu), y, y_bf16, s, copy));
+    else
+        POP_HIP(launch_down(L->w, L->is_bf16, d, m, L->ulist, L->n_ulist, 0, L->h, L->mask, m, T, L->partial, L->n_slabs, y,
+                            y_bf16, s, copy));
+    return POP_OK;
+}
+
+int pop_decode_mask(pop_layer_t *L, const void *x_t, int B, const int *k, float *cand_scores, unsigned char *mask,
+                    int *active_idx, int *n_active, void *stream)
+{
+    const int rc = decode_select(L, x_t, B, k, stream);
+    if (rc != POP_OK) return rc;
+    POP_HIP(launch_step_copy(step_copy(L, B, cand_scores, mask, active_idx, n_active), as_stream(stream)));
     return POP_OK;
 }
 
@@ -666,10 +687,11 @@ int pop_decode_step(pop_layer_t *L, const void *x_t, int B, const int *k, void *
         if (kb < 0 || kb > L->n_cand) return POP_ESHAPE;
     }
     // the launches of the two calls (a single-sequence step on a shape the fused kernel takes: that kernel, then the
-    // small kernel that sums its workgroups' partial outputs)
-    int rc = pop_decode_mask(L, x_t, B, k, cand_scores, mask, active_idx, n_active, stream);
+    // small kernel that sums its workgroups' partial outputs), the last of which also copies what the caller takes
+    const int rc = decode_select(L, x_t, B, k, stream);
     if (rc != POP_OK) return rc;
-    return pop_pruned_ffn(L, nullptr, B, nullptr, 0, y, ydtype, stream);
+    const StepCopy copy = step_copy(L, B, cand_scores, mask, active_idx, n_active);
+    return decode_output(L, B, y, ydtype, &copy, as_stream(stream));
 }
 
 int pop_pruned_ffn(pop_layer_t *L, const void *x, int T, const unsigned char *mask, int mask_rows, void *y,
@@ -679,22 +701,7 @@ int pop_pruned_ffn(pop_layer_t *L, const void *x, int T, const unsigned char *ma
     if (ydtype != POP_F32 && ydtype != POP_BF16) return POP_EINVAL;
     hipStream_t s = as_stream(stream);
     const int m = L->m, d = L->d, y_bf16 = ydtype == POP_BF16, ysize = y_bf16 ? 2 : 4;
-    if (!mask) {
-        if (!L->has_step) return POP_ESTATE;
-        if (T != L->step_B) return POP_ESHAPE;
-        if (L->step_fused)
-            POP_HIP(launch_decode_tail(L->partial, L->plan.n_wg, d, y, y_bf16, s));
-        else if (T == 1)
-            POP_HIP(launch_down(L->w, L->is_bf16, d, m, L->active_idx, nullptr, L->n_ret + L->step_k.k[0], L->h,
-                                nullptr, 0, 1, L->partial, L->n_slabs, y, y_bf16, s));
-        else if (L->is_bf16 && T >= kSkinnyMinBatch)
-            POP_HIP(launch_skinny_down(L->w, L->is_bf16, d, m, L->ulist, L->n_ulist, L->h, L->mask, m, T, L->partial,
-                                       skinny_down_slabs(L->is_bf16, d, m, L->n_cu), y, y_bf16, s));
-        else
-            POP_HIP(launch_down(L->w, L->is_bf16, d, m, L->ulist, L->n_ulist, 0, L->h, L->mask, m, T, L->partial,
-                                L->n_slabs, y, y_bf16, s));
-        return POP_OK;
-    }
+    if (!mask) return decode_output(L, T, y, ydtype, nullptr, s);
     if (!x || !aligned16(x)) return POP_EINVAL;
     if (T < 1) return POP_ESHAPE;
     if (mask_rows != 1 && mask_rows != T) return POP_ESHAPE;

@@ -702,8 +702,13 @@ __global__ __launch_bounds__(MAXB) void decode_fused_kernel(FusedParams p)
 // so y does not depend on scheduling.
 constexpr int kTailWaves = 16;
 __global__ __launch_bounds__(1024) void decode_tail_kernel(const float *__restrict__ partial, int n_wg, int d,
-                                                           void *__restrict__ y, int y_bf16)
+                                                           void *__restrict__ y, int y_bf16, StepCopy copy)
 {
+    const int main_blocks = (d + kWave - 1) / kWave;
+    if ((int)blockIdx.x >= main_blocks) {  // what the step's caller takes of its selection
+        copy_step_block(copy, blockIdx.x - main_blocks, gridDim.x - main_blocks);
+        return;
+    }
     __shared__ float part[kTailWaves][kWave];
     const int lane = threadIdx.x % kWave, q = threadIdx.x / kWave;
     const int o = blockIdx.x * kWave + lane;
@@ -825,10 +830,12 @@ hipError_t launch_decode_fused(const FusedPlan &pl, int is_bf16, FusedParams &p,
     return fused_dispatch(is_bf16, pl.per, pl.block, FusedLaunchFn{pl, p, s});
 }
 
-hipError_t launch_decode_tail(const float *partial, int n_wg, int d, void *y, int y_bf16, hipStream_t s)
+hipError_t launch_decode_tail(const float *partial, int n_wg, int d, void *y, int y_bf16, hipStream_t s,
+                              const StepCopy *copy)
 {
-    hipLaunchKernelGGL(decode_tail_kernel, dim3((d + kWave - 1) / kWave), dim3(kTailWaves * kWave), 0, s, partial, n_wg, d,
-                       y, y_bf16);
+    const StepCopy c = copy ? *copy : StepCopy{};
+    hipLaunchKernelGGL(decode_tail_kernel, dim3((d + kWave - 1) / kWave + c.blocks(kTailWaves * kWave)),
+                       dim3(kTailWaves * kWave), 0, s, partial, n_wg, d, y, y_bf16, c);
     return hipGetLastError();
 }
 

@@ -431,8 +431,13 @@ __global__ __launch_bounds__(256) void down_kernel(const typename V::vec_t *__re
 // wave order, so the result does not depend on scheduling.  Sums in double: the slabs' partial sums are of the size of
 // the result, so a float32 chain over them would cost more than everything before it.
 __global__ __launch_bounds__(256) void down_reduce_kernel(const float *__restrict__ partial, int n_slabs, int total,
-                                                          void *__restrict__ y, int y_bf16)
+                                                          void *__restrict__ y, int y_bf16, StepCopy copy)
 {
+    const int main_blocks = (total + kWave - 1) / kWave;
+    if ((int)blockIdx.x >= main_blocks) {  // what the step's caller takes of its selection
+        copy_step_block(copy, blockIdx.x - main_blocks, gridDim.x - main_blocks);
+        return;
+    }
     __shared__ double part[4][kWave];
     const int lane = threadIdx.x % kWave, q = threadIdx.x / kWave;
     const int i = blockIdx.x * kWave + lane;
@@ -460,10 +465,29 @@ __global__ __launch_bounds__(256) void down_reduce_kernel(const float *__restric
     }
 }
 
+static hipError_t launch_down_reduce(const float *partial, int n_slabs, int total, void *y, int y_bf16, const StepCopy *copy,
+                                     hipStream_t s)
+{
+    const StepCopy c = copy ? *copy : StepCopy{};
+    hipLaunchKernelGGL(down_reduce_kernel, dim3((total + kWave - 1) / kWave + c.blocks(256)), dim3(256), 0, s, partial, n_slabs,
+                       total, y, y_bf16, c);
+    return hipGetLastError();
+}
+
+__global__ __launch_bounds__(256) void step_copy_kernel(StepCopy c) { copy_step_block(c, blockIdx.x, gridDim.x); }
+
+hipError_t launch_step_copy(const StepCopy &c, hipStream_t s)
+{
+    const int blocks = c.blocks(256);
+    if (blocks == 0) return hipSuccess;
+    hipLaunchKernelGGL(step_copy_kernel, dim3(blocks), dim3(256), 0, s, c);
+    return hipGetLastError();
+}
+
 template <class V>
 static hipError_t down_dispatch(const void *w, int nvec, int d, int m, const int *list, const int *n_dev, int n_host,
                                 const float *h, const unsigned char *mask, int mask_stride, int B, float *partial,
-                                int n_slabs, void *y, int y_bf16, hipStream_t s)
+                                int n_slabs, void *y, int y_bf16, hipStream_t s, const StepCopy *copy)
 {
     typedef typename V::vec_t vec_t;
     dim3 grid((nvec + kWave - 1) / kWave, n_slabs);
@@ -478,9 +502,7 @@ static hipError_t down_dispatch(const void *w, int nvec, int d, int m, const int
     }
 #undef POP_DN
     int total = B * d;
-    hipLaunchKernelGGL(down_reduce_kernel, dim3((total + kWave - 1) / kWave), dim3(256), 0, s, partial, n_slabs, total,
-                       y, y_bf16);
-    return hipGetLastError();
+    return launch_down_reduce(partial, n_slabs, total, y, y_bf16, copy, s);
 }
 
 int down_num_slabs(int d, int is_bf16)
@@ -495,13 +517,13 @@ int down_num_slabs(int d, int is_bf16)
 
 hipError_t launch_down(const void *w, int is_bf16, int d, int m, const int *list, const int *n_dev, int n_host,
                        const float *h, const unsigned char *mask, int mask_stride, int B, float *partial, int n_slabs,
-                       void *y, int y_bf16, hipStream_t s)
+                       void *y, int y_bf16, hipStream_t s, const StepCopy *copy)
 {
     if (is_bf16)
         return down_dispatch<VecBF16>(w, d / 8, d, m, list, n_dev, n_host, h, mask, mask_stride, B, partial, n_slabs,
-                                      y, y_bf16, s);
+                                      y, y_bf16, s, copy);
     return down_dispatch<VecF32>(w, d / 4, d, m, list, n_dev, n_host, h, mask, mask_stride, B, partial, n_slabs, y,
-                                 y_bf16, s);
+                                 y_bf16, s, copy);
 }
 
 // ---------------------------------------------------------------- down projection of up to 31 tokens on the matrix cores
@@ -690,15 +712,12 @@ static hipError_t launch_skinny_down_partials(const void *w, int d, int m, const
 
 hipError_t launch_skinny_down(const void *w, int is_bf16, int d, int m, const int *list, const int *n_dev, const float *h,
                               const unsigned char *mask, int mask_stride, int T, float *partial, int n_slabs, void *y,
-                              int y_bf16, hipStream_t s)
+                              int y_bf16, hipStream_t s, const StepCopy *copy)
 {
     hipError_t e = is_bf16 ? launch_skinny_down_partials(w, d, m, list, n_dev, h, mask, mask_stride, T, partial, n_slabs, s)
                            : launch_down_f32_partials(w, d, m, list, n_dev, h, mask, mask_stride, T, partial, n_slabs, s);
     if (e != hipSuccess) return e;
-    const int total = T * d;
-    hipLaunchKernelGGL(down_reduce_kernel, dim3((total + kWave - 1) / kWave), dim3(256), 0, s, partial, n_slabs, total, y,
-                       y_bf16);
-    return hipGetLastError();
+    return launch_down_reduce(partial, n_slabs, T * d, y, y_bf16, copy, s);
 }
 
 }  // namespace pop

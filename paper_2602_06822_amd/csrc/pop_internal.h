@@ -131,6 +131,46 @@ hipError_t launch_retained_mask(const unsigned char *region, int m, unsigned cha
 hipError_t launch_mask_to_list(const unsigned char *mask, int rows, int m, int *list, int *n_list, hipStream_t s,
                                uint16_t *pad_hc = nullptr, int pad_ld = 0, int pad_T = 0);
 
+// What the caller of a decode step takes of its selection, copied from the layer's state by extra workgroups of the step's
+// last launch (or of a launch of its own): every destination may be null.
+struct StepCopy {
+    int B = 0, m = 0, n_cand = 0, n_list = 0;  // rows of the layer's arrays are m apart; n_list = n_ret + n_cand
+    const float *cscore = nullptr;
+    const unsigned char *mask_src = nullptr;   // (16-byte aligned)
+    const int *act_src = nullptr, *n_act_src = nullptr;
+    float *cand_scores = nullptr;              // [B][n_cand]
+    unsigned char *mask = nullptr;             // [B][m]
+    int *active_idx = nullptr, *n_active = nullptr;  // [B][n_list], [B]
+    bool any() const { return (cand_scores && n_cand) || mask || (active_idx && n_list) || n_active; }
+    // workgroups of `threads` threads that copy it, a few elements per thread
+    int blocks(int threads) const
+    {
+        if (!any()) return 0;
+        const long n = (cand_scores ? (long)B * n_cand : 0) + (mask ? (long)B * m / 16 : 0) + (active_idx ? (long)B * n_list : 0);
+        const long b = (n + 4L * threads - 1) / (4L * threads);
+        return b < 1 ? 1 : (b > 64 ? 64 : (int)b);
+    }
+};
+// workgroup `block` of n_blocks
+__device__ __forceinline__ void copy_step_block(const StepCopy &c, int block, int n_blocks)
+{
+    const int at = block * blockDim.x + threadIdx.x, step = n_blocks * blockDim.x;
+    if (c.cand_scores)
+        for (int i = at; i < c.B * c.n_cand; i += step)
+            c.cand_scores[i] = c.cscore[(size_t)(i / c.n_cand) * c.m + i % c.n_cand];
+    if (c.active_idx)
+        for (int i = at; i < c.B * c.n_list; i += step)
+            c.active_idx[i] = c.act_src[(size_t)(i / c.n_list) * c.m + i % c.n_list];
+    if (c.n_active && block == 0 && (int)threadIdx.x < c.B) c.n_active[threadIdx.x] = c.n_act_src[threadIdx.x];
+    if (c.mask) {
+        const int n = c.B * c.m, n16 = (reinterpret_cast<uintptr_t>(c.mask) & 15u) == 0 ? n / 16 : 0;
+        for (int i = at; i < n16; i += step)
+            reinterpret_cast<uint4 *>(c.mask)[i] = reinterpret_cast<const uint4 *>(c.mask_src)[i];
+        for (int i = n16 * 16 + at; i < n; i += step) c.mask[i] = c.mask_src[i];
+    }
+}
+hipError_t launch_step_copy(const StepCopy &c, hipStream_t s);
+
 // ---- decode GEMVs (pop_gemv.hip) ----
 // h[b][j] = silu(x_b . gate_j) * (x_b . up_j) for j in rows[0..n_rows); if cscore != null, rows [0, n_score)
 // also get cscore[b][pos] = nrm[j] * |h|.  n_rows_dev (optional) overrides n_rows with a device-side count.
@@ -141,7 +181,7 @@ hipError_t launch_gateup(const void *w, int is_bf16, int d, int m, const void *x
 // Two stages: slab partials then a fixed-order reduction; y written as float32 or bf16.
 hipError_t launch_down(const void *w, int is_bf16, int d, int m, const int *list, const int *n_dev, int n_host,
                        const float *h, const unsigned char *mask, int mask_stride, int B, float *partial, int n_slabs,
-                       void *y, int y_bf16, hipStream_t s);
+                       void *y, int y_bf16, hipStream_t s, const StepCopy *copy = nullptr);
 int down_num_slabs(int d, int is_bf16);
 // The same for up to kSkMaxTokens (bf16 layers) or kF32MaxTokens rows of h ([T][m] float32, by channel) on the matrix cores; masks one row per token
 // (mask_stride) or null.  partial: [n_slabs][T][d] float32.
@@ -149,7 +189,7 @@ constexpr int kSkMaxTokens = 32;  // (bf16)
 int skinny_down_slabs(int is_bf16, int d, int m, int n_cu);
 hipError_t launch_skinny_down(const void *w, int is_bf16, int d, int m, const int *list, const int *n_dev, const float *h,
                               const unsigned char *mask, int mask_stride, int T, float *partial, int n_slabs, void *y,
-                              int y_bf16, hipStream_t s);
+                              int y_bf16, hipStream_t s, const StepCopy *copy = nullptr);
 // Batched decode (2 <= B <= POP_MAX_BATCH) with the per-sequence selection inside the gate/up kernel: the listed
 // rows are the n_cand candidates followed by the n_ret retained channels; all workgroups evaluate the candidates
 // first, then the last B workgroups wait (bounded) for everybody's candidate scores and select for one sequence
@@ -200,7 +240,8 @@ bool fused_plan(int d, int is_bf16, int n_ret, int n_cand, int wg_target, FusedP
 // Largest grid of this shape that is co-resident on n_cu compute units.
 hipError_t fused_resident_limit(int is_bf16, const FusedPlan &pl, int n_cu, int *max_wg);
 hipError_t launch_decode_fused(const FusedPlan &pl, int is_bf16, FusedParams &p, hipStream_t s);
-hipError_t launch_decode_tail(const float *partial, int n_wg, int d, void *y, int y_bf16, hipStream_t s);
+hipError_t launch_decode_tail(const float *partial, int n_wg, int d, void *y, int y_bf16, hipStream_t s,
+                              const StepCopy *copy = nullptr);
 hipError_t launch_fill_int(int *p, int n, int value, hipStream_t s);
 
 // ---- measurement aids (pop_probe.hip): bare reads, nothing of the method ----
