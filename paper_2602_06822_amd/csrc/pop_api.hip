@@ -132,9 +132,9 @@ StepCopy step_copy(const pop_layer *L, int B, float *cand_scores, unsigned char 
 constexpr int kFfnMfmaMinTokens = 32;
 
 // From this many sequences on a bf16 layer's batched step takes the matrix cores for its down projection: the vector
-// kernel's multiply-adds grow with the batch (13B shape: 22.2 us at 4 sequences, 27.8 at 8), the matrix-core kernel's time
-// does not (22 us).
-constexpr int kSkinnyMinBatch = 5;
+// kernel's multiply-adds grow with the batch, the matrix-core kernel's time does not (whole step at the 13B shape, vector /
+// matrix: 2 sequences 56.3 / 57.3 us, 3 60.1 / 58.6, 4 61.4 / 59.4, 8 74.3 / 67.6).
+constexpr int kSkinnyMinBatch = 3;
 
 // hipMalloc that leaves no pending error behind when it fails (a later launch check would report it as its own).
 bool dev_alloc(void **p, size_t bytes)

@@ -701,13 +701,17 @@ __global__ __launch_bounds__(MAXB) void decode_fused_kernel(FusedParams p)
 // contiguous sixteenth of the partial rows (independent loads, fixed order) and wave 0 combines them in wave order,
 // so y does not depend on scheduling.
 constexpr int kTailWaves = 16;
+struct NoCopy {};  // (most steps: nothing taken, nothing passed)
+template <class Copy>
 __global__ __launch_bounds__(1024) void decode_tail_kernel(const float *__restrict__ partial, int n_wg, int d,
-                                                           void *__restrict__ y, int y_bf16, StepCopy copy)
+                                                           void *__restrict__ y, int y_bf16, Copy copy)
 {
-    const int main_blocks = (d + kWave - 1) / kWave;
-    if ((int)blockIdx.x >= main_blocks) {  // what the step's caller takes of its selection
-        copy_step_block(copy, blockIdx.x - main_blocks, gridDim.x - main_blocks);
-        return;
+    if constexpr (std::is_same<Copy, StepCopy>::value) {
+        const int main_blocks = (d + kWave - 1) / kWave;
+        if ((int)blockIdx.x >= main_blocks) {  // what the step's caller takes of its selection
+            copy_step_block(copy, blockIdx.x - main_blocks, gridDim.x - main_blocks);
+            return;
+        }
     }
     __shared__ float part[kTailWaves][kWave];
     const int lane = threadIdx.x % kWave, q = threadIdx.x / kWave;
@@ -833,9 +837,12 @@ hipError_t launch_decode_fused(const FusedPlan &pl, int is_bf16, FusedParams &p,
 hipError_t launch_decode_tail(const float *partial, int n_wg, int d, void *y, int y_bf16, hipStream_t s,
                               const StepCopy *copy)
 {
-    const StepCopy c = copy ? *copy : StepCopy{};
-    hipLaunchKernelGGL(decode_tail_kernel, dim3((d + kWave - 1) / kWave + c.blocks(kTailWaves * kWave)),
-                       dim3(kTailWaves * kWave), 0, s, partial, n_wg, d, y, y_bf16, c);
+    const dim3 grid((d + kWave - 1) / kWave), block(kTailWaves * kWave);
+    if (copy && copy->any())
+        hipLaunchKernelGGL(decode_tail_kernel<StepCopy>, dim3(grid.x + copy->blocks(block.x)), block, 0, s, partial, n_wg, d, y,
+                           y_bf16, *copy);
+    else
+        hipLaunchKernelGGL(decode_tail_kernel<NoCopy>, grid, block, 0, s, partial, n_wg, d, y, y_bf16, NoCopy{});
     return hipGetLastError();
 }
 
