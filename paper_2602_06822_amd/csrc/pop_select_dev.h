@@ -15,11 +15,10 @@ constexpr int kSelLdsKeys = 4096;  // candidate keys staged in LDS when they fit
 struct SelShared {
     unsigned int hist[3][256];  // digit histograms of three consecutive radix passes (see radix_threshold)
     unsigned int hist2[3][256]; // the second threshold's histograms when several are sought in one sweep
-    unsigned int hist3[3][256]; // the third threshold's
     int wave_tot[6][kSelMaxWaves];
     int digit;
     int remaining;
-    int list_len[3];            // lengths of the key lists of radix_thresholds_lists
+    int list_len[2];            // lengths of the key lists of radix_thresholds_lists
     uint32_t keys[kSelLdsKeys];
 };
 
@@ -188,7 +187,7 @@ __device__ __forceinline__ void radix_threshold(KeyFn key, int n, int n_top, Sel
     take_eq = remaining;
 }
 
-// NT (2 or 3) thresholds in the same sweeps: kth[t] = key of the n_top[t]-th best element, 1 <= n_top[t] <= n, with
+// NT (2) thresholds in the same sweeps: kth[t] = key of the n_top[t]-th best element, 1 <= n_top[t] <= n, with
 // its take count, as NT calls of radix_threshold would give them.  The common leading bits and the leading digit's
 // histogram serve all; from the second digit on a key is counted for the threshold(s) whose prefix it matches.
 // Made for a large key set: digits are cut from the highest differing bit down (so the leading digit spreads the
@@ -202,7 +201,7 @@ __device__ __forceinline__ void radix_thresholds_lists(KeyFn key, int n, const i
                                                        uint32_t (&kth)[NT], int (&take)[NT], bool have_diff = false,
                                                        uint32_t diff_in = 0, unsigned long long *tr = nullptr)
 {
-    static_assert(NT == 2 || NT == 3, "two or three thresholds");
+    static_assert(NT == 2, "two thresholds: two sets of histograms");
     constexpr int kCap = kSelLdsKeys / NT;
     unsigned int *scratch = &sh.hist[2][0];
     if (threadIdx.x == 0) {
@@ -244,12 +243,10 @@ __device__ __forceinline__ void radix_thresholds_lists(KeyFn key, int n, const i
         const uint32_t dmask = (1u << (hi - lo + 1)) - 1u;
         // pass p counts into set p % 3 and clears set (p + 1) % 3, last read in pass p - 2 (one barrier per pass); the
         // leading digit's histogram is shared
-        unsigned int *hist[3] = {sh.hist[pass % 3], pass == 0 ? sh.hist[0] : sh.hist2[pass % 3],
-                                 pass == 0 ? sh.hist[0] : sh.hist3[pass % 3]};
+        unsigned int *hist[NT] = {sh.hist[pass % 3], pass == 0 ? sh.hist[0] : sh.hist2[pass % 3]};
         for (int i = threadIdx.x; i < 256; i += blockDim.x) {
             sh.hist[(pass + 1) % 3][i] = 0;
             sh.hist2[(pass + 1) % 3][i] = 0;
-            if (NT > 2) sh.hist3[(pass + 1) % 3][i] = 0;
         }
         if (pass == 0) {
             const int n_round = (n + blockDim.x - 1) / blockDim.x * blockDim.x;
