@@ -453,11 +453,12 @@ __device__ __forceinline__ void pm_tile(const uint16_t *__restrict__ w, const ui
         pb[p] = w + ((size_t)j * 3 + which) * d + src_kv;
     }
     const int n_k = d / kPfBK;
-    // k-step s of this tile is columns kof(s) (steps beyond the last repeat it).  With one token tile nobody shares this
-    // tile's weight rows, and every chunk starts at a column of its own: rows are a power of two apart in most models, so
-    // workgroups in step with each other would keep asking the same few memory channels (256 tokens: 58.7 -> 54.4 us).
-    // Where token tiles share weight rows through the L2 it gained nothing, and they start at column 0.
-    const int rot = n_tt == 1 ? ctile % n_k : 0;
+    // k-step s is columns kof(s) (steps beyond the last repeat it).  Sums in float32 take the columns in the same order in
+    // every tile: a sum must not depend on its channel's place, or channels with equal weights would not tie.  Rows are a
+    // power of two apart in most models, and tiles in step with each other keep asking the same few memory channels.  So
+    // the sums in double, where the order is lost in the rounding to float32, start at a column of their own per chunk (24
+    // tokens, d 4096, m 11008: whole call 83 -> 73 us; eight experts of about 256 tokens would gain 1215 -> 1079 us).
+    const int rot = kPrecise ? ctile % n_k : 0;
     auto kof = [&](int step) {
         const int q = min(step, n_k - 1) + rot;
         return (q >= n_k ? q - n_k : q) * kPfBK;

@@ -126,3 +126,39 @@ def max_abs_rel(y: np.ndarray, ref: np.ndarray) -> float:
     """max |y - ref| / max |ref|."""
     den = float(np.max(np.abs(ref)))
     return float(np.max(np.abs(y - ref)) / (den if den > 0 else 1.0))
+
+
+# The tile choice of the prompt kernels on the matrix cores, as the launch code makes it: for tests that mean to reach a
+# certain tile and have to say whether they do.
+
+def prefill_tiles(n_ch: int, n_tt: int, mf: int, n_cu: int):
+    """(f, number of tiles, cost) of n_tt token tiles of 64 mf tokens: tiles are 8 f channels wide."""
+    best = None
+    for f in (12, 11, 10, 8, 7, 6, 4):
+        total = -(-n_ch // (8 * f)) * n_tt
+        cost = -(-total // n_cu) * max(16 * mf * f + 8 * (4 * mf + f) + 60, 100 * f // n_tt)
+        if best is None or cost < best[2]:
+            best = (f, total, cost)
+    return best
+
+
+def prefill_tile(T: int, m: int, n_cu: int):
+    """(mf, f) of the direct-load contraction over T >= 32 tokens and all m channels."""
+    best = None
+    for mf in range(1, 6):
+        f, _, cost = prefill_tiles(m, -(-T // (64 * mf)), mf, n_cu)
+        if best is None or cost < best[2]:
+            best = (mf, f, cost)
+    return best[:2]
+
+
+def down_tile(T: int, d: int, n_cu: int):
+    """(mf, number of splits) of the direct-load down-projection GEMM: tiles of 64 mf tokens."""
+    best = None
+    for mf in range(5, 0, -1):
+        tiles = -(-T // (64 * mf)) * -(-d // 128)
+        split = min(max(n_cu // tiles, 1), 8)
+        cost = -(-tiles * split // n_cu) * (144 * mf + 100) * 840 // split
+        if best is None or cost < best[2]:
+            best = (mf, split, cost)
+    return best[:2]

@@ -11,7 +11,7 @@ import torch
 
 from paper_2602_06822_amd import synth
 
-from gpu_util import GpuLayer, dev, host, max_abs_rel, score_rel_err
+from gpu_util import GpuLayer, dev, host, max_abs_rel, prefill_tile, prefill_tiles, score_rel_err
 
 pytestmark = pytest.mark.gpu
 
@@ -529,6 +529,30 @@ def test_prefill_direct_load_tiles(pop, oracle, mf, f, d):
     with GpuLayer(pop, L, max_tokens=T, max_batch=1) as G:
         _check_prefill(oracle, G, L, x, n_ret, n_cand)
         _check_prefill_forward(oracle, G, L, x, n_ret, n_cand, k, F32, FFN_MFMA_TOL_F32, rows=rows)
+
+
+# T, m, d and the tile that takes their products (64 mf tokens x 8 f channels, n_tt token tiles)
+EQUAL_CHANNEL_CASES = [(24, 8197, 192, (1, 6, 1)), (187, 8165, 256, (3, 4, 1)), (251, 14341, 192, (4, 8, 1)),
+                       (315, 10245, 320, (5, 6, 1)), (379, 4085, 192, (3, 4, 2))]
+
+
+@pytest.mark.parametrize("T,m,d,tile", EQUAL_CHANNEL_CASES)
+def test_equal_channels_have_equal_scores(pop, T, m, d, tile):
+    """Channels with the same weights have the same score, bit for bit, whichever tile of the contraction forms them and
+    wherever they lie in it: ties are ranked by channel number, so a score must not depend on its channel's place.  37
+    different channels, repeated over several k-steps and channel chunks."""
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    got = prefill_tile(T, m, n_cu) if T >= 32 else (1, prefill_tiles(m, 1, 1, n_cu)[0])
+    assert got + (-(-T // (64 * got[0])),) == tile
+    L = synth.make_layer(synth.small_config("equal_channels", d, 37, BF16))
+    x = synth.make_activations(L, T, "prompt")
+    rep = np.arange(m) % 37
+    L = synth.Layer(synth.small_config("equal_channels", d, m, BF16), L.w_gate[rep], L.w_up[rep],
+                    np.ascontiguousarray(L.w_down[:, rep]))
+    with GpuLayer(pop, L, max_tokens=T, max_batch=1) as G:
+        scores = G.prefill(x, m // 2, m // 4)[0]
+        assert np.array_equal(scores, scores[rep])
+        assert np.array_equal(scores, G.prefill_forward(x, m // 2, m // 4, m // 8, F32)[0])
 
 
 @pytest.mark.parametrize("m", [1, 63, 257, 1025, 2049, 4100, 11265, 14337, 20481, 33000])
