@@ -594,13 +594,15 @@ __device__ __forceinline__ void pm_tile(const uint16_t *__restrict__ w, const ui
     const int col = lane % 16, row0 = wave * MF * 16 + lane / 16 * 4;  // first token row of this lane
     const bool upper = col >= 8;
     const int c_odd = 8 * (F - 1) + col % 8, r_odd = upper ? 2 : 0;
+    // (a lane's squares are summed rows 0 and 1 of each fragment first, then rows 2 and 3, as the two lanes that share a
+    // channel of the odd fragment do it: a channel's score does not depend on its place in the tile)
     float ss[(F + 1) / 2];
 #pragma unroll
     for (int p = 0; p < F / 2; ++p) {
         const int c = 16 * p + col;
         const bool live_c = c < cn;
         const int j = (kList && (kPrecise || st.tmask) && live_c) ? st.list[c0 + c] : c0 + c;
-        ss[p] = 0.f;
+        float sq[2] = {0.f, 0.f};
 #pragma unroll
         for (int a = 0; a < MF; ++a)
 #pragma unroll
@@ -609,7 +611,7 @@ __device__ __forceinline__ void pm_tile(const uint16_t *__restrict__ w, const ui
                 float h = kPrecise ? silu_mul(acc[a][2 * p][v], acc[a][2 * p + 1][v])
                                    : silu_mul_tile(acc[a][2 * p][v], acc[a][2 * p + 1][v]);
                 h = (t < T && live_c) ? h : 0.f;  // (padding holds products of the rows its loads were pointed at)
-                ss[p] = fmaf(h, h, ss[p]);
+                sq[v / 2] = fmaf(h, h, sq[v / 2]);
                 if (kPrecise) {
                     if (t < T && live_c) st.h32[(size_t)t * m + j] = h;
                 } else if (kMode != 0) {
@@ -617,6 +619,7 @@ __device__ __forceinline__ void pm_tile(const uint16_t *__restrict__ w, const ui
                     hs[(row0 + a * 16 + v) * HS + c] = f32_to_bf16(h);
                 }
             }
+        ss[p] = sq[0] + sq[1];
     }
     if (F % 2) {
         const bool live_c = c_odd < cn;

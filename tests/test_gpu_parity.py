@@ -533,7 +533,10 @@ def test_prefill_direct_load_tiles(pop, oracle, mf, f, d):
 
 # T, m, d and the tile that takes their products (64 mf tokens x 8 f channels, n_tt token tiles)
 EQUAL_CHANNEL_CASES = [(24, 8197, 192, (1, 6, 1)), (187, 8165, 256, (3, 4, 1)), (251, 14341, 192, (4, 8, 1)),
-                       (315, 10245, 320, (5, 6, 1)), (379, 4085, 192, (3, 4, 2))]
+                       (315, 10245, 320, (5, 6, 1)), (379, 4085, 192, (3, 4, 2)),
+                       # (tiles with a fragment that two channel groups share)
+                       (24, 12293, 192, (1, 7, 1)), (187, 13605, 128, (3, 7, 1)), (315, 6805, 128, (3, 7, 2)),
+                       (507, 10245, 64, (4, 11, 2))]
 
 
 @pytest.mark.parametrize("T,m,d,tile", EQUAL_CHANNEL_CASES)
