@@ -541,7 +541,7 @@ constexpr int kSkChunk = 256;      // channels staged at a time
 constexpr int kSkCols = 128;       // columns per workgroup
 constexpr int kSkLd = kSkChunk + 8;  // LDS row stride of the staged h planes (16-byte aligned, rows four banks apart)
 
-// f = hi + mid + lo exactly (24 significant bits in three bf16 values of 8; the rests are exact differences)
+// f = hi + mid + lo exactly for finite f (24 significant bits in three bf16 values of 8; the rests are exact differences)
 __device__ __forceinline__ void split3(float f, uint16_t &hi, uint16_t &mid, uint16_t &lo)
 {
     const uint32_t b0 = __float_as_uint(f) & 0xffff0000u;
@@ -670,7 +670,19 @@ __global__ __launch_bounds__(kSkThreads) void skinny_down_kernel(const uint4 *__
                 double s = 0.0;
 #pragma unroll
                 for (int q = 0; q < kSkThreads / kWave; ++q) s += (double)red[q * 16 * kSkCols + i];
-                partial[((size_t)blockIdx.y * T + tok) * d + col] = (float)s;
+                float v = (float)s;
+                if (!__builtin_isfinite(v)) {
+                    // An infinity is not the sum of three parts, and parts that are zero make NaN of an infinite weight:
+                    // here the sum is what the vector kernel's multiply-adds give.
+                    v = 0.f;
+                    for (int p = s0; p < s1; ++p) {
+                        const int j = list[p];
+                        const float hv = !kMask || mask[(size_t)tok * mask_stride + j] ? h[(size_t)tok * m + j] : 0.f;
+                        const uint16_t wv = reinterpret_cast<const uint16_t *>(w)[((size_t)j * 3 + 2) * d + col];
+                        v = fmaf(hv, __uint_as_float((uint32_t)wv << 16), v);
+                    }
+                }
+                partial[((size_t)blockIdx.y * T + tok) * d + col] = v;
             }
         }
     }

@@ -622,6 +622,38 @@ def test_short_prompts_in_one_pass(pop, oracle, T, dtype, d, m):
         _check_prefill_forward(oracle, G, L, x, n_ret, n_cand, k, F32, SHORT_PROMPT_TOL)
 
 
+@pytest.mark.parametrize("kind,T", [("step", 2), ("step", 3), ("step", 8), ("ffn", 7), ("ffn", 24), ("ffn_rows", 24),
+                                    ("forward", 17)])
+def test_overflowing_hidden_activation(pop, kind, T):
+    """Finite inputs whose hidden activation overflows float32 in one channel of one token: that token's outputs are
+    infinities with the sign of the channel's down weight, as float32 products give them; an infinite down weight
+    does the same to its output of every token with the sign of h; everything else stays finite."""
+    d, m, j, b = 192, 700, 333, 1
+    L = synth.make_layer(synth.small_config("overflow", d, m, BF16))
+    for w in (L.w_gate, L.w_up):
+        w[:, 0] = 0
+        w[j, 0] = synth.f32_to_bf16_bits(np.array([1.0], np.float32))[0]
+    L.w_down[5, j] = 0x7f80
+    x = synth.make_activations(L, T, "overflow")
+    x[b, 0] = synth.f32_to_bf16_bits(np.array([1e20], np.float32))[0]
+    down = synth.bf16_bits_to_f32(L.w_down)
+    with GpuLayer(pop, L, max_tokens=64, max_batch=8) as G:
+        if kind == "step":
+            G.prefill(x[:1], m, 0)
+            y = G.decode(x, 0, F32)["y"]
+        elif kind == "forward":
+            y = G.prefill_forward(x, m, 0, 0, F32)[5]
+        else:
+            y = G.ffn(x, np.ones((T, m) if kind == "ffn_rows" else m, np.uint8), F32)
+    xf, wg, wu = (synth.storage_to_f64(a, BF16) for a in (x, L.w_gate, L.w_up))
+    g = xf @ wg[j]
+    h = g / (1 + np.exp(-np.minimum(g, 80))) * (xf @ wu[j])
+    assert np.array_equal(y[b], np.sign(down[:, j]) * np.inf)
+    rest = np.delete(np.arange(T), b)
+    assert np.array_equal(y[rest, 5], np.sign(h[rest]) * np.inf)
+    assert np.isfinite(np.delete(y[rest], 5, axis=1)).all()
+
+
 @pytest.mark.parametrize("dtype", [F32, BF16])
 @pytest.mark.parametrize("T,m,shift", [(1, 1, 0), (7, 63, 0), (8, 64, 0), (129, 72, 0), (1025, 200, 0), (2047, 1000, 0),
                                        (130, 72, 1), (9000, 40, 0), (8193, 8200, 0)])
