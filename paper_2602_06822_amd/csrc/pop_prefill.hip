@@ -753,14 +753,19 @@ __global__ __launch_bounds__(kF32Waves * 64) void gateup_f32_kernel(const float 
         }
 #pragma unroll
         for (int u = 0; u < kF32Steps; ++u) {
-            const bool live = (s + u * kF32Waves) * 16 + 4 * g < d;  // (beyond the row: zero times the row's start)
+            if ((s + u * kF32Waves) * 16 + 4 * g >= d) {  // (beyond the row: zeros of both operands, an infinite weight may stand
+                                                         // at the row's start)
+#pragma unroll
+                for (int a = 0; a < TA; ++a) va[u][a] = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+                for (int b = 0; b < NB; ++b) vb[u][b] = make_float4(0.f, 0.f, 0.f, 0.f);
+            }
 #pragma unroll
             for (int e = 0; e < 4; ++e)
 #pragma unroll
                 for (int a = 0; a < TA; ++a) {
                     const float4 &q = va[u][a];
-                    const float f = e == 0 ? q.x : (e == 1 ? q.y : (e == 2 ? q.z : q.w));
-                    const double fa = live ? (double)f : 0.0;
+                    const double fa = (double)(e == 0 ? q.x : (e == 1 ? q.y : (e == 2 ? q.z : q.w)));
 #pragma unroll
                     for (int b = 0; b < NB; ++b) {
                         const float4 &r = vb[u][b];
@@ -872,7 +877,9 @@ __global__ __launch_bounds__(kF32Waves * 64) void down_f32_kernel(const float4 *
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const bool live = p0 + 4 * kF32Waves * u + g < s1;
-            const double fw[4] = {(double)vw[u].x, (double)vw[u].y, (double)vw[u].z, (double)vw[u].w};
+            // (beyond the slab: zeros of both operands, an infinite weight may stand in the row read there)
+            const float4 q = live ? vw[u] : make_float4(0.f, 0.f, 0.f, 0.f);
+            const double fw[4] = {(double)q.x, (double)q.y, (double)q.z, (double)q.w};
 #pragma unroll
             for (int a = 0; a < TA; ++a) {
                 const double fa = live && mk[u][a] ? (double)va[u][a] : 0.0;

@@ -654,6 +654,26 @@ def test_overflowing_hidden_activation(pop, kind, T):
     assert np.isfinite(np.delete(y[rest], 5, axis=1)).all()
 
 
+@pytest.mark.parametrize("d,T", [(72, 20), (260, 70), (512, 2)])
+def test_infinite_weights_of_a_float32_layer(pop, d, T):
+    """An infinite up weight makes its channel's h infinite and an infinite down weight its output, with the signs of what
+    they are multiplied by: the padding of the matrix-core kernels (columns beyond a row, channels beyond a list, which
+    read a row that exists) adds no product of it with zero."""
+    m, j = 90, 17
+    L = synth.make_layer(synth.small_config("inf_f32", d, m, F32))
+    L.w_up[j, 0] = np.inf
+    L.w_down[3, m - 1] = np.inf
+    x = synth.make_activations(L, T, "inf_f32")
+    x[:, 0] = 1.0
+    g, u = x.astype(np.float64) @ L.w_gate.T, x.astype(np.float64) @ np.delete(L.w_up, j, axis=0).T
+    with GpuLayer(pop, L, max_tokens=T, max_batch=1) as G:
+        y = G.ffn(x, (np.arange(m) != m - 1).astype(np.uint8), F32)
+        assert np.array_equal(y, np.sign(g[:, j:j + 1]) * np.sign(L.w_down[:, j]) * np.inf)
+        y = G.ffn(x, (np.arange(m) != j).astype(np.uint8), F32)
+        assert np.array_equal(y[:, 3], np.sign(g[:, -1] * u[:, -1]) * np.inf)
+        assert np.isfinite(np.delete(y, 3, axis=1)).all()
+
+
 @pytest.mark.parametrize("dtype", [F32, BF16])
 @pytest.mark.parametrize("T,m,shift", [(1, 1, 0), (7, 63, 0), (8, 64, 0), (129, 72, 0), (1025, 200, 0), (2047, 1000, 0),
                                        (130, 72, 1), (9000, 40, 0), (8193, 8200, 0)])
