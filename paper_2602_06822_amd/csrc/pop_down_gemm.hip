@@ -349,7 +349,9 @@ __global__ __launch_bounds__(kDdThreads, 1) void down_gemm_dma_kernel(const uint
                 }
                 bw = __builtin_bit_cast(bf16x8_t, u32x4_t{v[0], v[1], v[2], v[3]});
             }
-            // (two wait states: the compiler does not see that a product reads what a permute has just written)
+            // (two wait states: the compiler does not see that a product reads what a permute has just written.  Nothing else
+            // writes an operand that late as long as the loop below stays one body: a second copy of it for an odd last step
+            // had the compiler move every accumulator out and back in between its products.)
             if (m_ == 0)
                 asm volatile("s_nop 1\n\tv_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc[m_][e]) : "v"(af[set][m_]), "v"(bw));
             else
@@ -419,15 +421,14 @@ __global__ __launch_bounds__(kDdThreads, 1) void down_gemm_dma_kernel(const uint
                 __builtin_amdgcn_sched_barrier(0);
             }
         };
-        int s = 0;
-        for (; s + 2 <= n_steps; s += 2) {
-            k_step(s);
-            k_step(s + 1);
-        }
-        if (s < n_steps) k_step(s);
+        for (int s = 0; s < n_steps; ++s) k_step(s);
         // the surplus requests, before the LDS is given up; the products' results before they are read (the compiler does
         // not see the products, so it adds no wait states for them)
         asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_nop 15\n\ts_nop 15" ::: "memory");
+#pragma unroll
+        for (int i = 0; i < MF; ++i)
+#pragma unroll
+            for (int f = 0; f < F; ++f) asm volatile("" : "+a"(acc[i][f]));  // (no read of them moves ahead of the wait)
     }
 
     // register v of product e is token 4 (lane / 16) + v of the fragment, column 8 (lane % 16) + e

@@ -578,6 +578,10 @@ __device__ __forceinline__ void pm_tile(const uint16_t *__restrict__ w, const ui
     // compiler does not see the products, so it adds no wait states for them)
     asm volatile("s_waitcnt vmcnt(0)\n\ts_nop 15\n\ts_nop 15" ::: "memory");
     __syncthreads();
+    if constexpr (!kPrecise) {
+#pragma unroll
+        for (int i = 0; i < MF * F; ++i) asm volatile("" : "+a"(acc[i / F][i % F]));  // (no read of them moves ahead of the wait)
+    }
     if constexpr (kPrecise) {
         add_up();
 #pragma unroll
