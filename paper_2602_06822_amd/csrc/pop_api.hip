@@ -786,7 +786,7 @@ int pop_importance_reduce(const void *h, pop_dtype_t hdtype, int T, int m, const
     if (hdtype != POP_F32 && hdtype != POP_BF16) return POP_EINVAL;
     if (T < 1 || m < 1) return POP_ESHAPE;
     hipStream_t s = as_stream(stream);
-    const size_t bytes = importance_reduce_scratch_bytes(T, m);
+    const size_t bytes = importance_reduce_scratch_bytes(h, hdtype == POP_BF16, T, m);
     if (bytes == 0) {
         POP_HIP(launch_importance_reduce(h, hdtype == POP_BF16, T, m, nrm, scores, nullptr, s));
         return POP_OK;

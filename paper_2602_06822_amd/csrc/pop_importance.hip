@@ -8,8 +8,9 @@
 //    no scratch is needed.  A row segment is one or two cache lines; 16 waves x 8 loads of 16 bytes per lane keep 128 KB on
 //    their way per compute unit, so a 1024-token prompt is a single round trip.  1024 x 13824 bf16: 7 us, against 20 + 6 us
 //    for the two launches below and the allocation of their scratch around them.
-//  * long prompts of few columns (fewer than kIrMinGroups workgroups, more than kIrLongPrompt tokens) would leave most
-//    of the chip idle for many rounds: tokens split into chunks, per-chunk partial sums in scratch.
+//  * long prompts of few columns (fewer than kIrMinGroups workgroups, more than kIrLongPrompt tokens; or narrow rows that
+//    can only be read one element at a time) would leave most of the chip idle for many rounds: tokens split into chunks,
+//    per-chunk partial sums in scratch.  8192 x 1000 bf16: 24 us in columns, 41 in chunks; 16384 x 8200: 69 and 207.
 //      stage 1  part[chunk][j] = sum over the chunk's tokens of H[t][j]^2; 256 adjacent columns of one token chunk per
 //               workgroup, a lane one column of each 64-column group, eight rows in flight per lane; the four waves take
 //               the chunk's rows round robin and meet through LDS in wave order.
@@ -37,6 +38,10 @@ constexpr int kIcWaves = 16;
 constexpr int kIcRows = 8;         // loads in flight per lane
 constexpr int kIrMinGroups = 128;
 constexpr int kIrLongPrompt = 8192;
+// Narrow rows read one element at a time: a few workgroups with a sixteenth of the bytes in flight (8192 x 1001 bf16: 47 us
+// in columns, 41 in chunks; 8192 x 63: 41 and 26; 8192 x 1001 float32: 45 and 84; 5000 x 1001 bf16: 29 and 31).
+constexpr int kIrLongPromptSingle = 5120;
+constexpr int kIrNarrowRow = 2048;  // bytes
 
 // E columns per lane: 16-byte loads (8 bf16, 4 float32; rows and base 16-byte aligned) or, E = 1, one element.
 // nrm == nullptr: the sums themselves.
@@ -169,18 +174,28 @@ static int importance_chunks(int T, int m)
     return n < 1 ? 1 : n;
 }
 
-static bool importance_in_chunks(int T, int m) { return T > kIrLongPrompt && (m + kIcCols - 1) / kIcCols < kIrMinGroups; }
-
-size_t importance_reduce_scratch_bytes(int T, int m)
+// Whether rows can be read 16 bytes at a time.
+static bool importance_vec(const void *h, int is_bf16, int m)
 {
-    return importance_in_chunks(T, m) ? (size_t)importance_chunks(T, m) * m * sizeof(double) : 0;
+    return (reinterpret_cast<uintptr_t>(h) & 15u) == 0 && m % (is_bf16 ? 8 : 4) == 0;
+}
+
+static bool importance_in_chunks(const void *h, int is_bf16, int T, int m)
+{
+    if (!importance_vec(h, is_bf16, m) && T > kIrLongPromptSingle && (long long)m * (is_bf16 ? 2 : 4) <= kIrNarrowRow) return true;
+    return T > kIrLongPrompt && (m + kIcCols - 1) / kIcCols < kIrMinGroups;
+}
+
+size_t importance_reduce_scratch_bytes(const void *h, int is_bf16, int T, int m)
+{
+    return importance_in_chunks(h, is_bf16, T, m) ? (size_t)importance_chunks(T, m) * m * sizeof(double) : 0;
 }
 
 static hipError_t launch_importance_columns(const void *h, int is_bf16, int T, int m, const float *nrm, float *scores,
                                             hipStream_t s)
 {
     const dim3 grid((m + kIcCols - 1) / kIcCols), block(kIcWaves * kWave);
-    const bool vec = (reinterpret_cast<uintptr_t>(h) & 15u) == 0 && m % (is_bf16 ? 8 : 4) == 0;
+    const bool vec = importance_vec(h, is_bf16, m);
     if (is_bf16 && vec)
         hipLaunchKernelGGL((importance_columns_kernel<true, 8>), grid, block, 0, s, h, T, m, nrm, scores);
     else if (is_bf16)
@@ -195,7 +210,7 @@ static hipError_t launch_importance_columns(const void *h, int is_bf16, int T, i
 hipError_t launch_importance_reduce(const void *h, int is_bf16, int T, int m, const float *nrm, float *scores,
                                     void *scratch, hipStream_t s)
 {
-    if (!importance_in_chunks(T, m)) return launch_importance_columns(h, is_bf16, T, m, nrm, scores, s);
+    if (!importance_in_chunks(h, is_bf16, T, m)) return launch_importance_columns(h, is_bf16, T, m, nrm, scores, s);
     const int n_chunks = importance_chunks(T, m);
     const int rows_per_chunk = (T + n_chunks - 1) / n_chunks;
     double *part = (double *)scratch;
@@ -262,10 +277,11 @@ extern "C" int pop_importance_reduce_static(const void *h, pop_dtype_t hdtype, i
     if (!h || !nrm || !scores) return POP_EINVAL;
     if (hdtype != POP_F32 && hdtype != POP_BF16) return POP_EINVAL;
     if (T < 1 || m < 1) return POP_ESHAPE;
-    if (m > kStaticMaxChannels || pop::importance_reduce_scratch_bytes(T, m) > kStaticScratchBytes)
+    const size_t bytes = pop::importance_reduce_scratch_bytes(h, hdtype == POP_BF16, T, m);
+    if (m > kStaticMaxChannels || bytes > kStaticScratchBytes)
         return POP_EUNSUPPORTED;  // beyond the static scratch: use pop_importance_reduce
     void *ptr = nullptr;
-    if (pop::importance_reduce_scratch_bytes(T, m) > 0 && static_scratch(&ptr) != hipSuccess) {
+    if (bytes > 0 && static_scratch(&ptr) != hipSuccess) {
         (void)hipGetLastError();
         return POP_EHIP;
     }

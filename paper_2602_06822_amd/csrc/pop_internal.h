@@ -312,8 +312,8 @@ hipError_t launch_mask_any(const unsigned char *mask, int rows, int m, unsigned 
 hipError_t launch_scores_from_partials(const float *s2_part, int n_tiles, int m, const float *nrm, float *scores,
                                        hipStream_t s);
 // stand-alone column reduction of a materialised H[T][m] (pop_importance.hip); scratch: device memory of
-// importance_reduce_scratch_bytes(T, m) bytes (0: none), 8-byte aligned, for the per-chunk partial sums
-size_t importance_reduce_scratch_bytes(int T, int m);
+// importance_reduce_scratch_bytes(h, is_bf16, T, m) bytes (0: none), 8-byte aligned, for the per-chunk partial sums
+size_t importance_reduce_scratch_bytes(const void *h, int is_bf16, int T, int m);
 hipError_t launch_importance_reduce(const void *h, int is_bf16, int T, int m, const float *nrm, float *scores,
                                     void *scratch, hipStream_t s);
 

@@ -676,7 +676,8 @@ def test_infinite_weights_of_a_float32_layer(pop, d, T):
 
 @pytest.mark.parametrize("dtype", [F32, BF16])
 @pytest.mark.parametrize("T,m,shift", [(1, 1, 0), (7, 63, 0), (8, 64, 0), (129, 72, 0), (1025, 200, 0), (2047, 1000, 0),
-                                       (130, 72, 1), (9000, 40, 0), (8193, 8200, 0)])
+                                       (130, 72, 1), (9000, 40, 0), (8193, 8200, 0),
+                                       (5120, 33, 0), (5121, 33, 0), (6000, 1025, 0), (5121, 256, 1)])
 def test_importance_reduce_forms(pop, T, m, shift, dtype):
     """The stand-alone reduction at the edges of its forms: 16-byte loads, single elements (row lengths or a base
     address that are no multiples of 16 bytes), rows beyond T in a round of loads, chunks for a long prompt of few
