@@ -16,13 +16,16 @@ namespace pop {
 // Search: the keys sit in registers (NS per thread).  One histogram over the 11 bits below the keys' common leading bits
 // leaves a threshold in a bucket of a few dozen to a few hundred keys, a second one (few keys take part) in one of a few,
 // whose ranks are counted out pairwise.  11 bits instead of 8 spread the LDS atomics over eight times as many words.
+// Only the bits between the highest and the lowest differing one are swept, and a bucket that still holds more than a list
+// when they are all known holds equal keys, which are counted out in channel order (part_equal_key; 1376 scores of eight
+// values: 20 -> 10 us, 11008: 31 -> 19).
 // A threshold is an element (key, channel): channels up to it in the order (key descending, channel ascending) are in.
 // 11008 channels with all of a layer's outputs: 13 us, against 25 us for the four 8-bit sweeps of one workgroup and 6 us for
 // the launch that spread its lists; comparing all pairs of keys instead, 64 channels per workgroup, took 27 us.
 constexpr int kPartThreads = 1024;
 constexpr int kPartBins = 2048;
-constexpr int kPartList = 256;     // keys of a bucket counted out pairwise at most
-constexpr int kPartSmall = 32;     // another digit is swept while a bucket holds more: that is cheaper than the pairs
+constexpr int kPartList = 32;      // keys of a bucket counted out pairwise at most: while a bucket holds more, another digit
+                                   // is swept, which is cheaper than the pairs
 constexpr int kPartMaxSlots = 32;  // keys per thread held in registers at most: 32768 channels
 
 struct PartShared {
@@ -57,6 +60,73 @@ __device__ __forceinline__ void part_scan(int (&v)[N], int (&tot)[N], PartShared
         tot[q] = __builtin_amdgcn_readlane(ts, kWave - 1);
     }
     __syncthreads();
+}
+
+// *idx = the rank-th (1 ..) channel among those whose key is `want`.  Every wave counts its own 64 channels of every key
+// slot, 32 slots at a time, then finds the slot and wave where the rank is reached from all the counts (count: 512 words;
+// counted: they are there already, from a call for the same key).  More than four keys per thread are read again: held in
+// registers for this, they cost every partition half a microsecond.
+template <int NS, int NK>
+__device__ __forceinline__ void part_equal_key(const float *__restrict__ scores, const uint32_t (&keys)[NK], int m,
+                                               uint32_t want, int rank, bool counted, int *count, int *idx)
+{
+    constexpr int kWaves = kPartThreads / kWave;
+    static_assert(kPartMaxSlots * kWaves == 8 * kWave && 8 * kWave <= kPartBins, "eight counts per lane, in a histogram");
+    const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    for (int base = 0; base < m; base += kPartMaxSlots * kPartThreads) {
+        if (!counted) {
+            int mine = 0;
+            if constexpr (NS > 0 && NS <= 4) {
+#pragma unroll
+                for (int s = 0; s < NK; ++s) {
+                    const int c = __builtin_popcountll(__ballot(s * kPartThreads + (int)threadIdx.x < m && keys[s] == want));
+                    mine = lane == s ? c : mine;
+                }
+            } else {
+#pragma unroll 1
+                for (int s = 0; s < kPartMaxSlots && base + s * kPartThreads < m; s += 8) {
+                    float v[8];
+#pragma unroll
+                    for (int q = 0; q < 8; ++q) {  // (requested together)
+                        const int i = base + (s + q) * kPartThreads + (int)threadIdx.x;
+                        v[q] = scores[i < m ? i : 0];
+                    }
+#pragma unroll
+                    for (int q = 0; q < 8; ++q) {
+                        const int i = base + (s + q) * kPartThreads + (int)threadIdx.x;
+                        const int c = __builtin_popcountll(__ballot(i < m && score_key(v[q]) == want));
+                        mine = lane == s + q ? c : mine;
+                    }
+                }
+            }
+            __syncthreads();  // the counts' readers are done
+            if (lane < kPartMaxSlots) count[lane * kWaves + wave] = mine;
+            __syncthreads();
+        }
+        int v[8], sum = 0;  // (slot, wave) in channel order
+#pragma unroll
+        for (int q = 0; q < 8; ++q) v[q] = count[8 * lane + q], sum += v[q];
+        const int inc = wave_incl_scan(sum);
+        const unsigned long long hit = __ballot(inc - sum < rank && rank <= inc);
+        if (hit == 0) {  // beyond these slots
+            rank -= __builtin_amdgcn_readlane(inc, kWave - 1);
+            continue;
+        }
+        const int at = __builtin_ctzll(hit);
+        int before = __builtin_amdgcn_readlane(inc - sum, at), entry = 8 * at;
+#pragma unroll
+        for (int q = 0; q < 7; ++q) {
+            const int c = __builtin_amdgcn_readlane(v[q], at);
+            if (entry == 8 * at + q && before + c < rank) before += c, ++entry;
+        }
+        if (wave == entry % kWaves) {
+            const int i = base + entry / kWaves * kPartThreads + (int)threadIdx.x;
+            const bool eq = i < m && score_key(scores[i < m ? i : 0]) == want;
+            const unsigned long long eqs = __ballot(eq);
+            if (eq && before + __builtin_popcountll(eqs & ((1ull << lane) - 1ull)) == rank - 1) *idx = i;
+        }
+        return;
+    }
 }
 
 // What one channel's place in the partition writes; r, c, t: retained, candidate and top channels before it.
@@ -135,22 +205,24 @@ __global__ __launch_bounds__(kPartThreads) void partition_kernel(const float *__
     __syncthreads();
     const uint32_t diff = sh.key_or & sh.key_nand;
 
-    // thresholds: retained (rank n_ret), retained + candidate (rank n_ret + n_cand), the n_top best; a set of none is
-    // sought as a set of one and closed at the end
+    // thresholds: retained (rank n_ret), retained + candidate (rank n_ret + n_cand), the n_top best; a set of none needs no
+    // search (matching 0) and is closed at the end
     const int want[NT] = {n_ret, n_ret + n_cand, n_top};
     uint32_t known = 0u, prefix[NT];
     int remaining[NT], matching[NT];
 #pragma unroll
-    for (int t = 0; t < NT; ++t) remaining[t] = max(want[t], 1), matching[t] = m;
-    const int top_bit = diff ? 31 - __builtin_clz(diff) : -1;
+    for (int t = 0; t < NT; ++t) remaining[t] = max(want[t], 1), matching[t] = want[t] > 0 ? m : 0;
+    // (only the bits between the highest and the lowest differing one are sought: coarse scores end after one digit)
+    const int top_bit = diff ? 31 - __builtin_clz(diff) : -1, low_bit = diff ? __builtin_ctz(diff) : 0;
     known = top_bit == 31 ? 0u : ~((2u << top_bit) - 1u);  // (top_bit -1: every bit is known)
     if (top_bit < 0) known = 0xffffffffu;
+    known |= (1u << low_bit) - 1u;
 #pragma unroll
     for (int t = 0; t < NT; ++t) prefix[t] = sh.key_or & known;
     int hi = top_bit;
     bool first = true;
-    while (hi >= 0 && (matching[0] > kPartSmall || matching[1] > kPartSmall || matching[2] > kPartSmall)) {
-        const int lo = hi >= 10 ? hi - 10 : 0;
+    while (hi >= low_bit && (matching[0] > kPartList || matching[1] > kPartList || matching[2] > kPartList)) {
+        const int lo = max(hi - 10, low_bit);
         const uint32_t dmask = (1u << (hi - lo + 1)) - 1u;
         if (first) {  // one prefix: one histogram for all thresholds
             sweep([&](uint32_t k, int) { atomicAdd(&sh.hist[0][(k >> lo) & dmask], 1u); });
@@ -187,7 +259,7 @@ __global__ __launch_bounds__(kPartThreads) void partition_kernel(const float *__
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
             prefix[t] |= (uint32_t)sh.digit[t] << lo;
-            remaining[t] = sh.remaining[t], matching[t] = sh.matching[t];
+            remaining[t] = sh.remaining[t], matching[t] = want[t] > 0 ? sh.matching[t] : 0;
         }
         known |= dmask << lo;
         hi = lo - 1;
@@ -197,7 +269,7 @@ __global__ __launch_bounds__(kPartThreads) void partition_kernel(const float *__
     sweep([&](uint32_t k, int i) {
 #pragma unroll
         for (int t = 0; t < NT; ++t)
-            if (matching[t] <= kPartList && (k & known) == prefix[t]) {
+            if (matching[t] > 0 && matching[t] <= kPartList && (k & known) == prefix[t]) {
                 const int at = atomicAdd(&sh.list_len[t], 1);
                 sh.list_key[t][at] = k, sh.list_idx[t][at] = i;
             }
@@ -230,18 +302,21 @@ __global__ __launch_bounds__(kPartThreads) void partition_kernel(const float *__
         }
     }
     // more equal keys than a list holds: the remaining-th of them in channel order
+    if (matching[0] > kPartList || matching[1] > kPartList || matching[2] > kPartList) {
+        __syncthreads();
 #pragma unroll
-    for (int t = 0; t < NT; ++t) {
-        if (matching[t] <= kPartList) continue;
-        int seen = 0;
-        for (int s = 0; s * kPartThreads < m; ++s) {
-            const int i = s * kPartThreads + tid;
-            const bool eq = i < m && score_key(scores[i < m ? i : 0]) == prefix[t];
-            int v[1] = {eq ? 1 : 0}, tot[1];
-            part_scan<1>(v, tot, sh);
-            if (eq && seen + v[0] == remaining[t] - 1) sh.thr_key[t] = prefix[t], sh.thr_idx[t] = i;
-            seen += tot[0];
-            if (seen >= remaining[t]) break;
+        for (int t = 0; t < NT; ++t)
+            if (tid == t && matching[t] > kPartList) sh.thr_key[t] = prefix[t], sh.remaining[t] = remaining[t];
+        __syncthreads();
+        int last = -1;
+#pragma unroll 1
+        for (int t = 0; t < NT; ++t) {  // (one copy of the code)
+            const int matches = t == 0 ? matching[0] : (t == 1 ? matching[1] : matching[2]);
+            if (matches <= kPartList) continue;
+            const bool counted = m <= kPartMaxSlots * kPartThreads && last >= 0 && sh.thr_key[last] == sh.thr_key[t];
+            part_equal_key<NS>(scores, keys, m, sh.thr_key[t], sh.remaining[t], counted, reinterpret_cast<int *>(&sh.hist[0][0]),
+                               &sh.thr_idx[t]);
+            last = t;
         }
     }
     __syncthreads();

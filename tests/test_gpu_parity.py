@@ -73,6 +73,28 @@ def test_partition_from_scores_shaped_keys(pop, oracle, shape):
             assert np.array_equal(host(cand), cand0), (m, n_ret, n_cand, shape)
 
 
+@pytest.mark.parametrize("m", [33, 1025, 4097, 11008, 32768, 32769, 70000])
+@pytest.mark.parametrize("values", [1, 3, 40])
+def test_partition_of_equal_scores(pop, oracle, m, values):
+    """Few distinct scores, coarse ones and ones whose low bits differ: the thresholds fall among equal scores and are
+    counted out in channel order, at ranks on both sides of waves' and key slots' borders, in registers and (beyond 32768
+    channels) from memory, with thresholds that share a score and ones that do not."""
+    g = synth.rng("equal_scores", m, values)
+    s = (g.integers(0, values, size=m) * np.float32(0.37)).astype(np.float32)
+    ranks = sorted({r for r in (1, 64, 65, 1023, 1024, 1025, 4096, m // 2, m - 1, m) if r <= m})
+    for n_ret, n_in in [(r, min(m, r + 1)) for r in ranks] + [(0, r) for r in ranks[:3]] + [(m // 3, m)]:
+        n_top = (n_ret + n_in) // 2
+        region = torch.full((m,), 9, dtype=torch.uint8, device="cuda")
+        ret = torch.full((max(n_ret, 1),), -1, dtype=torch.int32, device="cuda")
+        cand = torch.full((max(n_in - n_ret, 1),), -1, dtype=torch.int32, device="cuda")
+        top = torch.full((max(n_top, 1),), -1, dtype=torch.int32, device="cuda")
+        pop.pop_partition_top_from_scores(dev(s), m, n_ret, n_in - n_ret, n_top, region, ret, cand, None, top)
+        r0, ret0, cand0 = oracle.partition(s, n_ret, n_in - n_ret)
+        assert np.array_equal(host(region), r0), (n_ret, n_in)
+        assert np.array_equal(host(ret)[:n_ret], ret0) and np.array_equal(host(cand)[:n_in - n_ret], cand0), (n_ret, n_in)
+        assert np.array_equal(host(top)[:n_top], oracle.partition(s, n_top, 0)[1]), (n_ret, n_in)
+
+
 @pytest.mark.parametrize("kind", ["none", "some", "all", "zeros"] + list(synth.SCORE_SHAPES))
 def test_partition_top_from_scores_bit_exact(pop, oracle, kind):
     """The partition launch that also emits the n_top best channels (the prompt's own mask): regions as before, and
