@@ -140,8 +140,9 @@ int pop_decode_mask(pop_layer_t *layer, const void *x_t, int B, const int *k,
  *       partition.  An all-ones mask gives the dense FFN.  bf16 layers with T >= 32 run this on the matrix
  *       cores: gate/up over the channels active in any row, H rounded to bf16, then one GEMM over those channels
  *       (scratch is allocated at the first such call and when T grows, which synchronises the device); smaller
- *       T and float32 layers keep H in float32 (bf16 layers with d % 64 == 0: all tokens in one pass over the weights,
- *       float32 layers 64 at a time; otherwise the decode kernels, up to eight tokens at a time).
+ *       T and float32 layers keep H in float32 (a few tokens on a layer of few channels, and bf16 layers with d % 64 != 0:
+ *       the decode kernels, up to eight tokens at a time; otherwise bf16 layers all tokens in one pass over the weights,
+ *       float32 layers 64 at a time).
  * Errors: mask == NULL without a preceding decode step -> POP_ESTATE; T mismatch, bad mask_rows -> POP_ESHAPE. */
 int pop_pruned_ffn(pop_layer_t *layer, const void *x, int T, const unsigned char *mask, int mask_rows,
                    void *y, pop_dtype_t ydtype, void *stream);

@@ -127,9 +127,19 @@ StepCopy step_copy(const pop_layer *L, int B, float *cand_scores, unsigned char 
     return c;
 }
 
-// From this many tokens on a bf16 layer's stand-alone pruned FFN runs on the matrix cores (below it, the decode
-// kernels take the tokens eight at a time).
+// From this many tokens on a bf16 layer's stand-alone pruned FFN runs on the matrix cores with H rounded to bf16.
 constexpr int kFfnMfmaMinTokens = 32;
+
+// A stand-alone FFN of a few tokens: one pass of the decode kernels over a list where T fits one and T x m is below this, else
+// the pass whose time hardly grows with T (bf16 / float32 matrix cores).  Whole call, decode / other, shared mask: 7B shape
+// (m 11008) 2 tokens 42.8 / 49.0 us, 5 tokens 46.5 / 48.3, 6 tokens 49.3 / 48.5, 8 tokens 53.9 / 48.7; d 2048, m 14336, 4
+// tokens 38.5 / 40.4, 5 tokens 40.6 / 40.3; d 2048, m 5632, 8 tokens 27.5 / 28.7; float32 d 2048, m 5632, 2 tokens 28.1 / 33.4,
+// 8 tokens 34.9 / 33.2.
+constexpr int kFewTokenChannels = 60000;
+
+// Per-token masks of up to this many bytes become a list in one launch; larger ones are combined by the whole chip first, two
+// launches more (d 512, m 768, 8 tokens: 20 us against 25; m 11008, 2 tokens: 54.4 / 55.6, 8 tokens: 76 / 58).
+constexpr int kMaskListBytes = 24576;
 
 // From this many sequences on a bf16 layer's batched step takes the matrix cores for its down projection: the vector
 // kernel's multiply-adds grow with the batch, the matrix-core kernel's time does not (whole step at the 13B shape, vector /
@@ -708,14 +718,15 @@ int pop_pruned_ffn(pop_layer_t *L, const void *x, int T, const unsigned char *ma
     L->has_step = false;  // the step scratch is reused below
     L->ulist_prefix_ok = false;
     if (L->is_bf16 && T >= kFfnMfmaMinTokens) return pruned_ffn_mfma(L, x, T, mask, mask_rows, y, y_bf16, s);
-    if (const int few = precise_max_tokens(L->is_bf16, d); T > 1 && few > 0) {
+    const int few = precise_max_tokens(L->is_bf16, d);
+    if (few > 0 && T > 1 && (T > L->chunk || (long long)T * m >= kFewTokenChannels)) {
         // a few tokens (bf16 layers: all of them) per pass over the weights
-        const unsigned char *rows = mask;
-        if (mask_rows > 1) {
+        if (mask_rows > 1 && (long long)mask_rows * m > kMaskListBytes) {
             POP_HIP(launch_mask_any(mask, T, m, L->ffn_any, s));
-            rows = L->ffn_any;
+            POP_HIP(launch_mask_to_list(L->ffn_any, 1, m, L->ulist, L->n_ulist, s));
+        } else {
+            POP_HIP(launch_mask_to_list(mask, mask_rows, m, L->ulist, L->n_ulist, s));
         }
-        POP_HIP(launch_mask_to_list(rows, 1, m, L->ulist, L->n_ulist, s));
         for (int t0 = 0; t0 < T; t0 += few) {
             const int n = T - t0 < few ? T - t0 : few;
             POP_HIP(launch_precise_gateup(L->w, L->is_bf16, d, m, (const char *)x + (size_t)t0 * d * L->esize, n, L->ulist,

@@ -618,12 +618,13 @@ SHORT_PROMPT_TOL = 1e-5
 @pytest.mark.parametrize("T,dtype,d,m", [(T, BF16, d, m) for T in (2, 15, 16, 17, 31)
                                          for d, m in ((64, 300), (192, 1100), (640, 2900), (136, 300))] +
                          [(T, F32, d, m) for T in (2, 15, 16, 17, 31, 64, 70, 129)
-                          for d, m in ((4, 9), (260, 333), (512, 1376), (72, 4200))])
+                          for d, m in ((4, 9), (260, 333), (512, 1376), (72, 4200))] +
+                         [(5, BF16, 64, 11008), (6, BF16, 64, 11008), (8, F32, 72, 7499), (8, F32, 72, 7500)])
 def test_short_prompts_in_one_pass(pop, oracle, T, dtype, d, m):
     """bf16 prompts below 32 tokens, float32 prompts of any length (one pass over the weights, hidden activations in float32, down projection on the
     matrix cores in exact parts or in double): stand-alone FFN under shared and per-token masks whose lists are empty, one
     channel, whole and ragged chunks, and the prompt's own forward pass with its scores; a row length that is no whole
-    k-step takes the decode kernels."""
+    k-step takes the decode kernels, and so does a stand-alone FFN of up to eight tokens on a layer of few channels."""
     L = synth.make_layer(synth.small_config("short_prompt", d, m, dtype, heavy_tail=dtype == BF16))
     x = synth.make_activations(L, T, "prompt")
     g = synth.rng("short_prompt_mask", d, m, T)
