@@ -142,9 +142,12 @@ constexpr int kFewTokenChannels = 60000;
 constexpr int kMaskListBytes = 24576;
 
 // From this many sequences on a bf16 layer's batched step takes the matrix cores for its down projection: the vector
-// kernel's multiply-adds grow with the batch, the matrix-core kernel's time does not (whole step at the 13B shape, vector /
-// matrix: 2 sequences 56.3 / 57.3 us, 3 60.1 / 58.6, 4 61.4 / 59.4, 8 74.3 / 67.6).
-constexpr int kSkinnyMinBatch = 3;
+// kernel's multiply-adds grow with the batch, the matrix-core kernel's time does not.  Whole step, vector / matrix, weights
+// from memory: 13B shape, sparsity .5: 3 sequences 66.5 / 65.8 us, 4 68.3 / 67.4, 8 84.6 / 79.3 (with two sequences 56.3 /
+// 57.3); 7B shape, .35: 3 sequences 52.7 / 51.4, 8 63.1 / 55.9; d 1024, m 2816: 3 sequences 24.9 / 21.8.  The largest layers
+// keep the vector kernel's shorter lists busy for longer: d 8192, m 28672, .35: 3 sequences 184.8 / 191.3, 5 198.7 / 201.8, 8
+// 229.0 / 224.5.
+int skinny_min_batch(int d, int m) { return (long long)d * m > (128ll << 20) ? 6 : 3; }
 
 // hipMalloc that leaves no pending error behind when it fails (a later launch check would report it as its own).
 bool dev_alloc(void **p, size_t bytes)
@@ -666,7 +669,7 @@ static int decode_output(pop_layer_t *L, int T, void *y, pop_dtype_t ydtype, con
     else if (T == 1)
         POP_HIP(launch_down(L->w, L->is_bf16, d, m, L->active_idx, nullptr, L->n_ret + L->step_k.k[0], L->h, nullptr, 0, 1,
                             L->partial, L->n_slabs, y, y_bf16, s, copy));
-    else if (L->is_bf16 && T >= kSkinnyMinBatch)
+    else if (L->is_bf16 && T >= skinny_min_batch(d, m))
         POP_HIP(launch_skinny_down(L->w, L->is_bf16, d, m, L->ulist, L->n_ulist, L->h, L->mask, m, T, L->partial,
                                    skinny_down_slabs(L->is_bf16, d, m, L->n_cu), y, y_bf16, s, copy));
     else
