@@ -11,7 +11,7 @@ import torch
 
 from paper_2602_06822_amd import synth
 
-from gpu_util import GpuLayer, dev, host, max_abs_rel, prefill_tile, prefill_tiles, score_rel_err
+from gpu_util import GpuLayer, dev, down_tile, host, max_abs_rel, prefill_tile, prefill_tiles, score_rel_err
 
 pytestmark = pytest.mark.gpu
 
@@ -420,9 +420,9 @@ def test_pruned_ffn_prompt_sized_bf16(pop, oracle, T):
 def test_pruned_ffn_direct_load_gemm_step_counts(pop, oracle, T):
     """The down-projection GEMM whose operands go straight into a ring of LDS buffers (d a multiple of 128): numbers
     of active channels that give every split 0, 1, 2, 3 and more k-steps of 64 channels (the ring's first requests
-    and its one- and two-step remainders), whole and ragged last k-steps, prompts of one ragged and of two token
-    tiles; then a short list after a long one on the same handle (the columns behind a list's end hold the longer
-    list's values, which meet rows of zeros)."""
+    and its one- and two-step remainders), whole and ragged last k-steps, prompts of two and of five 64-token tiles; then a
+    short list after a long one on the same handle (the columns behind a list's end hold the longer list's values, which
+    meet rows of zeros).  The taller tiles follow below."""
     d, m = 256, 2000
     L = synth.make_layer(synth.small_config("ffn_direct_gemm", d, m, BF16))
     x = synth.make_activations(L, T, "tokens")
@@ -434,6 +434,26 @@ def test_pruned_ffn_direct_load_gemm_step_counts(pop, oracle, T):
             y_ref = oracle.pruned_ffn(x, L.w_gate, L.w_up, L.w_down, BF16, mask)
             y = G.ffn(x, mask, F32)
             err = max_abs_rel(y, y_ref)
+            assert err <= FFN_MFMA_TOL_F32, f"T={T} a={a} err {err:.3e}"
+
+
+@pytest.mark.parametrize("mf,T", [(1, 59), (2, 123), (3, 187), (4, 251), (5, 315), (2, 70), (5, 300)])
+def test_pruned_ffn_direct_load_gemm_tile_heights(pop, oracle, mf, T):
+    """The same GEMM with tiles of 64 mf tokens, whose rings and waits differ: splits of 0 to 5 k-steps, even and odd, whole
+    and ragged lists, a short list after a long one.  Sampled token rows, the first and the last among them."""
+    d, m = 4096, 2100
+    assert down_tile(T, d, torch.cuda.get_device_properties(0).multi_processor_count) == (mf, 8)
+    L = synth.make_layer(synth.small_config("ffn_gemm_tiles", d, m, BF16))
+    x = synth.make_activations(L, T, "tokens")
+    g = synth.rng("ffn_gemm_tiles_masks", T)
+    rows = np.unique(np.append(g.choice(T, size=3, replace=False), [0, T - 1]))
+    with GpuLayer(pop, L, max_tokens=T, max_batch=1) as G:
+        for a in (2100, 1, 64, 130, 512, 700, 1024, 1536, 65):
+            mask = np.zeros(m, np.uint8)
+            mask[g.choice(m, size=a, replace=False)] = 1
+            y_ref = oracle.pruned_ffn(x[rows], L.w_gate, L.w_up, L.w_down, BF16, mask)
+            y = G.ffn(x, mask, F32)
+            err = max_abs_rel(y[rows], y_ref)
             assert err <= FFN_MFMA_TOL_F32, f"T={T} a={a} err {err:.3e}"
 
 
@@ -537,13 +557,14 @@ def test_prefill_rows_of_whole_k_steps(pop, oracle, d, m, T):
         _check_decode(oracle, G, L, region, cand, xt, k)
 
 
-@pytest.mark.parametrize("mf,f,d", [(1, 4, 64), (1, 12, 128), (2, 11, 192), (3, 7, 64), (4, 6, 128), (4, 11, 64), (5, 8, 64),
-                                    (5, 10, 128), (5, 12, 64)])
-def test_prefill_direct_load_tiles(pop, oracle, mf, f, d):
+@pytest.mark.parametrize("mf,f,d,T,m", [(mf, f, d, 64 * mf - 5, 2048 * f - 3) for mf, f, d in (
+    (1, 4, 64), (1, 12, 128), (3, 7, 64), (4, 11, 64), (5, 8, 64), (5, 10, 128), (5, 12, 64))] +
+    [(2, 11, 192, 251, 11008), (4, 7, 128, 251, 12293)])
+def test_prefill_direct_load_tiles(pop, oracle, mf, f, d, T, m):
     """Every tile height (64 mf tokens) and a spread of chunk widths (8 f channels, odd f with its shared fragment) of
     the direct-load contraction, a few rows and channels short of whole tiles and with row lengths shorter than the LDS
     ring: scores of all channels against the oracle, then the kept-H form through the prompt's output."""
-    T, m = 64 * mf - 5, 2048 * f - 3
+    assert prefill_tile(T, m, torch.cuda.get_device_properties(0).multi_processor_count) == (mf, f)
     L = synth.make_layer(synth.small_config("direct_tiles", d, m, BF16))
     x = synth.make_activations(L, T, "prompt")
     n_ret, n_cand, k = m // 2, m // 8, m // 16
