@@ -15,7 +15,8 @@
  *   - pointers marked "dev" are device (HBM) pointers, "host" are host pointers.  The caller owns every
  *     buffer it passes; the library never frees or keeps them beyond the call, except that
  *     pop_layer_create reads the three weight matrices once and keeps its own repacked copy
- *     (device memory cost: one extra copy of the weights plus O(max_batch * m) scratch).
+ *     (device memory cost: one extra copy of the weights plus scratch: about a hundred rows of m floats, up to 4096 rows
+ *     of d floats, and a row of m floats per 16 (float32) or 64 (bf16) tokens of max_tokens).
  *   - argument errors are found on the host before anything is launched.  Device work is enqueued on
  *     the given HIP stream (a hipStream_t passed as void*, NULL = the null stream) and is NOT
  *     synchronised: the caller synchronises the stream before reading outputs.
@@ -110,10 +111,12 @@ int pop_prefill_partition(pop_layer_t *layer, const void *x, int T, int n_ret, i
  * the retained channels plus the best k0 candidates by prefill score (same order as above), i.e. the n_ret + k0
  * channels of highest prefill importance.  mask: dev [m], 1 = active (may be NULL).
  * On bf16 layers with T >= 32 the hidden activations of the contraction are kept (rounded to bf16), the active
- * columns are gathered, and the down projection runs as one matrix-core GEMM; otherwise the call is
- * pop_prefill_partition followed by pop_pruned_ffn(mask).  Scratch for H (2 x T x m x 2 bytes, plus up to
- * 8 x 256 x d x 4 bytes of partial outputs) is allocated at the first call and when T grows, which synchronises
- * the device; it stays with the layer.
+ * columns are gathered, and the down projection runs as one matrix-core GEMM.  Shorter prompts (bf16 layers with
+ * d % 64 == 0: T < 32, float32 layers: T <= 64) keep them in float32 and need no second pass over the gate and up rows.
+ * Otherwise, and under the input-side reading, the call is pop_prefill_partition followed by pop_pruned_ffn(mask).
+ * Scratch of the T >= 32 path (H: 2 x T x m x 2 bytes, m rounded up to 64; partial outputs: n x T x d x 4 bytes where
+ * the contraction is split n = 2 .. 8 ways to fill the chip) is allocated at the first call and when T grows, which
+ * synchronises the device; it stays with the layer.
  * Errors: as pop_prefill_partition; k0 < 0 or k0 > n_cand -> POP_ESHAPE; y == NULL or bad ydtype -> POP_EINVAL. */
 int pop_prefill_forward(pop_layer_t *layer, const void *x, int T, int n_ret, int n_cand, int k0,
                         void *y, pop_dtype_t ydtype, float *scores, unsigned char *region, int *ret_idx,
@@ -151,8 +154,9 @@ int pop_pruned_ffn(pop_layer_t *layer, const void *x, int T, const unsigned char
  * channels, candidate re-scoring, per-token selection, then the output over retained and selected channels):
  * the same results, bit for bit, as pop_decode_mask followed by pop_pruned_ffn(mask = NULL), with y: dev [B][d] of
  * dtype ydtype and the other outputs as in pop_decode_mask (each may be NULL).
- * It issues exactly those two calls' launches.  A B == 1 step on a shape the fused single-sequence kernel takes is
- * two launches: that kernel, whose workgroups hand each other the candidates' h and the selection inside the launch,
+ * It issues those two calls' launches, except that the selection results the caller takes are copied by the last of
+ * them, where pop_decode_mask needs a launch for that.  A B == 1 step on a shape the fused single-sequence kernel
+ * takes is two launches: that kernel, whose workgroups hand each other the candidates' h and the selection inside the launch,
  * and a small kernel that sums their partial outputs.  Neither keeps host-side state per launch, so captured
  * launches can be replayed.  The waits inside the fused launch, and inside the first launch of a B > 1 step (its
  * selecting workgroups wait for the candidates' scores), are bounded (pop_layer_set_wait_limit): if one gives

@@ -74,7 +74,7 @@ struct pop_layer {
     int *fctr = nullptr;                  // [16]: [0] epoch, [1] finished workgroups, [2] sticky error flag
     int spin_limit = 1 << 16;             // looks a bounded in-kernel wait takes before it gives up
     BatchK step_k = {};
-    float *h = nullptr;                // [max_batch][m]
+    float *h = nullptr;                // [chunk][m]
     float *cscore = nullptr;           // [max_batch][m]
     unsigned char *mask = nullptr;     // [max_batch][m]
     unsigned char *selflag = nullptr;  // [m][POP_MAX_BATCH]: per-sequence selection by candidate position (B > 1)
@@ -82,7 +82,7 @@ struct pop_layer {
     int *n_active = nullptr;           // [max_batch]
     int *ulist = nullptr;              // [m]
     int *n_ulist = nullptr;            // [1]
-    float *partial = nullptr;          // max([n_slabs][max_batch][d], [fused workgroups][d])
+    float *partial = nullptr;          // max([n_slabs][chunk][d], [fused workgroups][d], [skinny slabs][32 or 64][d])
     int n_slabs = 0;
     // whole-prompt pruned FFN on the matrix cores (bf16 layers), allocated at its first use
     uint16_t *ffn_hc = nullptr;        // [tokens][ldh] bf16: H of the active channels, compact

@@ -215,8 +215,8 @@ __global__ __launch_bounds__(512) void down_gemm_bf16_kernel(const uint16_t *__r
 // unit ^ ((r / 2) % 8) (conflict-free 16-byte fragment reads).  Weight tile: 64 rows x 256 bytes as they come: a quarter
 // wave reads one whole row.  The weight fragments are transposed in registers (two 16-byte rows, one byte permute per
 // register), which measured the same as the transposing LDS read and leaves all reads to the compiler's own counting.
-// One wave per SIMD, pipelined by hand like the prefill contraction (and as bound by power: 16x16x32 products move fewer
-// accumulator bytes, four waves read 48 KB of fragments per 32-element slice where eight of 64 x 64 read 64 KB): while the
+// One wave per SIMD, pipelined by hand like the prefill contraction (16x16x32 products move fewer accumulator bytes, four
+// waves read 48 KB of fragments per 32-element slice where eight of 64 x 64 read 64 KB): while the
 // products of one slice issue, the fragments of the next are read; a k-step is two slices, the first with the requests for
 // weight rows and channel numbers, then the barrier, the second with the requests for Hc rows.
 // Every wave issues the same loads in every k-step, so a step waits with an exact count for its own rows only.  Nothing is
@@ -224,8 +224,10 @@ __global__ __launch_bounds__(512) void down_gemm_bf16_kernel(const uint16_t *__r
 // pointed at a row of zeros (zero_row, 256 bytes), which makes it irrelevant what the Hc columns beyond a hold, as long as
 // it is finite (the buffer is cleared when it is allocated and only ever holds H values).  Needs d % 128 == 0 and
 // ldh >= a rounded up to 64.
-// d 4096, 7155 channels: 512 tokens 45 us (the kernel of eight waves and 32x32x16 products it replaced: 42), 2048 tokens 122
-// us (123 to 136); 13B shape, 333 tokens, 6912 channels 43 us (47); 270 tokens, 9318 channels 41 us (48).
+// Dispatch times inside a prompt's forward call (in parentheses the kernel of eight waves, 256-token tiles and 32x32x16
+// products it replaced): d 4096, 9318 channels, 270 tokens 40.0 us (50.8); 13B shape, 6912 channels, 333 tokens 45.4 (46.7);
+// d 4096, 7155 channels, 512 tokens 45.5 (39.3), 2048 tokens 140.6 (126.4): where 256-token tiles come out even, eight waves
+// with half the columns each were the better form.
 constexpr int kDdThreads = 256;
 constexpr int kDdMaxMF = 5;
 constexpr int kDdSlots = 8;  // k-steps whose channel numbers are kept

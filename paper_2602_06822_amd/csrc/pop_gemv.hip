@@ -526,7 +526,7 @@ hipError_t launch_down(const void *w, int is_bf16, int d, int m, const int *list
                                  y_bf16, s, copy);
 }
 
-// ---------------------------------------------------------------- down projection of up to 31 tokens on the matrix cores
+// ---------------------------------------------------------------- down projection of up to 32 tokens on the matrix cores
 // y[t][:] = sum over listed j of h[t][j] * W_down[:, j], h in float32.  Bound by the weight stream: the vector kernel above
 // spends a fused multiply-add per token and weight (eight sequences: 27 us where the rows take 15), and takes eight tokens
 // at a time.  Here a float32 h is the exact sum of three bf16 values, so three 16x16x32 products per 16 tokens give what

@@ -372,7 +372,8 @@ __device__ __forceinline__ void pm_row_channel(int r, int &ch, int &which)
 }
 
 // Tiles of one launch: F and the counts that follow.  Shared by host and device (the list form learns its channel
-// count on the device).
+// count on the device).  Every width of the ladder is a code path of each kernel; without 9 and 5 a chunk is at most a
+// ninth or a fifth wider than the best one.
 struct PmTiles {
     int f, n_ct, total, per_xcd;
 };
@@ -457,7 +458,8 @@ __device__ __forceinline__ void pm_tile(const uint16_t *__restrict__ w, const ui
     // every tile: a sum must not depend on its channel's place, or channels with equal weights would not tie.  Rows are a
     // power of two apart in most models, and tiles in step with each other keep asking the same few memory channels.  So
     // the sums in double, where the order is lost in the rounding to float32, start at a column of their own per chunk (24
-    // tokens, d 4096, m 11008: whole call 83 -> 73 us; eight experts of about 256 tokens would gain 1215 -> 1079 us).
+    // tokens, d 4096, m 11008: whole call 83 -> 73 us); in one tile of float32 sums it gained as much (270 tokens, m 14336: 98
+    // -> 80 us).
     const int rot = kPrecise ? ctile % n_k : 0;
     auto kof = [&](int step) {
         const int q = min(step, n_k - 1) + rot;

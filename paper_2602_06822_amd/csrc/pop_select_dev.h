@@ -195,11 +195,10 @@ __device__ __forceinline__ void radix_threshold(KeyFn key, int n, int n_top, Sel
 // copies the keys that share a threshold's leading digit into a short list in sh.keys (one NT-th of it per
 // threshold; thresholds under one leading digit share a list), which the sweeps for the remaining digits read
 // instead of all n keys.  A threshold whose leading digit holds more keys than its list can take keeps sweeping all
-// keys.  Must not be used while sh.keys holds data.  have_diff: diff_in holds the bits in which any two keys differ.
+// keys.  Must not be used while sh.keys holds data.
 template <int NT, class KeyFn>
 __device__ __forceinline__ void radix_thresholds_lists(KeyFn key, int n, const int (&n_top)[NT], SelShared &sh,
-                                                       uint32_t (&kth)[NT], int (&take)[NT], bool have_diff = false,
-                                                       uint32_t diff_in = 0, unsigned long long *tr = nullptr)
+                                                       uint32_t (&kth)[NT], int (&take)[NT])
 {
     static_assert(NT == 2, "two thresholds: two sets of histograms");
     constexpr int kCap = kSelLdsKeys / NT;
@@ -214,16 +213,12 @@ __device__ __forceinline__ void radix_thresholds_lists(KeyFn key, int n, const i
         for (int i = threadIdx.x + blockDim.x; i < 256; i += blockDim.x) sh.hist[0][i] = 0;
     __syncthreads();
     const uint32_t k0 = key(0);
-    // bits in which any two keys differ: from the caller (who had every key in hand), else one sweep
-    uint32_t diff = diff_in;
-    if (!have_diff) {
-        diff = 0;
-        for (int i = threadIdx.x; i < n; i += blockDim.x) diff |= key(i) ^ k0;
-        diff = wave_or_rows(diff);
-        if (threadIdx.x % 16 == 0 && diff) atomicOr(&scratch[0], diff);
-        __syncthreads();
-        diff = scratch[0];
-    }
+    uint32_t diff = 0;  // bits in which any two keys differ
+    for (int i = threadIdx.x; i < n; i += blockDim.x) diff |= key(i) ^ k0;
+    diff = wave_or_rows(diff);
+    if (threadIdx.x % 16 == 0 && diff) atomicOr(&scratch[0], diff);
+    __syncthreads();
+    diff = scratch[0];
     if (diff == 0) {  // all keys equal
         __syncthreads();
 #pragma unroll
@@ -297,7 +292,6 @@ __device__ __forceinline__ void radix_thresholds_lists(KeyFn key, int n, const i
             }
         }
         __syncthreads();
-        if (tr && threadIdx.x == 0 && pass < 4) tr[pass] = wall_clock64();  // (profiling builds: the sweep is done)
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
             int c[4], lane_tot = 0;

@@ -220,7 +220,7 @@ def test_decode_strategies_full_size(pop, oracle, strategy, gamma):
 def test_prefill_alternating_prompt_lengths_on_one_layer(pop, oracle):
     """One layer of the benchmark shape, prefilled with a 512-token prompt (one contraction tile per compute unit: the
     launch forms the scores itself, counting the tiles of each channel chunk in), a 2048-token prompt (several tiles
-    per compute unit: the partition launch sums the partial rows), a 130-token prompt (the small-tile form) and the
+    per compute unit: a launch of its own sums the partial rows), a 130-token prompt (the small-tile form) and the
     first prompt again: every call's scores against the oracle, and the last call bit for bit the first - the chunk
     counters are back at rest after every launch, whatever ran before."""
     cfg = synth.CFG2

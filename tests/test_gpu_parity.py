@@ -502,7 +502,7 @@ def _check_prefill_forward(oracle, G, L, x, n_ret, n_cand, k0, ydtype, y_tol, ro
 
 @pytest.mark.parametrize("dtype,T", [(F32, 40), (BF16, 20), (BF16, 150), (BF16, 290)])
 def test_prefill_forward_small(pop, oracle, dtype, T):
-    """Partition + pruned output of the prompt in one call: float32 and short prompts (decode kernels), bf16
+    """Partition + pruned output of the prompt in one call: float32 and short prompts (H in float32), bf16
     prompts of 32 tokens and more (kept H, gathered columns, matrix-core GEMM); degenerate region sizes; the
     partition it leaves serves the decode steps that follow."""
     d, m = (264, 301) if dtype == BF16 else (260, 301)
@@ -524,8 +524,9 @@ def test_prefill_forward_small(pop, oracle, dtype, T):
 
 @pytest.mark.parametrize("cfg_name,T,r", [("CFG4", 1024, 0.50), ("CFG5", 300, 0.35)])
 def test_prefill_forward_other_shapes(pop, oracle, cfg_name, T, r):
-    """The prompt's forward pass on the Llama-2-13B-shaped layer (d = 5120: 40 column tiles, 4 token tiles, no
-    split) and on a Mixtral-shaped expert with a ragged share of the prompt (128-token tiles, the last one short)."""
+    """The prompt's forward pass on the Llama-2-13B-shaped layer (d = 5120: 40 column tiles, 192-token tiles
+    of the down projection, no split) and on a Mixtral-shaped expert with a ragged share of the prompt (one tile of 320
+    tokens, eight splits)."""
     cfg = getattr(synth, cfg_name)
     L = synth.make_layer(cfg, layer_id=0)
     m = cfg.m
@@ -540,8 +541,8 @@ def test_prefill_forward_other_shapes(pop, oracle, cfg_name, T, r):
 @pytest.mark.parametrize("d,m,T", [(192, 301, 20), (128, 130, 150), (192, 301, 300), (320, 97, 257)])
 def test_prefill_rows_of_whole_k_steps(pop, oracle, d, m, T):
     """bf16 layers whose rows are a whole number of 64-element k-steps take the prefill kernel's direct global -> LDS
-    staging: every score against the oracle, with ragged token tiles, channel chunks that do not fill a tile, both
-    tile forms and both token-tile sizes; then the forward pass (kept H, list form) and a decode step."""
+    staging: every score against the oracle, with ragged token tiles and channel chunks that do not fill a
+    tile; then the forward pass (kept H, list form) and a decode step."""
     L = synth.make_layer(synth.small_config("whole_k_steps", d, m, BF16))
     x = synth.make_activations(L, T, "prompt")
     xt = synth.make_activations(L, 1, "decode")
