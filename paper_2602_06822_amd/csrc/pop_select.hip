@@ -211,7 +211,10 @@ __global__ __launch_bounds__(kPartThreads) void partition_kernel(const float *__
     uint32_t known = 0u, prefix[NT];
     int remaining[NT], matching[NT];
 #pragma unroll
-    for (int t = 0; t < NT; ++t) remaining[t] = max(want[t], 1), matching[t] = want[t] > 0 ? m : 0;
+    for (int t = 0; t < NT; ++t) {
+        remaining[t] = max(want[t], 1), matching[t] = want[t] > 0 && diff ? m : 0;
+        if (diff == 0 && tid == t) sh.thr_key[t] = sh.key_or, sh.thr_idx[t] = want[t] - 1;  // all equal: in channel order
+    }
     // (only the bits between the highest and the lowest differing one are sought: coarse scores end after one digit)
     const int top_bit = diff ? 31 - __builtin_clz(diff) : -1, low_bit = diff ? __builtin_ctz(diff) : 0;
     known = top_bit == 31 ? 0u : ~((2u << top_bit) - 1u);  // (top_bit -1: every bit is known)
