@@ -143,11 +143,15 @@ constexpr int kMaskListBytes = 24576;
 
 // From this many sequences on a bf16 layer's batched step takes the matrix cores for its down projection: the vector
 // kernel's multiply-adds grow with the batch, the matrix-core kernel's time does not.  Whole step, vector / matrix, weights
-// from memory: 13B shape, sparsity .5: 3 sequences 66.5 / 65.8 us, 4 68.3 / 67.4, 8 84.6 / 79.3 (with two sequences 56.3 /
-// 57.3); 7B shape, .35: 3 sequences 52.7 / 51.4, 8 63.1 / 55.9; d 1024, m 2816: 3 sequences 24.9 / 21.8.  The largest layers
-// keep the vector kernel's shorter lists busy for longer: d 8192, m 28672, .35: 3 sequences 184.8 / 191.3, 5 198.7 / 201.8, 8
-// 229.0 / 224.5.
-int skinny_min_batch(int d, int m) { return (long long)d * m > (128ll << 20) ? 6 : 3; }
+// from memory: d 1024, m 2816: 3 sequences 24.9 / 21.8 us; d 4104, m 5000: 3 sequences 41.3 / 39.9; 7B shape: 3 sequences at
+// sparsity .35 52.7 / 51.4 and at .5 50.0 / 50.7, 4 sequences 54.4 / 52.4 and 52.5 / 51.8; 13B shape: 3 sequences 73.1 / 74.4
+// and 66.5 / 65.8, 4 sequences 74.7 / 73.9 and 68.3 / 67.4, 8 84.6 / 79.3; d 8192, m 28672, .35: 3 sequences 184.8 / 191.3, 5
+// 198.7 / 201.8, 8 229.0 / 224.5.
+int skinny_min_batch(int d, int m)
+{
+    const long long weights = (long long)d * m;
+    return weights > (128ll << 20) ? 6 : (weights > (32ll << 20) ? 4 : 3);
+}
 
 // hipMalloc that leaves no pending error behind when it fails (a later launch check would report it as its own).
 bool dev_alloc(void **p, size_t bytes)
