@@ -13,36 +13,71 @@ namespace pop {
 // own 1024 channels.  Finding them in one place and handing them on would cost a launch or a grid-wide wait, as long as
 // the search itself; done by everybody at once it costs nothing more, and the outputs (a dozen arrays in a layer's
 // prefill) are written by the whole chip.
-// Search: the keys sit in registers (NS per thread).  One histogram over the 11 bits below the keys' common leading bits
-// leaves a threshold in a bucket of a few dozen to a few hundred keys, a second one (few keys take part) in one of a few,
-// whose ranks are counted out pairwise.  11 bits instead of 8 spread the LDS atomics over eight times as many words.
-// Only the bits between the highest and the lowest differing one are swept, and a bucket that still holds more than a list
-// when they are all known holds equal keys, which are counted out in channel order (part_equal_key; 1376 scores of eight
-// values: 20 -> 10 us, 11008: 31 -> 19).
+// Search: the keys sit in registers (NS per thread), as distances u from the largest key, so that the best channel has 0.
+// One histogram over 8192 equal intervals between the largest and the smallest key leaves a threshold in an interval of a
+// dozen keys, whose ranks are counted out pairwise.  (Intervals of the keys' range and not leading bits of the keys: scores on
+// both sides of a power of two differ in their leading bits however close they are.)  An interval that holds more than a list
+// is cut into 2048 again; where that ends at equal keys, they are counted out in channel order (part_equal_key).
 // A threshold is an element (key, channel): channels up to it in the order (key descending, channel ascending) are in.
-// 11008 channels with all of a layer's outputs: 13 us, against 25 us for the four 8-bit sweeps of one workgroup and 6 us for
-// the launch that spread its lists; comparing all pairs of keys instead, 64 channels per workgroup, took 27 us.
+// Bound by the sixteen waves' issue and the barriers: a sweep over all keys takes 0.6 to 1 us, a phase between two barriers half
+// a microsecond at least, so there are seven phases of which two sweep.  Launches back to back: 11008 channels 13.6 -> 9.1 us,
+// 14336 16.0 -> 10.3, up to 2800 at the rate of launches (the kernel itself 8.8 -> 5 us at 1376), against leading bits of the
+// keys, a second histogram in most partitions and scans of each output's count; eight distinct scores 18.9 -> 18.0, all equal
+// 8.5 -> 8.1.
 constexpr int kPartThreads = 1024;
-constexpr int kPartBins = 2048;
-constexpr int kPartList = 32;      // keys of a bucket counted out pairwise at most: while a bucket holds more, another digit
-                                   // is swept, which is cheaper than the pairs
+constexpr int kPartWaves = kPartThreads / kWave;
+constexpr int kPartBits = 13, kPartBins = 1 << kPartBits;          // intervals of the first histogram
+constexpr int kPartMoreBits = 11, kPartMoreBins = 1 << kPartMoreBits;  // of a further one (three of them at a time)
+constexpr int kPartList = 64;      // keys of an interval counted out pairwise at most, one per lane
 constexpr int kPartMaxSlots = 32;  // keys per thread held in registers at most: 32768 channels
 
 struct PartShared {
-    unsigned int hist[3][kPartBins];
-    __attribute__((aligned(16))) uint32_t list_key[3][kPartList];
+    __attribute__((aligned(16))) unsigned int hist[kPartBins];
+    __attribute__((aligned(16))) uint32_t list_u[3][kPartList];
     __attribute__((aligned(16))) int list_idx[3][kPartList];
     int list_len[3];
-    int digit[3], remaining[3], matching[3];
-    uint32_t thr_key[3];
-    int thr_idx[3];
-    uint32_t key_or, key_nand;
-    int wave_tot[6][kPartThreads / kWave];
+    uint32_t lo[3];                     // start of the threshold's interval
+    int remaining[3], matching[3];      // rank within it, keys in it
+    uint32_t thr_u[3];
+    int thr_idx[3], base_list[3];       // base_list: keys of the list that are in and belong to earlier channels
+    uint32_t extreme[2][kPartWaves], bits[kPartWaves];
+    int wave_tot[3][kPartWaves];
+    uint32_t own[2][3][kPartWaves];
 };
 
-// Exclusive scan of N streams over the workgroup, totals in tot.
+// Inclusive scan within each row of 16 lanes.
+__device__ __forceinline__ uint32_t row_incl_scan(uint32_t v)
+{
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, false);  // row_shr:1
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, false);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, false);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, false);
+    return v;
+}
+
+// op over each row of 16 lanes (every lane of the row gets it).
+template <class Op>
+__device__ __forceinline__ uint32_t row_reduce(uint32_t v, Op op)
+{
+    v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xf, 0xf, true));   // quad_perm 1,0,3,2
+    v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xf, 0xf, true));   // quad_perm 2,3,0,1
+    v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xf, 0xf, true));  // row_half_mirror
+    v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x140, 0xf, 0xf, true));  // row_mirror
+    return v;
+}
+
+// op over the wave, in its last lane.
+template <class Op>
+__device__ __forceinline__ uint32_t wave_reduce_last(uint32_t v, Op op)
+{
+    v = row_reduce(v, op);
+    v = op(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x142, 0xa, 0xf, false));  // row_bcast:15
+    return op(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x143, 0xc, 0xf, false));  // row_bcast:31
+}
+
+// Exclusive scan of N streams over the workgroup.
 template <int N>
-__device__ __forceinline__ void part_scan(int (&v)[N], int (&tot)[N], PartShared &sh)
+__device__ __forceinline__ void part_scan(int (&v)[N], PartShared &sh)
 {
     const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     int inc[N];
@@ -54,23 +89,21 @@ __device__ __forceinline__ void part_scan(int (&v)[N], int (&tot)[N], PartShared
     __syncthreads();
 #pragma unroll
     for (int q = 0; q < N; ++q) {
-        const int t = lane < kPartThreads / kWave ? sh.wave_tot[q][lane] : 0;
-        const int ts = wave_incl_scan(t);
-        v[q] = (wave > 0 ? __builtin_amdgcn_readlane(ts, wave - 1) : 0) + inc[q] - v[q];
-        tot[q] = __builtin_amdgcn_readlane(ts, kWave - 1);
+        const uint32_t ts = row_incl_scan((uint32_t)sh.wave_tot[q][lane % kPartWaves]);
+        v[q] = (wave > 0 ? __builtin_amdgcn_readlane((int)ts, wave - 1) : 0) + inc[q] - v[q];
     }
-    __syncthreads();
 }
 
-// *idx = the rank-th (1 ..) channel among those whose key is `want`.  Every wave counts its own 64 channels of every key
-// slot, 32 slots at a time, then finds the slot and wave where the rank is reached from all the counts (count: 512 words;
+// *idx = the rank-th (1 ..) channel among those whose key is key_max - want.  Every wave counts its own 64 channels of every
+// key slot, 32 slots at a time, then finds the slot and wave where the rank is reached from all the counts (count: 512 words;
 // counted: they are there already, from a call for the same key).  More than four keys per thread are read again: held in
 // registers for this, they cost every partition half a microsecond.
 template <int NS, int NK>
-__device__ __forceinline__ void part_equal_key(const float *__restrict__ scores, const uint32_t (&keys)[NK], int m,
-                                               uint32_t want, int rank, bool counted, int *count, int *idx)
+__device__ __forceinline__ void part_equal_key(const float *__restrict__ scores, const uint32_t (&u)[NK], int m,
+                                               uint32_t key_max, uint32_t want, int rank, bool counted, int *count, int *idx)
 {
-    constexpr int kWaves = kPartThreads / kWave;
+    constexpr int kWaves = kPartWaves;
+    const uint32_t want_key = key_max - want;
     static_assert(kPartMaxSlots * kWaves == 8 * kWave && 8 * kWave <= kPartBins, "eight counts per lane, in a histogram");
     const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     for (int base = 0; base < m; base += kPartMaxSlots * kPartThreads) {
@@ -79,7 +112,7 @@ __device__ __forceinline__ void part_equal_key(const float *__restrict__ scores,
             if constexpr (NS > 0 && NS <= 4) {
 #pragma unroll
                 for (int s = 0; s < NK; ++s) {
-                    const int c = __builtin_popcountll(__ballot(s * kPartThreads + (int)threadIdx.x < m && keys[s] == want));
+                    const int c = __builtin_popcountll(__ballot(s * kPartThreads + (int)threadIdx.x < m && u[s] == want));
                     mine = lane == s ? c : mine;
                 }
             } else {
@@ -94,7 +127,7 @@ __device__ __forceinline__ void part_equal_key(const float *__restrict__ scores,
 #pragma unroll
                     for (int q = 0; q < 8; ++q) {
                         const int i = base + (s + q) * kPartThreads + (int)threadIdx.x;
-                        const int c = __builtin_popcountll(__ballot(i < m && score_key(v[q]) == want));
+                        const int c = __builtin_popcountll(__ballot(i < m && score_key(v[q]) == want_key));
                         mine = lane == s + q ? c : mine;
                     }
                 }
@@ -121,7 +154,7 @@ __device__ __forceinline__ void part_equal_key(const float *__restrict__ scores,
         }
         if (wave == entry % kWaves) {
             const int i = base + entry / kWaves * kPartThreads + (int)threadIdx.x;
-            const bool eq = i < m && score_key(scores[i < m ? i : 0]) == want;
+            const bool eq = i < m && score_key(scores[i < m ? i : 0]) == want_key;
             const unsigned long long eqs = __ballot(eq);
             if (eq && before + __builtin_popcountll(eqs & ((1ull << lane) - 1ull)) == rank - 1) *idx = i;
         }
@@ -164,15 +197,8 @@ __global__ __launch_bounds__(kPartThreads) void partition_kernel(const float *__
 {
     __shared__ PartShared sh;
     constexpr int NT = 3, NK = NS > 0 ? NS : 1;
-    const int tid = threadIdx.x;
-    if (blockIdx.x == 0 && tid < o.n_sync) o.sync[tid] = 0;
-    if (blockIdx.x == 0 && tid == 0 && o.top_count) *o.top_count = n_top;
-    for (int i = tid; i < kPartBins; i += kPartThreads) sh.hist[0][i] = 0;
-    if (tid == 0) sh.key_or = sh.key_nand = 0;
-    if (tid < NT) sh.list_len[tid] = 0;
-    if (tid < NT * kPartList) (&sh.list_key[0][0])[tid] = 0u, (&sh.list_idx[0][0])[tid] = 0x7fffffff;  // (before nothing)
-    uint32_t keys[NK];
-    uint32_t my_or = 0, my_nand = 0;
+    const int tid = threadIdx.x, lane = tid % kWave, wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    uint32_t u[NK];
     if (NS > 0) {
         float v[NK];
 #pragma unroll
@@ -181,191 +207,279 @@ __global__ __launch_bounds__(kPartThreads) void partition_kernel(const float *__
             v[s] = scores[i < m ? i : 0];
         }
 #pragma unroll
-        for (int s = 0; s < NK; ++s) keys[s] = score_key(v[s]);
+        for (int s = 0; s < NK; ++s) u[s] = __float_as_uint(v[s]);
     }
-    // f(key, channel) for every key of this thread
+    if (blockIdx.x == 0 && tid < o.n_sync) o.sync[tid] = 0;
+    if (blockIdx.x == 0 && tid == 0 && o.top_count) *o.top_count = n_top;
+    for (int i = tid; i < kPartBins / 4; i += kPartThreads) reinterpret_cast<uint4 *>(sh.hist)[i] = make_uint4(0, 0, 0, 0);
+    if (tid < NT) sh.list_len[tid] = sh.base_list[tid] = 0;
+    if (tid < NT * kPartList) (&sh.list_u[0][0])[tid] = 0xffffffffu, (&sh.list_idx[0][0])[tid] = 0x7fffffff;  // (before nothing)
+
+    const auto larger = [](uint32_t a, uint32_t b) { return a > b ? a : b; };
+    const auto smaller = [](uint32_t a, uint32_t b) { return a < b ? a : b; };
+    const auto either = [](uint32_t a, uint32_t b) { return a | b; };
+    uint32_t key_max = 0u, key_min = 0xffffffffu, bits = 0u;  // (bits: in which any two keys differ)
+    if (NS > 0) {
+#pragma unroll
+        for (int s = 0; s < NK; ++s) u[s] = score_key(__uint_as_float(u[s]));
+        const uint32_t key_0 = __builtin_amdgcn_readfirstlane(u[0]);
+#pragma unroll
+        for (int s = 0; s < NK; ++s) {  // (slots beyond the last channel repeat channel 0)
+            key_max = larger(key_max, u[s]), key_min = smaller(key_min, u[s]), bits |= u[s] ^ key_0;
+        }
+    } else {
+        const uint32_t key_0 = score_key(scores[0]);
+        for (int i = tid; i < m; i += kPartThreads) {
+            const uint32_t k = score_key(scores[i]);
+            key_max = larger(key_max, k), key_min = smaller(key_min, k), bits |= k ^ key_0;
+        }
+    }
+    key_max = wave_reduce_last(key_max, larger), key_min = wave_reduce_last(key_min, smaller);
+    bits = wave_reduce_last(bits, either);
+    if (lane == kWave - 1) sh.extreme[0][wave] = key_max, sh.extreme[1][wave] = key_min, sh.bits[wave] = bits;
+    __syncthreads();
+    key_max = __builtin_amdgcn_readfirstlane(row_reduce(sh.extreme[0][lane % kPartWaves], larger));
+    key_min = __builtin_amdgcn_readfirstlane(row_reduce(sh.extreme[1][lane % kPartWaves], smaller));
+    bits = __builtin_amdgcn_readfirstlane(row_reduce(sh.bits[lane % kPartWaves] | (sh.extreme[0][lane % kPartWaves] ^ key_max), either));
+    // f(distance from the largest key, channel) for every key of this thread
     auto sweep = [&](auto f) {
         if (NS > 0) {
 #pragma unroll
             for (int s = 0; s < NK; ++s) {
                 const int i = s * kPartThreads + tid;
-                if (i < m) f(keys[s], i);
+                if (i < m) f(u[s], i);
             }
         } else {
-            for (int i = tid; i < m; i += kPartThreads) f(score_key(scores[i]), i);
+            for (int i = tid; i < m; i += kPartThreads) f(key_max - score_key(scores[i]), i);
         }
     };
-    __syncthreads();
-    sweep([&](uint32_t k, int) { my_or |= k, my_nand |= ~k; });
-    my_or = wave_or_rows(my_or), my_nand = wave_or_rows(my_nand);
-    if (tid % 16 == 0) {
-        atomicOr(&sh.key_or, my_or);
-        atomicOr(&sh.key_nand, my_nand);
+    const uint32_t range = key_max - key_min;
+    // Intervals are 2^shift wide; below the lowest bit in which keys differ there is nothing to cut (a few coarse scores come
+    // to lie in neighbouring words of the histogram, and what stays crowded there is equal).
+    const int low = bits ? __builtin_ctz(bits) : 0;
+    int shift = max(low, 32 - kPartBits - (range ? __builtin_clz(range) : 32));
+    if (NS > 0) {
+#pragma unroll
+        for (int s = 0; s < NK; ++s) u[s] = key_max - u[s];
     }
-    __syncthreads();
-    const uint32_t diff = sh.key_or & sh.key_nand;
 
     // thresholds: retained (rank n_ret), retained + candidate (rank n_ret + n_cand), the n_top best; a set of none needs no
     // search (matching 0) and is closed at the end
     const int want[NT] = {n_ret, n_ret + n_cand, n_top};
-    uint32_t known = 0u, prefix[NT];
+    uint32_t lo[NT];
     int remaining[NT], matching[NT];
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-        remaining[t] = max(want[t], 1), matching[t] = want[t] > 0 && diff ? m : 0;
-        if (diff == 0 && tid == t) sh.thr_key[t] = sh.key_or, sh.thr_idx[t] = want[t] - 1;  // all equal: in channel order
-    }
-    // (only the bits between the highest and the lowest differing one are sought: coarse scores end after one digit)
-    const int top_bit = diff ? 31 - __builtin_clz(diff) : -1, low_bit = diff ? __builtin_ctz(diff) : 0;
-    known = top_bit == 31 ? 0u : ~((2u << top_bit) - 1u);  // (top_bit -1: every bit is known)
-    if (top_bit < 0) known = 0xffffffffu;
-    known |= (1u << low_bit) - 1u;
-#pragma unroll
-    for (int t = 0; t < NT; ++t) prefix[t] = sh.key_or & known;
-    int hi = top_bit;
-    bool first = true;
-    while (hi >= low_bit && (matching[0] > kPartList || matching[1] > kPartList || matching[2] > kPartList)) {
-        const int lo = max(hi - 10, low_bit);
-        const uint32_t dmask = (1u << (hi - lo + 1)) - 1u;
-        if (first) {  // one prefix: one histogram for all thresholds
-            sweep([&](uint32_t k, int) { atomicAdd(&sh.hist[0][(k >> lo) & dmask], 1u); });
-        } else {
-            for (int i = tid; i < NT * kPartBins; i += kPartThreads) (&sh.hist[0][0])[i] = 0;
-            __syncthreads();
-            sweep([&](uint32_t k, int) {
-#pragma unroll
-                for (int t = 0; t < NT; ++t)
-                    if ((k & known) == prefix[t]) atomicAdd(&sh.hist[t][(k >> lo) & dmask], 1u);
-            });
-        }
-        __syncthreads();
-        // thread t owns the bins 2047 - 2t and 2046 - 2t: scanned from the largest digit down
-        int c[NT][2], v[NT], tot[NT];
+    auto take_interval = [&]() {
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
-            const uint2 two = *reinterpret_cast<const uint2 *>(&sh.hist[first ? 0 : t][kPartBins - 2 - 2 * tid]);
-            c[t][0] = (int)two.y, c[t][1] = (int)two.x;
+            lo[t] = __builtin_amdgcn_readfirstlane(sh.lo[t]);
+            remaining[t] = __builtin_amdgcn_readfirstlane(sh.remaining[t]);
+            matching[t] = __builtin_amdgcn_readfirstlane(sh.matching[t]);
+        }
+    };
+    if (range == 0) {  // all equal (11008 additions to one word would take as long as all the rest)
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            lo[t] = 0u, remaining[t] = max(want[t], 1), matching[t] = want[t] > 0 ? m : 0;
+            if (tid == t) sh.remaining[t] = remaining[t];
+        }
+    } else {
+        sweep([&](uint32_t v, int) { atomicAdd(&sh.hist[v >> shift], 1u); });
+        __syncthreads();
+        const uint4 h0 = reinterpret_cast<const uint4 *>(sh.hist)[2 * tid], h1 = reinterpret_cast<const uint4 *>(sh.hist)[2 * tid + 1];
+        const int c[8] = {(int)h0.x, (int)h0.y, (int)h0.z, (int)h0.w, (int)h1.x, (int)h1.y, (int)h1.z, (int)h1.w};
+        int v[1] = {((c[0] + c[1]) + (c[2] + c[3])) + ((c[4] + c[5]) + (c[6] + c[7]))};
+        const int sum = v[0];
+        part_scan<1>(v, sh);
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            const int rank = max(want[t], 1);
+            if (v[0] < rank && rank <= v[0] + sum) {
+                int before = v[0], bin = 8 * tid, in_bin = 0;
+#pragma unroll
+                for (int q = 0; q < 8; ++q) {
+                    const bool here = before < rank && rank <= before + c[q];
+                    if (here) sh.remaining[t] = rank - before, bin = 8 * tid + q, in_bin = c[q];
+                    before += c[q];
+                }
+                sh.lo[t] = (uint32_t)bin << shift, sh.matching[t] = want[t] > 0 ? in_bin : 0;
+            }
+        }
+        __syncthreads();
+        take_interval();
+    }
+    auto crowded = [&]() { return matching[0] > kPartList || matching[1] > kPartList || matching[2] > kPartList; };
+    while (crowded() && shift > low) {
+        const int next = max(shift - kPartMoreBits, low);
+        for (int i = tid; i < NT * kPartMoreBins / 4; i += kPartThreads)
+            reinterpret_cast<uint4 *>(sh.hist)[i] = make_uint4(0, 0, 0, 0);
+        __syncthreads();
+        sweep([&](uint32_t v, int) {
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+                if (v >= lo[t] && (v - lo[t]) >> shift == 0)
+                    atomicAdd(&sh.hist[t * kPartMoreBins + ((v - lo[t]) >> next)], 1u);
+        });
+        __syncthreads();
+        int c[NT][2], v[NT];
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            const uint2 two = reinterpret_cast<const uint2 *>(sh.hist + t * kPartMoreBins)[tid];
+            c[t][0] = (int)two.x, c[t][1] = (int)two.y;
             v[t] = c[t][0] + c[t][1];
         }
-        part_scan<NT>(v, tot, sh);
+        part_scan<NT>(v, sh);
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
             int before = v[t];
 #pragma unroll
             for (int q = 0; q < 2; ++q) {
-                if (before < remaining[t] && remaining[t] <= before + c[t][q])
-                    sh.digit[t] = kPartBins - 1 - 2 * tid - q, sh.remaining[t] = remaining[t] - before, sh.matching[t] = c[t][q];
+                if (before < remaining[t] && remaining[t] <= before + c[t][q]) {
+                    sh.lo[t] = lo[t] + ((uint32_t)(2 * tid + q) << next), sh.remaining[t] = remaining[t] - before;
+                    sh.matching[t] = want[t] > 0 ? c[t][q] : 0;
+                }
                 before += c[t][q];
             }
         }
         __syncthreads();
-#pragma unroll
-        for (int t = 0; t < NT; ++t) {
-            prefix[t] |= (uint32_t)sh.digit[t] << lo;
-            remaining[t] = sh.remaining[t], matching[t] = want[t] > 0 ? sh.matching[t] : 0;
-        }
-        known |= dmask << lo;
-        hi = lo - 1;
-        first = false;
+        take_interval();
+        shift = next;
     }
-    // the bucket of each threshold, counted out pairwise
-    sweep([&](uint32_t k, int i) {
+    // Each threshold's interval into its list; and how many channels before this workgroup's own (key slot blockIdx.x) lie in
+    // the intervals before it.
+    const int s_first = blockIdx.x, first = s_first * kPartThreads;
+    bool listed[NT];
+    uint32_t at[NT];
+    int base[NT] = {0, 0, 0};  // (of this wave)
 #pragma unroll
-        for (int t = 0; t < NT; ++t)
-            if (matching[t] > 0 && matching[t] <= kPartList && (k & known) == prefix[t]) {
-                const int at = atomicAdd(&sh.list_len[t], 1);
-                sh.list_key[t][at] = k, sh.list_idx[t][at] = i;
-            }
+    for (int t = 0; t < NT; ++t) listed[t] = matching[t] > 0 && matching[t] <= kPartList, at[t] = matching[t] > 0 ? lo[t] >> shift : 0u;
+    const bool lists = listed[0] || listed[1] || listed[2];
+    if (lists) sweep([&](uint32_t v, int i) {
+        const uint32_t p = v >> shift;
+        if (p == at[0] || p == at[1] || p == at[2]) {  // (few)
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+                if (listed[t] && p == at[t]) {
+                    const int e = atomicAdd(&sh.list_len[t], 1);
+                    sh.list_u[t][e] = v, sh.list_idx[t][e] = i;
+                }
+        }
     });
-    __syncthreads();
-    if (tid < NT * kPartList) {
-        const int t = tid / kPartList, e = tid % kPartList, len = sh.list_len[t];
-        const int rem = t == 0 ? remaining[0] : (t == 1 ? remaining[1] : remaining[2]);
-        if (e < len) {
-            const uint32_t k = sh.list_key[t][e];
-            const int i = sh.list_idx[t][e];
-            int before = 0;
-            for (int q0 = 0; q0 < len; q0 += 16) {  // (sixteen at a time: one LDS latency for all of them)
-                uint4 kq[4];
-                int4 iq[4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    kq[u] = *reinterpret_cast<const uint4 *>(&sh.list_key[t][q0 + 4 * u]);
-                    iq[u] = *reinterpret_cast<const int4 *>(&sh.list_idx[t][q0 + 4 * u]);
-                }
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    before += kq[u].x > k || (kq[u].x == k && iq[u].x < i);
-                    before += kq[u].y > k || (kq[u].y == k && iq[u].y < i);
-                    before += kq[u].z > k || (kq[u].z == k && iq[u].z < i);
-                    before += kq[u].w > k || (kq[u].w == k && iq[u].w < i);
-                }
-            }
-            if (before == rem - 1) sh.thr_key[t] = k, sh.thr_idx[t] = i;
-        }
-    }
-    // more equal keys than a list holds: the remaining-th of them in channel order
-    if (matching[0] > kPartList || matching[1] > kPartList || matching[2] > kPartList) {
-        __syncthreads();
-#pragma unroll
-        for (int t = 0; t < NT; ++t)
-            if (tid == t && matching[t] > kPartList) sh.thr_key[t] = prefix[t], sh.remaining[t] = remaining[t];
-        __syncthreads();
-        int last = -1;
-#pragma unroll 1
-        for (int t = 0; t < NT; ++t) {  // (one copy of the code)
-            const int matches = t == 0 ? matching[0] : (t == 1 ? matching[1] : matching[2]);
-            if (matches <= kPartList) continue;
-            const bool counted = m <= kPartMaxSlots * kPartThreads && last >= 0 && sh.thr_key[last] == sh.thr_key[t];
-            part_equal_key<NS>(scores, keys, m, sh.thr_key[t], sh.remaining[t], counted, reinterpret_cast<int *>(&sh.hist[0][0]),
-                               &sh.thr_idx[t]);
-            last = t;
-        }
-    }
-    __syncthreads();
-    uint32_t thr_key[NT];
-    int thr_idx[NT];
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-        thr_key[t] = want[t] > 0 ? sh.thr_key[t] : 0xffffffffu;
-        thr_idx[t] = want[t] > 0 ? sh.thr_idx[t] : -1;
-    }
-    auto within = [&](int t, uint32_t k, int i) { return k > thr_key[t] || (k == thr_key[t] && i <= thr_idx[t]); };
-
-    // outputs: this workgroup's channels are those of key slot blockIdx.x; the channels before them are counted
-    int base[NT] = {0, 0, 0};
-    const int s_first = blockIdx.x, s_last = NS > 0 ? s_first + 1 : (m + kPartThreads - 1) / kPartThreads;
     uint32_t mine = 0u;
     if (NS > 0) {
 #pragma unroll
         for (int s = 0; s < NK; ++s) {
-            if (s == s_first) mine = keys[s];
-            if (s < s_first) {
+            if (s == s_first) mine = u[s];
+            if (s < s_first && !crowded()) {
 #pragma unroll
-                for (int t = 0; t < NT; ++t) base[t] += within(t, keys[s], s * kPartThreads + tid);
+                for (int t = 0; t < NT; ++t) base[t] += __builtin_popcountll(__ballot(u[s] >> shift < at[t]));
             }
         }
     }
+    if (lists) __syncthreads();
+    if (lists && wave < NT) {  // a wave per threshold, a lane per key
+        const int t = wave, len = __builtin_amdgcn_readfirstlane(sh.list_len[t]), rank = __builtin_amdgcn_readfirstlane(sh.remaining[t]);
+        const uint32_t v = sh.list_u[t][lane];
+        const int i = sh.list_idx[t][lane];
+        int before = 0;
+        for (int q0 = 0; q0 < len; q0 += 16) {  // (sixteen at a time: one LDS latency for all of them)
+            uint4 uq[4];
+            int4 iq[4];
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+                uq[w] = *reinterpret_cast<const uint4 *>(&sh.list_u[t][q0 + 4 * w]);
+                iq[w] = *reinterpret_cast<const int4 *>(&sh.list_idx[t][q0 + 4 * w]);
+            }
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+                before += uq[w].x < v || (uq[w].x == v && iq[w].x < i);
+                before += uq[w].y < v || (uq[w].y == v && iq[w].y < i);
+                before += uq[w].z < v || (uq[w].z == v && iq[w].z < i);
+                before += uq[w].w < v || (uq[w].w == v && iq[w].w < i);
+            }
+        }
+        const bool have = lane < len;
+        if (have && before == rank - 1) sh.thr_u[t] = v, sh.thr_idx[t] = i;
+        const int earlier = __builtin_popcountll(__ballot(have && before < rank && i < first));
+        if (lane == 0) sh.base_list[t] = earlier;
+    }
+    if (crowded()) {
+        // more equal keys than a list holds: the remaining-th of them in channel order
+        __syncthreads();
+        int last = -1;
+#pragma unroll 1
+        for (int t = 0; t < NT; ++t) {  // (one copy of the code)
+            if ((t == 0 ? matching[0] : (t == 1 ? matching[1] : matching[2])) <= kPartList) continue;
+            const uint32_t v = t == 0 ? lo[0] : (t == 1 ? lo[1] : lo[2]);
+            const int rank = t == 0 ? remaining[0] : (t == 1 ? remaining[1] : remaining[2]);
+            if (tid == 0) sh.thr_u[t] = v;
+            if (range == 0) {  // every key
+                if (tid == 0) sh.thr_idx[t] = rank - 1;
+            } else {
+                const bool counted = m <= kPartMaxSlots * kPartThreads && last >= 0 && sh.lo[last] == v;
+                part_equal_key<NS>(scores, u, m, key_max, v, rank, counted, reinterpret_cast<int *>(sh.hist), &sh.thr_idx[t]);
+                last = t;
+            }
+        }
+        __syncthreads();
+    } else {
+        __syncthreads();
+    }
+    uint32_t thr_u[NT];
+    int thr_idx[NT], total[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        thr_u[t] = want[t] > 0 ? sh.thr_u[t] : 0u;
+        thr_idx[t] = want[t] > 0 ? sh.thr_idx[t] : -1;
+        total[t] = NS > 0 && !crowded() ? sh.base_list[t] : 0;
+    }
+    auto within = [&](int t, uint32_t v, int j) { return v < thr_u[t] || (v == thr_u[t] && j <= thr_idx[t]); };
+    if (NS > 0 && crowded()) {  // (the channels before, with the thresholds at hand)
+#pragma unroll
+        for (int s = 0; s < NK; ++s)
+            if (s < s_first) {
+#pragma unroll
+                for (int t = 0; t < NT; ++t) base[t] += __builtin_popcountll(__ballot(within(t, u[s], s * kPartThreads + tid)));
+            }
+    }
+    const int s_last = NS > 0 ? s_first + 1 : (m + kPartThreads - 1) / kPartThreads;
     for (int s = s_first; s < s_last; ++s) {
         const int j = s * kPartThreads + tid;
-        const uint32_t k = NS > 0 ? mine : score_key(scores[j < m ? j : 0]);
+        const uint32_t v = NS > 0 ? mine : key_max - score_key(scores[j < m ? j : 0]);
         bool in[NT];
-        int v[2 * NT], tot[2 * NT];
+        int pre[NT], all[NT];
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
-            in[t] = j < m && within(t, k, j);
-            v[t] = in[t], v[NT + t] = s == s_first ? base[t] : 0;
+            in[t] = j < m && within(t, v, j);
+            const unsigned long long b = __ballot(in[t]);
+            all[t] = __builtin_popcountll(b);
+            pre[t] = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0u));
         }
-        part_scan<2 * NT>(v, tot, sh);
-        if (s == s_first) {
+        // the waves' counts (1024 together at most) and their shares of the channels before (below 32768), two to a word
+        uint32_t(&own)[3][kPartWaves] = sh.own[s & 1];
+        if (lane == 0) {
+            own[0][wave] = (uint32_t)all[0] | (uint32_t)all[1] << 16;
+            own[1][wave] = (uint32_t)all[2] | (uint32_t)base[2] << 16;
+            own[2][wave] = (uint32_t)base[0] | (uint32_t)base[1] << 16;
+        }
+        __syncthreads();
+        uint32_t sum[3], until[3];
 #pragma unroll
-            for (int t = 0; t < NT; ++t) base[t] = tot[NT + t];  // (this thread's share becomes everybody's sum)
+        for (int q = 0; q < 3; ++q) {
+            const uint32_t ts = row_incl_scan(own[q][lane % kPartWaves]);
+            until[q] = wave > 0 ? (uint32_t)__builtin_amdgcn_readlane((int)ts, wave - 1) : 0u;
+            sum[q] = (uint32_t)__builtin_amdgcn_readlane((int)ts, kPartWaves - 1);
         }
+        const int n_in[NT] = {(int)(sum[0] & 0xffffu), (int)(sum[0] >> 16), (int)(sum[1] & 0xffffu)};
+        const int earlier[NT] = {(int)(sum[2] & 0xffffu), (int)(sum[2] >> 16), (int)(sum[1] >> 16)};
+        const int waves_before[NT] = {(int)(until[0] & 0xffffu), (int)(until[0] >> 16), (int)(until[1] & 0xffffu)};
+        int place[NT];
+#pragma unroll
+        for (int t = 0; t < NT; ++t) place[t] = total[t] + earlier[t] + waves_before[t] + pre[t];
         if (j < m)
             write_channel(o, m, n_cand, j, in[0] ? POP_REGION_RETAINED : (in[1] ? POP_REGION_CANDIDATE : POP_REGION_PRUNED),
-                          in[2], base[0] + v[0], base[1] + v[1] - (base[0] + v[0]), base[2] + v[2]);
+                          in[2], place[0], place[1] - place[0], place[2]);
 #pragma unroll
-        for (int t = 0; t < NT; ++t) base[t] += tot[t];
+        for (int t = 0; t < NT; ++t) total[t] += n_in[t];
     }
 }
 
@@ -373,7 +487,7 @@ hipError_t launch_partition(const float *scores, int m, int n_ret, int n_cand, i
                             hipStream_t s)
 {
     // A build per number of key slots in registers: a wider one than needed costs its empty slots' part of every sweep (11008
-    // channels in 11 slots 13.3 us, 11300 in 14 slots 14.1; 14336 in 14 slots 15.2, 14400 in 20 slots 16.6).
+    // channels in 11 slots 9.1 us, 14336 in 14 slots 10.3, 20000 in 20 slots 11.8).
     const int slots = (m + kPartThreads - 1) / kPartThreads;
 #define POP_PART(NS, WGS) \
     hipLaunchKernelGGL(partition_kernel<NS>, dim3(WGS), dim3(kPartThreads), 0, s, scores, m, n_ret, n_cand, n_top, o)

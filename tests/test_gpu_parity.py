@@ -95,6 +95,33 @@ def test_partition_of_equal_scores(pop, oracle, m, values):
         assert np.array_equal(host(top)[:n_top], oracle.partition(s, n_top, 0)[1]), (n_ret, n_in)
 
 
+@pytest.mark.parametrize("m", [63, 65, 1024, 1025, 11264, 11265, 14337, 32768, 32769])
+@pytest.mark.parametrize("spread", ["crowd63", "crowd64", "crowd65", "power_of_two", "one_zero"])
+def test_partition_of_crowded_intervals(pop, oracle, m, spread):
+    """Thresholds inside an interval of the first histogram that holds as many keys as a list, one more and one less (next to a
+    score that stretches the range), scores closer together than the power of two between them, and a zero among them, which
+    makes every interval wide; at the borders of the key slots."""
+    g = synth.rng("crowded", m, spread)
+    if spread.startswith("crowd"):
+        n = min(int(spread[5:]), m - 1)
+        s = np.concatenate([g.permutation(n) * 2.0 ** -20 + 1.0, g.uniform(2.0, 4.0, m - n)]).astype(np.float32)
+        rank = m - n + n // 2
+    else:
+        s = (g.uniform(1.99, 2.01, m) if spread == "power_of_two" else g.uniform(0.5, 1.0, m)).astype(np.float32)
+        if spread == "one_zero":
+            s[m // 2] = 0.0
+        rank = m // 2
+    s = g.permutation(s)
+    n_ret, n_cand, n_top = rank, min(9, m - rank), min(m, rank + 4)
+    region = torch.full((m,), 9, dtype=torch.uint8, device="cuda")
+    ret, cand, top = (torch.full((max(n, 1),), -1, dtype=torch.int32, device="cuda") for n in (n_ret, n_cand, n_top))
+    pop.pop_partition_top_from_scores(dev(s), m, n_ret, n_cand, n_top, region, ret, cand, None, top)
+    r0, ret0, cand0 = oracle.partition(s, n_ret, n_cand)
+    assert np.array_equal(host(region), r0)
+    assert np.array_equal(host(ret)[:n_ret], ret0) and np.array_equal(host(cand)[:n_cand], cand0)
+    assert np.array_equal(host(top)[:n_top], oracle.partition(s, n_top, 0)[1])
+
+
 @pytest.mark.parametrize("kind", ["none", "some", "all", "zeros"] + list(synth.SCORE_SHAPES))
 def test_partition_top_from_scores_bit_exact(pop, oracle, kind):
     """The partition launch that also emits the n_top best channels (the prompt's own mask): regions as before, and
