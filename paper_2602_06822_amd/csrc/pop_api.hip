@@ -43,7 +43,7 @@ unsigned long long *g_trace = nullptr;  // profiling builds: device buffer the f
 
 struct pop_layer {
     int d = 0, m = 0, esize = 0, is_bf16 = 0, max_tokens = 0, max_batch = 0;
-    void *w = nullptr;     // [m][3][d]: gate row, up row, down column of each channel
+    void *w = nullptr;     // gate row, up row, down column of each channel, channel_vectors() apart
     float *nrm = nullptr;  // [m]
     int n_cu = 0, wg_target = 0;
     bool shared_mask = false;    // B > 1: one selection for the batch from scores aggregated over its sequences
@@ -420,7 +420,7 @@ int pop_layer_create(pop_layer_t **out, int d, int m, pop_dtype_t wdtype, const 
     if (partial_rows < skinny_rows) partial_rows = skinny_rows;
     struct Req { void **p; size_t bytes; };
     Req reqs[] = {
-        {&L->w, mm * 3 * d * esize},
+        {&L->w, mm * channel_vectors(d * esize / 16, is_bf16) * 16},
         {(void **)&L->nrm, mm * 4},
         {(void **)&L->scores, mm * 4},
         {(void **)&L->s2_part, (size_t)L->tiles_cap * mm * 4},
@@ -847,7 +847,7 @@ int pop_probe_step_read(pop_layer_t *L, int k, int workgroups, unsigned int *sin
     if (!L->has_partition) return POP_ESTATE;
     if (k < 0 || k > L->n_cand || workgroups < 1 || workgroups > 65535) return POP_ESHAPE;
     if (L->n_ret + L->n_cand == 0) return POP_OK;
-    POP_HIP(launch_probe_step_read(L->w, L->d / (L->is_bf16 ? 8 : 4), L->rc_idx, L->n_ret + L->n_cand, L->ret_idx,
+    POP_HIP(launch_probe_step_read(L->w, L->d / (L->is_bf16 ? 8 : 4), channel_vectors(L->d / (L->is_bf16 ? 8 : 4), L->is_bf16), L->rc_idx, L->n_ret + L->n_cand, L->ret_idx,
                                    L->n_ret, L->cand_idx, k, workgroups, sink, as_stream(stream)));
     return POP_OK;
 }

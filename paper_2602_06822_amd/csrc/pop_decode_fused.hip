@@ -202,7 +202,9 @@ __device__ __forceinline__ double sq_dot(const float4 &g, const float4 &u, const
     return acc;
 }
 
-template <class V, int PER, int MAXB>
+// GAP: the layer's channels are channel_gap() apart (a build of its own: with the gap worked out at run time, steps of layers
+// without one took 4 % longer at d 2048).
+template <class V, int PER, int MAXB, bool GAP>
 __global__ __launch_bounds__(MAXB) void decode_fused_kernel(FusedParams p)
 {
     typedef typename V::vec_t vec_t;
@@ -226,6 +228,7 @@ __global__ __launch_bounds__(MAXB) void decode_fused_kernel(FusedParams p)
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int b = blockIdx.x, n_wg = gridDim.x, n_workers = n_wg - 1, wb = b - 1;
     const int nvec = p.nvec;
+    constexpr uint32_t gap = GAP ? channel_gap(0, 1) : 0;
     const vec_t *w = reinterpret_cast<const vec_t *>(p.w);
     unsigned long long *const my_word = p.selw + (size_t)b * kSelStride;
     const int epoch = coherent_load(&p.ctr[0]);  // the tag of everything handed over in this step
@@ -332,9 +335,9 @@ __global__ __launch_bounds__(MAXB) void decode_fused_kernel(FusedParams p)
             work = true;
         }
 #pragma unroll
-        for (int t = 0; t < kRB; ++t) ds.boff[t] = (uint32_t)max(ds.jb[t], 0) * 3u * (uint32_t)nvec;
+        for (int t = 0; t < kRB; ++t) ds.boff[t] = (uint32_t)max(ds.jb[t], 0) * (3u * (uint32_t)nvec + gap);
 #pragma unroll
-        for (int a = 0; a < kXL; ++a) ds.xoff[a] = (uint32_t)max(ds.xrow[a], 0) * (uint32_t)nvec;
+        for (int a = 0; a < kXL; ++a) ds.xoff[a] = (uint32_t)max(ds.xrow[a], 0) * (uint32_t)nvec + (uint32_t)max(ds.xrow[a], 0) / 3u * gap;
         ds.work = work;
     };
 
@@ -553,7 +556,7 @@ __global__ __launch_bounds__(MAXB) void decode_fused_kernel(FusedParams p)
                 if (rem_d) {
                     sl[a] = __builtin_ctz(rem_d);
                     rem_d &= rem_d - 1;
-                    off[a] = ((uint32_t)uniform(j_a[sl[a]]) * 3u + 2u) * (uint32_t)nvec;
+                    off[a] = ((uint32_t)uniform(j_a[sl[a]]) * 3u + 2u) * (uint32_t)nvec + (uint32_t)uniform(j_a[sl[a]]) * gap;
                 }
             }
 #pragma unroll
@@ -746,49 +749,51 @@ __global__ __launch_bounds__(1024) void decode_tail_kernel(const float *__restri
 // ---------------------------------------------------------------- host side
 // The kernel is built for two workgroup size limits: up to 512 threads (twice the registers per thread, enough for
 // two vector columns per thread without spilling) and up to 1024.
-template <class V, int PER, int MAXB>
+template <class V, int PER, int MAXB, bool GAP>
 static hipError_t fused_launch(const FusedPlan &pl, FusedParams &p, hipStream_t s)
 {
-    hipLaunchKernelGGL((decode_fused_kernel<V, PER, MAXB>), dim3(pl.n_wg), dim3(pl.block), 0, s, p);
+    hipLaunchKernelGGL((decode_fused_kernel<V, PER, MAXB, GAP>), dim3(pl.n_wg), dim3(pl.block), 0, s, p);
     return hipGetLastError();
 }
 
-template <class V, int PER, int MAXB>
+template <class V, int PER, int MAXB, bool GAP>
 static hipError_t fused_occupancy(int block, int *blocks_per_cu)
 {
-    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, decode_fused_kernel<V, PER, MAXB>, block, 0);
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, decode_fused_kernel<V, PER, MAXB, GAP>, block, 0);
 }
 
-// Calls fn.template operator()<V, PER, MAXB>() for the plan's variant.
-template <class Fn>
-static hipError_t fused_dispatch(int is_bf16, int per, int block, Fn fn)
+// Calls fn.template operator()<V, PER, MAXB, GAP>() for the plan's variant.
+template <class V, bool GAP, class Fn>
+static hipError_t fused_dispatch_shape(const FusedPlan &pl, Fn fn)
 {
-    const bool small = block <= 512;
-    if (is_bf16) {
-        if (per == 1) return small ? fn.template operator()<VecBF16, 1, 512>() : fn.template operator()<VecBF16, 1, 1024>();
-        return small ? fn.template operator()<VecBF16, 2, 512>() : fn.template operator()<VecBF16, 2, 1024>();
-    }
-    if (per == 1) return small ? fn.template operator()<VecF32, 1, 512>() : fn.template operator()<VecF32, 1, 1024>();
-    return small ? fn.template operator()<VecF32, 2, 512>() : fn.template operator()<VecF32, 2, 1024>();
+    const bool small = pl.block <= 512;
+    if (pl.per == 1) return small ? fn.template operator()<V, 1, 512, GAP>() : fn.template operator()<V, 1, 1024, GAP>();
+    return small ? fn.template operator()<V, 2, 512, GAP>() : fn.template operator()<V, 2, 1024, GAP>();
+}
+template <class Fn>
+static hipError_t fused_dispatch(int is_bf16, const FusedPlan &pl, Fn fn)
+{
+    if (!is_bf16) return fused_dispatch_shape<VecF32, false>(pl, fn);
+    return pl.gap ? fused_dispatch_shape<VecBF16, true>(pl, fn) : fused_dispatch_shape<VecBF16, false>(pl, fn);
 }
 
 struct FusedOccupancyFn {
     int block;
     int *blocks_per_cu;
-    template <class V, int PER, int MAXB>
+    template <class V, int PER, int MAXB, bool GAP>
     hipError_t operator()() const
     {
-        return fused_occupancy<V, PER, MAXB>(block, blocks_per_cu);
+        return fused_occupancy<V, PER, MAXB, GAP>(block, blocks_per_cu);
     }
 };
 struct FusedLaunchFn {
     const FusedPlan &pl;
     FusedParams &p;
     hipStream_t s;
-    template <class V, int PER, int MAXB>
+    template <class V, int PER, int MAXB, bool GAP>
     hipError_t operator()() const
     {
-        return fused_launch<V, PER, MAXB>(pl, p, s);
+        return fused_launch<V, PER, MAXB, GAP>(pl, p, s);
     }
 };
 
@@ -806,6 +811,7 @@ bool fused_plan(int d, int is_bf16, int n_ret, int n_cand, int wg_target, FusedP
         if (const char *e = getenv("POP_FUSED_PER")) per = atoi(e) == 1 ? 1 : 2;
     if (nvec > 2048) return false;
     pl->per = per;
+    pl->gap = channel_gap(nvec, is_bf16) != 0;
     pl->block = ((nvec + per * kWave - 1) / (per * kWave)) * kWave;
     const int rounds_total = (n_ret + kRB - 1) / kRB;
     int workers = rounds_total;
@@ -822,7 +828,7 @@ bool fused_plan(int d, int is_bf16, int n_ret, int n_cand, int wg_target, FusedP
 hipError_t fused_resident_limit(int is_bf16, const FusedPlan &pl, int n_cu, int *max_wg)
 {
     int per_cu = 0;
-    hipError_t e = fused_dispatch(is_bf16, pl.per, pl.block, FusedOccupancyFn{pl.block, &per_cu});
+    hipError_t e = fused_dispatch(is_bf16, pl, FusedOccupancyFn{pl.block, &per_cu});
     if (e != hipSuccess) return e;
     *max_wg = per_cu * n_cu;
     return hipSuccess;
@@ -831,7 +837,7 @@ hipError_t fused_resident_limit(int is_bf16, const FusedPlan &pl, int n_cu, int 
 hipError_t launch_decode_fused(const FusedPlan &pl, int is_bf16, FusedParams &p, hipStream_t s)
 {
     p.n_static = pl.n_static;
-    return fused_dispatch(is_bf16, pl.per, pl.block, FusedLaunchFn{pl, p, s});
+    return fused_dispatch(is_bf16, pl, FusedLaunchFn{pl, p, s});
 }
 
 hipError_t launch_decode_tail(const float *partial, int n_wg, int d, void *y, int y_bf16, hipStream_t s,

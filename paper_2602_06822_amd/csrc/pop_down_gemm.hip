@@ -94,7 +94,7 @@ __global__ __launch_bounds__(512) void down_gemm_bf16_kernel(const uint16_t *__r
 #pragma unroll
         for (int p = 0; p < 2; ++p) {
             const int j = chn[set][p] | chn_off[set][p];
-            rb[set][p] = *reinterpret_cast<const uint4 *>(w + ((size_t)max(j, 0) * 3 + 2) * d + n_col);
+            rb[set][p] = *reinterpret_cast<const uint4 *>(w + (size_t)max(j, 0) * channel_elems_bf16(d) + 2 * d + n_col);
             rb_on[set][p] = (j >= 0 && n_ok) ? 0xffffffffu : 0u;
         }
     };
@@ -314,7 +314,7 @@ __global__ __launch_bounds__(kDdThreads, 1) void down_gemm_dma_kernel(const uint
             // (selected with a mask: a conditional would put the load under a branch and make its wait inexact)
             const int ks = ks0 + step;
             const uintptr_t live = -(uintptr_t)(ks < ks1 && ks * kDgBK + b_row + p * 16 < a);
-            const uintptr_t p_row = (uintptr_t)(w + ((size_t)c * 3 + 2) * d + b_src);
+            const uintptr_t p_row = (uintptr_t)(w + (size_t)c * channel_elems_bf16(d) + 2 * d + b_src);
             const uintptr_t p_zero = (uintptr_t)(zero_row + (lane % 16) * 8);
             const uint16_t *row = (const uint16_t *)(p_zero ^ ((p_row ^ p_zero) & live));
             __builtin_amdgcn_global_load_lds((glb_t *)row, (lds_t *)(Bs + buf * BT + (p * 16 + wave * 4) * kDgBN), 16, 0, 0);

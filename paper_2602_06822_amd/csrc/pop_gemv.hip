@@ -32,8 +32,15 @@ __device__ __forceinline__ void gateup_row(const typename V::vec_t *__restrict__
     constexpr int U = B >= 5 ? kGuUnroll / 2 : kGuUnroll;
     const int group = kWave * U;
     const int nvec_full = nvec / group * group;
-    const vec_t *g = w + (size_t)j * 3 * nvec;
+    j = __builtin_amdgcn_readfirstlane(j);  // (one channel per wave)
+    const vec_t *g = w + (uint64_t)(uint32_t)j * (uint32_t)channel_vectors(nvec, V::kElems == 8);
     const vec_t *u = g + nvec;
+    // (few sequences: the rows' addresses as scalar registers, which the compiler otherwise spreads over vector ones: 13B shape,
+    // four sequences 123 -> 120.4 us for two layers; five and more are 2 % faster the other way)
+    if constexpr (B <= 4) {
+        asm("" : "+s"(g));
+        asm("" : "+s"(u));
+    }
     // Two 16-byte vectors' products (sixteen exact products for bf16 rows) are summed in the row's accumulator type,
     // the pairs of a lane and then the lanes in double: a long float32 chain would round every add at the magnitude
     // of the largest product met so far, and so would a float32 tree over the lanes.
@@ -59,6 +66,8 @@ __device__ __forceinline__ void gateup_row(const typename V::vec_t *__restrict__
             }
         }
     }
+    constexpr int kTailUnroll = B <= 4 ? 2 : 1;
+#pragma unroll kTailUnroll
     for (int c = nvec_full + lane; c < nvec; c += kWave) {
         vec_t wg = g[c], wu = u[c];
 #pragma unroll
@@ -356,6 +365,8 @@ __global__ __launch_bounds__(256) void down_kernel(const typename V::vec_t *__re
     const int n_slabs = gridDim.y, slab = blockIdx.y;
     const int col = blockIdx.x * kWave + lane;  // vector column
     const bool col_ok = col < nvec;
+    const uint32_t chan = channel_vectors(nvec, V::kElems == 8);
+    const vec_t *w_down = w + 2 * nvec + col;
     const int per_slab = (n + n_slabs - 1) / n_slabs;
     const int s0 = min(n, slab * per_slab), s1 = min(n, s0 + per_slab);
 
@@ -390,14 +401,14 @@ __global__ __launch_bounds__(256) void down_kernel(const typename V::vec_t *__re
             vec_t wv[kDownUnroll];
 #pragma unroll
             for (int q = 0; q < kDownUnroll; ++q)
-                wv[q] = col_ok ? w[((size_t)js[i + q] * 3 + 2) * nvec + col] : V::zero();
+                wv[q] = col_ok ? w_down[(uint64_t)(uint32_t)js[i + q] * chan] : V::zero();
 #pragma unroll
             for (int q = 0; q < kDownUnroll; ++q)
 #pragma unroll
                 for (int b = 0; b < B; ++b) V::axpy(hs[b][i + q], wv[q], acc[b]);
         }
         for (; i < r1; ++i) {
-            const vec_t wv1 = col_ok ? w[((size_t)js[i] * 3 + 2) * nvec + col] : V::zero();
+            const vec_t wv1 = col_ok ? w_down[(uint64_t)(uint32_t)js[i] * chan] : V::zero();
 #pragma unroll
             for (int b = 0; b < B; ++b) V::axpy(hs[b][i], wv1, acc[b]);
         }
@@ -571,7 +582,8 @@ __global__ __launch_bounds__(kSkThreads) void skinny_down_kernel(const uint4 *__
     const int s0 = min(n, (int)blockIdx.y * per_slab), s1 = min(n, s0 + per_slab);
     const int vcol = blockIdx.x * (kSkCols / 8) + c;  // this lane's vector column
     const bool col_ok = vcol < nvec;
-    const uint4 *wc = w + (col_ok ? vcol : 0);
+    const uint32_t chan = channel_vectors(nvec, 1);
+    const uint4 *wc = w + 2 * nvec + (col_ok ? vcol : 0);
 
     f32x4_t acc[TG][8];
 #pragma unroll
@@ -586,7 +598,7 @@ __global__ __launch_bounds__(kSkThreads) void skinny_down_kernel(const uint4 *__
     uint4 rows[2][8];
     auto request = [&](int set) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) rows[set][i] = wc[((size_t)js[set * kSkChunk + 32 * wave + 8 * g + i] * 3 + 2) * nvec];
+        for (int i = 0; i < 8; ++i) rows[set][i] = wc[(uint64_t)(uint32_t)js[set * kSkChunk + 32 * wave + 8 * g + i] * chan];
     };
     // h of the 256 channels at `at` as three planes; zero beyond the slab, beyond T and where a mask says so
     auto stage = [&](int set, int at) {
@@ -678,7 +690,7 @@ __global__ __launch_bounds__(kSkThreads) void skinny_down_kernel(const uint4 *__
                     for (int p = s0; p < s1; ++p) {
                         const int j = list[p];
                         const float hv = !kMask || mask[(size_t)tok * mask_stride + j] ? h[(size_t)tok * m + j] : 0.f;
-                        const uint16_t wv = reinterpret_cast<const uint16_t *>(w)[((size_t)j * 3 + 2) * d + col];
+                        const uint16_t wv = reinterpret_cast<const uint16_t *>(w)[(size_t)j * channel_elems_bf16(d) + 2 * d + col];
                         v = fmaf(hv, __uint_as_float((uint32_t)wv << 16), v);
                     }
                 }

@@ -114,7 +114,7 @@ __global__ __launch_bounds__(256) void input_side_scores_kernel(const typename V
     const int n_waves = gridDim.x * (blockDim.x / kWave);
     for (int p = blockIdx.x * (blockDim.x / kWave) + wave; p < n_rows; p += n_waves) {
         const int j = rows ? rows[p] : p;
-        const vec_t *g = w + (size_t)j * 3 * nvec;
+        const vec_t *g = w + (size_t)j * channel_vectors(nvec, V::kElems == 8);
         const vec_t *u = g + nvec;
         float a0 = 0.f, a1 = 0.f;
         for (int c = lane; c < nvec; c += kWave) {

@@ -32,6 +32,21 @@ __device__ __forceinline__ uint16_t f32_to_bf16(float f)
 
 __device__ __forceinline__ float silu_mul(float g, float u) { return g / (1.0f + expf(-g)) * u; }
 
+// 16-byte vectors between the weights of one channel [gate row | up row | down column] (nvec vectors each) and the next
+// channel's.  A 128-byte line on bf16 layers whose rows are a multiple of 8 KB: the contraction of a prompt, whose workgroups all
+// ask for the same columns of their rows at about the same time, otherwise keeps hitting the same few memory channels (d 4096,
+// weights from memory: 256 tokens, m 14336 95 -> 72 us, 512 tokens, m 11008 91 -> 77; two or three lines gain the same or
+// less).  None on other rows (13B shape, 10 KB: 333 tokens 67 -> 66 us), and none behind each row: the decode step reads a
+// channel's rows together and was 0.7 % slower with gaps between them.
+__host__ __device__ __forceinline__ constexpr int channel_gap(int nvec, int is_bf16) { return is_bf16 && nvec % 512 == 0 ? 8 : 0; }
+// From one channel's weights to the next's.
+__host__ __device__ __forceinline__ constexpr int channel_vectors(int nvec, int is_bf16)
+{
+    return 3 * nvec + channel_gap(nvec, is_bf16);
+}
+// The same in elements of a bf16 layer.
+__host__ __device__ __forceinline__ int channel_elems_bf16(int d) { return channel_vectors(d / 8, 1) * 8; }
+
 template <typename T>
 __device__ __forceinline__ T wave_sum(T v)
 {
@@ -232,6 +247,7 @@ struct FusedParams {
 struct FusedPlan {
     int n_wg, block, per;
     int n_static;  // retained rounds per worker
+    bool gap;      // the layer's channels are channel_gap() apart
 };
 int fused_max_workgroups();
 size_t fused_selw_words();  // 64-bit words of the selection-word buffer (one per workgroup, spaced apart)
@@ -246,7 +262,7 @@ hipError_t launch_fill_int(int *p, int n, int value, hipStream_t s);
 
 // ---- measurement aids (pop_probe.hip): bare reads, nothing of the method ----
 hipError_t launch_probe_read(const void *buf, size_t bytes, int workgroups, unsigned int *sink, hipStream_t s);
-hipError_t launch_probe_step_read(const void *w, int nvec, const int *gu_list, int n_gu, const int *dn_ret,
+hipError_t launch_probe_step_read(const void *w, int nvec, int chan, const int *gu_list, int n_gu, const int *dn_ret,
                                   int n_dn_ret, const int *dn_sel, int n_dn_sel, int workgroups, unsigned int *sink,
                                   hipStream_t s);
 

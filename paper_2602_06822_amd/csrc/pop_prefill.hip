@@ -211,7 +211,7 @@ __global__ __launch_bounds__(NW * 64) void prefill_bf16_kernel(const uint16_t *_
         pb[p] = nullptr;
         if (ch < cn) {
             const int j = kList ? st.list[c0 + ch] : c0 + ch;
-            pb[p] = w + ((size_t)j * 3 + which) * d;
+            pb[p] = w + (size_t)j * channel_elems_bf16(d) + which * d;
         }
     }
     auto load_global = [&](int k0) {
@@ -451,7 +451,7 @@ __device__ __forceinline__ void pm_tile(const uint16_t *__restrict__ w, const ui
         pm_row_channel<F>(ld_row + p * 32, ch, which);
         const int cc = min(ch, cn - 1);
         const int j = kList ? st.list[c0 + cc] : c0 + cc;
-        pb[p] = w + ((size_t)j * 3 + which) * d + src_kv;
+        pb[p] = w + (size_t)j * channel_elems_bf16(d) + which * d + src_kv;
     }
     const int n_k = d / kPfBK;
     // k-step s is columns kof(s) (steps beyond the last repeat it).  Sums in float32 take the columns in the same order in

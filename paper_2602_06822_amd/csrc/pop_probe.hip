@@ -30,27 +30,27 @@ __global__ __launch_bounds__(512) void probe_read_kernel(const uint4 *__restrict
     if (acc.x == 0x9e3779b9u) atomicOr(sink, 1u);  // (a value the compiler cannot rule out: keeps the loads alive)
 }
 
-// Gathered read of the rows of a decode step.  rows of w viewed as [3 m][nvec]: for list entry i < n_gu the gate row
+// Gathered read of the rows of a decode step.  channel j's rows of nvec vectors at j chan: for list entry i < n_gu the gate row
 // 3 j and the up row 3 j + 1 of channel j = gu_list[i]; for i < n_dn the down row 3 j + 2 of j = dn_list[i]
 // (i < n_dn_ret from dn_ret, the rest from dn_sel).  A workgroup takes whole rows (its threads cover the row's
 // vectors), kProbeInFlight rows at a time, the rows dealt round robin over the workgroups.
-__global__ __launch_bounds__(512) void probe_step_read_kernel(const uint4 *__restrict__ w, int nvec,
+__global__ __launch_bounds__(512) void probe_step_read_kernel(const uint4 *__restrict__ w, int nvec, int chan,
                                                               const int *__restrict__ gu_list, int n_gu,
                                                               const int *__restrict__ dn_ret, int n_dn_ret,
                                                               const int *__restrict__ dn_sel, int n_dn_sel,
                                                               unsigned int *__restrict__ sink)
 {
     const int n_rows = 2 * n_gu + n_dn_ret + n_dn_sel;
-    auto row_of = [&](int r) -> size_t {  // r-th row of the step -> row number in w
-        if (r < 2 * n_gu) return (size_t)gu_list[r >> 1] * 3 + (r & 1);
+    auto row_of = [&](int r) -> size_t {  // r-th row of the step -> its place in w
+        if (r < 2 * n_gu) return (size_t)gu_list[r >> 1] * chan + (r & 1) * nvec;
         r -= 2 * n_gu;
-        return (size_t)(r < n_dn_ret ? dn_ret[r] : dn_sel[r - n_dn_ret]) * 3 + 2;
+        return (size_t)(r < n_dn_ret ? dn_ret[r] : dn_sel[r - n_dn_ret]) * chan + 2 * nvec;
     };
     unsigned int acc = 0;
     for (int r0 = blockIdx.x * kProbeInFlight; r0 < n_rows; r0 += gridDim.x * kProbeInFlight) {
         size_t off[kProbeInFlight];
 #pragma unroll
-        for (int u = 0; u < kProbeInFlight; ++u) off[u] = row_of(min(r0 + u, n_rows - 1)) * (size_t)nvec;
+        for (int u = 0; u < kProbeInFlight; ++u) off[u] = row_of(min(r0 + u, n_rows - 1));
         for (int c = threadIdx.x; c < nvec; c += blockDim.x) {
             uint4 v[kProbeInFlight];
 #pragma unroll
@@ -69,11 +69,11 @@ hipError_t launch_probe_read(const void *buf, size_t bytes, int workgroups, unsi
     return hipGetLastError();
 }
 
-hipError_t launch_probe_step_read(const void *w, int nvec, const int *gu_list, int n_gu, const int *dn_ret,
+hipError_t launch_probe_step_read(const void *w, int nvec, int chan, const int *gu_list, int n_gu, const int *dn_ret,
                                   int n_dn_ret, const int *dn_sel, int n_dn_sel, int workgroups, unsigned int *sink,
                                   hipStream_t s)
 {
-    hipLaunchKernelGGL(probe_step_read_kernel, dim3(workgroups), dim3(512), 0, s, (const uint4 *)w, nvec, gu_list,
+    hipLaunchKernelGGL(probe_step_read_kernel, dim3(workgroups), dim3(512), 0, s, (const uint4 *)w, nvec, chan, gu_list,
                        n_gu, dn_ret, n_dn_ret, dn_sel, n_dn_sel, sink);
     return hipGetLastError();
 }

@@ -527,6 +527,29 @@ def _check_prefill_forward(oracle, G, L, x, n_ret, n_cand, k0, ydtype, y_tol, ro
     return scores, region, ret, cand
 
 
+@pytest.mark.parametrize("d", [4032, 4096, 4160, 8192])
+def test_rows_with_and_without_a_gap_between_channels(pop, oracle, d):
+    """Layers whose rows are a multiple of 8 KB keep their channels a line further apart: every kernel that reads weights, on
+    such layers and on ones whose rows are a k-step shorter and longer."""
+    m = 150
+    L = synth.make_layer(synth.small_config(f"gap_{d}", d, m, BF16, n_outlier=3, heavy_tail=True))
+    n_ret, n_cand = 70, 40
+    with GpuLayer(pop, L, max_tokens=70, max_batch=8) as G:
+        np.testing.assert_allclose(G.norms(), oracle.down_norms(L.w_down, BF16), rtol=2e-7)
+        for T in (5, 70):
+            x = synth.make_activations(L, T, "prompt")
+            _check_prefill_forward(oracle, G, L, x, n_ret, n_cand, 20, BF16, Y_TOL[BF16])
+            _, region, _, cand, _ = _check_prefill(oracle, G, L, x, n_ret, n_cand)
+            mask = np.stack([np.roll(region != 2, t) for t in range(T)]).astype(np.uint8)
+            h = oracle.hidden(x, L.w_gate, L.w_up, BF16)
+            for mk in (mask[0], mask):
+                y = G.ffn(x, mk, F32)
+                y_ref = oracle.down(h, L.w_down, BF16, np.broadcast_to(mk, (T, m)))
+                assert max_abs_rel(y, y_ref) <= 4e-3
+        for B in (1, 2, 3, 8):
+            _check_decode(oracle, G, L, region, cand, synth.make_activations(L, B, "decode"), 20, F32)
+
+
 @pytest.mark.parametrize("dtype,T", [(F32, 40), (BF16, 20), (BF16, 150), (BF16, 290)])
 def test_prefill_forward_small(pop, oracle, dtype, T):
     """Partition + pruned output of the prompt in one call: float32 and short prompts (H in float32), bf16
