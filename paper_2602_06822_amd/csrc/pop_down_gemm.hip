@@ -224,10 +224,12 @@ __global__ __launch_bounds__(512) void down_gemm_bf16_kernel(const uint16_t *__r
 // pointed at a row of zeros (zero_row, 256 bytes), which makes it irrelevant what the Hc columns beyond a hold, as long as
 // it is finite (the buffer is cleared when it is allocated and only ever holds H values).  Needs d % 128 == 0 and
 // ldh >= a rounded up to 64.
-// Dispatch times inside a prompt's forward call (in parentheses the kernel of eight waves, 256-token tiles and 32x32x16
-// products it replaced): d 4096, 9318 channels, 270 tokens 40.0 us (50.8); 13B shape, 6912 channels, 333 tokens 45.4 (46.7);
-// d 4096, 7155 channels, 512 tokens 45.5 (39.3), 2048 tokens 140.6 (126.4): where 256-token tiles come out even, eight waves
-// with half the columns each were the better form.
+// What bounds it: the loads into LDS, which deliver 32 bytes a cycle and compute unit at any depth (70 bytes/ns measured with nothing
+// else running): 48 KB a k-step at MF = 4 are 0.70 us, the whole loop without its products takes 0.77 and with them 1.2-1.3.
+// With one wave per SIMD, whatever does not fit between two products (12 cycles) comes on top, so the permutes of a fragment
+// stand between the products of the one before it and a weight row's address is one multiply-add (both in a bunch in front of their use
+// before): 333 tokens at the 13B shape 42.7 -> 40.5 us, 2048 tokens at d 4096 169 -> 159 (under the kernel trace), 256 tokens 33.6 -> 32.8,
+// of which 8-15 us are the start, the first rows and the partials' way out.
 constexpr int kDdThreads = 256;
 constexpr int kDdMaxMF = 5;
 constexpr int kDdSlots = 8;  // k-steps whose channel numbers are kept
@@ -286,10 +288,13 @@ __global__ __launch_bounds__(kDdThreads, 1) void down_gemm_dma_kernel(const uint
         // position lane % 8 of its row.  Weights: pass p covers rows 16 p + 4 w + lane / 16, unit lane % 16.
         const int a_row = wave * 8 + lane / 8;
         const int a_src = ((lane % 8) ^ ((a_row / 2) % 8)) * 8;  // (passes are 32 rows apart: same swizzle term)
-        const uint16_t *pa[PA];
+        const uint16_t *hc_tile = hc + (size_t)t0 * ldh;
+        uint32_t a_off[PA];  // bytes from the tile's first row
 #pragma unroll
-        for (int p = 0; p < PA; ++p) pa[p] = hc + (size_t)min(t0 + a_row + p * 32, T - 1) * ldh + a_src;
-        const int b_row = wave * 4 + lane / 16, b_src = n0 + (lane % 16) * 8;
+        for (int p = 0; p < PA; ++p) a_off[p] = 2 * ((uint32_t)(min(t0 + a_row + p * 32, T - 1) - t0) * (uint32_t)ldh + a_src);
+        const int b_row = wave * 4 + lane / 16;
+        const uintptr_t b_col = (uintptr_t)(w + 2 * d + n0 + (lane % 16) * 8), b_zero = (uintptr_t)(zero_row + (lane % 16) * 8);
+        const uint32_t b_stride = (uint32_t)(channel_elems_bf16(d) * sizeof(uint16_t));
         // Channel numbers of a k-step: one direct load of 64 of them into slot step % 8 of a small ring, two steps before
         // they are needed (every wave loads the same, so that its own waits cover it).
         auto load_channels = [&](int step) {
@@ -307,17 +312,17 @@ __global__ __launch_bounds__(kDdThreads, 1) void down_gemm_dma_kernel(const uint
                          : "memory");
         };
         auto load_a = [&](int p, int buf, int step) {
-            __builtin_amdgcn_global_load_lds((glb_t *)(pa[p] + min(ks0 + step, ks1 - 1) * kDgBK),
-                                             (lds_t *)(As + buf * AT + (p * 32 + wave * 8) * kDgBK), 16, 0, 0);
+            const char *k = (const char *)(hc_tile + min(ks0 + step, ks1 - 1) * kDgBK);
+            __builtin_amdgcn_global_load_lds((glb_t *)(k + a_off[p]), (lds_t *)(As + buf * AT + (p * 32 + wave * 8) * kDgBK), 16, 0, 0);
         };
+        // (the row is selected with a mask: a conditional would put the load under a branch and make its wait inexact; one 64-bit
+        // multiply-add for the address: what does not fit between two products is time lost)
         auto load_b = [&](int c, int p, int buf, int step) {
-            // (selected with a mask: a conditional would put the load under a branch and make its wait inexact)
-            const int ks = ks0 + step;
-            const uintptr_t live = -(uintptr_t)(ks < ks1 && ks * kDgBK + b_row + p * 16 < a);
-            const uintptr_t p_row = (uintptr_t)(w + (size_t)c * channel_elems_bf16(d) + 2 * d + b_src);
-            const uintptr_t p_zero = (uintptr_t)(zero_row + (lane % 16) * 8);
-            const uint16_t *row = (const uint16_t *)(p_zero ^ ((p_row ^ p_zero) & live));
-            __builtin_amdgcn_global_load_lds((glb_t *)row, (lds_t *)(Bs + buf * BT + (p * 16 + wave * 4) * kDgBN), 16, 0, 0);
+            const int ks = ks0 + step, n_live = ks < ks1 ? a - ks * kDgBK - p * 16 : 0;
+            const uintptr_t live = -(uintptr_t)(b_row < n_live);
+            const uintptr_t row = b_col + (uint64_t)(uint32_t)c * b_stride;
+            __builtin_amdgcn_global_load_lds((glb_t *)(b_zero ^ ((row ^ b_zero) & live)),
+                                             (lds_t *)(Bs + buf * BT + (p * 16 + wave * 4) * kDgBN), 16, 0, 0);
         };
         // Fragment reads.  A: row lane % 16 of the token fragment, unit 4 q + lane / 16 under the row's swizzle.  Weights: lane
         // (c, g) = (lane % 16, lane / 16) reads columns 8 c .. 8 c + 7 of rows 32 q + 8 g .. + 7, which is a transposed
@@ -337,27 +342,35 @@ __global__ __launch_bounds__(kDdThreads, 1) void down_gemm_dma_kernel(const uint
             else
                 af[set][i - 8] = *reinterpret_cast<const bf16x8_t *>(Ab + (i - 8) * 16 * kDgBK + koff[q]);
         };
-        // product i: fragment i / MF of the columns, i % MF of the tokens
-        bf16x8_t bw;
+        // product i: fragment i / MF of the columns, i % MF of the tokens.  The permutes that make a fragment of the columns
+        // stand between the products of the fragment before it; those of the next slice's first fragment between the last ones
+        // of this slice, when its rows have been read (one token fragment: reads last to the end, `first_pairs` follows them).
+        uint32_t bw[2][4];
+        auto pair = [&](int e, int q, int set) {
+            const u32x4_t r0 = __builtin_bit_cast(u32x4_t, rows[set][2 * q]);
+            const u32x4_t r1 = __builtin_bit_cast(u32x4_t, rows[set][2 * q + 1]);
+            bw[e % 2][q] = __builtin_amdgcn_perm(r1[e / 2], r0[e / 2], e % 2 ? 0x07060302u : 0x05040100u);
+        };
         auto product = [&](int i, int set) {
             const int e = i / MF, m_ = i % MF;
-            if (m_ == 0) {
-                uint32_t v[4];
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const u32x4_t r0 = __builtin_bit_cast(u32x4_t, rows[set][2 * q]);
-                    const u32x4_t r1 = __builtin_bit_cast(u32x4_t, rows[set][2 * q + 1]);
-                    v[q] = __builtin_amdgcn_perm(r1[e / 2], r0[e / 2], e % 2 ? 0x07060302u : 0x05040100u);
-                }
-                bw = __builtin_bit_cast(bf16x8_t, u32x4_t{v[0], v[1], v[2], v[3]});
-            }
-            // (two wait states: the compiler does not see that a product reads what a permute has just written.  Nothing else
-            // writes an operand that late as long as the loop below stays one body: a second copy of it for an odd last step
-            // had the compiler move every accumulator out and back in between its products.)
-            if (m_ == 0)
-                asm volatile("s_nop 1\n\tv_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc[m_][e]) : "v"(af[set][m_]), "v"(bw));
+            const u32x4_t b = {bw[e % 2][0], bw[e % 2][1], bw[e % 2][2], bw[e % 2][3]};
+            // (two wait states behind the last permute, which the compiler does not see that a product needs: two products
+            // where a fragment has three or more.  Nothing else writes an operand that late as long as the loop below stays one
+            // body: a second copy of it for an odd last step had the compiler move every accumulator out and back in between
+            // its products.)
+            if (MF < 3 && m_ == 0)
+                asm volatile("s_nop 1\n\tv_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc[m_][e]) : "v"(af[set][m_]), "v"(b));
             else
-                asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc[m_][e]) : "v"(af[set][m_]), "v"(bw));
+                asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc[m_][e]) : "v"(af[set][m_]), "v"(b));
+            constexpr int kGaps = MF < 3 ? 1 : MF - 2;
+            if (m_ < kGaps && (MF > 1 || e + 1 < F)) {
+#pragma unroll
+                for (int q = m_ * 4 / kGaps; q < (m_ + 1) * 4 / kGaps; ++q) pair((e + 1) % F, q, e + 1 < F ? set : set ^ 1);
+            }
+        };
+        auto first_pairs = [&](int set) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) pair(0, q, set);
         };
         // Requests in program order: ... A(s + NA - 1) | C(s + NB + 1), B(s + NB - 1) [wait for step s + 1] A(s + NA) | ...: the
         // wait may leave in flight what was issued after A(s + 1), B(s + 1) and the C that the next B requests use
@@ -390,6 +403,7 @@ __global__ __launch_bounds__(kDdThreads, 1) void down_gemm_dma_kernel(const uint
         constexpr int kSpread = NP > 8 ? NP * 3 / 4 : NP;  // products the reads are spread over: the last have time to arrive
 #pragma unroll
         for (int i = 0; i < NR; ++i) fetch(Al, Bl, i, 0, 0);
+        first_pairs(0);
         auto k_step = [&](int s) {
             const uint16_t *Ab = Al + abuf * AT, *Bb = Bl + bbuf * BT;
             load_channels(s + NB + 1);
@@ -404,6 +418,7 @@ __global__ __launch_bounds__(kDdThreads, 1) void down_gemm_dma_kernel(const uint
                 for (int p = i * PB / NP; p < (i + 1) * PB / NP; ++p) load_b(chn[p], p, bprev, s + NB - 1);
                 __builtin_amdgcn_sched_barrier(0);
             }
+            if (MF == 1) first_pairs(1);
             // this wave's reads of the buffers are over and its rows of the next step have landed; after the barrier so are
             // everybody's and have everybody's
             asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(kYounger) : "memory");
@@ -422,6 +437,7 @@ __global__ __launch_bounds__(kDdThreads, 1) void down_gemm_dma_kernel(const uint
                 for (int p = i * PA / NP; p < (i + 1) * PA / NP; ++p) load_a(p, a_free, s + NA);
                 __builtin_amdgcn_sched_barrier(0);
             }
+            if (MF == 1) first_pairs(0);
         };
         for (int s = 0; s < n_steps; ++s) k_step(s);
         // the surplus requests, before the LDS is given up; the products' results before they are read (the compiler does
