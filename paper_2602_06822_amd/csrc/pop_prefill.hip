@@ -357,6 +357,16 @@ struct PmRing {
     static constexpr int NB = MF >= 3 ? 3 : (MF == 2 ? 4 : 5);
     static constexpr size_t kBytes = (size_t)(NA * 64 * MF + NB * 16 * kPmMaxF) * kPfBK * sizeof(uint16_t);
 };
+// Narrow chunks of four token fragments (F up to kPmDeepF): their weight rows leave room for a third step of token rows.  A wave's
+// requests return in order, so with two steps of token rows every wait for the next one is also a wait for all but
+// the youngest step of weight rows, however many their ring holds; with three both have a step longer.  d 4096, m 14336, F 7, with
+// weights from memory: 256 tokens 80.4 -> 72.9 us (from the last-level cache 58.8 -> 55.1), 512 tokens at the 13B shape 145 ->
+// 139.5.  Wider chunks: no room; five fragments leave none for token rows at any width that is used.
+constexpr int kPmDeepMF = 4, kPmDeepF = 8;
+struct PmDeepRing {
+    static constexpr int NA = 3, NB = 3;
+    static constexpr size_t kBytes = (size_t)(NA * 64 * kPmDeepMF + NB * 16 * kPmDeepF) * kPfBK * sizeof(uint16_t);
+};
 
 // Channel (relative to the chunk) and matrix (0 gate, 1 up) of B row r: fragments of 16 rows go in pairs, the gate rows
 // of 16 channels and the up rows of the same; an odd last fragment is [gate of 8 channels | up of the same 8].
@@ -418,7 +428,7 @@ __host__ __device__ inline PmTiles pm_tiles(int n_ch, int n_tt, int mf, int n_cu
 // waves in lockstep): 512 tokens 102 -> 80 us (1.16 PFLOP/s), 2048 tokens 380 -> 292 us (1.26), 256 tokens 54 us.  Without
 // the products it takes 65 us, without the direct loads 63: neither alone is the bound, and at 2.4 GHz the loop would be
 // a third faster.
-template <int MF, int F, int kMode>
+template <int MF, int F, int kMode, class Ring>
 __device__ __forceinline__ void pm_tile(const uint16_t *__restrict__ w, const uint16_t *__restrict__ x, int T, int d,
                                         int m, int n_ch, int n_tt, int logical, float *__restrict__ s2_part,
                                         const PfStore &st, uint16_t *lds, float (&colsum)[4][kPfChunk])
@@ -426,7 +436,7 @@ __device__ __forceinline__ void pm_tile(const uint16_t *__restrict__ w, const ui
     typedef __attribute__((address_space(3))) void lds_t;
     typedef __attribute__((address_space(1))) const void glb_t;
     typedef float f32x4_t __attribute__((ext_vector_type(4)));
-    constexpr int NA = PmRing<MF>::NA, NB = PmRing<MF>::NB;
+    constexpr int NA = Ring::NA, NB = Ring::NB;
     constexpr bool kList = kMode == 1 || kMode == 4, kPrecise = kMode >= 3;
     constexpr int BM = 64 * MF, BC = 8 * F;             // tokens and channels of the tile
     constexpr int PA = BM / 32, PB = (F + 1) / 2;       // direct loads per wave and k-step (32 rows a pass)
@@ -693,10 +703,34 @@ __global__ __launch_bounds__(kPmThreads, 1) void prefill_mma_kernel(const uint16
         if (logical >= g.total) break;
         switch (g.f) {
 #define POP_PM(FF)                                                                               \
-    case FF:                                                                                     \
-        pm_tile<MF, FF, kMode>(w, x, T, d, m, n_ch, n_tt, logical, s2_part, st, pf_lds, colsum); \
+    case FF:                                                                                                 \
+        pm_tile<MF, FF, kMode, PmRing<MF>>(w, x, T, d, m, n_ch, n_tt, logical, s2_part, st, pf_lds, colsum); \
         break;
             POP_PM(12) POP_PM(11) POP_PM(10) POP_PM(8) POP_PM(7) POP_PM(6) POP_PM(4)
+#undef POP_PM
+        }
+        __syncthreads();  // the next tile's direct loads overwrite the LDS
+    }
+}
+
+// The same for four token fragments and narrow chunks: three steps of token rows in the ring.
+template <int kMode>
+__global__ __launch_bounds__(kPmThreads, 1) void prefill_deep_kernel(const uint16_t *__restrict__ w,
+                                                                     const uint16_t *__restrict__ x, int T, int d, int m,
+                                                                     int n_tt, PmTiles g, float *__restrict__ s2_part,
+                                                                     PfStore st)
+{
+    extern __shared__ __attribute__((aligned(16))) uint16_t pf_lds[];
+    __shared__ float colsum[4][kPfChunk];
+    for (int i = blockIdx.x / 8; i < g.per_xcd; i += gridDim.x / 8) {
+        const int logical = (blockIdx.x % 8) * g.per_xcd + i;
+        if (logical >= g.total) break;
+        switch (g.f) {
+#define POP_PM(FF)                                                                                                \
+    case FF:                                                                                                      \
+        pm_tile<kPmDeepMF, FF, kMode, PmDeepRing>(w, x, T, d, m, m, n_tt, logical, s2_part, st, pf_lds, colsum); \
+        break;
+            POP_PM(8) POP_PM(7) POP_PM(6) POP_PM(4)
 #undef POP_PM
         }
         __syncthreads();  // the next tile's direct loads overwrite the LDS
@@ -993,13 +1027,18 @@ template <int MF, int kMode>
 static hipError_t launch_pm(const void *w, int d, int m, const void *x, int T, const PmTiles &g, float *s2_part, int n_cu,
                             const PfStore &st, hipStream_t s)
 {
-    const size_t lds = PmRing<MF>::kBytes;
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&prefill_mma_kernel<MF, kMode>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    void (*kernel)(const uint16_t *, const uint16_t *, int, int, int, int, PmTiles, float *, PfStore) =
+        prefill_mma_kernel<MF, kMode>;
+    size_t lds = PmRing<MF>::kBytes;
+    // (the list form learns its F on the device; wider chunks do not leave the room)
+    if constexpr (MF == kPmDeepMF && (kMode == 0 || kMode == 2))
+        if (g.f <= kPmDeepF) kernel = prefill_deep_kernel<kMode>, lds = PmDeepRing::kBytes;
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       (int)lds);
     if (e != hipSuccess) return e;
     const int n_tt = (T + 64 * MF - 1) / (64 * MF), all = kMode == 1 || kMode == 4 ? n_cu : (g.total < n_cu ? g.total : n_cu);
-    hipLaunchKernelGGL((prefill_mma_kernel<MF, kMode>), dim3((all + 7) / 8 * 8), dim3(kPmThreads), lds, s,
-                       (const uint16_t *)w, (const uint16_t *)x, T, d, m, n_tt, g, s2_part, st);
+    hipLaunchKernelGGL(kernel, dim3((all + 7) / 8 * 8), dim3(kPmThreads), lds, s, (const uint16_t *)w, (const uint16_t *)x, T,
+                       d, m, n_tt, g, s2_part, st);
     return hipGetLastError();
 }
 

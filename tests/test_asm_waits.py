@@ -380,3 +380,22 @@ def test_prefill_contraction(assembly):
             pb = (products // (2 * mf) + 1) // 2
             assert (before, after) == (pb, 2 * mf), (name, loops)
             assert left == most_left_in_flight(na, nb, 2 * mf, pb, False), (name, before, left)
+
+
+@needs_hipcc
+def test_prefill_contraction_with_three_steps_of_token_rows(tmp_path):
+    out = tmp_path / "pop_prefill.s"
+    subprocess.run(["hipcc", "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Xclang", "-target-feature", "-Xclang",
+                    "-packed-fp32-ops", "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-S", "--cuda-device-only",
+                    os.path.join(CSRC, "pop_prefill.hip"), "-o", str(out)], check=True, capture_output=True, timeout=900)
+    bodies = re.findall(r"^_ZN3pop\d+prefill_deep_kernelI\w+:(.*?)^\.Lfunc_end", out.read_text(), re.M | re.S)
+    assert len(bodies) == 2
+    for body in bodies:
+        code = parse(body.split("\n")[1:])
+        assert not loads_in_flight(code)[1]
+        assert not product_hazards(code)[1]
+        loops = counted_waits(code)
+        assert sorted(p // 8 for _, _, _, p in loops) == [4, 6, 7, 8]
+        for before, after, left, products in loops:
+            pb = (products // 8 + 1) // 2
+            assert (before, after, left) == (pb, 8, most_left_in_flight(3, 3, 8, pb, False))

@@ -527,6 +527,18 @@ def _check_prefill_forward(oracle, G, L, x, n_ret, n_cand, k0, ydtype, y_tol, ro
     return scores, region, ret, cand
 
 
+@pytest.mark.parametrize("d,m,T", [(64, 14336, 256), (128, 14329, 193), (192, 16384, 250), (320, 14336, 449)])
+def test_prompt_of_four_token_fragments_and_narrow_chunks(pop, oracle, d, m, T):
+    """The contraction whose ring holds three steps of token rows (tiles of 256 tokens, chunks of up to 64 channels): one
+    k-step, fewer than the ring holds, and more; ragged prompts and a ragged last chunk."""
+    L = synth.make_layer(synth.small_config(f"deep_{d}_{m}", d, m, BF16, n_outlier=2, heavy_tail=True))
+    x = synth.make_activations(L, T, "prompt")
+    n_ret, n_cand = int(0.6 * m), int(0.1 * m)
+    with GpuLayer(pop, L, max_tokens=T, max_batch=1) as G:
+        _check_prefill_forward(oracle, G, L, x, n_ret, n_cand, n_cand // 2, F32, FFN_MFMA_TOL_F32)
+        _check_prefill(oracle, G, L, x, n_ret, n_cand)
+
+
 @pytest.mark.parametrize("d", [4032, 4096, 4160, 8192])
 def test_rows_with_and_without_a_gap_between_channels(pop, oracle, d):
     """Layers whose rows are a multiple of 8 KB keep their channels a line further apart: every kernel that reads weights, on
