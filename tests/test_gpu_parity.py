@@ -539,6 +539,30 @@ def test_prompt_of_four_token_fragments_and_narrow_chunks(pop, oracle, d, m, T):
         _check_prefill(oracle, G, L, x, n_ret, n_cand)
 
 
+@pytest.mark.parametrize("m", [1, 63, 1023, 1024, 1025, 2500])
+def test_channel_list_of_one_mask(pop, oracle, m):
+    """The list of a mask's channels, formed by a workgroup per 1024 of them: whole and ragged blocks, aligned and unaligned masks,
+    any byte but zero counts, none, one and all channels on."""
+    d, T = 128, 40
+    L = synth.make_layer(synth.small_config(f"mask_list_{m}", d, m, BF16))
+    x = synth.make_activations(L, T, "tokens")
+    g = synth.rng("mask_list", m)
+    xd = torch.from_numpy(x.view(np.int16).copy()).cuda()
+    y = torch.empty((T, d), dtype=torch.float32, device="cuda")
+    last = np.zeros(m, np.uint8)
+    last[-1] = 128
+    with GpuLayer(pop, L, max_tokens=T, max_batch=1) as G:
+        for mask in (np.full(m, 255, np.uint8), (g.random(m) < 0.5) * g.integers(1, 256, m), last, np.zeros(m, np.uint8)):
+            mask = mask.astype(np.uint8)
+            y_ref = oracle.pruned_ffn(x, L.w_gate, L.w_up, L.w_down, BF16, (mask != 0).astype(np.uint8))
+            for shift in (0, 1):
+                buf = torch.zeros(m + 1, dtype=torch.uint8, device="cuda")
+                buf[shift:shift + m] = torch.from_numpy(mask).cuda()
+                pop.pop_pruned_ffn(G.handle, xd, T, buf[shift:shift + m], 1, y, F32)
+                got = y.cpu().numpy()
+                assert not got.any() if not y_ref.any() else max_abs_rel(got, y_ref) <= FFN_MFMA_TOL_F32
+
+
 @pytest.mark.parametrize("d", [4032, 4096, 4160, 8192])
 def test_rows_with_and_without_a_gap_between_channels(pop, oracle, d):
     """Layers whose rows are a multiple of 8 KB keep their channels a line further apart: every kernel that reads weights, on
