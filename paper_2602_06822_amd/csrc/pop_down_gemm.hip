@@ -288,10 +288,15 @@ __global__ __launch_bounds__(kDdThreads, 1) void down_gemm_dma_kernel(const uint
         // position lane % 8 of its row.  Weights: pass p covers rows 16 p + 4 w + lane / 16, unit lane % 16.
         const int a_row = wave * 8 + lane / 8;
         const int a_src = ((lane % 8) ^ ((a_row / 2) % 8)) * 8;  // (passes are 32 rows apart: same swizzle term)
-        const uint16_t *hc_tile = hc + (size_t)t0 * ldh;
-        uint32_t a_off[PA];  // bytes from the tile's first row
+        // (32 bits reach over the 32 rows of a pass whatever their length: 44 million channels at most)
+        const uint16_t *hc_pass[PA];  // the pass's first row
+        uint32_t a_off[PA];           // bytes from there
 #pragma unroll
-        for (int p = 0; p < PA; ++p) a_off[p] = 2 * ((uint32_t)(min(t0 + a_row + p * 32, T - 1) - t0) * (uint32_t)ldh + a_src);
+        for (int p = 0; p < PA; ++p) {
+            const int first = min(t0 + p * 32, T - 1);
+            hc_pass[p] = hc + (size_t)first * ldh;
+            a_off[p] = 2 * ((uint32_t)(min(t0 + a_row + p * 32, T - 1) - first) * (uint32_t)ldh + a_src);
+        }
         const int b_row = wave * 4 + lane / 16;
         const uintptr_t b_col = (uintptr_t)(w + 2 * d + n0 + (lane % 16) * 8), b_zero = (uintptr_t)(zero_row + (lane % 16) * 8);
         const uint32_t b_stride = (uint32_t)(channel_elems_bf16(d) * sizeof(uint16_t));
@@ -312,7 +317,7 @@ __global__ __launch_bounds__(kDdThreads, 1) void down_gemm_dma_kernel(const uint
                          : "memory");
         };
         auto load_a = [&](int p, int buf, int step) {
-            const char *k = (const char *)(hc_tile + min(ks0 + step, ks1 - 1) * kDgBK);
+            const char *k = (const char *)(hc_pass[p] + min(ks0 + step, ks1 - 1) * kDgBK);
             __builtin_amdgcn_global_load_lds((glb_t *)(k + a_off[p]), (lds_t *)(As + buf * AT + (p * 32 + wave * 8) * kDgBK), 16, 0, 0);
         };
         // (the row is selected with a mask: a conditional would put the load under a branch and make its wait inexact; one 64-bit

@@ -563,6 +563,38 @@ def test_channel_list_of_one_mask(pop, oracle, m):
                 assert not got.any() if not y_ref.any() else max_abs_rel(got, y_ref) <= FFN_MFMA_TOL_F32
 
 
+def test_down_gemm_of_rows_four_gigabytes_into_a_tile(pop, oracle):
+    """A layer of so many channels that the last token row of a down-projection tile starts more than 2^32 bytes behind its
+    first (the row stride of H follows the number of channels, whatever the mask): 64 tokens, d 128, a few active channels
+    of 34.4 million."""
+    d, m, T = 128, 34_400_000, 64
+    free, _ = torch.cuda.mem_get_info()
+    if free < 100 << 30:
+        pytest.skip("needs 60 GB of device memory")
+    assert down_tile(T, d, 256)[0] == 1 and 63 * 2 * m > 1 << 32
+    g = synth.rng("far_rows")
+    act = np.sort(g.choice(m, 150, replace=False))
+    L = synth.make_layer(synth.small_config("far_rows", d, len(act), BF16))
+    x = synth.make_activations(L, T, "tokens")
+    where = torch.from_numpy(act).cuda()
+    wg, wu, wd = (torch.zeros(s, dtype=torch.int16, device="cuda") for s in ((m, d), (m, d), (d, m)))
+    wg[where], wu[where], wd[:, where] = dev(L.w_gate), dev(L.w_up), dev(L.w_down)
+    handle = pop.pop_layer_create(d, m, BF16, wg, wu, wd, T, 1)
+    try:
+        del wg, wu, wd
+        mask = torch.zeros(m, dtype=torch.uint8, device="cuda")
+        mask[where] = 1
+        y = torch.empty((T, d), dtype=torch.float32, device="cuda")
+        pop.pop_pruned_ffn(handle, dev(x), T, mask, 1, y, F32)
+        got = host(y)
+    finally:
+        pop.pop_layer_destroy(handle)
+        torch.cuda.empty_cache()
+    want = oracle.pruned_ffn(x, L.w_gate, L.w_up, L.w_down, BF16, np.ones(len(act), np.uint8))
+    assert max_abs_rel(got, want) <= FFN_MFMA_TOL_F32
+    assert max_abs_rel(got[63], want[63]) <= FFN_MFMA_TOL_F32
+
+
 @pytest.mark.parametrize("d", [4032, 4096, 4160, 8192])
 def test_rows_with_and_without_a_gap_between_channels(pop, oracle, d):
     """Layers whose rows are a multiple of 8 KB keep their channels a line further apart: every kernel that reads weights, on
