@@ -539,10 +539,11 @@ def test_prompt_of_four_token_fragments_and_narrow_chunks(pop, oracle, d, m, T):
         _check_prefill(oracle, G, L, x, n_ret, n_cand)
 
 
-@pytest.mark.parametrize("m", [1, 63, 1023, 1024, 1025, 2500])
+@pytest.mark.parametrize("m", [1, 15, 17, 63, 1023, 1024, 1025, 2500, 3055, 16383, 16385, 32769, 65536, 65537])
 def test_channel_list_of_one_mask(pop, oracle, m):
-    """The list of a mask's channels, formed by a workgroup per 1024 of them: whole and ragged blocks, aligned and unaligned masks,
-    any byte but zero counts, none, one and all channels on."""
+    """The list of a mask's channels, formed by a workgroup per 1024 of them (up to 65536, by one beyond): whole and ragged blocks
+    and sixteens, masks longer than what the workgroup reads at once, aligned and unaligned ones, any byte but zero counts,
+    none, one and all channels on."""
     d, T = 128, 40
     L = synth.make_layer(synth.small_config(f"mask_list_{m}", d, m, BF16))
     x = synth.make_activations(L, T, "tokens")
