@@ -33,14 +33,17 @@ __device__ __forceinline__ void gateup_row(const typename V::vec_t *__restrict__
     const int group = kWave * U;
     const int nvec_full = nvec / group * group;
     j = __builtin_amdgcn_readfirstlane(j);  // (one channel per wave)
-    const vec_t *g = w + (uint64_t)(uint32_t)j * (uint32_t)channel_vectors(nvec, V::kElems == 8);
-    const vec_t *u = g + nvec;
-    // (few sequences: the rows' addresses as scalar registers, which the compiler otherwise spreads over vector ones: 13B shape,
-    // four sequences 123 -> 120.4 us for two layers; five and more are 2 % faster the other way)
-    if constexpr (B <= 4) {
-        asm("" : "+s"(g));
-        asm("" : "+s"(u));
-    }
+    // The start of each row as one value: taken apart by the compiler (the base, the channel and the lane in one sum, per load) the
+    // addresses cost registers and with them loads in flight.  Two layers: 13B shape, four sequences 122.5 -> 120.0 us, five
+    // 124.1 -> 122.7; 7B shape, four 97.7 -> 95.4, six 100.0 -> 98.8; float32 d 1024, m 2816, three 48.6 -> 47.4, eight
+    // 65.3 -> 64.0; two and three sequences of bf16 layers the same.  The pointers say that they are global: what comes out
+    // of the asm as a plain pointer is read by flat loads, which count as LDS operations too and are waited for all at once.
+    typedef uint32_t raw_t __attribute__((ext_vector_type(4)));
+    typedef __attribute__((address_space(1))) const raw_t row_t;
+    row_t *g = (row_t *)(w + (uint64_t)(uint32_t)j * (uint32_t)channel_vectors(nvec, V::kElems == 8));
+    row_t *u = g + nvec;
+    asm("" : "+s"(g));
+    asm("" : "+s"(u));
     // Two 16-byte vectors' products (sixteen exact products for bf16 rows) are summed in the row's accumulator type,
     // the pairs of a lane and then the lanes in double: a long float32 chain would round every add at the magnitude
     // of the largest product met so far, and so would a float32 tree over the lanes.
@@ -53,8 +56,8 @@ __device__ __forceinline__ void gateup_row(const typename V::vec_t *__restrict__
         vec_t wg[U], wu[U];
 #pragma unroll
         for (int q = 0; q < U; ++q) {
-            wg[q] = g[c0 + q * kWave + lane];
-            wu[q] = u[c0 + q * kWave + lane];
+            wg[q] = __builtin_bit_cast(vec_t, g[c0 + q * kWave + lane]);
+            wu[q] = __builtin_bit_cast(vec_t, u[c0 + q * kWave + lane]);
         }
 #pragma unroll
         for (int q = 0; q < U; q += 2) {
@@ -69,7 +72,7 @@ __device__ __forceinline__ void gateup_row(const typename V::vec_t *__restrict__
     constexpr int kTailUnroll = B <= 4 ? 2 : 1;
 #pragma unroll kTailUnroll
     for (int c = nvec_full + lane; c < nvec; c += kWave) {
-        vec_t wg = g[c], wu = u[c];
+        const vec_t wg = __builtin_bit_cast(vec_t, g[c]), wu = __builtin_bit_cast(vec_t, u[c]);
 #pragma unroll
         for (int b = 0; b < B; ++b) {
             vec_t xv = xs[b * nvec + c];

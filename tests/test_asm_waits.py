@@ -399,3 +399,30 @@ def test_prefill_contraction_with_three_steps_of_token_rows(tmp_path):
         for before, after, left, products in loops:
             pb = (products // 8 + 1) // 2
             assert (before, after, left) == (pb, 8, most_left_in_flight(3, 3, 8, pb, False))
+
+
+@needs_hipcc
+def test_batched_gate_up_rows_are_global_loads(tmp_path):
+    """The weight rows of the batched gate/up kernels are read by global loads (a flat load counts as an LDS operation too, and the
+    kernels read x from LDS between the rows); the decode step's kernel of bf16 layers requests a group of 2 U row vectors
+    together and the first wait behind them leaves some of the group in flight."""
+    out = tmp_path / "pop_gemv.s"
+    subprocess.run(["hipcc", "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Xclang", "-target-feature", "-Xclang",
+                    "-packed-fp32-ops", "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-S", "--cuda-device-only",
+                    os.path.join(CSRC, "pop_gemv.hip"), "-o", str(out)], check=True, capture_output=True, timeout=900)
+    bodies = re.findall(r"^_ZN3pop\d+(gateup_(?:select_)?kernel)INS_\d+(VecBF16|VecF32)ELi(\d)\w+:(.*?)^\.Lfunc_end", out.read_text(),
+                        re.M | re.S)
+    assert len(bodies) == 2 * (8 + 7)
+    for kernel, vec, batch, body in bodies:
+        code = parse(body.split("\n")[1:])
+        assert not [i.text for i in code if i.op.startswith("flat_")], (kernel, vec, batch)
+        if kernel == "gateup_kernel" or vec == "VecF32":  # (float32 rows: spilled registers come back in between)
+            continue
+        together, waits = 0, []
+        for i in code:
+            together += i.op == "global_load_dwordx4"
+            if "vmcnt" in i.wait:
+                if together >= 2 * (8 if int(batch) < 5 else 4):
+                    waits.append(i.wait["vmcnt"])
+                together = 0
+        assert waits and max(waits) > 0, (vec, batch, waits)
