@@ -236,7 +236,8 @@ __global__ __launch_bounds__(MAXB) void decode_fused_kernel(FusedParams p)
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int b = blockIdx.x, n_wg = gridDim.x, n_workers = n_wg - 1, wb = b - 1;
     const int nvec = p.nvec;
-    constexpr uint32_t gap = GAP ? channel_gap(0, 1) : 0;
+    constexpr uint32_t gap = GAP ? channel_gap(512, 1) : 0;
+    static_assert(channel_gap(512, 1) == channel_gap(1024, 1), "one gap");
     const vec_t *w = reinterpret_cast<const vec_t *>(p.w);
     unsigned long long *const my_word = p.selw + (size_t)b * kSelStride;
     const int epoch = coherent_load(&p.ctr[0]);  // the tag of everything handed over in this step
@@ -776,7 +777,11 @@ static hipError_t fused_dispatch_shape(const FusedPlan &pl, Fn fn)
 {
     const bool small = pl.block <= 512;
     if (pl.per == 1) return small ? fn.template operator()<V, 1, 512, GAP>() : fn.template operator()<V, 1, 1024, GAP>();
-    return small ? fn.template operator()<V, 2, 512, GAP>() : fn.template operator()<V, 2, 1024, GAP>();
+    if (small) return fn.template operator()<V, 2, 512, GAP>();
+    if constexpr (GAP)
+        return hipErrorInvalidValue;  // (rows with a gap behind them fit 512 threads with two vectors each)
+    else
+        return fn.template operator()<V, 2, 1024, GAP>();
 }
 template <class Fn>
 static hipError_t fused_dispatch(int is_bf16, const FusedPlan &pl, Fn fn)

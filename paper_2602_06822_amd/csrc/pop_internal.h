@@ -33,12 +33,19 @@ __device__ __forceinline__ uint16_t f32_to_bf16(float f)
 __device__ __forceinline__ float silu_mul(float g, float u) { return g / (1.0f + expf(-g)) * u; }
 
 // 16-byte vectors between the weights of one channel [gate row | up row | down column] (nvec vectors each) and the next
-// channel's.  A 128-byte line on bf16 layers whose rows are a multiple of 8 KB: the contraction of a prompt, whose workgroups all
-// ask for the same columns of their rows at about the same time, otherwise keeps hitting the same few memory channels (d 4096,
-// weights from memory: 256 tokens, m 14336 95 -> 72 us, 512 tokens, m 11008 91 -> 77; two or three lines gain the same or
-// less).  None on other rows (13B shape, 10 KB: 333 tokens 67 -> 66 us), and none behind each row: the decode step reads a
-// channel's rows together and was 0.7 % slower with gaps between them.
-__host__ __device__ __forceinline__ constexpr int channel_gap(int nvec, int is_bf16) { return is_bf16 && nvec % 512 == 0 ? 8 : 0; }
+// channel's.  A 128-byte line on bf16 layers whose rows are 8 or 16 KB: the contraction of a prompt, whose workgroups all
+// ask for the same columns of their rows at about the same time, otherwise keeps hitting the same few memory channels.  Prompt
+// calls with weights from memory, without / with it: d 4096, m 14336, 256 tokens 82.0 / 80.1 us (the contraction alone, before its
+// third step of token rows, 95 / 72), m 11008, 512 tokens 90.2 / 86.8, eight experts 1142 / 1098; d 8192, m 14336, 256 tokens
+// 154.6 / 140.4, 512 tokens 232.5 / 225.5.  Two or three lines gain the same or less.  Not on other rows: 2, 4, 6 and 10 KB (d 1024 to
+// 5120) are within 1 % with and without, 12 KB (d 6144, m 16384) 128-138 / 126 at 256 tokens and 193-200 / 190 at 512.  Not on 24 and
+// 32 KB either (d 16384, m 16384, 256 tokens 324 / 291): there the single-sequence step's kernel keeps 190 registers in scratch
+// memory, and its build with the gap takes 1 to 3 % longer than the one without.  None behind each row: the decode step reads
+// a channel's rows together and was 0.7 % slower with gaps between them.
+__host__ __device__ __forceinline__ constexpr int channel_gap(int nvec, int is_bf16)
+{
+    return is_bf16 && (nvec == 512 || nvec == 1024) ? 8 : 0;
+}
 // From one channel's weights to the next's.
 __host__ __device__ __forceinline__ constexpr int channel_vectors(int nvec, int is_bf16)
 {

@@ -596,14 +596,15 @@ def test_down_gemm_of_rows_four_gigabytes_into_a_tile(pop, oracle):
     assert max_abs_rel(got[63], want[63]) <= FFN_MFMA_TOL_F32
 
 
-@pytest.mark.parametrize("d", [4032, 4096, 4160, 8192])
+@pytest.mark.parametrize("d", [4032, 4096, 4160, 8192, 12288])
 def test_rows_with_and_without_a_gap_between_channels(pop, oracle, d):
-    """Layers whose rows are a multiple of 8 KB keep their channels a line further apart: every kernel that reads weights, on
-    such layers and on ones whose rows are a k-step shorter and longer."""
+    """Layers whose rows are 8 or 16 KB keep their channels a line further apart: every kernel that reads weights, on
+    such layers, on ones whose rows are a k-step shorter and longer, and on wider ones."""
     m = 150
     L = synth.make_layer(synth.small_config(f"gap_{d}", d, m, BF16, n_outlier=3, heavy_tail=True))
     n_ret, n_cand = 70, 40
-    with GpuLayer(pop, L, max_tokens=70, max_batch=8) as G:
+    largest = min(8, 160 * 1024 // (2 * d))  # sequences whose x fits the LDS
+    with GpuLayer(pop, L, max_tokens=70, max_batch=largest) as G:
         np.testing.assert_allclose(G.norms(), oracle.down_norms(L.w_down, BF16), rtol=2e-7)
         for T in (5, 70):
             x = synth.make_activations(L, T, "prompt")
@@ -615,7 +616,7 @@ def test_rows_with_and_without_a_gap_between_channels(pop, oracle, d):
                 y = G.ffn(x, mk, F32)
                 y_ref = oracle.down(h, L.w_down, BF16, np.broadcast_to(mk, (T, m)))
                 assert max_abs_rel(y, y_ref) <= 4e-3
-        for B in (1, 2, 3, 8):
+        for B in (1, 2, 3, largest):
             _check_decode(oracle, G, L, region, cand, synth.make_activations(L, B, "decode"), 20, F32)
 
 
