@@ -122,6 +122,53 @@ def test_partition_of_crowded_intervals(pop, oracle, m, spread):
     assert np.array_equal(host(top)[:n_top], oracle.partition(s, n_top, 0)[1])
 
 
+def _key_order(s):
+    """Channels in the order of their scores' keys: as floats from the largest down, equal ones by channel; a NaN with the sign
+    bit clear comes before +inf and one with the sign bit set behind -inf, by their bits."""
+    b = s.view(np.uint32).copy()
+    b[b == 0x80000000] = 0
+    key = np.where(b & 0x80000000, ~b, b | 0x80000000).astype(np.int64)
+    return np.lexsort((np.arange(len(s)), -key))
+
+
+@pytest.mark.parametrize("m", [65, 1025, 14337, 32769])
+@pytest.mark.parametrize("kind", ["inf", "minus_inf", "both", "many_inf", "nan", "many_nan", "largest"])
+def test_partition_of_infinities_and_nan(pop, oracle, m, kind):
+    """Scores that stretch the keys' range as far as it goes, among ordinary ones, at thresholds among the ordinary scores, among
+    the extreme ones and between them: a few infinities of either sign, more equal ones than a list holds, NaN of both signs with
+    different bits or in a crowd, the largest and smallest finite values."""
+    g = synth.rng("extreme_scores", m, kind)
+    s = np.exp(g.standard_normal(m)).astype(np.float32)
+    few, many = g.permutation(m)[:9], g.permutation(m)[:m // 3]
+    b = s.view(np.uint32)
+    if kind in ("inf", "both"):
+        b[few[:5]] = 0x7f800000
+    if kind in ("minus_inf", "both"):
+        b[few[5:]] = 0xff800000
+    if kind == "many_inf":
+        b[many] = 0x7f800000
+    if kind == "nan":
+        b[few[:7]] = [0x7fc00000, 0x7fffffff, 0xffc00000, 0xffffffff, 0x7f800001, 0x7f800000, 0xff800000]
+    if kind == "many_nan":
+        b[many] = np.where(g.random(len(many)) < 0.5, 0x7fc00000, 0xffc00000).astype(np.uint32)
+    if kind == "largest":
+        s[few] = np.float32([3.4e38, -3.4e38, 1e-45, -1e-45, 0.0, -0.0, 3.4e38, 1e-45, 0.0])
+    order = _key_order(s)
+    for n_ret in sorted({0, 1, 3, 5, m // 6, m // 3, m // 2, m - 4, m - 1}):
+        n_cand, n_top = min(m // 10, m - n_ret), min(m, n_ret + 4)
+        region = torch.full((m,), 9, dtype=torch.uint8, device="cuda")
+        ret, cand, top = (torch.full((max(n, 1),), -1, dtype=torch.int32, device="cuda") for n in (n_ret, n_cand, n_top))
+        pop.pop_partition_top_from_scores(dev(s), m, n_ret, n_cand, n_top, region, ret, cand, None, top)
+        want = np.full(m, 2, np.uint8)
+        want[order[:n_ret]], want[order[n_ret:n_ret + n_cand]] = 0, 1
+        assert np.array_equal(host(region), want), n_ret
+        assert np.array_equal(host(ret)[:n_ret], np.flatnonzero(want == 0)), n_ret
+        assert np.array_equal(host(cand)[:n_cand], np.flatnonzero(want == 1)), n_ret
+        assert np.array_equal(host(top)[:n_top], np.sort(order[:n_top])), n_ret
+        if not np.isnan(s).any():
+            assert np.array_equal(want, oracle.partition(s, n_ret, n_cand)[0]), n_ret
+
+
 @pytest.mark.parametrize("kind", ["none", "some", "all", "zeros"] + list(synth.SCORE_SHAPES))
 def test_partition_top_from_scores_bit_exact(pop, oracle, kind):
     """The partition launch that also emits the n_top best channels (the prompt's own mask): regions as before, and
