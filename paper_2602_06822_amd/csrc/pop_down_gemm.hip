@@ -224,8 +224,10 @@ __global__ __launch_bounds__(512) void down_gemm_bf16_kernel(const uint16_t *__r
 // pointed at a row of zeros (zero_row, 256 bytes), which makes it irrelevant what the Hc columns beyond a hold, as long as
 // it is finite (the buffer is cleared when it is allocated and only ever holds H values).  Needs d % 128 == 0 and
 // ldh >= a rounded up to 64.
-// What bounds it: the loads into LDS, which deliver 32 bytes a cycle and compute unit at any depth (70 bytes/ns measured with nothing
-// else running): 48 KB a k-step at MF = 4 are 0.70 us, the whole loop without its products takes 0.77 and with them 1.2-1.3.
+// What bounds it: the loads into LDS, which deliver 30 bytes a cycle and compute unit at any depth (measured with nothing else running):
+// the 48 KB of a k-step at MF = 4 are 1650 cycles of the 2060 it takes at 2048 tokens, its products 1024.  Without the
+// products 2048 tokens take 94 us of 133, 333 tokens at the 13B shape 31 of 42, an expert's 256 tokens 30 of 32; with the channel
+// numbers counted up instead of read, or all rows from 64 channels, at most 2 us less in any of them.
 // With one wave per SIMD, whatever does not fit between two products (12 cycles) comes on top, so the permutes of a fragment
 // stand between the products of the one before it and a weight row's address is one multiply-add (both in a bunch in front of their use
 // before): 333 tokens at the 13B shape 42.7 -> 40.5 us, 2048 tokens at d 4096 169 -> 159 (under the kernel trace), 256 tokens 33.6 -> 32.8,

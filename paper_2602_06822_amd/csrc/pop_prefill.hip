@@ -409,10 +409,12 @@ __host__ __device__ inline PmTiles pm_tiles(int n_ch, int n_tt, int mf, int n_cu
     return best;
 }
 
-// Bound by the loads into LDS and the matrix pipe together.  Direct loads deliver 32 bytes a cycle and compute unit at any depth (70
-// bytes/ns with nothing else running): the 54 KB of a k-step at MF = 4, F = 11 are 1728 cycles of the 2000 it takes,
-// its products 1408 (512 tokens: pipe busy for 67 % of the waves' time at 2.1 GHz).  So what counts is work per byte
-// loaded and per product: 16x16x32 products move fewer accumulator bytes per flop than 32x32x16 ones (7 % faster here at
+// Bound by the loads into LDS, the matrix pipe and the chip's power together.  Direct loads deliver 30 bytes a cycle and compute unit
+// at any depth (70 bytes/ns at 2.4 GHz, nothing else running): the 54 KB of a k-step at MF = 4, F = 11 are 1850 cycles of the 2040
+// it takes, its products 1390 (512 tokens: pipe busy for 68 % of the waves' time), and with the pipe that busy the clock
+// falls to about 2.0 GHz: without its products the launch takes 51 instead of 77 us, 2048 tokens 231 instead of 309.  An expert's
+// 256 tokens (F 7) leave the pipe idle for two thirds of the time, the clock near 2.4 GHz, and take as long without products (71
+// of 72 us: weights from memory).  So what counts is work per byte loaded and per product: 16x16x32 products move fewer accumulator bytes per flop than 32x32x16 ones (7 % faster here at
 // equal cycles), a wave keeps all 16 F rows against its 16 MF tokens (MF + F fragment reads of 1 KB for MF * F products
 // of 16 cycles), and F follows the channel count in eights instead of padding it to 96.  Token rows straight into
 // registers instead (a wave is the only reader of its own) were bit-identical and a third slower (512 tokens 75 -> 100
@@ -428,8 +430,7 @@ __host__ __device__ inline PmTiles pm_tiles(int n_ch, int n_tt, int mf, int n_cu
 // issues the same loads in every k-step (rows beyond T or beyond the chunk are pointed at a row that exists, steps
 // beyond the last at the last step), so each wait counts exactly.
 // Measured, d 4096, m 11008 (before: eight waves of 64 tokens x 96 rows, 32x32x16 products, reads and products of all
-// waves in lockstep): 512 tokens 102 -> 80 us (1.16 PFLOP/s), 2048 tokens 380 -> 292 us (1.26), 256 tokens 54 us.  Without
-// the products it takes 65 us, without the direct loads 63: neither alone is the bound.
+// waves in lockstep): 512 tokens 102 -> 80 us (1.16 PFLOP/s), 2048 tokens 380 -> 292 us (1.26), 256 tokens 54 us.
 template <int MF, int F, int kMode, class Ring>
 __device__ __forceinline__ void pm_tile(const uint16_t *__restrict__ w, const uint16_t *__restrict__ x, int T, int d,
                                         int m, int n_ch, int n_tt, int logical, float *__restrict__ s2_part,

@@ -10,6 +10,8 @@ compiles both files to assembly and follows every instantiation's instructions a
 * no other instruction reads or writes a product's result before the product has left the pipe;
 * each k-step of the main loops issues the direct loads that its tile calls for, and its one counted wait leaves no load
   in flight that the next step, by the schedule of the LDS rings, reads.
+
+The batched gate/up kernels are read for the kind of their weight rows' loads.
 """
 import os
 import re
