@@ -104,14 +104,14 @@ namespace {
 // Launch shape of the fused single-sequence step for the layer's current region sizes, sized to be co-resident.
 int plan_fused_step(pop_layer *L)
 {
-    L->fused_ok = fused_plan(L->d, L->is_bf16, L->n_ret, L->n_cand, L->wg_target, &L->plan);
+    L->fused_ok = fused_plan(L->d, L->m, L->is_bf16, L->n_ret, L->n_cand, L->wg_target, &L->plan);
     if (L->fused_ok) {
         int max_wg = 0;
         POP_HIP(fused_resident_limit(L->is_bf16, L->plan, L->n_cu, &max_wg));
         if (max_wg < 2) {
             L->fused_ok = false;
         } else if (L->plan.n_wg > max_wg) {
-            L->fused_ok = fused_plan(L->d, L->is_bf16, L->n_ret, L->n_cand, max_wg, &L->plan) && L->plan.n_wg <= max_wg;
+            L->fused_ok = fused_plan(L->d, L->m, L->is_bf16, L->n_ret, L->n_cand, max_wg, &L->plan) && L->plan.n_wg <= max_wg;
         }
     }
     return POP_OK;

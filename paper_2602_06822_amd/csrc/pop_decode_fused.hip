@@ -115,7 +115,7 @@ __device__ __forceinline__ void load_round(RoundBuf<V, PER> &rb, const RoundDesc
 #pragma unroll
             for (int q = 0; q < PER; ++q) {
                 const uint32_t idx = (ok[q] && ds.xrow[a] >= 0) ? ds.xoff[a] + (uint32_t)col[q] : 0u;
-                rb.xl[a][q] = w[idx];
+                rb.xl[a][q] = load_row<V>(w, idx);
             }
     }
     uint32_t idx[kRB][PER];
@@ -125,14 +125,14 @@ __device__ __forceinline__ void load_round(RoundBuf<V, PER> &rb, const RoundDesc
         for (int q = 0; q < PER; ++q) {
             const bool ld = ok[q] && ds.jb[t] >= 0;
             idx[t][q] = ld ? ds.boff[t] + (uint32_t)col[q] : 0u;
-            rb.g[t][q] = w[idx[t][q]];
-            rb.u[t][q] = w[ld ? idx[t][q] + (uint32_t)nvec : 0u];
+            rb.g[t][q] = load_row<V>(w, idx[t][q]);
+            rb.u[t][q] = load_row<V>(w, (ld ? idx[t][q] + (uint32_t)nvec : 0u));
         }
 #pragma unroll
     for (int t = 0; t < kRB; ++t)
 #pragma unroll
         for (int q = 0; q < PER; ++q)
-            rb.dn[t][q] = w[(ok[q] && ds.jb[t] >= 0 && !ds.bcand()) ? idx[t][q] + 2u * (uint32_t)nvec : 0u];
+            rb.dn[t][q] = load_row<V>(w, ((ok[q] && ds.jb[t] >= 0 && !ds.bcand()) ? idx[t][q] + 2u * (uint32_t)nvec : 0u));
 }
 
 // Sum over the 16 lanes of each DPP row, result in every lane of the row (4 cross-lane adds, no LDS).
@@ -787,6 +787,7 @@ template <class Fn>
 static hipError_t fused_dispatch(int is_bf16, const FusedPlan &pl, Fn fn)
 {
     if (!is_bf16) return fused_dispatch_shape<VecF32, false>(pl, fn);
+    if (pl.stream) return pl.gap ? fused_dispatch_shape<StreamBF16, true>(pl, fn) : fused_dispatch_shape<StreamBF16, false>(pl, fn);
     return pl.gap ? fused_dispatch_shape<VecBF16, true>(pl, fn) : fused_dispatch_shape<VecBF16, false>(pl, fn);
 }
 
@@ -814,7 +815,7 @@ int fused_max_workgroups() { return 1024; }
 size_t fused_selw_words() { return (size_t)1024 * kSelStride; }
 
 // Chooses the launch shape; false when the fused kernel does not support this shape.
-bool fused_plan(int d, int is_bf16, int n_ret, int n_cand, int wg_target, FusedPlan *pl)
+bool fused_plan(int d, int m, int is_bf16, int n_ret, int n_cand, int wg_target, FusedPlan *pl)
 {
     const int E = is_bf16 ? 8 : 4, nvec = d / E;
     // one vector column per thread up to 512 threads, then two (a workgroup of up to 512 threads has twice the
@@ -825,6 +826,7 @@ bool fused_plan(int d, int is_bf16, int n_ret, int n_cand, int wg_target, FusedP
     if (nvec > 2048) return false;
     pl->per = per;
     pl->gap = channel_gap(nvec, is_bf16) != 0;
+    pl->stream = stream_rows(d, m, is_bf16, kStreamStepBytes);
     pl->block = ((nvec + per * kWave - 1) / (per * kWave)) * kWave;
     const int rounds_total = (n_ret + kRB - 1) / kRB;
     int workers = rounds_total;

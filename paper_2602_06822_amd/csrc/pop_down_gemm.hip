@@ -242,15 +242,11 @@ struct DdRing {
     static constexpr size_t kBytes = (size_t)(NA * 64 * MF * kDgBK + NB * kDgBK * kDgBN) * sizeof(uint16_t) + kDdSlots * kDgBK * 4;
 };
 
-template <int MF>
-__global__ __launch_bounds__(kDdThreads, 1) void down_gemm_dma_kernel(const uint16_t *__restrict__ w, int d,
-                                                                      const int *__restrict__ list,
-                                                                      const int *__restrict__ n_list,
-                                                                      const uint16_t *__restrict__ hc, int ldh, int T,
-                                                                      int n_tt, int n_nt, int n_split, int per_xcd,
-                                                                      const uint16_t *__restrict__ zero_row,
-                                                                      float *__restrict__ part, void *__restrict__ y,
-                                                                      int y_bf16)
+template <int MF, bool kStream>
+__device__ __forceinline__ void dd_tile(const uint16_t *__restrict__ w, int d, const int *__restrict__ list,
+                                        const int *__restrict__ n_list, const uint16_t *__restrict__ hc, int ldh, int T,
+                                        int n_tt, int n_nt, int n_split, int per_xcd, const uint16_t *__restrict__ zero_row,
+                                        float *__restrict__ part, void *__restrict__ y, int y_bf16)
 {
     typedef __attribute__((address_space(3))) void lds_t;
     typedef __attribute__((address_space(1))) const void glb_t;
@@ -329,7 +325,8 @@ __global__ __launch_bounds__(kDdThreads, 1) void down_gemm_dma_kernel(const uint
             const uintptr_t live = -(uintptr_t)(b_row < n_live);
             const uintptr_t row = b_col + (uint64_t)(uint32_t)c * b_stride;
             __builtin_amdgcn_global_load_lds((glb_t *)(b_zero ^ ((row ^ b_zero) & live)),
-                                             (lds_t *)(Bs + buf * BT + (p * 16 + wave * 4) * kDgBN), 16, 0, 0);
+                                             (lds_t *)(Bs + buf * BT + (p * 16 + wave * 4) * kDgBN), 16, 0,
+                                             kStream ? 2 : 0);  // (2: non-temporal)
         };
         // Fragment reads.  A: row lane % 16 of the token fragment, unit 4 q + lane / 16 under the row's swizzle.  Weights: lane
         // (c, g) = (lane % 16, lane / 16) reads columns 8 c .. 8 c + 7 of rows 32 q + 8 g .. + 7, which is a transposed
@@ -479,6 +476,33 @@ __global__ __launch_bounds__(kDdThreads, 1) void down_gemm_dma_kernel(const uint
         }
 }
 
+template <int MF>
+__global__ __launch_bounds__(kDdThreads, 1) void down_gemm_dma_kernel(const uint16_t *__restrict__ w, int d,
+                                                                      const int *__restrict__ list,
+                                                                      const int *__restrict__ n_list,
+                                                                      const uint16_t *__restrict__ hc, int ldh, int T,
+                                                                      int n_tt, int n_nt, int n_split, int per_xcd,
+                                                                      const uint16_t *__restrict__ zero_row,
+                                                                      float *__restrict__ part, void *__restrict__ y,
+                                                                      int y_bf16)
+{
+    dd_tile<MF, false>(w, d, list, n_list, hc, ldh, T, n_tt, n_nt, n_split, per_xcd, zero_row, part, y, y_bf16);
+}
+
+// The same with weight rows past the caches: one token tile, so every row is read once, on layers of stream_rows.
+template <int MF>
+__global__ __launch_bounds__(kDdThreads, 1) void down_gemm_stream_kernel(const uint16_t *__restrict__ w, int d,
+                                                                         const int *__restrict__ list,
+                                                                         const int *__restrict__ n_list,
+                                                                         const uint16_t *__restrict__ hc, int ldh, int T,
+                                                                         int n_tt, int n_nt, int n_split, int per_xcd,
+                                                                         const uint16_t *__restrict__ zero_row,
+                                                                         float *__restrict__ part, void *__restrict__ y,
+                                                                         int y_bf16)
+{
+    dd_tile<MF, true>(w, d, list, n_list, hc, ldh, T, n_tt, n_nt, n_split, per_xcd, zero_row, part, y, y_bf16);
+}
+
 // y = sum over the splits, in split order, of part[split]; n4 = T * d / 4 vectors.
 __global__ __launch_bounds__(256) void down_gemm_reduce_kernel(const float4 *__restrict__ part, int n_split, size_t n4,
                                                                void *__restrict__ y, int y_bf16)
@@ -537,11 +561,14 @@ static hipError_t launch_dd(const void *w, int d, const int *list, const int *n_
                             int n_split, float *part, void *y, int y_bf16, hipStream_t s, const uint16_t *zero_row)
 {
     const size_t lds = DdRing<MF>::kBytes;
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&down_gemm_dma_kernel<MF>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
     const int n_tt = (T + 64 * MF - 1) / (64 * MF), n_nt = d / kDgBN, per_xcd = (n_tt * n_nt * n_split + 7) / 8;
-    hipLaunchKernelGGL(down_gemm_dma_kernel<MF>, dim3(per_xcd * 8), dim3(kDdThreads), lds, s, (const uint16_t *)w, d, list,
+    // (ldh: the layer's channels rounded up to 64)
+    const bool stream = n_tt == 1 && stream_rows(d, ldh, 1, kStreamPromptBytes);
+    const auto kernel = stream ? down_gemm_stream_kernel<MF> : down_gemm_dma_kernel<MF>;
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       (int)lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kernel, dim3(per_xcd * 8), dim3(kDdThreads), lds, s, (const uint16_t *)w, d, list,
                        n_list, hc, ldh, T, n_tt, n_nt, n_split, per_xcd, zero_row, part, y, y_bf16);
     return hipGetLastError();
 }

@@ -38,8 +38,13 @@ __device__ __forceinline__ void gateup_row(const typename V::vec_t *__restrict__
     // 124.1 -> 122.7; 7B shape, four 97.7 -> 95.4, six 100.0 -> 98.8; float32 d 1024, m 2816, three 48.6 -> 47.4, eight
     // 65.3 -> 64.0; two and three sequences of bf16 layers the same.  The pointers say that they are global: what comes out
     // of the asm as a plain pointer is read by flat loads, which count as LDS operations too and are waited for all at once.
-    typedef uint32_t raw_t __attribute__((ext_vector_type(4)));
-    typedef __attribute__((address_space(1))) const raw_t row_t;
+    typedef __attribute__((address_space(1))) const raw_vec_t row_t;
+    auto row_vec = [](row_t *p) -> decltype(auto) {
+        if constexpr (V::kStream)
+            return __builtin_nontemporal_load(p);
+        else
+            return (*p);  // (a reference)
+    };
     row_t *g = (row_t *)(w + (uint64_t)(uint32_t)j * (uint32_t)channel_vectors(nvec, V::kElems == 8));
     row_t *u = g + nvec;
     asm("" : "+s"(g));
@@ -56,8 +61,8 @@ __device__ __forceinline__ void gateup_row(const typename V::vec_t *__restrict__
         vec_t wg[U], wu[U];
 #pragma unroll
         for (int q = 0; q < U; ++q) {
-            wg[q] = __builtin_bit_cast(vec_t, g[c0 + q * kWave + lane]);
-            wu[q] = __builtin_bit_cast(vec_t, u[c0 + q * kWave + lane]);
+            wg[q] = __builtin_bit_cast(vec_t, row_vec(&g[c0 + q * kWave + lane]));
+            wu[q] = __builtin_bit_cast(vec_t, row_vec(&u[c0 + q * kWave + lane]));
         }
 #pragma unroll
         for (int q = 0; q < U; q += 2) {
@@ -74,7 +79,7 @@ __device__ __forceinline__ void gateup_row(const typename V::vec_t *__restrict__
     constexpr int kTailUnroll = B <= (V::kElems == 8 ? 4 : 3) ? 2 : 1;
 #pragma unroll kTailUnroll
     for (int c = nvec_full + lane; c < nvec; c += kWave) {
-        const vec_t wg = __builtin_bit_cast(vec_t, g[c]), wu = __builtin_bit_cast(vec_t, u[c]);
+        const vec_t wg = __builtin_bit_cast(vec_t, row_vec(&g[c])), wu = __builtin_bit_cast(vec_t, row_vec(&u[c]));
 #pragma unroll
         for (int b = 0; b < B; ++b) {
             vec_t xv = xs[b * nvec + c];
@@ -288,6 +293,9 @@ hipError_t launch_gateup(const void *w, int is_bf16, int d, int m, const void *x
                          const int *n_rows_dev, float *h, const float *nrm, float *cscore, int cs_stride, int n_score,
                          int n_cu, hipStream_t s)
 {
+    if (stream_rows(d, m, is_bf16, kStreamStepBytes))
+        return gateup_dispatch<StreamBF16>(w, d / 8, x, B, rows, n_rows, n_rows_dev, h, m, nrm, cscore, cs_stride,
+                                           n_score, n_cu, s);
     if (is_bf16)
         return gateup_dispatch<VecBF16>(w, d / 8, x, B, rows, n_rows, n_rows_dev, h, m, nrm, cscore, cs_stride,
                                         n_score, n_cu, s);
@@ -337,6 +345,8 @@ hipError_t launch_gateup_select(const void *w, int is_bf16, int d, int m, const 
 {
     GateupSelectArgs sa = {cand_idx, n_cand, n_ret, k, act_stride, mask, active_idx, n_active, selflag,
                            union_list, n_union, counters, err_flag, spin_limit};
+    if (stream_rows(d, m, is_bf16, kStreamStepBytes))
+        return gateup_select_dispatch<StreamBF16>(w, d / 8, x, B, rows, h, m, nrm, cscore, cs_stride, sa, n_cu, fused, s);
     if (is_bf16)
         return gateup_select_dispatch<VecBF16>(w, d / 8, x, B, rows, h, m, nrm, cscore, cs_stride, sa, n_cu, fused, s);
     return gateup_select_dispatch<VecF32>(w, d / 4, x, B, rows, h, m, nrm, cscore, cs_stride, sa, n_cu, fused, s);
@@ -406,14 +416,14 @@ __global__ __launch_bounds__(256) void down_kernel(const typename V::vec_t *__re
             vec_t wv[kDownUnroll];
 #pragma unroll
             for (int q = 0; q < kDownUnroll; ++q)
-                wv[q] = col_ok ? w_down[(uint64_t)(uint32_t)js[i + q] * chan] : V::zero();
+                wv[q] = col_ok ? load_row<V>(w_down, (uint64_t)(uint32_t)js[i + q] * chan) : V::zero();
 #pragma unroll
             for (int q = 0; q < kDownUnroll; ++q)
 #pragma unroll
                 for (int b = 0; b < B; ++b) V::axpy(hs[b][i + q], wv[q], acc[b]);
         }
         for (; i < r1; ++i) {
-            const vec_t wv1 = col_ok ? w_down[(uint64_t)(uint32_t)js[i] * chan] : V::zero();
+            const vec_t wv1 = col_ok ? load_row<V>(w_down, (uint64_t)(uint32_t)js[i] * chan) : V::zero();
 #pragma unroll
             for (int b = 0; b < B; ++b) V::axpy(hs[b][i], wv1, acc[b]);
         }
@@ -535,6 +545,9 @@ hipError_t launch_down(const void *w, int is_bf16, int d, int m, const int *list
                        const float *h, const unsigned char *mask, int mask_stride, int B, float *partial, int n_slabs,
                        void *y, int y_bf16, hipStream_t s, const StepCopy *copy)
 {
+    if (stream_rows(d, m, is_bf16, kStreamStepBytes))
+        return down_dispatch<StreamBF16>(w, d / 8, d, m, list, n_dev, n_host, h, mask, mask_stride, B, partial, n_slabs,
+                                         y, y_bf16, s, copy);
     if (is_bf16)
         return down_dispatch<VecBF16>(w, d / 8, d, m, list, n_dev, n_host, h, mask, mask_stride, B, partial, n_slabs,
                                       y, y_bf16, s, copy);
@@ -568,7 +581,7 @@ __device__ __forceinline__ void split3(float f, uint16_t &hi, uint16_t &mid, uin
 }
 
 // TG groups of 16 tokens; kMask: masks per token (else none)
-template <int TG, bool kMask>
+template <class V, int TG, bool kMask>
 __global__ __launch_bounds__(kSkThreads) void skinny_down_kernel(const uint4 *__restrict__ w, int nvec,
                                                                  const int *__restrict__ list, const int *__restrict__ n_dev,
                                                                  const float *__restrict__ h, int m,
@@ -603,7 +616,7 @@ __global__ __launch_bounds__(kSkThreads) void skinny_down_kernel(const uint4 *__
     uint4 rows[2][8];
     auto request = [&](int set) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) rows[set][i] = wc[(uint64_t)(uint32_t)js[set * kSkChunk + 32 * wave + 8 * g + i] * chan];
+        for (int i = 0; i < 8; ++i) rows[set][i] = load_row<V>(wc, (uint64_t)(uint32_t)js[set * kSkChunk + 32 * wave + 8 * g + i] * chan);
     };
     // h of the 256 channels at `at` as three planes; zero beyond the slab, beyond T and where a mask says so
     auto stage = [&](int set, int at) {
@@ -714,6 +727,7 @@ int skinny_down_slabs(int is_bf16, int d, int m, int n_cu)
     return slabs < 1 ? 1 : (slabs > 64 ? 64 : slabs);
 }
 
+template <class V>
 static hipError_t launch_skinny_down_partials(const void *w, int d, int m, const int *list, const int *n_dev,
                                               const float *h, const unsigned char *mask, int mask_stride, int T,
                                               float *partial, int n_slabs, hipStream_t s)
@@ -725,10 +739,10 @@ static hipError_t launch_skinny_down_partials(const void *w, int d, int m, const
     hipError_t e = hipSuccess;
 #define POP_SK(TG, MK)                                                                                                    \
     do {                                                                                                                  \
-        e = hipFuncSetAttribute(reinterpret_cast<const void *>(&skinny_down_kernel<TG, MK>),                              \
+        e = hipFuncSetAttribute(reinterpret_cast<const void *>(&skinny_down_kernel<V, TG, MK>),                              \
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);                                    \
         if (e != hipSuccess) return e;                                                                                    \
-        hipLaunchKernelGGL((skinny_down_kernel<TG, MK>), grid, dim3(kSkThreads), lds, s, (const uint4 *)w, d / 8, list,   \
+        hipLaunchKernelGGL((skinny_down_kernel<V, TG, MK>), grid, dim3(kSkThreads), lds, s, (const uint4 *)w, d / 8, list,   \
                            n_dev, h, m, mask, mask_stride, T, partial, d);                                                \
     } while (0)
     if (tg == 1 && mask) POP_SK(1, true);
@@ -743,8 +757,12 @@ hipError_t launch_skinny_down(const void *w, int is_bf16, int d, int m, const in
                               const unsigned char *mask, int mask_stride, int T, float *partial, int n_slabs, void *y,
                               int y_bf16, hipStream_t s, const StepCopy *copy)
 {
-    hipError_t e = is_bf16 ? launch_skinny_down_partials(w, d, m, list, n_dev, h, mask, mask_stride, T, partial, n_slabs, s)
-                           : launch_down_f32_partials(w, d, m, list, n_dev, h, mask, mask_stride, T, partial, n_slabs, s);
+    // (a step's sequences or a short prompt)
+    const bool stream = stream_rows(d, m, is_bf16, T <= POP_MAX_BATCH ? kStreamStepBytes : kStreamPromptBytes);
+    hipError_t e =
+        stream    ? launch_skinny_down_partials<StreamBF16>(w, d, m, list, n_dev, h, mask, mask_stride, T, partial, n_slabs, s)
+        : is_bf16 ? launch_skinny_down_partials<VecBF16>(w, d, m, list, n_dev, h, mask, mask_stride, T, partial, n_slabs, s)
+                  : launch_down_f32_partials(w, d, m, list, n_dev, h, mask, mask_stride, T, partial, n_slabs, s);
     if (e != hipSuccess) return e;
     return launch_down_reduce(partial, n_slabs, T * d, y, y_bf16, copy, s);
 }

@@ -80,16 +80,12 @@ hipError_t launch_input_squares(const void *x, int is_bf16, int B, int d, float 
     return hipGetLastError();
 }
 
-template <class V>
-__device__ __forceinline__ void is_unpack(const typename V::vec_t &v, float (&f)[8]);
-template <>
-__device__ __forceinline__ void is_unpack<VecBF16>(const uint4 &v, float (&f)[8])
+__device__ __forceinline__ void is_unpack(const uint4 &v, float (&f)[8])
 {
     f[0] = bf16_lo(v.x), f[1] = bf16_hi(v.x), f[2] = bf16_lo(v.y), f[3] = bf16_hi(v.y);
     f[4] = bf16_lo(v.z), f[5] = bf16_hi(v.z), f[6] = bf16_lo(v.w), f[7] = bf16_hi(v.w);
 }
-template <>
-__device__ __forceinline__ void is_unpack<VecF32>(const float4 &v, float (&f)[8])
+__device__ __forceinline__ void is_unpack(const float4 &v, float (&f)[8])
 {
     f[0] = v.x, f[1] = v.y, f[2] = v.z, f[3] = v.w;
     f[4] = f[5] = f[6] = f[7] = 0.f;
@@ -119,8 +115,8 @@ __global__ __launch_bounds__(256) void input_side_scores_kernel(const typename V
         float a0 = 0.f, a1 = 0.f;
         for (int c = lane; c < nvec; c += kWave) {
             float fg[8], fu[8];
-            is_unpack<V>(g[c], fg);
-            is_unpack<V>(u[c], fu);
+            is_unpack(load_row<V>(g, c), fg);
+            is_unpack(load_row<V>(u, c), fu);
 #pragma unroll
             for (int e = 0; e < E; ++e) {
                 const float ww = fmaf(fg[e], fg[e], fu[e] * fu[e]);
@@ -146,8 +142,16 @@ hipError_t launch_input_side_scores(const void *w, int is_bf16, int d, const flo
     int bx = (n_rows + 3) / 4;
     if (bx > 1024) bx = 1024;
     dim3 grid(bx, (S + 1) / 2);
+    // (a prompt's scores over all channels; a step's candidates are read again for h)
+    const bool stream = !rows && S <= 2 && stream_rows(d, n_rows, is_bf16, kStreamPromptBytes);
     hipError_t e;
-    if (is_bf16) {
+    if (stream) {
+        e = hipFuncSetAttribute(reinterpret_cast<const void *>(&input_side_scores_kernel<StreamBF16>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(input_side_scores_kernel<StreamBF16>, grid, dim3(256), lds, s, (const uint4 *)w, d / 8, s2, S,
+                           rows, n_rows, out, out_stride);
+    } else if (is_bf16) {
         e = hipFuncSetAttribute(reinterpret_cast<const void *>(&input_side_scores_kernel<VecBF16>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;

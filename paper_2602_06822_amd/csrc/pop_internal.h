@@ -46,6 +46,16 @@ __host__ __device__ __forceinline__ constexpr int channel_gap(int nvec, int is_b
 {
     return is_bf16 && (nvec == 512 || nvec == 1024) ? 8 : 0;
 }
+// Weight rows that a launch reads once are loaded past the caches (non-temporal) on layers too large for the next pass to find
+// them there.  A plain read of rows from memory: 5.7-6.0 TB/s with ordinary loads, 6.4 with these; of rows that the 256 MB
+// last-level cache holds up to 7 % slower.  So the rule is the size of a layer's weights (3 d m, bf16), and as two layers in turn
+// stay in that cache up to about 128 MB each, that is where it lies for prompts: one layer of 67 MB, 256 tokens 56.9 us without /
+// 59.8 with, 24 tokens 35.8 / 36.9, of 101 MB 70.8 / 71.3 and 44.1 / 44.5, of 270 MB 69.3 / 64.3 (24 tokens).  Decode steps, which
+// do nothing but read, gain earlier: two layers of 67 MB 41.1 / 40.7 and four 86.9 / 81.8 (four sequences, two layers: 58.4 / 57.9),
+// of 49 MB 37.8 / 38.8 and 82.0 / 77.6 (51.8 / 53.9), of 101 MB 45.6 / 43.3, of 270 MB 155.1 / 143.9 (four).
+constexpr long long kStreamStepBytes = 64ll << 20, kStreamPromptBytes = 128ll << 20;
+inline bool stream_rows(int d, int m, int is_bf16, long long limit) { return is_bf16 && 6ll * d * m >= limit; }
+
 // From one channel's weights to the next's.
 __host__ __device__ __forceinline__ constexpr int channel_vectors(int nvec, int is_bf16)
 {
@@ -255,11 +265,12 @@ struct FusedPlan {
     int n_wg, block, per;
     int n_static;  // retained rounds per worker
     bool gap;      // the layer's channels are channel_gap() apart
+    bool stream;   // weight rows past the caches (stream_rows)
 };
 int fused_max_workgroups();
 size_t fused_selw_words();  // 64-bit words of the selection-word buffer (one per workgroup, spaced apart)
 // Launch shape for (d, dtype, region sizes); false when the fused kernel does not support the shape.
-bool fused_plan(int d, int is_bf16, int n_ret, int n_cand, int wg_target, FusedPlan *pl);
+bool fused_plan(int d, int m, int is_bf16, int n_ret, int n_cand, int wg_target, FusedPlan *pl);
 // Largest grid of this shape that is co-resident on n_cu compute units.
 hipError_t fused_resident_limit(int is_bf16, const FusedPlan &pl, int n_cu, int *max_wg);
 hipError_t launch_decode_fused(const FusedPlan &pl, int is_bf16, FusedParams &p, hipStream_t s);

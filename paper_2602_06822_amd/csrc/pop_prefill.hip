@@ -21,6 +21,8 @@
 // float32: FP64 matrix-core tiles (gateup_f32_kernel), described there.
 #include <stdlib.h>
 
+#include <type_traits>
+
 #include "pop_internal.h"
 
 namespace pop {
@@ -431,7 +433,7 @@ __host__ __device__ inline PmTiles pm_tiles(int n_ch, int n_tt, int mf, int n_cu
 // beyond the last at the last step), so each wait counts exactly.
 // Measured, d 4096, m 11008 (before: eight waves of 64 tokens x 96 rows, 32x32x16 products, reads and products of all
 // waves in lockstep): 512 tokens 102 -> 80 us (1.16 PFLOP/s), 2048 tokens 380 -> 292 us (1.26), 256 tokens 54 us.
-template <int MF, int F, int kMode, class Ring>
+template <int MF, int F, int kMode, class Ring, bool kStream>
 __device__ __forceinline__ void pm_tile(const uint16_t *__restrict__ w, const uint16_t *__restrict__ x, int T, int d,
                                         int m, int n_ch, int n_tt, int logical, float *__restrict__ s2_part,
                                         const PfStore &st, uint16_t *lds, float (&colsum)[4][kPfChunk])
@@ -484,7 +486,7 @@ __device__ __forceinline__ void pm_tile(const uint16_t *__restrict__ w, const ui
     };
     auto load_b = [&](int p, int buf, int k0) {
         __builtin_amdgcn_global_load_lds((glb_t *)(pb[p] + k0), (lds_t *)(Bs + buf * BT + (p * 32 + wave * 8) * kPfBK), 16,
-                                         0, 0);
+                                         0, kStream ? 2 : 0);  // (2: non-temporal)
     };
 
     f32x4_t acc[MF][F];
@@ -687,7 +689,48 @@ __device__ __forceinline__ void pm_tile(const uint16_t *__restrict__ w, const ui
 }
 
 // One workgroup per compute unit; each walks its share of the tiles of its XCD (the token tiles of a channel chunk are
-// neighbours there and meet in its L2).
+// neighbours there and meet in its L2).  prefill_stream_kernel: weight rows past the caches, for layers of stream_rows and up to
+// two token tiles per chunk, which ask for a row at the same time (512 tokens, d 4096, m 11008: 87.9 -> 81.3 us; 2048 tokens
+// no change); with the narrow chunks' deeper ring where it is used.  A list of channels reads part of the layer only: one token
+// tile, and layers half as large again (100 tokens, half of d 4096, m 5504: 42.0 without / 42.8 with; two tiles, 333 tokens at
+// the 13B shape 107.6 / 108.3).
+template <int kMode>
+inline bool pm_streams(int d, int m, int n_tt)
+{
+    constexpr bool kList = kMode == 1 || kMode == 4;
+    return n_tt <= (kList ? 1 : 2) && stream_rows(d, m, 1, kList ? kStreamPromptBytes * 3 / 2 : kStreamPromptBytes);
+}
+constexpr bool pm_deep(int mf, int f, int mode) { return mf == kPmDeepMF && f <= kPmDeepF && (mode == 0 || mode == 2); }
+template <int MF, int kMode>
+__global__ __launch_bounds__(kPmThreads, 1) void prefill_stream_kernel(const uint16_t *__restrict__ w,
+                                                                       const uint16_t *__restrict__ x, int T, int d, int m,
+                                                                       int n_tt, PmTiles g, float *__restrict__ s2_part,
+                                                                       PfStore st)
+{
+    extern __shared__ __attribute__((aligned(16))) uint16_t pf_lds[];
+    __shared__ float colsum[4][kPfChunk];
+    int n_ch = m;  // channels the chunks run over
+    if (kMode == 1 || kMode == 4) {
+        n_ch = *st.n_list;
+        g = pm_tiles(n_ch, n_tt, MF, st.n_cu);
+    }
+    for (int i = blockIdx.x / 8; i < g.per_xcd; i += gridDim.x / 8) {
+        const int logical = (blockIdx.x % 8) * g.per_xcd + i;
+        if (logical >= g.total) break;
+        switch (g.f) {
+#define POP_PM(FF)                                                                                                         \
+    case FF: {                                                                                                             \
+        typedef typename std::conditional<pm_deep(MF, FF, kMode), PmDeepRing, PmRing<MF>>::type ring_t;                    \
+        pm_tile<MF, FF, kMode, ring_t, true>(w, x, T, d, m, n_ch, n_tt, logical, s2_part, st, pf_lds, colsum);             \
+        break;                                                                                                             \
+    }
+            POP_PM(12) POP_PM(11) POP_PM(10) POP_PM(8) POP_PM(7) POP_PM(6) POP_PM(4)
+#undef POP_PM
+        }
+        __syncthreads();  // the next tile's direct loads overwrite the LDS
+    }
+}
+
 template <int MF, int kMode>
 __global__ __launch_bounds__(kPmThreads, 1) void prefill_mma_kernel(const uint16_t *__restrict__ w,
                                                                     const uint16_t *__restrict__ x, int T, int d, int m,
@@ -707,7 +750,7 @@ __global__ __launch_bounds__(kPmThreads, 1) void prefill_mma_kernel(const uint16
         switch (g.f) {
 #define POP_PM(FF)                                                                               \
     case FF:                                                                                                 \
-        pm_tile<MF, FF, kMode, PmRing<MF>>(w, x, T, d, m, n_ch, n_tt, logical, s2_part, st, pf_lds, colsum); \
+        pm_tile<MF, FF, kMode, PmRing<MF>, false>(w, x, T, d, m, n_ch, n_tt, logical, s2_part, st, pf_lds, colsum); \
         break;
             POP_PM(12) POP_PM(11) POP_PM(10) POP_PM(8) POP_PM(7) POP_PM(6) POP_PM(4)
 #undef POP_PM
@@ -731,7 +774,7 @@ __global__ __launch_bounds__(kPmThreads, 1) void prefill_deep_kernel(const uint1
         switch (g.f) {
 #define POP_PM(FF)                                                                                                \
     case FF:                                                                                                      \
-        pm_tile<kPmDeepMF, FF, kMode, PmDeepRing>(w, x, T, d, m, m, n_tt, logical, s2_part, st, pf_lds, colsum); \
+        pm_tile<kPmDeepMF, FF, kMode, PmDeepRing, false>(w, x, T, d, m, m, n_tt, logical, s2_part, st, pf_lds, colsum); \
         break;
             POP_PM(8) POP_PM(7) POP_PM(6) POP_PM(4)
 #undef POP_PM
@@ -1036,10 +1079,12 @@ static hipError_t launch_pm(const void *w, int d, int m, const void *x, int T, c
     // (the list form learns its F on the device; wider chunks do not leave the room)
     if constexpr (MF == kPmDeepMF && (kMode == 0 || kMode == 2))
         if (g.f <= kPmDeepF) kernel = prefill_deep_kernel<kMode>, lds = PmDeepRing::kBytes;
+    const int n_tt = (T + 64 * MF - 1) / (64 * MF);
+    if (pm_streams<kMode>(d, m, n_tt)) kernel = prefill_stream_kernel<MF, kMode>;
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
                                        (int)lds);
     if (e != hipSuccess) return e;
-    const int n_tt = (T + 64 * MF - 1) / (64 * MF), all = kMode == 1 || kMode == 4 ? n_cu : (g.total < n_cu ? g.total : n_cu);
+    const int all = kMode == 1 || kMode == 4 ? n_cu : (g.total < n_cu ? g.total : n_cu);
     hipLaunchKernelGGL(kernel, dim3((all + 7) / 8 * 8), dim3(kPmThreads), lds, s, (const uint16_t *)w, (const uint16_t *)x, T,
                        d, m, n_tt, g, s2_part, st);
     return hipGetLastError();

@@ -13,6 +13,7 @@ struct VecBF16 {
     typedef uint4 vec_t;
     typedef float acc_t;
     static constexpr int kElems = 8;
+    static constexpr bool kStream = false;
     static __device__ __forceinline__ vec_t zero() { return make_uint4(0, 0, 0, 0); }
     static __device__ __forceinline__ float dot(const vec_t &w, const vec_t &x, float acc)
     {
@@ -39,6 +40,7 @@ struct VecF32 {
     typedef float4 vec_t;
     typedef double acc_t;
     static constexpr int kElems = 4;
+    static constexpr bool kStream = false;
     static __device__ __forceinline__ vec_t zero() { return make_float4(0.f, 0.f, 0.f, 0.f); }
     static __device__ __forceinline__ double dot(const vec_t &w, const vec_t &x, double acc)
     {
@@ -56,6 +58,22 @@ struct VecF32 {
         acc[3] = fmaf(a, w.w, acc[3]);
     }
 };
+
+// bf16 rows of a large layer: read past the caches (stream_rows).
+struct StreamBF16 : VecBF16 {
+    static constexpr bool kStream = true;
+};
+
+// Vector `at` of a weight row.
+typedef uint32_t raw_vec_t __attribute__((ext_vector_type(4)));
+template <class V, class I>
+__device__ __forceinline__ decltype(auto) load_row(const typename V::vec_t *row, I at)
+{
+    if constexpr (V::kStream)
+        return __builtin_bit_cast(typename V::vec_t, __builtin_nontemporal_load(reinterpret_cast<const raw_vec_t *>(row + at)));
+    else
+        return (row[at]);  // (a reference)
+}
 
 // ---- cross-lane sums in double (DPP moves on the two halves, no LDS).  The partial dot products of a bf16 row are
 // float32 values whose sum can cancel; adding them up in double keeps the rounding of the cross-lane tree (a dozen
