@@ -129,12 +129,14 @@ __device__ __forceinline__ void pf_chunk_scores(const float (&colsum)[TW][kPfChu
         float tot = 0.f;
 #pragma unroll
         for (int q = 0; q < TW; ++q) tot += colsum[q][tid];
-        if (st.fin_ctr)
+        if (st.fin_ctr && n_ttiles == 1)  // (no other tile to wait for)
+            st.scores[c0 + tid] = (float)((double)st.nrm[c0 + tid] * sqrt((double)tot));
+        else if (st.fin_ctr)
             coherent_store(&s2_part[(size_t)ttile * m + c0 + tid], tot);
         else
             s2_part[(size_t)ttile * m + c0 + tid] = tot;
     }
-    if (st.fin_ctr) {
+    if (st.fin_ctr && n_ttiles > 1) {
         // Scores of this chunk's channels (Eq. 3): I_j = n_j * sqrt(sum over the token tiles, in tile order and in
         // double, of the partial sums).  The partial rows are written through and read with device-coherent loads;
         // a tile counts itself in once its own row has been acknowledged, and the tile that completes the count does
