@@ -188,8 +188,8 @@ int ffn_scratch(pop_layer *L, int T, bool keep_all, int *ldh, int *n_split, hipS
     if (rc == POP_OK && L->ffn_hc_cap != hc_before)
         POP_HIP(launch_fill_int((int *)L->ffn_hc, (int)(L->ffn_hc_cap / 2), 0, s));
     if (rc == POP_OK && !L->zero_row) {
-        if (!dev_alloc((void **)&L->zero_row, 256)) return POP_ENOMEM;
-        POP_HIP(launch_fill_int((int *)L->zero_row, 64, 0, s));
+        if (!dev_alloc((void **)&L->zero_row, kZeroRowBytes)) return POP_ENOMEM;
+        POP_HIP(launch_fill_int((int *)L->zero_row, kZeroRowBytes / 4, 0, s));
     }
     size_t part_rows = *n_split > 1 ? (size_t)*n_split * T : 0;
     if (shorter_too)  // a shorter prompt is split more ways: room for every prompt length up to T
@@ -199,7 +199,9 @@ int ffn_scratch(pop_layer *L, int T, bool keep_all, int *ldh, int *n_split, hipS
         }
     if (rc == POP_OK && part_rows)
         rc = grow((void **)&L->ffn_part, &L->ffn_part_cap, part_rows * L->d, sizeof(float));
-    if (rc == POP_OK && keep_all) rc = grow((void **)&L->ffn_hall, &L->ffn_hall_cap, (size_t)T * *ldh, sizeof(uint16_t));
+    // (by token or by channel)
+    if (rc == POP_OK && keep_all)
+        rc = grow((void **)&L->ffn_hall, &L->ffn_hall_cap, (size_t)((T + 63) / 64 * 64) * *ldh + kRowsSlack, sizeof(uint16_t));
     return rc;
 }
 
@@ -532,11 +534,14 @@ int pop_prefill_forward(pop_layer_t *L, const void *x, int T, int n_ret, int n_c
     L->has_partition = false;
     L->has_step = false;
     int ldh = 0, n_split = 1;
+    const bool by_channel = down_gemm_by_channel(d);
+    const int ldt = (T + 63) / 64 * 64;
     if (keep) {
         int rc = ffn_scratch(L, T, true, &ldh, &n_split, s);
         if (rc != POP_OK) return rc;
         const PrefillScores fin{L->pf_ctr, L->nrm, L->scores};
-        POP_HIP(launch_prefill_gateup_keep_bf16(L->w, d, m, x, T, L->s2_part, L->ffn_hall, ldh, L->n_cu, s, &fin));
+        POP_HIP(launch_prefill_gateup_keep_bf16(L->w, d, m, x, T, L->s2_part, L->ffn_hall, by_channel ? ldt : ldh, by_channel, L->n_cu,
+                                                s, &fin));
     } else {
         if (T == 0) {
             POP_HIP(launch_fill_int((int *)L->scores, m, 0, s));  // no tokens: all importances zero
@@ -564,6 +569,11 @@ int pop_prefill_forward(pop_layer_t *L, const void *x, int T, int n_ret, int n_c
         if (rc != POP_OK) return rc;
     }
     if (T == 0) return POP_OK;  // no token rows to produce
+    if (keep && by_channel) {
+        POP_HIP(launch_down_gemm_rows(L->w, d, m, L->top_list, L->top_list + m, L->ffn_hall, ldt, T, n_split, L->n_cu, L->ffn_part, y,
+                                      ydtype == POP_BF16, s, L->zero_row));
+        return POP_OK;
+    }
     if (keep) {
         POP_HIP(launch_compact_hidden(L->ffn_hall, ldh, T, L->top_list, L->top_list + m, n_ret + k0, L->ffn_hc, ldh, s));
         POP_HIP(launch_down_gemm_bf16(L->w, d, L->top_list, L->top_list + m, L->ffn_hc, ldh, T, n_split, L->n_cu, L->ffn_part, y,

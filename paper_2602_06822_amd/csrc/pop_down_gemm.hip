@@ -24,6 +24,7 @@ namespace pop {
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 typedef short s16x4_t __attribute__((ext_vector_type(4)));
 typedef short s16x8_t __attribute__((ext_vector_type(8)));
@@ -242,6 +243,32 @@ struct DdRing {
     static constexpr size_t kBytes = (size_t)(NA * 64 * MF * kDgBK + NB * kDgBK * kDgBN) * sizeof(uint16_t) + kDdSlots * kDgBK * 4;
 };
 
+// The tile's results: register v of product e is token 4 (lane / 16) + v of the fragment, column 8 (lane % 16) + e; row0 is register
+// 0's token in fragment 0, fragments are `apart` tokens apart.
+template <int MF>
+__device__ __forceinline__ void dd_store(const f32x4_t (&acc)[MF][kDgBN / 16], int row0, int apart, size_t col, int split, int T,
+                                         int d, float *__restrict__ part, void *__restrict__ y, int y_bf16)
+{
+#pragma unroll
+    for (int i = 0; i < MF; ++i)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int t = row0 + i * apart + v;
+            if (t >= T) continue;
+            if (part || !y_bf16) {
+                float4 *dst = reinterpret_cast<float4 *>((part ? part + (size_t)split * T * d : (float *)y) + (size_t)t * d + col);
+                dst[0] = make_float4(acc[i][0][v], acc[i][1][v], acc[i][2][v], acc[i][3][v]);
+                dst[1] = make_float4(acc[i][4][v], acc[i][5][v], acc[i][6][v], acc[i][7][v]);
+            } else {
+                uint32_t q[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    q[e] = (uint32_t)f32_to_bf16(acc[i][2 * e][v]) | ((uint32_t)f32_to_bf16(acc[i][2 * e + 1][v]) << 16);
+                *reinterpret_cast<uint4 *>((uint16_t *)y + (size_t)t * d + col) = make_uint4(q[0], q[1], q[2], q[3]);
+            }
+        }
+}
+
 template <int MF, bool kStream>
 __device__ __forceinline__ void dd_tile(const uint16_t *__restrict__ w, int d, const int *__restrict__ list,
                                         const int *__restrict__ n_list, const uint16_t *__restrict__ hc, int ldh, int T,
@@ -250,7 +277,6 @@ __device__ __forceinline__ void dd_tile(const uint16_t *__restrict__ w, int d, c
 {
     typedef __attribute__((address_space(3))) void lds_t;
     typedef __attribute__((address_space(1))) const void glb_t;
-    typedef float f32x4_t __attribute__((ext_vector_type(4)));
     constexpr int NA = DdRing<MF>::NA, NB = DdRing<MF>::NB, F = kDgBN / 16;
     constexpr int BM = 64 * MF, AT = BM * kDgBK, BT = kDgBK * kDgBN;  // elements per stage
     constexpr int PA = BM / 32, PB = 4;  // direct loads per wave and k-step (and one of channel numbers)
@@ -453,27 +479,7 @@ __device__ __forceinline__ void dd_tile(const uint16_t *__restrict__ w, int d, c
             for (int f = 0; f < F; ++f) asm volatile("" : "+a"(acc[i][f]));  // (no read of them moves ahead of the wait)
     }
 
-    // register v of product e is token 4 (lane / 16) + v of the fragment, column 8 (lane % 16) + e
-    const int row0 = t0 + wave * MF * 16 + lane / 16 * 4;
-    const size_t col = n0 + lane % 16 * 8;
-#pragma unroll
-    for (int i = 0; i < MF; ++i)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int t = row0 + i * 16 + v;
-            if (t >= T) continue;
-            if (part || !y_bf16) {
-                float4 *dst = reinterpret_cast<float4 *>((part ? part + (size_t)split * T * d : (float *)y) + (size_t)t * d + col);
-                dst[0] = make_float4(acc[i][0][v], acc[i][1][v], acc[i][2][v], acc[i][3][v]);
-                dst[1] = make_float4(acc[i][4][v], acc[i][5][v], acc[i][6][v], acc[i][7][v]);
-            } else {
-                uint32_t q[4];
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    q[e] = (uint32_t)f32_to_bf16(acc[i][2 * e][v]) | ((uint32_t)f32_to_bf16(acc[i][2 * e + 1][v]) << 16);
-                *reinterpret_cast<uint4 *>((uint16_t *)y + (size_t)t * d + col) = make_uint4(q[0], q[1], q[2], q[3]);
-            }
-        }
+    dd_store<MF>(acc, t0 + wave * MF * 16 + lane / 16 * 4, 16, n0 + lane % 16 * 8, split, T, d, part, y, y_bf16);
 }
 
 template <int MF>
@@ -501,6 +507,220 @@ __global__ __launch_bounds__(kDdThreads, 1) void down_gemm_stream_kernel(const u
                                                                          int y_bf16)
 {
     dd_tile<MF, true>(w, d, list, n_list, hc, ldh, T, n_tt, n_nt, n_split, per_xcd, zero_row, part, y, y_bf16);
+}
+
+// The same contraction over H by channel, ht[j][ldt] of all m channels (written so by the prompt's own contraction): both operands
+// are rows of the listed channels, so there is no gather of H's columns in front (17 us at 2048 tokens, 6 at an expert's 256).
+// H tile: MF panels of 64 channels x 64 tokens, rows of 128 bytes as they come; a wave owns 16 tokens of every panel (its fragment i
+// is of panel i) and fetches them with the transposing LDS read: of each 16 lanes, lane l points at the 4 tokens 4 (l % 4) .. of
+// row l / 4 and receives the 4 channels of token l, twice for the 8 of a fragment.  The 32-byte pieces of row r are stored at piece
+// ^ ((r / 2) % 2 + 2 ((r / 8) % 2)): the eight rows of a half wave's read fall into different banks.
+// Everything else as in dd_tile: list positions beyond the a channels are rows of zeros in both operands; tokens beyond T belong to
+// rows that are not stored (behind the last row kRowsSlack elements are readable).  A step's channel numbers are read once, for the
+// H rows NA steps and the weight rows NB - 1 steps ahead, and loaded a step earlier than there.
+template <int MF, bool kStream>
+__global__ __launch_bounds__(kDdThreads, 1) void down_gemm_rows_kernel(const uint16_t *__restrict__ w, int d,
+                                                                       const int *__restrict__ list,
+                                                                       const int *__restrict__ n_list,
+                                                                       const uint16_t *__restrict__ ht, int ldt, int T,
+                                                                       int n_tt, int n_nt, int n_split, int per_xcd,
+                                                                       const uint16_t *__restrict__ zero_row,
+                                                                       float *__restrict__ part, void *__restrict__ y,
+                                                                       int y_bf16)
+{
+    constexpr int NA = DdRing<MF>::NA, NB = DdRing<MF>::NB, F = kDgBN / 16;
+    constexpr int BM = 64 * MF, PT = 64 * kDgBK, AT = MF * PT, BT = kDgBK * kDgBN;  // elements per panel and stage
+    constexpr int PA = 2 * MF, PB = 4;  // direct loads per wave and k-step (and one of channel numbers)
+    extern __shared__ __attribute__((aligned(16))) uint16_t dg_lds[];
+    uint16_t *As = dg_lds;            // [NA][MF][64 * 64]
+    uint16_t *Bs = dg_lds + NA * AT;  // [NB][64 * 128]
+    int *Cs = reinterpret_cast<int *>(Bs + NB * BT);  // [8][64]
+
+    const int logical = dg_xcd_logical_block(blockIdx.x, per_xcd);
+    if (logical >= n_tt * n_nt * n_split) return;
+    const int ttile = logical % n_tt, ntile = (logical / n_tt) % n_nt, split = logical / (n_tt * n_nt);
+    const int t0 = ttile * BM, n0 = ntile * kDgBN;
+
+    const int a = *n_list;
+    const int steps_all = (a + kDgBK - 1) / kDgBK, steps_per = (steps_all + n_split - 1) / n_split;
+    const int ks0 = min(split * steps_per, steps_all), ks1 = min(ks0 + steps_per, steps_all);
+    const int n_steps = ks1 - ks0;
+
+    const int tid = threadIdx.x, lane = tid % kWave;
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+
+    f32x4_t acc[MF][F];
+#pragma unroll
+    for (int i = 0; i < MF; ++i)
+#pragma unroll
+        for (int f = 0; f < F; ++f)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) acc[i][f][v] = 0.f;
+
+    if (n_steps > 0) {
+        // direct loads.  H: half q of a panel is 32 rows, 8 of them by this wave, this lane the unit that belongs at position lane % 8
+        // of row a_row; the same rows of every panel.  Weights: pass p covers rows 16 p + 4 w + lane / 16, unit lane % 16.
+        const int a_row = wave * 8 + lane / 8;
+        const int a_src = ((lane % 8 / 2) ^ (lane / 16 % 2 + 2 * (wave % 2))) * 16 + lane % 2 * 8;
+        const uintptr_t a_col = (uintptr_t)(ht + t0 + a_src), a_zero = (uintptr_t)(zero_row + a_src);
+        const uint32_t a_stride = (uint32_t)ldt * (uint32_t)sizeof(uint16_t);
+        const int b_row = wave * 4 + lane / 16;
+        const uintptr_t b_col = (uintptr_t)(w + 2 * d + n0 + (lane % 16) * 8), b_zero = (uintptr_t)(zero_row + (lane % 16) * 8);
+        const uint32_t b_stride = (uint32_t)(channel_elems_bf16(d) * sizeof(uint16_t));
+        // (direct loads as inline assembly: the compiler takes a transposing read for one of everything that direct loads write, and
+        // would wait for all of them in front of it.  They have no register results, and all waits for them are the counted ones.)
+        auto lds_at = [](const void *p) { return __builtin_amdgcn_readfirstlane((int)(uint32_t)(uintptr_t)p); };
+        auto load_channels = [&](int step) {
+            const int *src = list + min(min(ks0 + step, ks1 - 1) * kDgBK + lane, a - 1);
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off"
+                         :
+                         : "s"(lds_at(Cs + step % kDdSlots * kDgBK)), "v"(src));
+        };
+        // (read with their own wait, as in dd_tile)
+        auto channels = [&](int (&ca)[2], int (&cb)[PB], int step_a, int step_b) {
+            const uint32_t at_a = (uint32_t)(uintptr_t)(Cs + step_a % kDdSlots * kDgBK + a_row);
+            const uint32_t at_b = (uint32_t)(uintptr_t)(Cs + step_b % kDdSlots * kDgBK + b_row);
+            asm volatile("ds_read_b32 %0, %6\n\tds_read_b32 %1, %6 offset:128\n\tds_read_b32 %2, %7\n\t"
+                         "ds_read_b32 %3, %7 offset:64\n\tds_read_b32 %4, %7 offset:128\n\tds_read_b32 %5, %7 offset:192\n\t"
+                         "s_waitcnt lgkmcnt(0)"
+                         : "=&v"(ca[0]), "=&v"(ca[1]), "=&v"(cb[0]), "=&v"(cb[1]), "=&v"(cb[2]), "=&v"(cb[3])
+                         : "v"(at_a), "v"(at_b)
+                         : "memory");
+        };
+        // A row's address, with a row of zeros beyond the list (selected with masks: no branch around a load).
+        auto row_of = [&](int c, int row, int step, uintptr_t col, uint32_t stride, uintptr_t zero) {
+            const int ks = ks0 + step, n_live = ks < ks1 ? a - ks * kDgBK : 0;
+            const uintptr_t live = -(uintptr_t)(row < n_live), at = col + (uint64_t)(uint32_t)c * stride;
+            return zero ^ ((at ^ zero) & live);
+        };
+        // pass p: panel p / 2, rows 32 (p % 2) ..
+        auto load_a = [&](const uintptr_t (&rows)[2], int p, int buf) {
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
+                         :
+                         : "s"(lds_at(As + buf * AT + p / 2 * PT + (p % 2 * 32 + wave * 8) * 64)), "v"(rows[p % 2] + p / 2 * 128));
+        };
+        auto load_b = [&](int c, int p, int buf, int step) {
+            const uintptr_t row = row_of(c, b_row + 16 * p, step, b_col, b_stride, b_zero);
+            const int to = lds_at(Bs + buf * BT + (p * 16 + wave * 4) * kDgBN);
+            if constexpr (kStream)
+                asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off nt" : : "s"(to), "v"(row));
+            else
+                asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(to), "v"(row));
+        };
+        // Fragment reads.  H: lanes 16 g .. + 15 read rows 32 q + 8 g + 4 half + (lane % 16) / 4.  Weights as in dd_tile.
+        const uint16_t *Al = As + (lane / 16 * 8 + lane % 16 / 4) * 64 +
+                             (wave ^ (lane % 16 / 8 + 2 * (lane / 16 % 2))) * 16 + lane % 4 * 4;
+        const uint16_t *Bl = Bs + (lane / 16) * 8 * kDgBN + (lane % 16) * 8;
+        s16x4_t af[2][MF][2];
+        bf16x8_t rows[2][8];
+        constexpr int NR = 8 + 2 * MF, NP = MF * F;
+        auto fetch = [&](const uint16_t *Ab, const uint16_t *Bb, int i, int q, int set) {
+            if (i < 8)
+                rows[set][i] = *reinterpret_cast<const bf16x8_t *>(Bb + (q * 32 + i) * kDgBN);
+            else
+                af[set][(i - 8) / 2][i % 2] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                    (s16x4_t __attribute__((address_space(3))) *)(Ab + (i - 8) / 2 * PT + (q * 32 + i % 2 * 4) * 64));
+        };
+        uint32_t bw[2][4];
+        auto pair = [&](int e, int q, int set) {
+            const u32x4_t r0 = __builtin_bit_cast(u32x4_t, rows[set][2 * q]);
+            const u32x4_t r1 = __builtin_bit_cast(u32x4_t, rows[set][2 * q + 1]);
+            bw[e % 2][q] = __builtin_amdgcn_perm(r1[e / 2], r0[e / 2], e % 2 ? 0x07060302u : 0x05040100u);
+        };
+        auto product = [&](int i, int set) {
+            const int e = i / MF, m_ = i % MF;
+            const u32x4_t b = {bw[e % 2][0], bw[e % 2][1], bw[e % 2][2], bw[e % 2][3]};
+            const s16x8_t h = __builtin_shufflevector(af[set][m_][0], af[set][m_][1], 0, 1, 2, 3, 4, 5, 6, 7);
+            // (wait states as in dd_tile)
+            if (MF < 3 && m_ == 0)
+                asm volatile("s_nop 1\n\tv_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc[m_][e]) : "v"(h), "v"(b));
+            else
+                asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc[m_][e]) : "v"(h), "v"(b));
+            constexpr int kGaps = MF < 3 ? 1 : MF - 2;
+            if (m_ < kGaps && (MF > 1 || e + 1 < F)) {
+#pragma unroll
+                for (int q = m_ * 4 / kGaps; q < (m_ + 1) * 4 / kGaps; ++q) pair((e + 1) % F, q, e + 1 < F ? set : set ^ 1);
+            }
+        };
+        auto first_pairs = [&](int set) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) pair(0, q, set);
+        };
+        // Requests in program order: ... A(s + NA - 1) | C(s + NB + 2), B(s + NB - 1) [wait for step s + 1] A(s + NA) | ...: the
+        // wait may leave in flight what was issued after A(s + 1), B(s + 1) and the C that step s + 1 reads, C(s + 1 + NB) at most,
+        // issued one step before
+        constexpr int kAfterA = (NA - 1) * (PB + 1) + (NA - 2) * PA, kAfterB = (NB - 2) * (PA + PB + 1);
+        constexpr int kAfterC = PA + 2 * PB + 1;
+        constexpr int kRows = kAfterA < kAfterB ? kAfterA : kAfterB, kYounger = kRows < kAfterC ? kRows : kAfterC;
+        static_assert(kYounger < 64 && (NB - 2) * PB + (NA - 1) * PA < 64, "vmcnt is a 6-bit counter");
+        static_assert(NB + 3 <= kDdSlots && NA <= NB && NA >= 2 && NB >= 3, "rings");
+        static_assert(kYounger <= (NB - 3) * PB + (NA - 2) * PA + PB + 1, "the wait of the first step");
+        for (int q = 0; q <= NB + 1; ++q) load_channels(q);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        int cha[2], chn[PB];
+        uintptr_t ra[2];
+        constexpr int kDeep = NA > NB - 1 ? NA : NB - 1;
+#pragma unroll
+        for (int q = 0; q < kDeep; ++q) {
+            channels(cha, chn, q, q);
+            if (q < NB - 1) {
+#pragma unroll
+                for (int p = 0; p < PB; ++p) load_b(chn[p], p, q, q);
+            }
+            if (q < NA) {
+#pragma unroll
+                for (int e = 0; e < 2; ++e) ra[e] = row_of(cha[e], a_row + 32 * e, q, a_col, a_stride, a_zero);
+#pragma unroll
+                for (int p = 0; p < PA; ++p) load_a(ra, p, q);
+            }
+        }
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((NB - 2) * PB + (NA - 1) * PA) : "memory");
+        int abuf = 0, bbuf = 0, bprev = NB - 1;
+        constexpr int kSpread = NP > 8 ? NP * 3 / 4 : NP;  // products the reads are spread over: the last have time to arrive
+#pragma unroll
+        for (int i = 0; i < NR; ++i) fetch(Al, Bl, i, 0, 0);
+        first_pairs(0);
+        for (int s = 0; s < n_steps; ++s) {
+            const uint16_t *Ab = Al + abuf * AT, *Bb = Bl + bbuf * BT;
+            load_channels(s + NB + 2);
+            channels(cha, chn, s + NA, s + NB - 1);
+#pragma unroll
+            for (int i = 0; i < NP; ++i) {
+                product(i, 0);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int r = min(i, kSpread) * NR / kSpread; r < min(i + 1, kSpread) * NR / kSpread; ++r) fetch(Ab, Bb, r, 1, 1);
+#pragma unroll
+                for (int p = i * PB / NP; p < (i + 1) * PB / NP; ++p) load_b(chn[p], p, bprev, s + NB - 1);
+                if (i >= NP - 2) ra[i - (NP - 2)] = row_of(cha[i - (NP - 2)], a_row + 32 * (i - (NP - 2)), s + NA, a_col, a_stride, a_zero);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if (MF == 1) first_pairs(1);
+            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(kYounger) : "memory");
+            const int a_free = abuf;
+            bprev = bbuf;
+            abuf = abuf + 1 == NA ? 0 : abuf + 1;
+            bbuf = bbuf + 1 == NB ? 0 : bbuf + 1;
+            Ab = Al + abuf * AT, Bb = Bl + bbuf * BT;
+#pragma unroll
+            for (int i = 0; i < NP; ++i) {
+                product(i, 1);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int r = min(i, kSpread) * NR / kSpread; r < min(i + 1, kSpread) * NR / kSpread; ++r) fetch(Ab, Bb, r, 0, 0);
+#pragma unroll
+                for (int p = i * PA / NP; p < (i + 1) * PA / NP; ++p) load_a(ra, p, a_free);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if (MF == 1) first_pairs(0);
+        }
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_nop 15\n\ts_nop 15" ::: "memory");
+#pragma unroll
+        for (int i = 0; i < MF; ++i)
+#pragma unroll
+            for (int f = 0; f < F; ++f) asm volatile("" : "+a"(acc[i][f]));  // (no read of them moves ahead of the wait)
+    }
+    dd_store<MF>(acc, t0 + wave * 16 + lane / 16 * 4, 64, n0 + lane % 16 * 8, split, T, d, part, y, y_bf16);
 }
 
 // y = sum over the splits, in split order, of part[split]; n4 = T * d / 4 vectors.
@@ -573,6 +793,48 @@ static hipError_t launch_dd(const void *w, int d, const int *list, const int *n_
     return hipGetLastError();
 }
 
+static hipError_t down_gemm_reduce(const float *part, int n_split, int T, int d, void *y, int y_bf16, hipStream_t s)
+{
+    if (n_split <= 1) return hipSuccess;
+    const size_t n4 = (size_t)T * d / 4;
+    hipLaunchKernelGGL(down_gemm_reduce_kernel, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, s, (const float4 *)part,
+                       n_split, n4, y, y_bf16);
+    return hipGetLastError();
+}
+
+bool down_gemm_by_channel(int d) { return d % kDgBN == 0; }
+
+hipError_t launch_down_gemm_rows(const void *w, int d, int m, const int *list, const int *n_list, const uint16_t *ht, int ldt,
+                                 int T, int n_split, int n_cu, float *part, void *y, int y_bf16, hipStream_t s,
+                                 const uint16_t *zero_row)
+{
+    if (!down_gemm_by_channel(d) || ldt % 64 || ldt < T) return hipErrorInvalidValue;
+    int split = 1;
+    void (*kernel)(const uint16_t *, int, const int *, const int *, const uint16_t *, int, int, int, int, int, int,
+                   const uint16_t *, float *, void *, int);
+    size_t lds = 0;
+    const int mf = dd_shape(T, d, n_cu, &split), n_tt = (T + 64 * mf - 1) / (64 * mf);
+    const bool stream = n_tt == 1 && stream_rows(d, m, 1, kStreamPromptBytes);
+    switch (mf) {
+#define POP_DR(MF)                                                                           \
+    case MF:                                                                                 \
+        kernel = stream ? down_gemm_rows_kernel<MF, true> : down_gemm_rows_kernel<MF, false>; \
+        lds = DdRing<MF>::kBytes;                                                            \
+        break;
+        POP_DR(5) POP_DR(4) POP_DR(3) POP_DR(2) POP_DR(1)
+#undef POP_DR
+        default: return hipErrorInvalidValue;
+    }
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       (int)lds);
+    if (e != hipSuccess) return e;
+    const int n_nt = d / kDgBN, per_xcd = (n_tt * n_nt * n_split + 7) / 8;
+    hipLaunchKernelGGL(kernel, dim3(per_xcd * 8), dim3(kDdThreads), lds, s, (const uint16_t *)w, d, list, n_list, ht, ldt, T, n_tt,
+                       n_nt, n_split, per_xcd, zero_row, n_split > 1 ? part : nullptr, y, y_bf16);
+    e = hipGetLastError();
+    return e != hipSuccess ? e : down_gemm_reduce(part, n_split, T, d, y, y_bf16, s);
+}
+
 // bf16 only; d % 8 == 0, ldh % 8 == 0.  part: float32 [n_split][T][d], needed when n_split > 1.  zero_row: 256 bytes
 // of zeros (optional); with it, d % 128 == 0 and ldh % 64 == 0 the direct-load kernel runs, which reads Hc columns up to
 // the list length rounded up to 64.
@@ -603,11 +865,7 @@ hipError_t launch_down_gemm_bf16(const void *w, int d, const int *list, const in
                            n_list, hc, ldh, T, n_tt, n_nt, n_split, per_xcd, parts, y, y_bf16);
     }
     e = hipGetLastError();
-    if (e != hipSuccess || n_split <= 1) return e;
-    const size_t n4 = (size_t)T * d / 4;
-    hipLaunchKernelGGL(down_gemm_reduce_kernel, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, s, (const float4 *)part,
-                       n_split, n4, y, y_bf16);
-    return hipGetLastError();
+    return e != hipSuccess ? e : down_gemm_reduce(part, n_split, T, d, y, y_bf16, s);
 }
 
 }  // namespace pop

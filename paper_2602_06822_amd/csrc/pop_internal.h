@@ -311,10 +311,17 @@ int down_gemm_splits(int T, int d, int n_cu);
 hipError_t launch_down_gemm_bf16(const void *w, int d, const int *list, const int *n_list, const uint16_t *hc, int ldh,
                                  int T, int n_split, int n_cu, float *part, void *y, int y_bf16, hipStream_t s,
                                  const uint16_t *zero_row = nullptr);
+// The same with H of all m channels by channel, ht[j][ldt] (ldt a multiple of 64, kRowsSlack elements readable behind the last row):
+// rows are read by the list, nothing is gathered.  down_gemm_by_channel: widths it takes.  zero_row: kZeroRowBytes of zeros.
+constexpr int kRowsSlack = 512, kZeroRowBytes = 1024;
+bool down_gemm_by_channel(int d);
+hipError_t launch_down_gemm_rows(const void *w, int d, int m, const int *list, const int *n_list, const uint16_t *ht, int ldt,
+                                 int T, int n_split, int n_cu, float *part, void *y, int y_bf16, hipStream_t s,
+                                 const uint16_t *zero_row);
 // bf16 layers: the prefill contraction (s2_part as in launch_prefill_gateup) that also keeps H:
-// h_all[t][j] = bf16(H[t][j]), row stride ldh.
+// h_all[t][j] = bf16(H[t][j]), row stride ldh, or by channel (d a multiple of 64): h_all[j][t], ldh >= T a multiple of 64.
 hipError_t launch_prefill_gateup_keep_bf16(const void *w, int d, int m, const void *x, int T, float *s2_part,
-                                           uint16_t *h_all, int ldh, int n_cu, hipStream_t s,
+                                           uint16_t *h_all, int ldh, bool by_channel, int n_cu, hipStream_t s,
                                            const PrefillScores *fin = nullptr);
 // Gate/up of up to precise_max_tokens tokens (0: not for such layers) with sums in double and h[t][j] in float32 ([T][m],
 // by channel).  Without a list: all channels, and their scores as fin says (chunk_ctr zero before and after).  With one

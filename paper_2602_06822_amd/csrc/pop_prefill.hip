@@ -160,7 +160,8 @@ __device__ __forceinline__ void pf_chunk_scores(const float (&colsum)[TW][kPfChu
 
 // kMode 0: scores only (s2_part).  1: channels from st.list, H stored compact (no s2_part).  2: all m channels,
 // s2_part and H stored as [T][m padded].  Of the direct-load kernel also 3 and 4, for prompts too short for H in bf16: all
-// channels with s2_part, or those of st.list without, sums in double and H in float32 by channel.
+// channels with s2_part, or those of st.list without, sums in double and H in float32 by channel; and 5, as 2 with H by channel,
+// [m][ldh] with ldh >= T tokens a multiple of 64: rows that the down projection reads by the list of active channels.
 template <int BM, int NW, int NF, int kMode>
 __global__ __launch_bounds__(NW * 64) void prefill_bf16_kernel(const uint16_t *__restrict__ w,
                                                            const uint16_t *__restrict__ x, int T, int d, int m,
@@ -444,7 +445,7 @@ __device__ __forceinline__ void pm_tile(const uint16_t *__restrict__ w, const ui
     typedef __attribute__((address_space(1))) const void glb_t;
     typedef float f32x4_t __attribute__((ext_vector_type(4)));
     constexpr int NA = Ring::NA, NB = Ring::NB;
-    constexpr bool kList = kMode == 1 || kMode == 4, kPrecise = kMode >= 3;
+    constexpr bool kList = kMode == 1 || kMode == 4, kPrecise = kMode == 3 || kMode == 4, kRows = kMode == 5;
     constexpr int BM = 64 * MF, BC = 8 * F;             // tokens and channels of the tile
     constexpr int PA = BM / 32, PB = (F + 1) / 2;       // direct loads per wave and k-step (32 rows a pass)
     constexpr int AT = BM * kPfBK, BT = PB * 32 * kPfBK;  // elements of one buffer
@@ -612,8 +613,8 @@ __device__ __forceinline__ void pm_tile(const uint16_t *__restrict__ w, const ui
     // Accumulator register v of a lane: token 4 (lane / 16) + v of the fragment, B row lane % 16 of the fragment.  An odd
     // last fragment holds gate values in lanes 0..7 of each 16 and up values of the same channels in lanes 8..15: the
     // halves trade two registers each, so that every lane forms two of the four.
-    uint16_t *hs = lds;                 // [BM][BC + 8] bf16: H of the tile on its way out
-    constexpr int HS = BC + 8;
+    uint16_t *hs = lds;                 // [BM][BC + 8], by channel [BC][BM + 8] bf16: H of the tile on its way out
+    constexpr int HS = kRows ? BM + 8 : BC + 8;
     const int col = lane % 16, row0 = wave * MF * 16 + lane / 16 * 4;  // first token row of this lane
     const bool upper = col >= 8;
     const int c_odd = 8 * (F - 1) + col % 8, r_odd = upper ? 2 : 0;
@@ -627,7 +628,8 @@ __device__ __forceinline__ void pm_tile(const uint16_t *__restrict__ w, const ui
         const int j = (kList && (kPrecise || st.tmask) && live_c) ? st.list[c0 + c] : c0 + c;
         float sq[2] = {0.f, 0.f};
 #pragma unroll
-        for (int a = 0; a < MF; ++a)
+        for (int a = 0; a < MF; ++a) {
+            uint32_t four[4];
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 const int t = t0 + row0 + a * 16 + v;
@@ -637,11 +639,16 @@ __device__ __forceinline__ void pm_tile(const uint16_t *__restrict__ w, const ui
                 sq[v / 2] = fmaf(h, h, sq[v / 2]);
                 if (kPrecise) {
                     if (t < T && live_c) st.h32[(size_t)t * m + j] = h;
+                } else if (kRows) {
+                    four[v] = f32_to_bf16(h);
                 } else if (kMode != 0) {
                     if (kList && st.tmask && t < T && live_c && !st.tmask[(size_t)t * m + j]) h = 0.f;
                     hs[(row0 + a * 16 + v) * HS + c] = f32_to_bf16(h);
                 }
             }
+            if (kRows)
+                *reinterpret_cast<uint2 *>(hs + c * HS + row0 + a * 16) = make_uint2(four[0] | four[1] << 16, four[2] | four[3] << 16);
+        }
         ss[p] = sq[0] + sq[1];
     }
     if (F % 2) {
@@ -649,7 +656,8 @@ __device__ __forceinline__ void pm_tile(const uint16_t *__restrict__ w, const ui
         const int j = (kList && (kPrecise || st.tmask) && live_c) ? st.list[c0 + c_odd] : c0 + c_odd;
         ss[F / 2] = 0.f;
 #pragma unroll
-        for (int a = 0; a < MF; ++a)
+        for (int a = 0; a < MF; ++a) {
+            uint32_t two[2];
 #pragma unroll
             for (int v = 0; v < 2; ++v) {
                 const float mine = upper ? acc[a][F - 1][v + 2] : acc[a][F - 1][v];
@@ -662,11 +670,15 @@ __device__ __forceinline__ void pm_tile(const uint16_t *__restrict__ w, const ui
                 ss[F / 2] = fmaf(h, h, ss[F / 2]);
                 if (kPrecise) {
                     if (t < T && live_c) st.h32[(size_t)t * m + j] = h;
+                } else if (kRows) {
+                    two[v] = f32_to_bf16(h);
                 } else if (kMode != 0) {
                     if (kList && st.tmask && t < T && live_c && !st.tmask[(size_t)t * m + j]) h = 0.f;
                     hs[(row0 + a * 16 + r_odd + v) * HS + c_odd] = f32_to_bf16(h);
                 }
             }
+            if (kRows) *reinterpret_cast<uint32_t *>(hs + c_odd * HS + row0 + a * 16 + r_odd) = two[0] | two[1] << 16;
+        }
     }
     if (!kList) {
 #pragma unroll
@@ -678,6 +690,15 @@ __device__ __forceinline__ void pm_tile(const uint16_t *__restrict__ w, const ui
             if (lane < 16 && (p < F / 2 || lane < 8)) colsum[wave][16 * p + lane] = s;
         }
         pf_chunk_scores<4>(colsum, m, n_tt, ttile, ctile, c0, cn, s2_part, st);
+    }
+    if (kRows) {
+        __syncthreads();
+        for (int i = tid; i < BC * (BM / 8); i += kPmThreads) {
+            const int c = i / (BM / 8), t = t0 + i % (BM / 8) * 8;
+            if (c < cn && t < st.ldh)
+                *reinterpret_cast<uint4 *>(st.hc + (size_t)(c0 + c) * st.ldh + t) =
+                    *reinterpret_cast<const uint4 *>(hs + c * HS + i % (BM / 8) * 8);
+        }
     }
     if (kMode == 1 || kMode == 2) {
         __syncthreads();
@@ -702,12 +723,10 @@ inline bool pm_streams(int d, int m, int n_tt)
     constexpr bool kList = kMode == 1 || kMode == 4;
     return n_tt <= (kList ? 1 : 2) && stream_rows(d, m, 1, kList ? kStreamPromptBytes * 3 / 2 : kStreamPromptBytes);
 }
-constexpr bool pm_deep(int mf, int f, int mode) { return mf == kPmDeepMF && f <= kPmDeepF && (mode == 0 || mode == 2); }
-template <int MF, int kMode>
-__global__ __launch_bounds__(kPmThreads, 1) void prefill_stream_kernel(const uint16_t *__restrict__ w,
-                                                                       const uint16_t *__restrict__ x, int T, int d, int m,
-                                                                       int n_tt, PmTiles g, float *__restrict__ s2_part,
-                                                                       PfStore st)
+constexpr bool pm_deep(int mf, int f, int mode) { return mf == kPmDeepMF && f <= kPmDeepF && (mode == 0 || mode == 2 || mode == 5); }
+template <int MF, int kMode, bool kStream>
+__device__ __forceinline__ void pm_walk(const uint16_t *__restrict__ w, const uint16_t *__restrict__ x, int T, int d, int m,
+                                        int n_tt, PmTiles g, float *__restrict__ s2_part, const PfStore &st)
 {
     extern __shared__ __attribute__((aligned(16))) uint16_t pf_lds[];
     __shared__ float colsum[4][kPfChunk];
@@ -723,7 +742,7 @@ __global__ __launch_bounds__(kPmThreads, 1) void prefill_stream_kernel(const uin
 #define POP_PM(FF)                                                                                                         \
     case FF: {                                                                                                             \
         typedef typename std::conditional<pm_deep(MF, FF, kMode), PmDeepRing, PmRing<MF>>::type ring_t;                    \
-        pm_tile<MF, FF, kMode, ring_t, true>(w, x, T, d, m, n_ch, n_tt, logical, s2_part, st, pf_lds, colsum);             \
+        pm_tile<MF, FF, kMode, ring_t, kStream>(w, x, T, d, m, n_ch, n_tt, logical, s2_part, st, pf_lds, colsum);             \
         break;                                                                                                             \
     }
             POP_PM(12) POP_PM(11) POP_PM(10) POP_PM(8) POP_PM(7) POP_PM(6) POP_PM(4)
@@ -731,6 +750,25 @@ __global__ __launch_bounds__(kPmThreads, 1) void prefill_stream_kernel(const uin
         }
         __syncthreads();  // the next tile's direct loads overwrite the LDS
     }
+}
+
+template <int MF, int kMode>
+__global__ __launch_bounds__(kPmThreads, 1) void prefill_stream_kernel(const uint16_t *__restrict__ w,
+                                                                       const uint16_t *__restrict__ x, int T, int d, int m,
+                                                                       int n_tt, PmTiles g, float *__restrict__ s2_part,
+                                                                       PfStore st)
+{
+    pm_walk<MF, kMode, true>(w, x, T, d, m, n_tt, g, s2_part, st);
+}
+
+// H by channel (mode 5).
+template <int MF, bool kStream>
+__global__ __launch_bounds__(kPmThreads, 1) void prefill_rows_kernel(const uint16_t *__restrict__ w,
+                                                                     const uint16_t *__restrict__ x, int T, int d, int m,
+                                                                     int n_tt, PmTiles g, float *__restrict__ s2_part,
+                                                                     PfStore st)
+{
+    pm_walk<MF, 5, kStream>(w, x, T, d, m, n_tt, g, s2_part, st);
 }
 
 template <int MF, int kMode>
@@ -1075,14 +1113,18 @@ template <int MF, int kMode>
 static hipError_t launch_pm(const void *w, int d, int m, const void *x, int T, const PmTiles &g, float *s2_part, int n_cu,
                             const PfStore &st, hipStream_t s)
 {
-    void (*kernel)(const uint16_t *, const uint16_t *, int, int, int, int, PmTiles, float *, PfStore) =
-        prefill_mma_kernel<MF, kMode>;
-    size_t lds = PmRing<MF>::kBytes;
-    // (the list form learns its F on the device; wider chunks do not leave the room)
-    if constexpr (MF == kPmDeepMF && (kMode == 0 || kMode == 2))
-        if (g.f <= kPmDeepF) kernel = prefill_deep_kernel<kMode>, lds = PmDeepRing::kBytes;
+    void (*kernel)(const uint16_t *, const uint16_t *, int, int, int, int, PmTiles, float *, PfStore);
     const int n_tt = (T + 64 * MF - 1) / (64 * MF);
-    if (pm_streams<kMode>(d, m, n_tt)) kernel = prefill_stream_kernel<MF, kMode>;
+    // (the list form learns its F on the device; wider chunks do not leave the room)
+    const bool deep = pm_deep(MF, g.f, kMode), stream = pm_streams<kMode>(d, m, n_tt);
+    const size_t lds = deep ? PmDeepRing::kBytes : PmRing<MF>::kBytes;
+    if constexpr (kMode == 5) {
+        kernel = stream ? prefill_rows_kernel<MF, true> : prefill_rows_kernel<MF, false>;
+    } else {
+        kernel = stream ? prefill_stream_kernel<MF, kMode> : prefill_mma_kernel<MF, kMode>;
+        if constexpr (MF == kPmDeepMF && (kMode == 0 || kMode == 2))
+            if (deep && !stream) kernel = prefill_deep_kernel<kMode>;
+    }
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
                                        (int)lds);
     if (e != hipSuccess) return e;
@@ -1141,12 +1183,19 @@ static hipError_t launch_pf_bf16_all(const void *w, int d, int m, const void *x,
     return launch_pf_bf16<128, 4, 2, kMode>(blocks, s, w, x, T, d, m, n_tt, g, s2_part, st);
 }
 
-// bf16 only: the prefill contraction that also keeps H, h_all[t][j] = bf16(H[t][j]) with row stride ldh.
+// bf16 only: the prefill contraction that also keeps H, h_all[t][j] = bf16(H[t][j]) with row stride ldh, or by_channel (d a
+// multiple of 64) h_all[j][t] with ldh >= T a multiple of 64.
 hipError_t launch_prefill_gateup_keep_bf16(const void *w, int d, int m, const void *x, int T, float *s2_part,
-                                           uint16_t *h_all, int ldh, int n_cu, hipStream_t s, const PrefillScores *fin)
+                                           uint16_t *h_all, int ldh, bool by_channel, int n_cu, hipStream_t s,
+                                           const PrefillScores *fin)
 {
     PfStore st{nullptr, nullptr, h_all, ldh, nullptr, n_cu};
     if (fin) st.fin_ctr = fin->chunk_ctr, st.nrm = fin->nrm, st.scores = fin->scores;
+    if (by_channel) {
+        if (!prefill_direct(d)) return hipErrorInvalidValue;
+        if (!prefill_forms_scores(1, T, d, m, n_cu)) st.fin_ctr = nullptr;
+        return launch_pm_all<5>(w, d, m, x, T, s2_part, n_cu, st, s);
+    }
     return launch_pf_bf16_all<2>(w, d, m, x, T, s2_part, n_cu, st, s);
 }
 
