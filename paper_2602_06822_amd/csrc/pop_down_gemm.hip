@@ -509,6 +509,23 @@ __global__ __launch_bounds__(kDdThreads, 1) void down_gemm_stream_kernel(const u
     dd_tile<MF, true>(w, d, list, n_list, hc, ldh, T, n_tt, n_nt, n_split, per_xcd, zero_row, part, y, y_bf16);
 }
 
+// Loads straight into LDS, 16 or 4 bytes a lane to consecutive places from `to` on (the same in all lanes).  Inline assembly: the compiler
+// takes some LDS reads (of channel numbers, transposing ones) for reads of what direct loads write, and would wait for all of those in
+// flight in front of each.  They have no register results, and the kernels' own counted waits are the only ones they need.
+__device__ __forceinline__ int dd_lds(const void *to) { return __builtin_amdgcn_readfirstlane((int)(uint32_t)(uintptr_t)to); }
+template <bool kStream>
+__device__ __forceinline__ void dd_load16(const void *to, uintptr_t from)
+{
+    if constexpr (kStream)  // (non-temporal)
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off nt" : : "s"(dd_lds(to)), "v"(from));
+    else
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(dd_lds(to)), "v"(from));
+}
+__device__ __forceinline__ void dd_load4(const void *to, const void *from)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" : : "s"(dd_lds(to)), "v"(from));
+}
+
 // The same contraction over H by channel, ht[j][ldt] of all m channels (written so by the prompt's own contraction): both operands
 // are rows of the listed channels, so there is no gather of H's columns in front (17 us at 2048 tokens, 6 at an expert's 256).
 // H tile: MF panels of 64 channels x 64 tokens, rows of 128 bytes as they come; a wave owns 16 tokens of every panel (its fragment i
@@ -567,25 +584,14 @@ __global__ __launch_bounds__(kDdThreads, 1) void down_gemm_rows_kernel(const uin
         const int b_row = wave * 4 + lane / 16;
         const uintptr_t b_col = (uintptr_t)(w + 2 * d + n0 + (lane % 16) * 8), b_zero = (uintptr_t)(zero_row + (lane % 16) * 8);
         const uint32_t b_stride = (uint32_t)(channel_elems_bf16(d) * sizeof(uint16_t));
-        // (direct loads as inline assembly: the compiler takes a transposing read for one of everything that direct loads write, and
-        // would wait for all of them in front of it.  They have no register results, and all waits for them are the counted ones.)
-        auto lds_at = [](const void *p) { return __builtin_amdgcn_readfirstlane((int)(uint32_t)(uintptr_t)p); };
         auto load_channels = [&](int step) {
-            const int *src = list + min(min(ks0 + step, ks1 - 1) * kDgBK + lane, a - 1);
-            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off"
-                         :
-                         : "s"(lds_at(Cs + step % kDdSlots * kDgBK)), "v"(src));
+            dd_load4(Cs + step % kDdSlots * kDgBK, list + min(min(ks0 + step, ks1 - 1) * kDgBK + lane, a - 1));
         };
-        // (read with their own wait, as in dd_tile)
         auto channels = [&](int (&ca)[2], int (&cb)[PB], int step_a, int step_b) {
-            const uint32_t at_a = (uint32_t)(uintptr_t)(Cs + step_a % kDdSlots * kDgBK + a_row);
-            const uint32_t at_b = (uint32_t)(uintptr_t)(Cs + step_b % kDdSlots * kDgBK + b_row);
-            asm volatile("ds_read_b32 %0, %6\n\tds_read_b32 %1, %6 offset:128\n\tds_read_b32 %2, %7\n\t"
-                         "ds_read_b32 %3, %7 offset:64\n\tds_read_b32 %4, %7 offset:128\n\tds_read_b32 %5, %7 offset:192\n\t"
-                         "s_waitcnt lgkmcnt(0)"
-                         : "=&v"(ca[0]), "=&v"(ca[1]), "=&v"(cb[0]), "=&v"(cb[1]), "=&v"(cb[2]), "=&v"(cb[3])
-                         : "v"(at_a), "v"(at_b)
-                         : "memory");
+            const int *at_a = Cs + step_a % kDdSlots * kDgBK + a_row, *at_b = Cs + step_b % kDdSlots * kDgBK + b_row;
+            ca[0] = at_a[0], ca[1] = at_a[32];
+#pragma unroll
+            for (int p = 0; p < PB; ++p) cb[p] = at_b[16 * p];
         };
         // A row's address, with a row of zeros beyond the list (selected with masks: no branch around a load).
         auto row_of = [&](int c, int row, int step, uintptr_t col, uint32_t stride, uintptr_t zero) {
@@ -595,17 +601,10 @@ __global__ __launch_bounds__(kDdThreads, 1) void down_gemm_rows_kernel(const uin
         };
         // pass p: panel p / 2, rows 32 (p % 2) ..
         auto load_a = [&](const uintptr_t (&rows)[2], int p, int buf) {
-            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
-                         :
-                         : "s"(lds_at(As + buf * AT + p / 2 * PT + (p % 2 * 32 + wave * 8) * 64)), "v"(rows[p % 2] + p / 2 * 128));
+            dd_load16<false>(As + buf * AT + p / 2 * PT + (p % 2 * 32 + wave * 8) * 64, rows[p % 2] + p / 2 * 128);
         };
         auto load_b = [&](int c, int p, int buf, int step) {
-            const uintptr_t row = row_of(c, b_row + 16 * p, step, b_col, b_stride, b_zero);
-            const int to = lds_at(Bs + buf * BT + (p * 16 + wave * 4) * kDgBN);
-            if constexpr (kStream)
-                asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off nt" : : "s"(to), "v"(row));
-            else
-                asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(to), "v"(row));
+            dd_load16<kStream>(Bs + buf * BT + (p * 16 + wave * 4) * kDgBN, row_of(c, b_row + 16 * p, step, b_col, b_stride, b_zero));
         };
         // Fragment reads.  H: lanes 16 g .. + 15 read rows 32 q + 8 g + 4 half + (lane % 16) / 4.  Weights as in dd_tile.
         const uint16_t *Al = As + (lane / 16 * 8 + lane % 16 / 4) * 64 +
@@ -682,12 +681,12 @@ __global__ __launch_bounds__(kDdThreads, 1) void down_gemm_rows_kernel(const uin
         first_pairs(0);
         for (int s = 0; s < n_steps; ++s) {
             const uint16_t *Ab = Al + abuf * AT, *Bb = Bl + bbuf * BT;
-            load_channels(s + NB + 2);
-            channels(cha, chn, s + NA, s + NB - 1);
 #pragma unroll
             for (int i = 0; i < NP; ++i) {
                 product(i, 0);
                 __builtin_amdgcn_sched_barrier(0);
+                if (i == 0) channels(cha, chn, s + NA, s + NB - 1);
+                if (i == 1) load_channels(s + NB + 2);
 #pragma unroll
                 for (int r = min(i, kSpread) * NR / kSpread; r < min(i + 1, kSpread) * NR / kSpread; ++r) fetch(Ab, Bb, r, 1, 1);
 #pragma unroll
