@@ -446,6 +446,9 @@ __device__ __forceinline__ void pm_tile(const uint16_t *__restrict__ w, const ui
     typedef float f32x4_t __attribute__((ext_vector_type(4)));
     constexpr int NA = Ring::NA, NB = Ring::NB;
     constexpr bool kList = kMode == 1 || kMode == 4, kPrecise = kMode == 3 || kMode == 4, kRows = kMode == 5;
+    // An odd F leaves 16 rows for the last pass: half a request of each wave (without: two waves' whole ones, and the other two ask for
+    // rows again that are there, 2 KB of the 48 to 56 of a k-step.  With: eight experts 1015 -> 1005 us; 512 and 24 tokens the same).
+    constexpr bool kHalf = (kStream || kRows) && F % 2;
     constexpr int BM = 64 * MF, BC = 8 * F;             // tokens and channels of the tile
     constexpr int PA = BM / 32, PB = (F + 1) / 2;       // direct loads per wave and k-step (32 rows a pass)
     constexpr int AT = BM * kPfBK, BT = PB * 32 * kPfBK;  // elements of one buffer
@@ -466,10 +469,12 @@ __device__ __forceinline__ void pm_tile(const uint16_t *__restrict__ w, const ui
 #pragma unroll
     for (int p = 0; p < PB; ++p) {
         int ch, which;
-        pm_row_channel<F>(ld_row + p * 32, ch, which);
+        const bool half = kHalf && p == PB - 1;
+        const int row = p * 32 + (half ? wave * 4 + lane / 8 : ld_row);
+        pm_row_channel<F>(row, ch, which);
         const int cc = min(ch, cn - 1);
         const int j = kList ? st.list[c0 + cc] : c0 + cc;
-        pb[p] = w + (size_t)j * channel_elems_bf16(d) + which * d + src_kv;
+        pb[p] = w + (size_t)j * channel_elems_bf16(d) + which * d + (half ? ((lane % 8) ^ ((row / 2) % 8)) * 8 : src_kv);
     }
     const int n_k = d / kPfBK;
     // k-step s is columns kof(s) (steps beyond the last repeat it).  Sums in float32 take the columns in the same order in
@@ -488,6 +493,18 @@ __device__ __forceinline__ void pm_tile(const uint16_t *__restrict__ w, const ui
                                          0, 0);
     };
     auto load_b = [&](int p, int buf, int k0) {
+        if (kHalf && p == PB - 1) {
+            // (32 lanes; inline assembly, for there may be no branch around a load.  It leaves m0 and exec as they were.)
+            const int to = __builtin_amdgcn_readfirstlane((int)(uint32_t)(uintptr_t)(Bs + buf * BT + (p * 32 + wave * 4) * kPfBK));
+            int m0_was;
+            if constexpr (kStream)
+                asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_mov_b32 exec_hi, 0\n\tglobal_load_lds_dwordx4 %2, off nt\n\t"
+                             "s_mov_b32 exec_hi, -1\n\ts_mov_b32 m0, %0" : "=&s"(m0_was) : "s"(to), "v"(pb[p] + k0));
+            else
+                asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_mov_b32 exec_hi, 0\n\tglobal_load_lds_dwordx4 %2, off\n\t"
+                             "s_mov_b32 exec_hi, -1\n\ts_mov_b32 m0, %0" : "=&s"(m0_was) : "s"(to), "v"(pb[p] + k0));
+            return;
+        }
         __builtin_amdgcn_global_load_lds((glb_t *)(pb[p] + k0), (lds_t *)(Bs + buf * BT + (p * 32 + wave * 8) * kPfBK), 16,
                                          0, kStream ? 2 : 0);  // (2: non-temporal)
     };
