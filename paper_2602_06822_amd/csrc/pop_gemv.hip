@@ -563,12 +563,15 @@ hipError_t launch_down(const void *w, int is_bf16, int d, int m, const int *list
 // A workgroup owns 128 columns and a slab of the list, its eight waves 32 channels each of every 256.  Lane (c, g) =
 // (lane % 16, lane / 16) loads 16 bytes of the rows of channels 8 g .. 8 g + 7 at columns 8 c .. 8 c + 7 (256 contiguous
 // bytes per row), which is a transposed operand: one byte permute per register pairs the values of two channels, and
-// product e takes column 8 c + e of every lane.
-// 24 tokens, d 4096, 7155 channels: 19 us (3.0 TB/s); requesting rows or h further ahead took 25 to 80 us, for registers.
-constexpr int kSkThreads = 512;
-constexpr int kSkChunk = 256;      // channels staged at a time
+// product e takes column 8 c + e of every lane.  A wave sees to its own channels alone, h included, which passes through a piece of LDS
+// of its own: no barrier stands between requests and products, every wait leaves the rows of the wave's next group in flight, and the
+// eight waves run apart.  (With h staged by the workgroup, three bf16 planes of 256 channels between two barriers, its loads had to be
+// waited for behind the rows in flight, and the chip read at half its rate: FIGURES.)
+// Waves of a workgroup: with two groups of 16 tokens a wave needs more registers than a SIMD has for two of them.
+__host__ __device__ constexpr int sk_waves(int tq) { return tq <= 8 ? 8 : 4; }
+constexpr int kSkList = 4096;      // channels of a slab whose numbers are in LDS at a time
 constexpr int kSkCols = 128;       // columns per workgroup
-constexpr int kSkLd = kSkChunk + 8;  // LDS row stride of the staged h planes (16-byte aligned, rows four banks apart)
+constexpr int kSkPair = 68;        // floats between two pairs of tokens' h (64, and four banks)
 
 // f = hi + mid + lo exactly for finite f (24 significant bits in three bf16 values of 8; the rests are exact differences)
 __device__ __forceinline__ void split3(float f, uint16_t &hi, uint16_t &mid, uint16_t &lo)
@@ -580,9 +583,9 @@ __device__ __forceinline__ void split3(float f, uint16_t &hi, uint16_t &mid, uin
     hi = (uint16_t)(b0 >> 16), mid = (uint16_t)(b1 >> 16), lo = (uint16_t)(__float_as_uint(r2) >> 16);
 }
 
-// TG groups of 16 tokens; kMask: masks per token (else none)
-template <class V, int TG, bool kMask>
-__global__ __launch_bounds__(kSkThreads) void skinny_down_kernel(const uint4 *__restrict__ w, int nvec,
+// TQ pairs of tokens, of which T exist; kMask: masks per token (else none)
+template <class V, int TQ, bool kMask>
+__global__ __launch_bounds__(sk_waves(TQ) * kWave) void skinny_down_kernel(const uint4 *__restrict__ w, int nvec,
                                                                  const int *__restrict__ list, const int *__restrict__ n_dev,
                                                                  const float *__restrict__ h, int m,
                                                                  const unsigned char *__restrict__ mask, int mask_stride,
@@ -590,10 +593,13 @@ __global__ __launch_bounds__(kSkThreads) void skinny_down_kernel(const uint4 *__
 {
     typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
     typedef float f32x4_t __attribute__((ext_vector_type(4)));
+    constexpr int TG = (TQ + 7) / 8;  // groups of 16 tokens
+    constexpr int kWaves = sk_waves(TQ), kSkThreads = kWaves * kWave;
     extern __shared__ __attribute__((aligned(16))) unsigned char sk_lds[];
-    constexpr int kPlanes = 3 * 16 * TG * kSkLd * 2;        // bytes
-    uint16_t *hp = reinterpret_cast<uint16_t *>(sk_lds);  // [3][16 TG][kSkLd]: planes of h, rows by token
+    int *js = reinterpret_cast<int *>(sk_lds);  // [kSkList] channels of the slab
     const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    // this wave's h of 32 channels, [16 TG tokens][32]: pairs of tokens kSkPair floats apart (fragment reads hit all banks)
+    float *hw = reinterpret_cast<float *>(sk_lds + kSkList * 4) + wave * (8 * TG * kSkPair);
     const int c = lane % 16, g = lane / 16;
     const int n = *n_dev;
     const int n_slabs = gridDim.y, per_slab = (n + n_slabs - 1) / n_slabs;
@@ -609,81 +615,102 @@ __global__ __launch_bounds__(kSkThreads) void skinny_down_kernel(const uint4 *__
 #pragma unroll
         for (int e = 0; e < 8; ++e) acc[t][e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
-    // channels of two chunks behind the planes: chunk q's in js[q % 2], loaded two chunks ahead
-    int *js = reinterpret_cast<int *>(sk_lds + kPlanes);  // [2][kSkChunk]
-    const int li = threadIdx.x % kSkChunk, half = threadIdx.x / kSkChunk;
-    auto channel = [&](int at) { return list[min(at + li, s1 - 1)]; };  // beyond the slab: its last channel (h is 0 there)
     uint4 rows[2][8];
-    auto request = [&](int set) {
+    float hv[TQ];                // of tokens 2 q + lane / 32, channel lane % 32 of the group
+    unsigned char hm[kMask ? TQ : 1];
+    // group i of this wave: entries 32 (wave + kWaves i) .. + 31 of the list in LDS, of which `have` exist (the rest repeat the last)
+    auto entry = [&](int i, int k, int have) { return js[min(32 * (wave + kWaves * i) + k, have - 1)]; };
+    auto request_rows = [&](uint4 (&r)[8], int i, int have) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) rows[set][i] = load_row<V>(wc, (uint64_t)(uint32_t)js[set * kSkChunk + 32 * wave + 8 * g + i] * chan);
+        for (int q = 0; q < 8; ++q) r[q] = load_row<V>(wc, (uint64_t)(uint32_t)entry(i, 8 * g + q, have) * chan);
     };
-    // h of the 256 channels at `at` as three planes; zero beyond the slab, beyond T and where a mask says so
-    auto stage = [&](int set, int at) {
-        const int j = js[set * kSkChunk + li];
-        float v[8 * TG];
-        unsigned char mk[8 * TG];
+    auto request_h = [&](int i, int have) {
+        const int j = entry(i, lane % 32, have);
+        int half = lane / 32;
+        asm volatile("" : "+v"(half));  // (offsets made afresh: kept for all tokens they cost the registers of a group's rows)
 #pragma unroll
-        for (int q = 0; q < 8 * TG; ++q) {
-            const int t = min(2 * q + half, T - 1);
-            v[q] = h[(size_t)t * m + j];
-            if (kMask) mk[q] = mask[(size_t)t * mask_stride + j];
-        }
-#pragma unroll
-        for (int q = 0; q < 8 * TG; ++q) {
-            const int t = 2 * q + half;
-            uint16_t a, b, e;
-            split3(t < T && at + li < s1 && (!kMask || mk[q]) ? v[q] : 0.f, a, b, e);
-            hp[(0 * 16 * TG + t) * kSkLd + li] = a;
-            hp[(1 * 16 * TG + t) * kSkLd + li] = b;
-            hp[(2 * 16 * TG + t) * kSkLd + li] = e;
+        for (int q = 0; q < TQ; ++q) {
+            const int t = 2 * q + half < T ? 2 * q + half : 0;
+            // (atomic in name only: a plain load may move, and moves down to where its value is used)
+            hv[q] = __hip_atomic_load(h + (size_t)((uint32_t)t * (uint32_t)m + (uint32_t)j), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+            if (kMask)
+                hm[q] = __hip_atomic_load(mask + (size_t)((uint32_t)t * (uint32_t)mask_stride + (uint32_t)j), __ATOMIC_RELAXED,
+                                          __HIP_MEMORY_SCOPE_WAVEFRONT);
         }
     };
-    auto multiply = [&](int set) {
-        bf16x8_t bw[8];
+    // h to LDS; zero beyond the list, beyond T and where a mask says so
+    auto place_h = [&](int i, int have) {
+        const bool live = 32 * (wave + kWaves * i) + lane % 32 < have;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            uint32_t v[4];
+        for (int q = 0; q < TQ; ++q)
+            hw[q * kSkPair + lane] = live && 2 * q + lane / 32 < T && (!kMask || hm[kMask ? q : 0]) ? hv[q] : 0.f;
+    };
+    auto multiply = [&](const uint4 (&r)[8]) {
+#pragma unroll
+        for (int t = 0; t < TG; ++t) {
+            const float4 *at = reinterpret_cast<const float4 *>(hw + (8 * t + c / 2) * kSkPair + c % 2 * 32 + 8 * g);
+            const float4 f0 = at[0], f1 = at[1];
+            const float f[8] = {f0.x, f0.y, f0.z, f0.w, f1.x, f1.y, f1.z, f1.w};
+            uint32_t p[3][4];
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const uint4 &r0 = rows[set][2 * q], &r1 = rows[set][2 * q + 1];
-                const uint32_t a0 = e / 2 == 0 ? r0.x : (e / 2 == 1 ? r0.y : (e / 2 == 2 ? r0.z : r0.w));
-                const uint32_t a1 = e / 2 == 0 ? r1.x : (e / 2 == 1 ? r1.y : (e / 2 == 2 ? r1.z : r1.w));
-                v[q] = __builtin_amdgcn_perm(a1, a0, e % 2 ? 0x07060302u : 0x05040100u);
+                uint16_t a[3], b[3];
+                split3(f[2 * q], a[0], a[1], a[2]);
+                split3(f[2 * q + 1], b[0], b[1], b[2]);
+#pragma unroll
+                for (int k = 0; k < 3; ++k) p[k][q] = (uint32_t)a[k] | (uint32_t)b[k] << 16;
             }
-            bw[e] = __builtin_bit_cast(bf16x8_t, make_uint4(v[0], v[1], v[2], v[3]));
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                uint32_t v[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const uint4 &r0 = r[2 * q], &r1 = r[2 * q + 1];
+                    const uint32_t a0 = e / 2 == 0 ? r0.x : (e / 2 == 1 ? r0.y : (e / 2 == 2 ? r0.z : r0.w));
+                    const uint32_t a1 = e / 2 == 0 ? r1.x : (e / 2 == 1 ? r1.y : (e / 2 == 2 ? r1.z : r1.w));
+                    v[q] = __builtin_amdgcn_perm(a1, a0, e % 2 ? 0x07060302u : 0x05040100u);
+                }
+                const bf16x8_t bw = __builtin_bit_cast(bf16x8_t, make_uint4(v[0], v[1], v[2], v[3]));
+#pragma unroll
+                for (int k = 2; k >= 0; --k)  // (small parts first)
+                    acc[t][e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                        __builtin_bit_cast(bf16x8_t, make_uint4(p[k][0], p[k][1], p[k][2], p[k][3])), bw, acc[t][e], 0, 0, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
         }
-#pragma unroll
-        for (int t = 0; t < TG; ++t)
-#pragma unroll
-            for (int part = 2; part >= 0; --part) {  // (small parts first)
-                const bf16x8_t ha = *reinterpret_cast<const bf16x8_t *>(
-                    &hp[((part * TG + t) * 16 + c) * kSkLd + 32 * wave + 8 * g]);
-#pragma unroll
-                for (int e = 0; e < 8; ++e)
-                    acc[t][e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ha, bw[e], acc[t][e], 0, 0, 0);
-            }
     };
-    if (s0 < s1) {
-        if (half == 0) js[li] = channel(s0), js[kSkChunk + li] = channel(s0 + kSkChunk);
+#pragma unroll
+    for (int q = TQ; q < 8 * TG; ++q) hw[q * kSkPair + lane] = 0.f;
+    for (int l0 = s0; l0 < s1; l0 += kSkList) {
+        const int have = min(kSkList, s1 - l0);
+        __syncthreads();  // the readers of the list before are done
+        for (int i = threadIdx.x; i < have; i += kSkThreads) js[i] = list[l0 + i];
         __syncthreads();
-        request(0);
-        auto step = [&](int set, int at) {
-            const int next = channel(at + 2 * kSkChunk);
-            stage(set, at);
-            if (at + kSkChunk < s1) request(set ^ 1);
-            __syncthreads();
-            if (half == 0) js[set * kSkChunk + li] = next;
-            multiply(set);
-            __syncthreads();  // the planes' readers are done, the channels are there
+        const int groups = (have + 32 * kWaves - 1) / (32 * kWaves);
+        request_rows(rows[0], 0, have);
+        request_h(0, have);
+        request_rows(rows[1], 1, have);
+        auto step = [&](uint4 (&r)[8], int i) {
+            place_h(i, have);
+            request_h(i + 1, have);
+            __builtin_amdgcn_sched_barrier(0);  // (requests where they are written: earlier they cost registers)
+            multiply(r);
+            __builtin_amdgcn_sched_barrier(0);
+            request_rows(r, i + 2, have);
+            __builtin_amdgcn_sched_barrier(0);
         };
-        for (int at = s0; at < s1; at += 2 * kSkChunk) {
-            step(0, at);
-            if (at + kSkChunk < s1) step(1, at + kSkChunk);
+        int i = 0;
+        for (; i + 2 <= groups; i += 2) {
+            step(rows[0], i);
+            step(rows[1], i + 1);
+        }
+        if (i < groups) {
+            place_h(i, have);
+            multiply(rows[0]);
         }
     }
-    // the eight waves' sums in wave order, 16 tokens at a time; register v of product e is token 4 g + v, column 8 c + e
-    float *red = reinterpret_cast<float *>(sk_lds);  // [8 waves][16 tokens][128 columns]
+    // the waves' sums in wave order, 16 tokens at a time; register v of product e is token 4 g + v, column 8 c + e
+    float *red = reinterpret_cast<float *>(sk_lds);  // [waves][16 tokens][128 columns]
 #pragma unroll
     for (int t = 0; t < TG; ++t) {
         __syncthreads();
@@ -734,21 +761,25 @@ static hipError_t launch_skinny_down_partials(const void *w, int d, int m, const
 {
     if (T < 1 || T > kSkMaxTokens) return hipErrorInvalidValue;
     const dim3 grid((d + kSkCols - 1) / kSkCols, n_slabs);
-    const int tg = (T + 15) / 16;
-    const size_t stage = (size_t)3 * 16 * tg * kSkLd * 2 + 2 * kSkChunk * 4, red = (size_t)8 * 16 * kSkCols * 4, lds = stage > red ? stage : red;
     hipError_t e = hipSuccess;
-#define POP_SK(TG, MK)                                                                                                    \
+#define POP_SK(TQ)                                                                                                        \
     do {                                                                                                                  \
-        e = hipFuncSetAttribute(reinterpret_cast<const void *>(&skinny_down_kernel<V, TG, MK>),                              \
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);                                    \
+        constexpr size_t stage = (size_t)kSkList * 4 + (size_t)sk_waves(TQ) * ((TQ + 7) / 8 * 8) * kSkPair * 4;           \
+        constexpr size_t red = (size_t)sk_waves(TQ) * 16 * kSkCols * 4, lds = stage > red ? stage : red;                  \
+        const auto kernel = mask ? skinny_down_kernel<V, TQ, true> : skinny_down_kernel<V, TQ, false>;                    \
+        e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,       \
+                                (int)lds);                                                                                \
         if (e != hipSuccess) return e;                                                                                    \
-        hipLaunchKernelGGL((skinny_down_kernel<V, TG, MK>), grid, dim3(kSkThreads), lds, s, (const uint4 *)w, d / 8, list,   \
-                           n_dev, h, m, mask, mask_stride, T, partial, d);                                                \
+        hipLaunchKernelGGL(kernel, grid, dim3(sk_waves(TQ) * kWave), lds, s, (const uint4 *)w, d / 8, list, n_dev, h, m,  \
+                           mask, mask_stride, T, partial, d);                                                             \
     } while (0)
-    if (tg == 1 && mask) POP_SK(1, true);
-    else if (tg == 1) POP_SK(1, false);
-    else if (mask) POP_SK(2, true);
-    else POP_SK(2, false);
+    // (pairs of tokens are loaded whether they exist or not, h and mask byte of each channel: as many as that as rows)
+    if (T <= 4) POP_SK(2);
+    else if (T <= 6) POP_SK(3);
+    else if (T <= 8) POP_SK(4);
+    else if (T <= 16) POP_SK(8);
+    else if (T <= 24) POP_SK(12);
+    else POP_SK(16);
 #undef POP_SK
     return hipGetLastError();
 }
