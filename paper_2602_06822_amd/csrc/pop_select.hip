@@ -57,26 +57,6 @@ __device__ __forceinline__ uint32_t row_incl_scan(uint32_t v)
     return v;
 }
 
-// op over each row of 16 lanes (every lane of the row gets it).
-template <class Op>
-__device__ __forceinline__ uint32_t row_reduce(uint32_t v, Op op)
-{
-    v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xf, 0xf, true));   // quad_perm 1,0,3,2
-    v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xf, 0xf, true));   // quad_perm 2,3,0,1
-    v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xf, 0xf, true));  // row_half_mirror
-    v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x140, 0xf, 0xf, true));  // row_mirror
-    return v;
-}
-
-// op over the wave, in its last lane.
-template <class Op>
-__device__ __forceinline__ uint32_t wave_reduce_last(uint32_t v, Op op)
-{
-    v = row_reduce(v, op);
-    v = op(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x142, 0xa, 0xf, false));  // row_bcast:15
-    return op(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x143, 0xc, 0xf, false));  // row_bcast:31
-}
-
 // Exclusive scan of N streams over the workgroup.
 template <int N>
 __device__ __forceinline__ void part_scan(int (&v)[N], PartShared &sh)

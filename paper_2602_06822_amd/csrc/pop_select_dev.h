@@ -13,12 +13,13 @@ constexpr int kSelMaxWaves = 16;
 constexpr int kSelLdsKeys = 4096;  // candidate keys staged in LDS when they fit (16 KiB)
 
 struct SelShared {
-    unsigned int hist[3][256];  // digit histograms of three consecutive radix passes (see radix_threshold)
-    unsigned int hist2[3][256]; // the second threshold's histograms when several are sought in one sweep
+    // digit histograms of three consecutive radix passes (radix_threshold), or 1024 intervals (interval_threshold)
+    __attribute__((aligned(16))) unsigned int hist[4][256];
+    uint32_t list[kWave], extreme[2][kSelMaxWaves];
     int wave_tot[6][kSelMaxWaves];
     int digit;
     int remaining;
-    int list_len[2];            // lengths of the key lists of radix_thresholds_lists
+    int list_len;
     uint32_t keys[kSelLdsKeys];
 };
 
@@ -63,14 +64,24 @@ __device__ __forceinline__ void block_excl_scan(int (&v)[N], int (&tot)[N], SelS
     __syncthreads();
 }
 
-// OR over each row of 16 lanes (every lane of the row gets it).
-__device__ __forceinline__ uint32_t wave_or_rows(uint32_t v)
+// op over each row of 16 lanes (every lane of the row gets it).
+template <class Op>
+__device__ __forceinline__ uint32_t row_reduce(uint32_t v, Op op)
 {
-    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xf, 0xf, true);   // quad_perm 1,0,3,2
-    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xf, 0xf, true);   // quad_perm 2,3,0,1
-    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xf, 0xf, true);  // row_half_mirror
-    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x140, 0xf, 0xf, true);  // row_mirror
+    v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xf, 0xf, true));   // quad_perm 1,0,3,2
+    v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xf, 0xf, true));   // quad_perm 2,3,0,1
+    v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xf, 0xf, true));  // row_half_mirror
+    v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x140, 0xf, 0xf, true));  // row_mirror
     return v;
+}
+
+// op over the wave, in its last lane.
+template <class Op>
+__device__ __forceinline__ uint32_t wave_reduce_last(uint32_t v, Op op)
+{
+    v = row_reduce(v, op);
+    v = op(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x142, 0xa, 0xf, false));  // row_bcast:15
+    return op(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x143, 0xc, 0xf, false));  // row_bcast:31
 }
 
 // hist[d] += 1 for every lane with valid set, d < 256.  Lanes of a wave that hold the same digit as its first
@@ -187,141 +198,102 @@ __device__ __forceinline__ void radix_threshold(KeyFn key, int n, int n_top, Sel
     take_eq = remaining;
 }
 
-// NT (2) thresholds in the same sweeps: kth[t] = key of the n_top[t]-th best element, 1 <= n_top[t] <= n, with
-// its take count, as NT calls of radix_threshold would give them.  The common leading bits and the leading digit's
-// histogram serve all; from the second digit on a key is counted for the threshold(s) whose prefix it matches.
-// Made for a large key set: digits are cut from the highest differing bit down (so the leading digit spreads the
-// keys over all its values even when that bit is not at a byte boundary), and the sweep for the second digit also
-// copies the keys that share a threshold's leading digit into a short list in sh.keys (one NT-th of it per
-// threshold; thresholds under one leading digit share a list), which the sweeps for the remaining digits read
-// instead of all n keys.  A threshold whose leading digit holds more keys than its list can take keeps sweeping all
-// keys.  Must not be used while sh.keys holds data.
-template <int NT, class KeyFn>
-__device__ __forceinline__ void radix_thresholds_lists(KeyFn key, int n, const int (&n_top)[NT], SelShared &sh,
-                                                       uint32_t (&kth)[NT], int (&take)[NT])
+// The same for keys that are in LDS, with `cut` set when only some of the elements equal to kth belong to the top.  One histogram
+// over 1024 equal intervals between the largest and the smallest key leaves the threshold in an interval of a few keys, which are
+// ranked pairwise; an interval of more than 64 is cut again, down to equal keys.  Every wave reads the histogram and ranks the list for
+// itself: three barriers and two sweeps, where the digits above take seven and five.
+// One float32 step at d 512, m 1376 (550 candidates, two waves) 20.1 -> 16.1 us, two of d 1024, m 4000 39.7 -> 32.4, re-scoring all of 11008
+// channels 134.4 -> 124.9 (two layers).
+constexpr int kSelBits = 10, kSelBins = 1 << kSelBits;
+template <class KeyFn>
+__device__ __forceinline__ void interval_threshold(KeyFn key, int n, int n_top, SelShared &sh, uint32_t &kth, int &take, bool &cut)
 {
-    static_assert(NT == 2, "two thresholds: two sets of histograms");
-    constexpr int kCap = kSelLdsKeys / NT;
-    unsigned int *scratch = &sh.hist[2][0];
-    if (threadIdx.x == 0) {
-        scratch[0] = 0;
-#pragma unroll
-        for (int t = 0; t < NT; ++t) sh.list_len[t] = 0;
-    }
-    if (threadIdx.x < 256) sh.hist[0][threadIdx.x] = 0;
-    if (blockDim.x < 256)
-        for (int i = threadIdx.x + blockDim.x; i < 256; i += blockDim.x) sh.hist[0][i] = 0;
-    __syncthreads();
-    const uint32_t k0 = key(0);
-    uint32_t diff = 0;  // bits in which any two keys differ
-    for (int i = threadIdx.x; i < n; i += blockDim.x) diff |= key(i) ^ k0;
-    diff = wave_or_rows(diff);
-    if (threadIdx.x % 16 == 0 && diff) atomicOr(&scratch[0], diff);
-    __syncthreads();
-    diff = scratch[0];
-    if (diff == 0) {  // all keys equal
-        __syncthreads();
-#pragma unroll
-        for (int t = 0; t < NT; ++t) kth[t] = k0, take[t] = n_top[t];
+    cut = false;
+    if (n_top <= 0) {
+        kth = 0xffffffffu;
+        take = 0;
         return;
     }
-    const int top_bit = 31 - __builtin_clz(diff);
-    const int n_pass = top_bit / 8 + 1;
-    uint32_t known = top_bit == 31 ? 0u : ~((2u << top_bit) - 1u);
-    uint32_t prefix[NT];
-    int remaining[NT], matching[NT], list_of[NT];  // list_of[t]: the list threshold t reads (-1: sweeps all keys)
-#pragma unroll
-    for (int t = 0; t < NT; ++t) prefix[t] = k0 & known, remaining[t] = n_top[t], matching[t] = n, list_of[t] = -1;
-    const int lane = threadIdx.x % kWave;
-    for (int pass = 0; pass < n_pass; ++pass) {
-        const int hi = top_bit - 8 * pass, lo = hi >= 7 ? hi - 7 : 0;
-        const uint32_t dmask = (1u << (hi - lo + 1)) - 1u;
-        // pass p counts into set p % 3 and clears set (p + 1) % 3, last read in pass p - 2 (one barrier per pass); the
-        // leading digit's histogram is shared
-        unsigned int *hist[NT] = {sh.hist[pass % 3], pass == 0 ? sh.hist[0] : sh.hist2[pass % 3]};
-        for (int i = threadIdx.x; i < 256; i += blockDim.x) {
-            sh.hist[(pass + 1) % 3][i] = 0;
-            sh.hist2[(pass + 1) % 3][i] = 0;
-        }
-        if (pass == 0) {
-            const int n_round = (n + blockDim.x - 1) / blockDim.x * blockDim.x;
-            for (int i = threadIdx.x; i < n_round; i += blockDim.x) {
-                const uint32_t k = i < n ? key(i) : 0u;
-                wave_hist_add(hist[0], (k >> lo) & dmask, i < n);
-            }
-        } else if (pass == 1) {
-            // the one sweep that also fills the lists; a threshold under the same leading digit as an earlier one
-            // reads that one's list
-            bool fill[NT];
-#pragma unroll
-            for (int t = 0; t < NT; ++t) {
-                int same_as = -1;
-#pragma unroll
-                for (int u = 0; u < t; ++u)
-                    if (same_as < 0 && prefix[u] == prefix[t]) same_as = u;
-                fill[t] = same_as < 0 && matching[t] <= kCap;
-                list_of[t] = same_as >= 0 ? list_of[same_as] : (fill[t] ? t : -1);
-            }
-            for (int i = threadIdx.x; i < n; i += blockDim.x) {
-                const uint32_t k = key(i);
-                const uint32_t kk = k & known, dg = (k >> lo) & dmask;
-#pragma unroll
-                for (int t = 0; t < NT; ++t)
-                    if (kk == prefix[t]) {
-                        atomicAdd(&hist[t][dg], 1u);
-                        if (fill[t]) sh.keys[t * kCap + atomicAdd(&sh.list_len[t], 1)] = k;
-                    }
-            }
-        } else {
-#pragma unroll
-            for (int t = 0; t < NT; ++t) {
-                if (list_of[t] >= 0) {
-                    // (the list holds the keys that matched after the leading digit: a superset of the current matches)
-                    const uint32_t *lst = sh.keys + list_of[t] * kCap;
-                    const int len = sh.list_len[list_of[t]];
-                    for (int i = threadIdx.x; i < len; i += blockDim.x) {
-                        const uint32_t k = lst[i];
-                        if ((k & known) == prefix[t]) atomicAdd(&hist[t][(k >> lo) & dmask], 1u);
-                    }
-                } else {
-                    for (int i = threadIdx.x; i < n; i += blockDim.x) {
-                        const uint32_t k = key(i);
-                        if ((k & known) == prefix[t]) atomicAdd(&hist[t][(k >> lo) & dmask], 1u);
-                    }
-                }
-            }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int t = 0; t < NT; ++t) {
-            int c[4], lane_tot = 0;
+    const auto larger = [](uint32_t a, uint32_t b) { return a > b ? a : b; };
+    const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int nw = (blockDim.x + kWave - 1) / kWave;
+    unsigned int *const bins = &sh.hist[0][0];
+    uint32_t *const list = &sh.list[0];
+    for (int i = threadIdx.x; i < kSelBins / 4; i += blockDim.x) reinterpret_cast<uint4 *>(bins)[i] = make_uint4(0, 0, 0, 0);
+    if (threadIdx.x == 0) sh.list_len = 0;
+    uint32_t key_max = 0u, inv_min = 0u;  // (the smallest key as the largest complement)
+    for (int i = threadIdx.x; i < n; i += blockDim.x) {
+        const uint32_t k = key(i);
+        key_max = larger(key_max, k), inv_min = larger(inv_min, ~k);
+    }
+    key_max = wave_reduce_last(key_max, larger), inv_min = wave_reduce_last(inv_min, larger);
+    if (lane == kWave - 1) sh.extreme[0][wave] = key_max, sh.extreme[1][wave] = inv_min;
+    __syncthreads();
+    const bool some = lane % 16 < nw;
+    key_max = __builtin_amdgcn_readfirstlane(row_reduce(some ? sh.extreme[0][lane % 16] : 0u, larger));
+    inv_min = __builtin_amdgcn_readfirstlane(row_reduce(some ? sh.extreme[1][lane % 16] : 0u, larger));
+    const uint32_t range = key_max - ~inv_min;
+    int remaining = n_top, matching = n;
+    uint32_t lo = 0u;  // distances from the largest key; the interval is [lo, lo + 2^shift)
+    int shift = 0;
+    if (range != 0u) {
+        shift = max(0, 32 - __builtin_clz(range) - kSelBits);
+        for (int i = threadIdx.x; i < n; i += blockDim.x) atomicAdd(&bins[(key_max - key(i)) >> shift], 1u);
+        for (;;) {
+            __syncthreads();
+            // lane l owns bins 16 l .. 16 l + 15
+            int c[16], sum = 0;
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                c[q] = (int)hist[t][255 - (4 * lane + q)];
-                lane_tot += c[q];
+                const uint4 v = reinterpret_cast<const uint4 *>(bins)[4 * lane + q];
+                c[4 * q] = (int)v.x, c[4 * q + 1] = (int)v.y, c[4 * q + 2] = (int)v.z, c[4 * q + 3] = (int)v.w;
+                sum += (c[4 * q] + c[4 * q + 1]) + (c[4 * q + 2] + c[4 * q + 3]);
             }
-            int before = wave_incl_scan(lane_tot) - lane_tot;
-            int digit = -1, rem_new = 0, in_digit = 0;
+            int before = wave_incl_scan(sum) - sum;
+            const int owner = __builtin_ctzll(__ballot(before < remaining && remaining <= before + sum));
+            int bin = 0, rest = 0, in_bin = 0;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                if (before < remaining[t] && remaining[t] <= before + c[q]) {
-                    digit = 255 - (4 * lane + q);
-                    rem_new = remaining[t] - before;
-                    in_digit = c[q];
-                }
+            for (int q = 0; q < 16; ++q) {
+                if (before < remaining && remaining <= before + c[q]) bin = 16 * lane + q, rest = remaining - before, in_bin = c[q];
                 before += c[q];
             }
-            const int owner = __builtin_ctzll(__ballot(digit >= 0));
-            digit = __builtin_amdgcn_readlane(digit, owner);
-            remaining[t] = __builtin_amdgcn_readlane(rem_new, owner);
-            matching[t] = __builtin_amdgcn_readlane(in_digit, owner);
-            prefix[t] |= ((uint32_t)digit) << lo;
+            lo += (uint32_t)__builtin_amdgcn_readlane(bin, owner) << shift;
+            remaining = __builtin_amdgcn_readlane(rest, owner);
+            matching = __builtin_amdgcn_readlane(in_bin, owner);
+            if (matching <= kWave || shift == 0) break;
+            const int next = max(0, shift - kSelBits);
+            __syncthreads();
+            for (int i = threadIdx.x; i < kSelBins / 4; i += blockDim.x)
+                reinterpret_cast<uint4 *>(bins)[i] = make_uint4(0, 0, 0, 0);
+            __syncthreads();
+            for (int i = threadIdx.x; i < n; i += blockDim.x) {
+                const uint32_t u = key_max - key(i);
+                if (u >= lo && (u - lo) >> shift == 0) atomicAdd(&bins[(u - lo) >> next], 1u);
+            }
+            shift = next;
         }
-        known |= dmask << lo;
+    }
+    if (shift == 0) {  // equal keys
+        kth = key_max - lo;
+        take = remaining;
+        cut = remaining < matching;
+        return;
+    }
+    for (int i = threadIdx.x; i < n; i += blockDim.x) {
+        const uint32_t u = key_max - key(i);
+        if (u >= lo && (u - lo) >> shift == 0) list[atomicAdd(&sh.list_len, 1)] = u;
     }
     __syncthreads();
-#pragma unroll
-    for (int t = 0; t < NT; ++t) kth[t] = prefix[t], take[t] = remaining[t];
+    const uint32_t u = lane < matching ? list[lane] : 0xffffffffu;
+    int less = 0, equal = 0;
+    for (int q = 0; q < matching; ++q) {
+        const uint32_t v = (uint32_t)__builtin_amdgcn_readlane((int)u, q);
+        less += v < u, equal += v == u;
+    }
+    const int at = __builtin_ctzll(__ballot(lane < matching && less < remaining && remaining <= less + equal));
+    kth = key_max - (uint32_t)__builtin_amdgcn_readlane((int)u, at);
+    take = remaining - __builtin_amdgcn_readlane(less, at);
+    cut = take < __builtin_amdgcn_readlane(equal, at);
 }
 
 struct SelectNoHook {
@@ -393,22 +365,21 @@ __device__ __forceinline__ void block_select_candidates(const float *__restrict_
     uint32_t kth;
     int take;
     SEL_STAMP(1);
-    if (keys_ext && in_lds && k > 0) {
-        // a large key set in the caller's LDS: sh.keys is free for the short lists of the sweeps after the second
-        // digit (the two-threshold form, asked for the same rank twice)
-        const int cnt2[2] = {k, k};
-        uint32_t kth2[2];
-        int take2[2];
-        radix_thresholds_lists<2>(key, n_cand, cnt2, sh, kth2, take2);
-        kth = kth2[0], take = take2[0];
-    } else {
+    bool cut = true;  // some of the elements equal to kth are out: which, their order says
+    if (in_lds)
+        interval_threshold(key, n_cand, k, sh, kth, take, cut);
+    else
         radix_threshold(key, n_cand, k, sh, kth, take);
-    }
     SEL_STAMP(2);
 
     const int E = (n_cand + blockDim.x - 1) / blockDim.x;
     const int lo = min(n_cand, (int)threadIdx.x * E), hi = min(n_cand, lo + E);
     int cnt[2] = {0, 0}, tot[2];
+    if (!cut) {  // (where the selected stand among themselves is of no interest yet)
+        for (int i = threadIdx.x; i < n_cand; i += blockDim.x)
+            if (k > 0 && key(i) >= kth) on_selected(i);
+        after_selected();
+    }
     for (int i = lo; i < hi; ++i) {
         uint32_t kv = key(i);
         cnt[0] += (kv == kth);
@@ -416,16 +387,16 @@ __device__ __forceinline__ void block_select_candidates(const float *__restrict_
     }
     block_excl_scan<2>(cnt, tot, sh);
     SEL_STAMP(3);
-    {
+    if (cut) {
         int eq = cnt[0];
         for (int i = lo; i < hi; ++i) {
             uint32_t kv = key(i);
             if ((kv > kth) || (kv == kth && eq < take)) on_selected(i);
             eq += (kv == kth);
         }
+        SEL_STAMP(4);
+        after_selected();
     }
-    SEL_STAMP(4);
-    after_selected();
     SEL_STAMP(5);
     // position of a selected element = (# greater before it) + (# admitted equal before it)
     if (keys_ext && in_lds) {
