@@ -570,7 +570,7 @@ int pop_prefill_forward(pop_layer_t *L, const void *x, int T, int n_ret, int n_c
     }
     if (T == 0) return POP_OK;  // no token rows to produce
     if (keep && by_channel) {
-        POP_HIP(launch_down_gemm_rows(L->w, d, m, L->top_list, L->top_list + m, L->ffn_hall, ldt, T, n_split, L->n_cu, L->ffn_part, y,
+        POP_HIP(launch_down_gemm_rows(L->w, d, m, L->top_list, n_ret + k0, L->ffn_hall, ldt, T, n_split, L->n_cu, L->ffn_part, y,
                                       ydtype == POP_BF16, s, L->zero_row));
         return POP_OK;
     }

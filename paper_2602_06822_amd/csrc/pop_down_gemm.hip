@@ -537,8 +537,7 @@ __device__ __forceinline__ void dd_load4(const void *to, const void *from)
 // H rows NA steps and the weight rows NB - 1 steps ahead, and loaded a step earlier than there.
 template <int MF, bool kStream>
 __global__ __launch_bounds__(kDdThreads, 1) void down_gemm_rows_kernel(const uint16_t *__restrict__ w, int d,
-                                                                       const int *__restrict__ list,
-                                                                       const int *__restrict__ n_list,
+                                                                       const int *__restrict__ list, int a,
                                                                        const uint16_t *__restrict__ ht, int ldt, int T,
                                                                        int n_tt, int n_nt, int n_split, int per_xcd,
                                                                        const uint16_t *__restrict__ zero_row,
@@ -558,7 +557,6 @@ __global__ __launch_bounds__(kDdThreads, 1) void down_gemm_rows_kernel(const uin
     const int ttile = logical % n_tt, ntile = (logical / n_tt) % n_nt, split = logical / (n_tt * n_nt);
     const int t0 = ttile * BM, n0 = ntile * kDgBN;
 
-    const int a = *n_list;
     const int steps_all = (a + kDgBK - 1) / kDgBK, steps_per = (steps_all + n_split - 1) / n_split;
     const int ks0 = min(split * steps_per, steps_all), ks1 = min(ks0 + steps_per, steps_all);
     const int n_steps = ks1 - ks0;
@@ -803,14 +801,14 @@ static hipError_t down_gemm_reduce(const float *part, int n_split, int T, int d,
 
 bool down_gemm_by_channel(int d) { return d % kDgBN == 0; }
 
-hipError_t launch_down_gemm_rows(const void *w, int d, int m, const int *list, const int *n_list, const uint16_t *ht, int ldt,
+hipError_t launch_down_gemm_rows(const void *w, int d, int m, const int *list, int n_list, const uint16_t *ht, int ldt,
                                  int T, int n_split, int n_cu, float *part, void *y, int y_bf16, hipStream_t s,
                                  const uint16_t *zero_row)
 {
     if (!down_gemm_by_channel(d) || ldt % 64 || ldt < T) return hipErrorInvalidValue;
     int split = 1;
-    void (*kernel)(const uint16_t *, int, const int *, const int *, const uint16_t *, int, int, int, int, int, int,
-                   const uint16_t *, float *, void *, int);
+    void (*kernel)(const uint16_t *, int, const int *, int, const uint16_t *, int, int, int, int, int, int, const uint16_t *, float *,
+                   void *, int);
     size_t lds = 0;
     const int mf = dd_shape(T, d, n_cu, &split), n_tt = (T + 64 * mf - 1) / (64 * mf);
     const bool stream = n_tt == 1 && stream_rows(d, m, 1, kStreamPromptBytes);

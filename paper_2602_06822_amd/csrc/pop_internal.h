@@ -315,7 +315,7 @@ hipError_t launch_down_gemm_bf16(const void *w, int d, const int *list, const in
 // rows are read by the list, nothing is gathered.  down_gemm_by_channel: widths it takes.  zero_row: kZeroRowBytes of zeros.
 constexpr int kRowsSlack = 512, kZeroRowBytes = 1024;
 bool down_gemm_by_channel(int d);
-hipError_t launch_down_gemm_rows(const void *w, int d, int m, const int *list, const int *n_list, const uint16_t *ht, int ldt,
+hipError_t launch_down_gemm_rows(const void *w, int d, int m, const int *list, int n_list, const uint16_t *ht, int ldt,
                                  int T, int n_split, int n_cu, float *part, void *y, int y_bf16, hipStream_t s,
                                  const uint16_t *zero_row);
 // bf16 layers: the prefill contraction (s2_part as in launch_prefill_gateup) that also keeps H:
