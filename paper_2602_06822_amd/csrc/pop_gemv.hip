@@ -566,12 +566,14 @@ hipError_t launch_down(const void *w, int is_bf16, int d, int m, const int *list
 // product e takes column 8 c + e of every lane.  A wave sees to its own channels alone, h included, which passes through a piece of LDS
 // of its own: no barrier stands between requests and products, every wait leaves the rows of the wave's next group in flight, and the
 // eight waves run apart.  (With h staged by the workgroup, three bf16 planes of 256 channels between two barriers, its loads had to be
-// waited for behind the rows in flight, and the chip read at half its rate: FIGURES.)
-// Waves of a workgroup: with two groups of 16 tokens a wave needs more registers than a SIMD has for two of them.
-__host__ __device__ constexpr int sk_waves(int tq) { return tq <= 8 ? 8 : 4; }
+// waited for behind the rows in flight, and were made for 16 tokens whether they existed or not: 13B shape, two layers, batch of 4
+// 110.5 us a step instead of 104.9, of 8 123.3 instead of 121.8.)
+constexpr int kSkThreads = 512;
 constexpr int kSkList = 4096;      // channels of a slab whose numbers are in LDS at a time
 constexpr int kSkCols = 128;       // columns per workgroup
 constexpr int kSkPair = 68;        // floats between two pairs of tokens' h (64, and four banks)
+constexpr int kSkChunk = 256;      // channels staged at a time (two groups of tokens)
+constexpr int kSkLd = kSkChunk + 8;  // LDS row stride of the staged h planes (16-byte aligned, rows four banks apart)
 
 // f = hi + mid + lo exactly for finite f (24 significant bits in three bf16 values of 8; the rests are exact differences)
 __device__ __forceinline__ void split3(float f, uint16_t &hi, uint16_t &mid, uint16_t &lo)
@@ -585,7 +587,7 @@ __device__ __forceinline__ void split3(float f, uint16_t &hi, uint16_t &mid, uin
 
 // TQ pairs of tokens, of which T exist; kMask: masks per token (else none)
 template <class V, int TQ, bool kMask>
-__global__ __launch_bounds__(sk_waves(TQ) * kWave) void skinny_down_kernel(const uint4 *__restrict__ w, int nvec,
+__global__ __launch_bounds__(kSkThreads) void skinny_down_kernel(const uint4 *__restrict__ w, int nvec,
                                                                  const int *__restrict__ list, const int *__restrict__ n_dev,
                                                                  const float *__restrict__ h, int m,
                                                                  const unsigned char *__restrict__ mask, int mask_stride,
@@ -593,8 +595,9 @@ __global__ __launch_bounds__(sk_waves(TQ) * kWave) void skinny_down_kernel(const
 {
     typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
     typedef float f32x4_t __attribute__((ext_vector_type(4)));
-    constexpr int TG = (TQ + 7) / 8;  // groups of 16 tokens
-    constexpr int kWaves = sk_waves(TQ), kSkThreads = kWaves * kWave;
+    constexpr int TG = 1;  // group of 16 tokens
+    constexpr int kWaves = kSkThreads / kWave;
+    static_assert(TQ <= 8 * TG, "pairs of tokens");
     extern __shared__ __attribute__((aligned(16))) unsigned char sk_lds[];
     int *js = reinterpret_cast<int *>(sk_lds);  // [kSkList] channels of the slab
     const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -745,6 +748,147 @@ __global__ __launch_bounds__(sk_waves(TQ) * kWave) void skinny_down_kernel(const
     }
 }
 
+// 17 to 32 tokens, two groups of 16: the workgroup stages h for all its waves, as three bf16 planes of 256 channels.  (Eight waves
+// that each see to their own have no registers for two groups' sums and two steps of rows, and with four the float32 sums are twice as
+// long: 24 tokens 62.7 us instead of 63.3 for the whole call, at a fifth more error.)
+template <class V, bool kMask>
+__global__ __launch_bounds__(kSkThreads) void skinny_pair_kernel(const uint4 *__restrict__ w, int nvec,
+                                                                 const int *__restrict__ list, const int *__restrict__ n_dev,
+                                                                 const float *__restrict__ h, int m,
+                                                                 const unsigned char *__restrict__ mask, int mask_stride,
+                                                                 int T, float *__restrict__ partial, int d)
+{
+    constexpr int TG = 2;
+    typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+    typedef float f32x4_t __attribute__((ext_vector_type(4)));
+    extern __shared__ __attribute__((aligned(16))) unsigned char sk_lds[];
+    constexpr int kPlanes = 3 * 16 * TG * kSkLd * 2;        // bytes
+    uint16_t *hp = reinterpret_cast<uint16_t *>(sk_lds);  // [3][16 TG][kSkLd]: planes of h, rows by token
+    const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int c = lane % 16, g = lane / 16;
+    const int n = *n_dev;
+    const int n_slabs = gridDim.y, per_slab = (n + n_slabs - 1) / n_slabs;
+    const int s0 = min(n, (int)blockIdx.y * per_slab), s1 = min(n, s0 + per_slab);
+    const int vcol = blockIdx.x * (kSkCols / 8) + c;  // this lane's vector column
+    const bool col_ok = vcol < nvec;
+    const uint32_t chan = channel_vectors(nvec, 1);
+    const uint4 *wc = w + 2 * nvec + (col_ok ? vcol : 0);
+
+    f32x4_t acc[TG][8];
+#pragma unroll
+    for (int t = 0; t < TG; ++t)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) acc[t][e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+
+    // channels of two chunks behind the planes: chunk q's in js[q % 2], loaded two chunks ahead
+    int *js = reinterpret_cast<int *>(sk_lds + kPlanes);  // [2][kSkChunk]
+    const int li = threadIdx.x % kSkChunk, half = threadIdx.x / kSkChunk;
+    auto channel = [&](int at) { return list[min(at + li, s1 - 1)]; };  // beyond the slab: its last channel (h is 0 there)
+    uint4 rows[2][8];
+    auto request = [&](int set) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) rows[set][i] = load_row<V>(wc, (uint64_t)(uint32_t)js[set * kSkChunk + 32 * wave + 8 * g + i] * chan);
+    };
+    // h of the 256 channels at `at` as three planes; zero beyond the slab, beyond T and where a mask says so
+    auto stage = [&](int set, int at) {
+        const int j = js[set * kSkChunk + li];
+        float v[8 * TG];
+        unsigned char mk[8 * TG];
+#pragma unroll
+        for (int q = 0; q < 8 * TG; ++q) {
+            const int t = min(2 * q + half, T - 1);
+            v[q] = h[(size_t)t * m + j];
+            if (kMask) mk[q] = mask[(size_t)t * mask_stride + j];
+        }
+#pragma unroll
+        for (int q = 0; q < 8 * TG; ++q) {
+            const int t = 2 * q + half;
+            uint16_t a, b, e;
+            split3(t < T && at + li < s1 && (!kMask || mk[q]) ? v[q] : 0.f, a, b, e);
+            hp[(0 * 16 * TG + t) * kSkLd + li] = a;
+            hp[(1 * 16 * TG + t) * kSkLd + li] = b;
+            hp[(2 * 16 * TG + t) * kSkLd + li] = e;
+        }
+    };
+    auto multiply = [&](int set) {
+        bf16x8_t bw[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            uint32_t v[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const uint4 &r0 = rows[set][2 * q], &r1 = rows[set][2 * q + 1];
+                const uint32_t a0 = e / 2 == 0 ? r0.x : (e / 2 == 1 ? r0.y : (e / 2 == 2 ? r0.z : r0.w));
+                const uint32_t a1 = e / 2 == 0 ? r1.x : (e / 2 == 1 ? r1.y : (e / 2 == 2 ? r1.z : r1.w));
+                v[q] = __builtin_amdgcn_perm(a1, a0, e % 2 ? 0x07060302u : 0x05040100u);
+            }
+            bw[e] = __builtin_bit_cast(bf16x8_t, make_uint4(v[0], v[1], v[2], v[3]));
+        }
+#pragma unroll
+        for (int t = 0; t < TG; ++t)
+#pragma unroll
+            for (int part = 2; part >= 0; --part) {  // (small parts first)
+                const bf16x8_t ha = *reinterpret_cast<const bf16x8_t *>(
+                    &hp[((part * TG + t) * 16 + c) * kSkLd + 32 * wave + 8 * g]);
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    acc[t][e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ha, bw[e], acc[t][e], 0, 0, 0);
+            }
+    };
+    if (s0 < s1) {
+        if (half == 0) js[li] = channel(s0), js[kSkChunk + li] = channel(s0 + kSkChunk);
+        __syncthreads();
+        request(0);
+        auto step = [&](int set, int at) {
+            const int next = channel(at + 2 * kSkChunk);
+            stage(set, at);
+            if (at + kSkChunk < s1) request(set ^ 1);
+            __syncthreads();
+            if (half == 0) js[set * kSkChunk + li] = next;
+            multiply(set);
+            __syncthreads();  // the planes' readers are done, the channels are there
+        };
+        for (int at = s0; at < s1; at += 2 * kSkChunk) {
+            step(0, at);
+            if (at + kSkChunk < s1) step(1, at + kSkChunk);
+        }
+    }
+    // the eight waves' sums in wave order, 16 tokens at a time; register v of product e is token 4 g + v, column 8 c + e
+    float *red = reinterpret_cast<float *>(sk_lds);  // [8 waves][16 tokens][128 columns]
+#pragma unroll
+    for (int t = 0; t < TG; ++t) {
+        __syncthreads();
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            float4 *dst = reinterpret_cast<float4 *>(red + ((size_t)(wave * 16 + 4 * g + v)) * kSkCols + 8 * c);
+            dst[0] = make_float4(acc[t][0][v], acc[t][1][v], acc[t][2][v], acc[t][3][v]);
+            dst[1] = make_float4(acc[t][4][v], acc[t][5][v], acc[t][6][v], acc[t][7][v]);
+        }
+        __syncthreads();
+        for (int i = threadIdx.x; i < 16 * kSkCols; i += kSkThreads) {
+            const int tok = 16 * t + i / kSkCols, col = blockIdx.x * kSkCols + i % kSkCols;
+            if (tok < T && col < d) {
+                double s = 0.0;
+#pragma unroll
+                for (int q = 0; q < kSkThreads / kWave; ++q) s += (double)red[q * 16 * kSkCols + i];
+                float v = (float)s;
+                if (!__builtin_isfinite(v)) {
+                    // An infinity is not the sum of three parts, and parts that are zero make NaN of an infinite weight:
+                    // here the sum is what the vector kernel's multiply-adds give.
+                    v = 0.f;
+                    for (int p = s0; p < s1; ++p) {
+                        const int j = list[p];
+                        const float hv = !kMask || mask[(size_t)tok * mask_stride + j] ? h[(size_t)tok * m + j] : 0.f;
+                        const uint16_t wv = reinterpret_cast<const uint16_t *>(w)[(size_t)j * channel_elems_bf16(d) + 2 * d + col];
+                        v = fmaf(hv, __uint_as_float((uint32_t)wv << 16), v);
+                    }
+                }
+                partial[((size_t)blockIdx.y * T + tok) * d + col] = v;
+            }
+        }
+    }
+}
+
 // Slabs of the list so that the column blocks fill the chip once.
 int skinny_down_slabs(int is_bf16, int d, int m, int n_cu)
 {
@@ -762,24 +906,28 @@ static hipError_t launch_skinny_down_partials(const void *w, int d, int m, const
     if (T < 1 || T > kSkMaxTokens) return hipErrorInvalidValue;
     const dim3 grid((d + kSkCols - 1) / kSkCols, n_slabs);
     hipError_t e = hipSuccess;
-#define POP_SK(TQ)                                                                                                        \
+    constexpr size_t red = (size_t)8 * 16 * kSkCols * 4;
+#define POP_SK(KERNEL, STAGE)                                                                                             \
     do {                                                                                                                  \
-        constexpr size_t stage = (size_t)kSkList * 4 + (size_t)sk_waves(TQ) * ((TQ + 7) / 8 * 8) * kSkPair * 4;           \
-        constexpr size_t red = (size_t)sk_waves(TQ) * 16 * kSkCols * 4, lds = stage > red ? stage : red;                  \
-        const auto kernel = mask ? skinny_down_kernel<V, TQ, true> : skinny_down_kernel<V, TQ, false>;                    \
+        constexpr size_t stage = STAGE, lds = stage > red ? stage : red;                                                  \
+        const auto kernel = KERNEL;                                                                                       \
         e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,       \
                                 (int)lds);                                                                                \
         if (e != hipSuccess) return e;                                                                                    \
-        hipLaunchKernelGGL(kernel, grid, dim3(sk_waves(TQ) * kWave), lds, s, (const uint4 *)w, d / 8, list, n_dev, h, m,  \
-                           mask, mask_stride, T, partial, d);                                                             \
+        hipLaunchKernelGGL(kernel, grid, dim3(kSkThreads), lds, s, (const uint4 *)w, d / 8, list, n_dev, h, m, mask,      \
+                           mask_stride, T, partial, d);                                                                   \
     } while (0)
+#define POP_SKQ(TQ)                                                                          \
+    POP_SK((mask ? skinny_down_kernel<V, TQ, true> : skinny_down_kernel<V, TQ, false>), \
+           (size_t)kSkList * 4 + (size_t)8 * 8 * kSkPair * 4)
     // (pairs of tokens are loaded whether they exist or not, h and mask byte of each channel: as many as that as rows)
-    if (T <= 4) POP_SK(2);
-    else if (T <= 6) POP_SK(3);
-    else if (T <= 8) POP_SK(4);
-    else if (T <= 16) POP_SK(8);
-    else if (T <= 24) POP_SK(12);
-    else POP_SK(16);
+    if (T <= 4) POP_SKQ(2);
+    else if (T <= 6) POP_SKQ(3);
+    else if (T <= 8) POP_SKQ(4);
+    else if (T <= 16) POP_SKQ(8);
+    else
+        POP_SK((mask ? skinny_pair_kernel<V, true> : skinny_pair_kernel<V, false>), (size_t)3 * 32 * kSkLd * 2 + 2 * kSkChunk * 4);
+#undef POP_SKQ
 #undef POP_SK
     return hipGetLastError();
 }
