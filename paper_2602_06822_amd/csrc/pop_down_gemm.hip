@@ -10,7 +10,8 @@
 // receives it transposed, lane j the 4 k-values of column j.  Two such reads make the 8 values of one B fragment.
 //
 // Short prompts do not give enough tiles to fill the chip, so the contraction is split into n_split ranges whose float32
-// partial results are summed, in split order, by a second kernel (deterministic).  Two kernels:
+// partial results are summed, in split order, by a second kernel (deterministic).  Kernels:
+//  * down_gemm_rows_kernel (a prompt's own forward pass, d a multiple of 128): H by channel, [m][T], both operands are rows of the list;
 //  * down_gemm_dma_kernel (d a multiple of 128): both operands go from global memory straight into rings of unpadded,
 //    swizzled LDS buffers, with one exact wait per k-step (described at the kernel);
 //  * down_gemm_bf16_kernel (other d): 256 tokens x 128 columns per workgroup, 8 waves (4 along the tokens x 2 along n), wave

@@ -2,8 +2,8 @@
 // per-step candidate top-k (Sec. 3.3 "Decoding Stage") and the index-list compactions around them.
 //
 // All selections use one strict total order on channels: higher score first, equal scores by lower channel
-// index.  Scores are mapped to order-preserving 32-bit keys; a digit-wise select from the most significant bits down
-// finds the n-th best element, so the result is deterministic.
+// index.  Scores are mapped to order-preserving 32-bit keys; the n-th best element is found in equal intervals of their range
+// (by digits from the most significant bits down where they do not fit the LDS), so the result is deterministic.
 #include "pop_select_dev.h"
 
 namespace pop {
