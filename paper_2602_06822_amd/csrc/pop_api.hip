@@ -582,7 +582,7 @@ int pop_prefill_forward(pop_layer_t *L, const void *x, int T, int n_ret, int n_c
     }
     if (few) {
         POP_HIP(launch_skinny_down(L->w, L->is_bf16, d, m, L->top_list, L->top_list + m, L->hs, nullptr, 0, T, L->partial,
-                                   skinny_down_slabs(L->is_bf16, d, m, L->n_cu), y, ydtype == POP_BF16, s));
+                                   skinny_down_slabs(L->is_bf16, d, m, L->n_cu), y, ydtype == POP_BF16, kStreamPromptBytes, s));
         return POP_OK;
     }
     const int rc = pop_pruned_ffn(L, x, T, L->ffn_any, 1, y, ydtype, stream);
@@ -633,10 +633,10 @@ static int decode_select(pop_layer_t *L, const void *x_t, int B, const int *k, v
                                 s));
             if (B == 1)
                 POP_HIP(launch_gateup(L->w, L->is_bf16, L->d, m, x_t, 1, L->active_idx, n_ret + kk.k[0], nullptr, L->h,
-                                      nullptr, nullptr, 0, 0, L->n_cu, s));
+                                      nullptr, nullptr, 0, 0, L->n_cu, kStreamStepBytes, s));
             else
                 POP_HIP(launch_gateup(L->w, L->is_bf16, L->d, m, x_t, B, L->ulist, m, L->n_ulist, L->h, nullptr, nullptr,
-                                      0, 0, L->n_cu, s));
+                                      0, 0, L->n_cu, kStreamStepBytes, s));
             L->step_fused = false;
             L->step_B = B;
             L->step_k = kk;
@@ -655,7 +655,7 @@ static int decode_select(pop_layer_t *L, const void *x_t, int B, const int *k, v
                                          L->n_cu, &sel_inside, s));
         if (!sel_inside) {
             POP_HIP(launch_gateup(L->w, L->is_bf16, L->d, m, x_t, B, L->rc_idx, n_ret + n_cand, nullptr, L->h, L->nrm,
-                                  L->cscore, m, n_cand, L->n_cu, s));
+                                  L->cscore, m, n_cand, L->n_cu, kStreamStepBytes, s));
             // one mask for the batch: every sequence's row gets the scores aggregated over the batch, so the B
             // selections below come out identical
             if (shared) POP_HIP(launch_aggregate_scores(L->cscore, m, B, n_cand, s));
@@ -682,13 +682,13 @@ static int decode_output(pop_layer_t *L, int T, void *y, pop_dtype_t ydtype, con
         POP_HIP(launch_decode_tail(L->partial, L->plan.n_wg, d, y, y_bf16, s, copy));
     else if (T == 1)
         POP_HIP(launch_down(L->w, L->is_bf16, d, m, L->active_idx, nullptr, L->n_ret + L->step_k.k[0], L->h, nullptr, 0, 1,
-                            L->partial, L->n_slabs, y, y_bf16, s, copy));
+                            L->partial, L->n_slabs, y, y_bf16, kStreamStepBytes, s, copy));
     else if (L->is_bf16 && T >= skinny_min_batch(d, m))
         POP_HIP(launch_skinny_down(L->w, L->is_bf16, d, m, L->ulist, L->n_ulist, L->h, L->mask, m, T, L->partial,
-                                   skinny_down_slabs(L->is_bf16, d, m, L->n_cu), y, y_bf16, s, copy));
+                                   skinny_down_slabs(L->is_bf16, d, m, L->n_cu), y, y_bf16, kStreamStepBytes, s, copy));
     else
         POP_HIP(launch_down(L->w, L->is_bf16, d, m, L->ulist, L->n_ulist, 0, L->h, L->mask, m, T, L->partial, L->n_slabs, y,
-                            y_bf16, s, copy));
+                            y_bf16, kStreamStepBytes, s, copy));
     return POP_OK;
 }
 
@@ -751,7 +751,7 @@ int pop_pruned_ffn(pop_layer_t *L, const void *x, int T, const unsigned char *ma
             POP_HIP(launch_skinny_down(L->w, L->is_bf16, d, m, L->ulist, L->n_ulist, L->hs,
                                        mask_rows > 1 ? mask + (size_t)t0 * m : nullptr, m, n, L->partial,
                                        skinny_down_slabs(L->is_bf16, d, m, L->n_cu),
-                                       (char *)y + (size_t)t0 * d * ysize, y_bf16, s));
+                                       (char *)y + (size_t)t0 * d * ysize, y_bf16, kStreamPartBytes, s));
         }
         return POP_OK;
     }
@@ -762,9 +762,9 @@ int pop_pruned_ffn(pop_layer_t *L, const void *x, int T, const unsigned char *ma
         if (mk) POP_HIP(launch_mask_to_list(mk, Bc, m, L->ulist, L->n_ulist, s));
         const char *xc = (const char *)x + (size_t)t0 * d * L->esize;
         POP_HIP(launch_gateup(L->w, L->is_bf16, d, m, xc, Bc, L->ulist, m, L->n_ulist, L->h, nullptr, nullptr, 0, 0,
-                              L->n_cu, s));
+                              L->n_cu, kStreamPartBytes, s));
         POP_HIP(launch_down(L->w, L->is_bf16, d, m, L->ulist, L->n_ulist, 0, L->h, mk, m, Bc, L->partial, L->n_slabs,
-                            (char *)y + (size_t)t0 * d * ysize, y_bf16, s));
+                            (char *)y + (size_t)t0 * d * ysize, y_bf16, kStreamPartBytes, s));
     }
     return POP_OK;
 }

@@ -291,9 +291,9 @@ static hipError_t gateup_dispatch(const void *w, int nvec, const void *x, int B,
 
 hipError_t launch_gateup(const void *w, int is_bf16, int d, int m, const void *x, int B, const int *rows, int n_rows,
                          const int *n_rows_dev, float *h, const float *nrm, float *cscore, int cs_stride, int n_score,
-                         int n_cu, hipStream_t s)
+                         int n_cu, long long stream_from, hipStream_t s)
 {
-    if (stream_rows(d, m, is_bf16, kStreamStepBytes))
+    if (stream_rows(d, m, is_bf16, stream_from))
         return gateup_dispatch<StreamBF16>(w, d / 8, x, B, rows, n_rows, n_rows_dev, h, m, nrm, cscore, cs_stride,
                                            n_score, n_cu, s);
     if (is_bf16)
@@ -543,9 +543,9 @@ int down_num_slabs(int d, int is_bf16)
 
 hipError_t launch_down(const void *w, int is_bf16, int d, int m, const int *list, const int *n_dev, int n_host,
                        const float *h, const unsigned char *mask, int mask_stride, int B, float *partial, int n_slabs,
-                       void *y, int y_bf16, hipStream_t s, const StepCopy *copy)
+                       void *y, int y_bf16, long long stream_from, hipStream_t s, const StepCopy *copy)
 {
-    if (stream_rows(d, m, is_bf16, kStreamStepBytes))
+    if (stream_rows(d, m, is_bf16, stream_from))
         return down_dispatch<StreamBF16>(w, d / 8, d, m, list, n_dev, n_host, h, mask, mask_stride, B, partial, n_slabs,
                                          y, y_bf16, s, copy);
     if (is_bf16)
@@ -934,10 +934,9 @@ static hipError_t launch_skinny_down_partials(const void *w, int d, int m, const
 
 hipError_t launch_skinny_down(const void *w, int is_bf16, int d, int m, const int *list, const int *n_dev, const float *h,
                               const unsigned char *mask, int mask_stride, int T, float *partial, int n_slabs, void *y,
-                              int y_bf16, hipStream_t s, const StepCopy *copy)
+                              int y_bf16, long long stream_from, hipStream_t s, const StepCopy *copy)
 {
-    // (a step's sequences or a short prompt)
-    const bool stream = stream_rows(d, m, is_bf16, T <= POP_MAX_BATCH ? kStreamStepBytes : kStreamPromptBytes);
+    const bool stream = stream_rows(d, m, is_bf16, stream_from);
     hipError_t e =
         stream    ? launch_skinny_down_partials<StreamBF16>(w, d, m, list, n_dev, h, mask, mask_stride, T, partial, n_slabs, s)
         : is_bf16 ? launch_skinny_down_partials<VecBF16>(w, d, m, list, n_dev, h, mask, mask_stride, T, partial, n_slabs, s)

@@ -47,13 +47,16 @@ __host__ __device__ __forceinline__ constexpr int channel_gap(int nvec, int is_b
     return is_bf16 && (nvec == 512 || nvec == 1024) ? 8 : 0;
 }
 // Weight rows that a launch reads once are loaded past the caches (non-temporal) on layers too large for the next pass to find
-// them there.  A plain read of rows from memory: 5.7-6.0 TB/s with ordinary loads, 6.4 with these; of rows that the 256 MB
-// last-level cache holds up to 7 % slower.  So the rule is the size of a layer's weights (3 d m, bf16), and as two layers in turn
-// stay in that cache up to about 128 MB each, that is where it lies for prompts: one layer of 67 MB, 256 tokens 56.9 us without /
-// 59.8 with, 24 tokens 35.8 / 36.9, of 101 MB 70.8 / 71.3 and 44.1 / 44.5, of 270 MB 69.3 / 64.3 (24 tokens).  Decode steps, which
-// do nothing but read, gain earlier: two layers of 67 MB 41.1 / 40.7 and four 86.9 / 81.8 (four sequences, two layers: 58.4 / 57.9),
-// of 49 MB 37.8 / 38.8 and 82.0 / 77.6 (51.8 / 53.9), of 101 MB 45.6 / 43.3, of 270 MB 155.1 / 143.9 (four).
-constexpr long long kStreamStepBytes = 64ll << 20, kStreamPromptBytes = 128ll << 20;
+// them there.  A plain read of rows from memory: 5.7-6.0 TB/s with ordinary loads, 6.4 with these; but what they read does not stay in
+// the 256 MB last-level cache, so where it would have been there for the next pass they lose.  A call cannot know what runs before
+// the next one on its layer: the rule is the size of the layer's weights (3 d m, bf16), drawn where no call was slower
+// with several layers in turn.  Time of a call past the caches over its time with ordinary loads:
+//   decode steps, six layers in turn: of 50 MB 1.02-1.08, of 67 MB .97-.98, of 94 MB .94-.98, of 157 MB .93-.95, of 270 MB .90-.93
+//   a prompt's own forward pass (all of gate and up, most of down), three layers: of 86 MB 1.02-1.08 (4 to 40 tokens), of 113 MB
+//   .97-.99, of 138 MB .97, of 270 MB .92-.94
+//   a stand-alone FFN (two thirds of the layer), three layers: of 67 MB 1.04-1.14 (1 to 40 tokens), of 138 MB .99-1.03, of 157 MB .96-1.00, of
+//   270 MB .90-.97
+constexpr long long kStreamStepBytes = 64ll << 20, kStreamPromptBytes = 128ll << 20, kStreamPartBytes = 144ll << 20;
 inline bool stream_rows(int d, int m, int is_bf16, long long limit) { return is_bf16 && 6ll * d * m >= limit; }
 
 // From one channel's weights to the next's.
@@ -206,14 +209,15 @@ hipError_t launch_step_copy(const StepCopy &c, hipStream_t s);
 // ---- decode GEMVs (pop_gemv.hip) ----
 // h[b][j] = silu(x_b . gate_j) * (x_b . up_j) for j in rows[0..n_rows); if cscore != null, rows [0, n_score)
 // also get cscore[b][pos] = nrm[j] * |h|.  n_rows_dev (optional) overrides n_rows with a device-side count.
+// stream_from, here and below: the size of layer from which rows go past the caches (stream_rows).
 hipError_t launch_gateup(const void *w, int is_bf16, int d, int m, const void *x, int B, const int *rows, int n_rows,
                          const int *n_rows_dev, float *h, const float *nrm, float *cscore, int cs_stride, int n_score,
-                         int n_cu, hipStream_t s);
+                         int n_cu, long long stream_from, hipStream_t s);
 // y[b][:] = sum_{i<n} hm(b, list[i]) * w[list[i]][2][:], hm = h[b][j] (masked by mask[b][j] when mask != null).
 // Two stages: slab partials then a fixed-order reduction; y written as float32 or bf16.
 hipError_t launch_down(const void *w, int is_bf16, int d, int m, const int *list, const int *n_dev, int n_host,
                        const float *h, const unsigned char *mask, int mask_stride, int B, float *partial, int n_slabs,
-                       void *y, int y_bf16, hipStream_t s, const StepCopy *copy = nullptr);
+                       void *y, int y_bf16, long long stream_from, hipStream_t s, const StepCopy *copy = nullptr);
 int down_num_slabs(int d, int is_bf16);
 // The same for up to kSkMaxTokens (bf16 layers) or kF32MaxTokens rows of h ([T][m] float32, by channel) on the matrix cores; masks one row per token
 // (mask_stride) or null.  partial: [n_slabs][T][d] float32.
@@ -221,7 +225,7 @@ constexpr int kSkMaxTokens = 32;  // (bf16)
 int skinny_down_slabs(int is_bf16, int d, int m, int n_cu);
 hipError_t launch_skinny_down(const void *w, int is_bf16, int d, int m, const int *list, const int *n_dev, const float *h,
                               const unsigned char *mask, int mask_stride, int T, float *partial, int n_slabs, void *y,
-                              int y_bf16, hipStream_t s, const StepCopy *copy = nullptr);
+                              int y_bf16, long long stream_from, hipStream_t s, const StepCopy *copy = nullptr);
 // Batched decode (2 <= B <= POP_MAX_BATCH) with the per-sequence selection inside the gate/up kernel: the listed
 // rows are the n_cand candidates followed by the n_ret retained channels; all workgroups evaluate the candidates
 // first, then the last B workgroups wait (bounded) for everybody's candidate scores and select for one sequence

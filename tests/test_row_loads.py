@@ -1,0 +1,95 @@
+"""Which calls load weight rows past the caches: the rule is the size of the layer and what the call reads of it, once or again.
+A call's kernels are read from its captured (never launched) graph, by name."""
+import ctypes
+import re
+
+import pytest
+import torch
+
+BF16, F32 = 1, 0
+
+
+class _KernelNode(ctypes.Structure):
+    _fields_ = [("block", ctypes.c_uint * 3), ("extra", ctypes.c_void_p), ("func", ctypes.c_void_p), ("grid", ctypes.c_uint * 3),
+                ("params", ctypes.c_void_p), ("shared", ctypes.c_uint)]
+
+
+def _kernels(call):
+    """Names of the kernels that call(stream) launches."""
+    hip = ctypes.CDLL("libamdhip64.so.7")  # (the one that torch has loaded)
+    hip.hipKernelNameRefByPtr.restype = ctypes.c_char_p
+    hip.hipKernelNameRefByPtr.argtypes = [ctypes.c_void_p, ctypes.c_void_p]
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        call(stream.cuda_stream)  # (scratch is allocated)
+    torch.cuda.synchronize()
+    graph, s = ctypes.c_void_p(), ctypes.c_void_p(stream.cuda_stream)
+    assert hip.hipStreamBeginCapture(s, 2) == 0
+    call(stream.cuda_stream)
+    assert hip.hipStreamEndCapture(s, ctypes.byref(graph)) == 0
+    count = ctypes.c_size_t()
+    assert hip.hipGraphGetNodes(graph, None, ctypes.byref(count)) == 0
+    nodes = (ctypes.c_void_p * count.value)()
+    assert hip.hipGraphGetNodes(graph, nodes, ctypes.byref(count)) == 0
+    names = []
+    for node in nodes:
+        kind, p = ctypes.c_int(), _KernelNode()
+        assert hip.hipGraphNodeGetType(ctypes.c_void_p(node), ctypes.byref(kind)) == 0 and kind.value == 0
+        assert hip.hipGraphKernelNodeGetParams(ctypes.c_void_p(node), ctypes.byref(p)) == 0
+        names.append(hip.hipKernelNameRefByPtr(p.func, s).decode())
+    assert hip.hipGraphDestroy(graph) == 0
+    return names
+
+
+_PAST = re.compile(r"StreamBF16|prefill_stream_kernel|down_gemm_stream_kernel|(prefill|down_gemm)_rows_kernelILi\dELb1E")
+_ROWS = re.compile(r"decode_fused_kernel|gateup\w*_kernel|skinny_\w+_kernel|down_kernel|down_gemm_\w*(rows|dma|stream|bf16)_kernel|"
+                   r"prefill_(mma|deep|stream|rows|bf16)_kernel|input_side_scores_kernel")
+
+
+def _past_the_caches(call):
+    """For every kernel of the call that reads weight rows, in order: whether past the caches."""
+    return [bool(_PAST.search(n)) for n in _kernels(call) if _ROWS.search(n)]
+
+
+@pytest.fixture
+def layer(request):
+    from paper_2602_06822_amd import binding as pop
+    d, m = request.param
+    w = [torch.zeros(s, dtype=torch.bfloat16, device="cuda") for s in ((m, d), (m, d), (d, m))]
+    h = pop.pop_layer_create(d, m, BF16, *w, 512, 8)
+    x = torch.zeros((512, d), dtype=torch.bfloat16, device="cuda")
+    y = torch.empty((512, d), device="cuda")
+    try:
+        yield pop, h, m, x, y
+    finally:
+        torch.cuda.synchronize()
+        pop.pop_layer_destroy(h)
+
+
+# (d, m of 67 MB, 94, 138 and 157 MB of weights; tokens): six layers in turn gain from 64 MiB on in decode steps, three in a
+# stand-alone FFN from 144 MiB on
+FFN = [((2048, 5504), False), ((2560, 6144), False), ((3200, 7200), False), ((4096, 6400), True)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("layer,past", FFN, indirect=["layer"])
+@pytest.mark.parametrize("T", [1, 2, 8, 12, 24, 40])
+@pytest.mark.parametrize("own_masks", [False, True])
+def test_stand_alone_ffn(layer, past, T, own_masks):
+    pop, h, m, x, y = layer
+    mask = torch.ones((T if own_masks else 1, m), dtype=torch.uint8, device="cuda")
+    got = _past_the_caches(lambda s: pop.pop_pruned_ffn(h, x[:T], T, mask, mask.shape[0], y[:T], F32, stream=s))
+    # (the matrix-core contraction over a list does from 192 MiB on)
+    few = T > 1 and T * m >= 60000
+    assert got == ([False, past] if few or T >= 32 else [past, past])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("layer", [(2048, 5504)], indirect=True)
+@pytest.mark.parametrize("B", [1, 2, 3, 8])
+def test_decode_step(layer, B):
+    pop, h, m, x, y = layer
+    n_ret, n_cand = m // 2, m // 8
+    pop.pop_prefill_partition(h, x[:64], 64, n_ret, n_cand)
+    got = _past_the_caches(lambda s: pop.pop_decode_step(h, x[:B], B, [n_cand // 2] * B, y[:B], F32, stream=s))
+    assert got and all(got)
