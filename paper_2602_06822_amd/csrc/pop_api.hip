@@ -208,7 +208,7 @@ int ffn_scratch(pop_layer *L, int T, bool keep_all, int *ldh, int *n_split, hipS
 // Whole-prompt pruned FFN (Sec. 3.4: forward pass under the pruning structure): active list from the mask(s),
 // gate/up over the listed channels with H written in compact bf16 form, then the K-gathered down-projection GEMM.
 int pruned_ffn_mfma(pop_layer *L, const void *x, int T, const unsigned char *mask, int mask_rows, void *y, int y_bf16,
-                    hipStream_t s)
+                    bool rows_read, hipStream_t s)
 {
     const int m = L->m, d = L->d;
     int ldh, n_split;
@@ -221,9 +221,53 @@ int pruned_ffn_mfma(pop_layer *L, const void *x, int T, const unsigned char *mas
         POP_HIP(launch_mask_to_list(L->ffn_any, 1, m, L->ulist, L->n_ulist, s, L->ffn_hc, ldh, T));
         tmask = mask;
     }
-    POP_HIP(launch_gateup_list_bf16(L->w, d, m, x, T, L->ulist, L->n_ulist, tmask, L->ffn_hc, ldh, L->n_cu, s));
+    POP_HIP(launch_gateup_list_bf16(L->w, d, m, x, T, L->ulist, L->n_ulist, tmask, L->ffn_hc, ldh, L->n_cu,
+                                   rows_read ? kStreamTwiceBytes : kStreamListBytes, s));
     POP_HIP(launch_down_gemm_bf16(L->w, d, L->ulist, L->n_ulist, L->ffn_hc, ldh, T, n_split, L->n_cu, L->ffn_part, y, y_bf16, s,
                                   L->zero_row));
+    return POP_OK;
+}
+
+// Pruned FFN of x under the given masks.  rows_read: the call has just read the layer's gate and up rows.
+int pruned_ffn(pop_layer *L, const void *x, int T, const unsigned char *mask, int mask_rows, void *y, int y_bf16, bool rows_read,
+               hipStream_t s)
+{
+    const int m = L->m, d = L->d, ysize = y_bf16 ? 2 : 4;
+    L->has_step = false;  // the step scratch is reused below
+    L->ulist_prefix_ok = false;
+    if (L->is_bf16 && T >= kFfnMfmaMinTokens) return pruned_ffn_mfma(L, x, T, mask, mask_rows, y, y_bf16, rows_read, s);
+    const int few = precise_max_tokens(L->is_bf16, d);
+    if (few > 0 && T > 1 && (T > L->chunk || (long long)T * m >= kFewTokenChannels)) {
+        // a few tokens (bf16 layers: all of them) per pass over the weights
+        if (mask_rows > 1 && (long long)mask_rows * m > kMaskListBytes) {
+            POP_HIP(launch_mask_any(mask, T, m, L->ffn_any, s));
+            POP_HIP(launch_mask_to_list(L->ffn_any, 1, m, L->ulist, L->n_ulist, s));
+        } else {
+            POP_HIP(launch_mask_to_list(mask, mask_rows, m, L->ulist, L->n_ulist, s));
+        }
+        for (int t0 = 0; t0 < T; t0 += few) {
+            const int n = T - t0 < few ? T - t0 : few;
+            POP_HIP(launch_precise_gateup(L->w, L->is_bf16, d, m, (const char *)x + (size_t)t0 * d * L->esize, n, L->ulist,
+                                          L->n_ulist, L->hs, nullptr, nullptr, L->n_cu, rows_read ? kStreamTwiceBytes : kStreamListBytes, s));
+            POP_HIP(launch_skinny_down(L->w, L->is_bf16, d, m, L->ulist, L->n_ulist, L->hs,
+                                       mask_rows > 1 ? mask + (size_t)t0 * m : nullptr, m, n, L->partial,
+                                       skinny_down_slabs(L->is_bf16, d, m, L->n_cu),
+                                       (char *)y + (size_t)t0 * d * ysize, y_bf16, kStreamPartBytes, s));
+        }
+        return POP_OK;
+    }
+    if (mask_rows == 1) POP_HIP(launch_mask_to_list(mask, 1, m, L->ulist, L->n_ulist, s));
+    const bool again = T > L->chunk;  // (every pass reads the same rows)
+    for (int t0 = 0; t0 < T; t0 += L->chunk) {
+        const int Bc = (T - t0 < L->chunk) ? T - t0 : L->chunk;
+        const unsigned char *mk = mask_rows == 1 ? nullptr : mask + (size_t)t0 * m;
+        if (mk) POP_HIP(launch_mask_to_list(mk, Bc, m, L->ulist, L->n_ulist, s));
+        const char *xc = (const char *)x + (size_t)t0 * d * L->esize;
+        POP_HIP(launch_gateup(L->w, L->is_bf16, d, m, xc, Bc, L->ulist, m, L->n_ulist, L->h, nullptr, nullptr, 0, 0,
+                              L->n_cu, again ? kStreamAgainBytes : (rows_read ? kStreamTwiceBytes : kStreamPartBytes), s));
+        POP_HIP(launch_down(L->w, L->is_bf16, d, m, L->ulist, L->n_ulist, 0, L->h, mk, m, Bc, L->partial, L->n_slabs,
+                            (char *)y + (size_t)t0 * d * ysize, y_bf16, again ? kStreamAgainBytes : kStreamPartBytes, s));
+    }
     return POP_OK;
 }
 
@@ -497,11 +541,12 @@ int pop_prefill_partition(pop_layer_t *L, const void *x, int T, int n_ret, int n
         POP_HIP(launch_fill_int((int *)L->scores, m, 0, s));
     } else if (L->input_side) {
         POP_HIP(launch_input_norms(x, L->is_bf16, T, L->d, L->in_part, L->in_s2, s));
-        POP_HIP(launch_input_side_scores(L->w, L->is_bf16, L->d, L->in_s2, 1, nullptr, m, L->scores, m, s));
+        POP_HIP(launch_input_side_scores(L->w, L->is_bf16, L->d, L->in_s2, 1, nullptr, m, L->scores, m, kStreamPromptBytes, s));
     } else {
         const PrefillScores fin{L->pf_ctr, L->nrm, L->scores};
         if (few)  // (the same launch as pop_prefill_forward's: the same scores, bit for bit)
-            POP_HIP(launch_precise_gateup(L->w, L->is_bf16, L->d, m, x, T, nullptr, nullptr, L->hs, L->s2_part, &fin, L->n_cu, s));
+            POP_HIP(launch_precise_gateup(L->w, L->is_bf16, L->d, m, x, T, nullptr, nullptr, L->hs, L->s2_part, &fin, L->n_cu, kStreamPromptBytes,
+                                          s));
         else
             POP_HIP(launch_prefill_gateup(L->w, L->is_bf16, L->d, m, x, T, L->s2_part, L->n_cu, s, &fin));
     }
@@ -547,10 +592,11 @@ int pop_prefill_forward(pop_layer_t *L, const void *x, int T, int n_ret, int n_c
             POP_HIP(launch_fill_int((int *)L->scores, m, 0, s));  // no tokens: all importances zero
         } else if (L->input_side) {
             POP_HIP(launch_input_norms(x, L->is_bf16, T, d, L->in_part, L->in_s2, s));
-            POP_HIP(launch_input_side_scores(L->w, L->is_bf16, d, L->in_s2, 1, nullptr, m, L->scores, m, s));
+            POP_HIP(launch_input_side_scores(L->w, L->is_bf16, d, L->in_s2, 1, nullptr, m, L->scores, m, kStreamTwiceBytes, s));
         } else if (few) {
             const PrefillScores fin{L->pf_ctr, L->nrm, L->scores};
-            POP_HIP(launch_precise_gateup(L->w, L->is_bf16, d, m, x, T, nullptr, nullptr, L->hs, L->s2_part, &fin, L->n_cu, s));
+            POP_HIP(launch_precise_gateup(L->w, L->is_bf16, d, m, x, T, nullptr, nullptr, L->hs, L->s2_part, &fin, L->n_cu, kStreamPromptBytes,
+                                          s));
         } else {
             const PrefillScores fin{L->pf_ctr, L->nrm, L->scores};
             POP_HIP(launch_prefill_gateup(L->w, L->is_bf16, d, m, x, T, L->s2_part, L->n_cu, s, &fin));
@@ -585,8 +631,7 @@ int pop_prefill_forward(pop_layer_t *L, const void *x, int T, int n_ret, int n_c
                                    skinny_down_slabs(L->is_bf16, d, m, L->n_cu), y, ydtype == POP_BF16, kStreamPromptBytes, s));
         return POP_OK;
     }
-    const int rc = pop_pruned_ffn(L, x, T, L->ffn_any, 1, y, ydtype, stream);
-    return rc;
+    return pruned_ffn(L, x, T, L->ffn_any, 1, y, ydtype == POP_BF16, true, s);
 }
 
 // Pass 1 and the selection of a decode step; the results stay in the layer's state.
@@ -624,7 +669,8 @@ static int decode_select(pop_layer_t *L, const void *x_t, int B, const int *k, v
                 for (int b = 1; b < B; ++b)
                     if (kk.k[b] != kk.k[0]) return POP_ESHAPE;
             POP_HIP(launch_input_squares(x_t, L->is_bf16, B, L->d, L->in_s2, s));
-            POP_HIP(launch_input_side_scores(L->w, L->is_bf16, L->d, L->in_s2, B, L->cand_idx, n_cand, L->cscore, m, s));
+            POP_HIP(launch_input_side_scores(L->w, L->is_bf16, L->d, L->in_s2, B, L->cand_idx, n_cand, L->cscore, m, kStreamStepBytes,
+                                             s));
             // one mask for the batch: the root of the sum of the sequences' squared scores is this reading's importance
             // over the step's B rows (Eq. 1-2 with s_k over tokens and samples); every row gets it
             if (shared) POP_HIP(launch_aggregate_scores(L->cscore, m, B, n_cand, s));
@@ -727,46 +773,12 @@ int pop_pruned_ffn(pop_layer_t *L, const void *x, int T, const unsigned char *ma
     if (!L || !y || !aligned16(y)) return POP_EINVAL;
     if (ydtype != POP_F32 && ydtype != POP_BF16) return POP_EINVAL;
     hipStream_t s = as_stream(stream);
-    const int m = L->m, d = L->d, y_bf16 = ydtype == POP_BF16, ysize = y_bf16 ? 2 : 4;
+    const int y_bf16 = ydtype == POP_BF16;
     if (!mask) return decode_output(L, T, y, ydtype, nullptr, s);
     if (!x || !aligned16(x)) return POP_EINVAL;
     if (T < 1) return POP_ESHAPE;
     if (mask_rows != 1 && mask_rows != T) return POP_ESHAPE;
-    L->has_step = false;  // the step scratch is reused below
-    L->ulist_prefix_ok = false;
-    if (L->is_bf16 && T >= kFfnMfmaMinTokens) return pruned_ffn_mfma(L, x, T, mask, mask_rows, y, y_bf16, s);
-    const int few = precise_max_tokens(L->is_bf16, d);
-    if (few > 0 && T > 1 && (T > L->chunk || (long long)T * m >= kFewTokenChannels)) {
-        // a few tokens (bf16 layers: all of them) per pass over the weights
-        if (mask_rows > 1 && (long long)mask_rows * m > kMaskListBytes) {
-            POP_HIP(launch_mask_any(mask, T, m, L->ffn_any, s));
-            POP_HIP(launch_mask_to_list(L->ffn_any, 1, m, L->ulist, L->n_ulist, s));
-        } else {
-            POP_HIP(launch_mask_to_list(mask, mask_rows, m, L->ulist, L->n_ulist, s));
-        }
-        for (int t0 = 0; t0 < T; t0 += few) {
-            const int n = T - t0 < few ? T - t0 : few;
-            POP_HIP(launch_precise_gateup(L->w, L->is_bf16, d, m, (const char *)x + (size_t)t0 * d * L->esize, n, L->ulist,
-                                          L->n_ulist, L->hs, nullptr, nullptr, L->n_cu, s));
-            POP_HIP(launch_skinny_down(L->w, L->is_bf16, d, m, L->ulist, L->n_ulist, L->hs,
-                                       mask_rows > 1 ? mask + (size_t)t0 * m : nullptr, m, n, L->partial,
-                                       skinny_down_slabs(L->is_bf16, d, m, L->n_cu),
-                                       (char *)y + (size_t)t0 * d * ysize, y_bf16, kStreamPartBytes, s));
-        }
-        return POP_OK;
-    }
-    if (mask_rows == 1) POP_HIP(launch_mask_to_list(mask, 1, m, L->ulist, L->n_ulist, s));
-    for (int t0 = 0; t0 < T; t0 += L->chunk) {
-        const int Bc = (T - t0 < L->chunk) ? T - t0 : L->chunk;
-        const unsigned char *mk = mask_rows == 1 ? nullptr : mask + (size_t)t0 * m;
-        if (mk) POP_HIP(launch_mask_to_list(mk, Bc, m, L->ulist, L->n_ulist, s));
-        const char *xc = (const char *)x + (size_t)t0 * d * L->esize;
-        POP_HIP(launch_gateup(L->w, L->is_bf16, d, m, xc, Bc, L->ulist, m, L->n_ulist, L->h, nullptr, nullptr, 0, 0,
-                              L->n_cu, kStreamPartBytes, s));
-        POP_HIP(launch_down(L->w, L->is_bf16, d, m, L->ulist, L->n_ulist, 0, L->h, mk, m, Bc, L->partial, L->n_slabs,
-                            (char *)y + (size_t)t0 * d * ysize, y_bf16, kStreamPartBytes, s));
-    }
-    return POP_OK;
+    return pruned_ffn(L, x, T, mask, mask_rows, y, y_bf16, false, s);
 }
 
 int pop_partition_from_scores(const float *scores, int m, int n_ret, int n_cand, unsigned char *region, int *ret_idx,

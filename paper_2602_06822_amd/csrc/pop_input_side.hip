@@ -147,7 +147,7 @@ __global__ __launch_bounds__(256) void input_side_scores_kernel(const typename V
 
 // rows == nullptr: channels 0 .. n_rows-1.  s2: [S][d] float32.  out: [S][out_stride].
 hipError_t launch_input_side_scores(const void *w, int is_bf16, int d, const float *s2, int S, const int *rows,
-                                    int n_rows, float *out, int out_stride, hipStream_t s)
+                                    int n_rows, float *out, int out_stride, long long stream_from, hipStream_t s)
 {
     if (n_rows < 1 || S < 1) return hipSuccess;
     const int ns = S == 1 ? 1 : 2;
@@ -156,7 +156,7 @@ hipError_t launch_input_side_scores(const void *w, int is_bf16, int d, const flo
     if (bx > 1024) bx = 1024;
     dim3 grid(bx, (S + ns - 1) / ns);
     // (a prompt's scores over all channels; a step's candidates are read again for h)
-    const bool stream = !rows && S <= 2 && stream_rows(d, n_rows, is_bf16, kStreamPromptBytes);
+    const bool stream = !rows && ns == 1 && stream_rows(d, n_rows, is_bf16, stream_from);
     auto launch = [&](auto kernel, auto weights, int nvec) {
         const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -167,9 +167,7 @@ hipError_t launch_input_side_scores(const void *w, int is_bf16, int d, const flo
     if (!is_bf16)
         return ns == 1 ? launch(input_side_scores_kernel<VecF32, 1>, (const float4 *)w, d / 4)
                        : launch(input_side_scores_kernel<VecF32, 2>, (const float4 *)w, d / 4);
-    if (stream)
-        return ns == 1 ? launch(input_side_scores_kernel<StreamBF16, 1>, (const uint4 *)w, d / 8)
-                       : launch(input_side_scores_kernel<StreamBF16, 2>, (const uint4 *)w, d / 8);
+    if (stream) return launch(input_side_scores_kernel<StreamBF16, 1>, (const uint4 *)w, d / 8);
     return ns == 1 ? launch(input_side_scores_kernel<VecBF16, 1>, (const uint4 *)w, d / 8)
                    : launch(input_side_scores_kernel<VecBF16, 2>, (const uint4 *)w, d / 8);
 }

@@ -55,8 +55,13 @@ __host__ __device__ __forceinline__ constexpr int channel_gap(int nvec, int is_b
 //   a prompt's own forward pass (all of gate and up, most of down), three layers: of 86 MB 1.02-1.08 (4 to 40 tokens), of 113 MB
 //   .97-.99, of 138 MB .97, of 270 MB .92-.94
 //   a stand-alone FFN (two thirds of the layer), three layers: of 67 MB 1.04-1.14 (1 to 40 tokens), of 138 MB .99-1.03, of 157 MB .96-1.00, of
-//   270 MB .90-.97
+//   270 MB .90-.97; its matrix-core contraction over the list (half the layer and less) from 200 MB on
+// Rows that the same call asks for again stay in the cache, as long as it holds them: gate and up rows that scores of the
+// input-side reading come from and the prompt's forward pass reads after them (three layers, 40 tokens: of 138 MB 1.05, of 201 MB 1.02-1.07, of
+// 270 MB .98-.99), and the rows of an FFN that takes its tokens in several passes, two thirds of a layer in each (24 tokens: of 74 MB 1.08, of
+// 197 MB 1.03-1.04, of 271 MB 1.02-1.04).
 constexpr long long kStreamStepBytes = 64ll << 20, kStreamPromptBytes = 128ll << 20, kStreamPartBytes = 144ll << 20;
+constexpr long long kStreamListBytes = 192ll << 20, kStreamTwiceBytes = 240ll << 20, kStreamAgainBytes = 384ll << 20;
 inline bool stream_rows(int d, int m, int is_bf16, long long limit) { return is_bf16 && 6ll * d * m >= limit; }
 
 // From one channel's weights to the next's.
@@ -306,7 +311,7 @@ hipError_t launch_prefill_gateup(const void *w, int is_bf16, int d, int m, const
 // bf16 layers: gate/up over the channels of a device-resident list (n_list: its length, on the device);
 // hc[t][c] = bf16(H[t][list[c]]), times tmask[t][list[c]] if tmask ([T][m]) is given.  ldh % 8 == 0.
 hipError_t launch_gateup_list_bf16(const void *w, int d, int m, const void *x, int T, const int *list, const int *n_list,
-                                   const unsigned char *tmask, uint16_t *hc, int ldh, int n_cu, hipStream_t s);
+                                   const unsigned char *tmask, uint16_t *hc, int ldh, int n_cu, long long stream_from, hipStream_t s);
 // y[t][n] = sum_c hc[t][c] * w[list[c]][2][n] on the matrix cores; part (float32 [n_split][T][d]) is needed when
 // n_split = down_gemm_splits(...) > 1.  With zero_row (256 bytes of zeros), d % 128 == 0 and ldh % 64 == 0 the
 // operands go straight into LDS; that form reads hc columns up to the list length rounded up to 64, which must hold
@@ -334,7 +339,7 @@ constexpr int kF32MaxTokens = 64;
 int precise_max_tokens(int is_bf16, int d);
 hipError_t launch_precise_gateup(const void *w, int is_bf16, int d, int m, const void *x, int T, const int *list,
                                  const int *n_list, float *h, float *s2_part, const PrefillScores *fin, int n_cu,
-                                 hipStream_t s);
+                                 long long stream_from, hipStream_t s);
 // float32 layers, T <= kF32MaxTokens: the slab partials of the down projection (summed by launch_skinny_down)
 int f32_down_slabs(int d, int m, int n_cu);
 hipError_t launch_down_f32_partials(const void *w, int d, int m, const int *list, const int *n_dev, const float *h,
@@ -348,7 +353,7 @@ hipError_t launch_input_norms(const void *x, int is_bf16, int T, int d, double *
 hipError_t launch_input_squares(const void *x, int is_bf16, int B, int d, float *s2, hipStream_t s);
 // out[q][p] = sqrt(sum_k (w_gate[j][k]^2 + w_up[j][k]^2) s2[q][k]), j = rows ? rows[p] : p, q < S, p < n_rows
 hipError_t launch_input_side_scores(const void *w, int is_bf16, int d, const float *s2, int S, const int *rows,
-                                    int n_rows, float *out, int out_stride, hipStream_t s);
+                                    int n_rows, float *out, int out_stride, long long stream_from, hipStream_t s);
 // cs[b][p] <- sqrt(sum over b' < B of cs[b'][p]^2) for every b < B, p < n
 hipError_t launch_aggregate_scores(float *cs, int cs_stride, int B, int n, hipStream_t s);
 // any[j] = 1 if mask[t][j] != 0 for some t < rows, else 0

@@ -732,13 +732,12 @@ __device__ __forceinline__ void pm_tile(const uint16_t *__restrict__ w, const ui
 // neighbours there and meet in its L2).  prefill_stream_kernel: weight rows past the caches, for layers of stream_rows and up to
 // two token tiles per chunk, which ask for a row at the same time (512 tokens, d 4096, m 11008: 87.9 -> 81.3 us; 2048 tokens
 // no change); with the narrow chunks' deeper ring where it is used.  A list of channels reads part of the layer only: one token
-// tile, and layers half as large again (100 tokens, half of d 4096, m 5504: 42.0 without / 42.8 with; two tiles, 333 tokens at
+// tile, and layers half as large again (kStreamListBytes; 100 tokens, half of d 4096, m 5504: 42.0 without / 42.8 with; two tiles, 333 tokens at
 // the 13B shape 107.6 / 108.3).
 template <int kMode>
-inline bool pm_streams(int d, int m, int n_tt)
+inline bool pm_streams(int d, int m, int n_tt, long long stream_from)
 {
-    constexpr bool kList = kMode == 1 || kMode == 4;
-    return n_tt <= (kList ? 1 : 2) && stream_rows(d, m, 1, kList ? kStreamPromptBytes * 3 / 2 : kStreamPromptBytes);
+    return n_tt <= (kMode == 1 || kMode == 4 ? 1 : 2) && stream_rows(d, m, 1, stream_from);
 }
 constexpr bool pm_deep(int mf, int f, int mode) { return mf == kPmDeepMF && f <= kPmDeepF && (mode == 0 || mode == 2 || mode == 5); }
 template <int MF, int kMode, bool kStream>
@@ -1128,12 +1127,12 @@ static hipError_t launch_pf_bf16(int blocks, hipStream_t s, const void *w, const
 
 template <int MF, int kMode>
 static hipError_t launch_pm(const void *w, int d, int m, const void *x, int T, const PmTiles &g, float *s2_part, int n_cu,
-                            const PfStore &st, hipStream_t s)
+                            const PfStore &st, long long stream_from, hipStream_t s)
 {
     void (*kernel)(const uint16_t *, const uint16_t *, int, int, int, int, PmTiles, float *, PfStore);
     const int n_tt = (T + 64 * MF - 1) / (64 * MF);
     // (the list form learns its F on the device; wider chunks do not leave the room)
-    const bool deep = pm_deep(MF, g.f, kMode), stream = pm_streams<kMode>(d, m, n_tt);
+    const bool deep = pm_deep(MF, g.f, kMode), stream = pm_streams<kMode>(d, m, n_tt, stream_from);
     const size_t lds = deep ? PmDeepRing::kBytes : PmRing<MF>::kBytes;
     if constexpr (kMode == 5) {
         kernel = stream ? prefill_rows_kernel<MF, true> : prefill_rows_kernel<MF, false>;
@@ -1153,15 +1152,15 @@ static hipError_t launch_pm(const void *w, int d, int m, const void *x, int T, c
 
 template <int kMode>
 static hipError_t launch_pm_all(const void *w, int d, int m, const void *x, int T, float *s2_part, int n_cu,
-                                const PfStore &st, hipStream_t s)
+                                const PfStore &st, long long stream_from, hipStream_t s)
 {
     PmTiles g;
     switch (pm_token_fragments(T, m, n_cu, &g)) {  // (list form: priced as all m channels, cut up on the device)
-    case 1: return launch_pm<1, kMode>(w, d, m, x, T, g, s2_part, n_cu, st, s);
-    case 2: return launch_pm<2, kMode>(w, d, m, x, T, g, s2_part, n_cu, st, s);
-    case 3: return launch_pm<3, kMode>(w, d, m, x, T, g, s2_part, n_cu, st, s);
-    case 4: return launch_pm<4, kMode>(w, d, m, x, T, g, s2_part, n_cu, st, s);
-    default: return launch_pm<5, kMode>(w, d, m, x, T, g, s2_part, n_cu, st, s);
+    case 1: return launch_pm<1, kMode>(w, d, m, x, T, g, s2_part, n_cu, st, stream_from, s);
+    case 2: return launch_pm<2, kMode>(w, d, m, x, T, g, s2_part, n_cu, st, stream_from, s);
+    case 3: return launch_pm<3, kMode>(w, d, m, x, T, g, s2_part, n_cu, st, stream_from, s);
+    case 4: return launch_pm<4, kMode>(w, d, m, x, T, g, s2_part, n_cu, st, stream_from, s);
+    default: return launch_pm<5, kMode>(w, d, m, x, T, g, s2_part, n_cu, st, stream_from, s);
     }
 }
 
@@ -1187,7 +1186,7 @@ static hipError_t launch_pf_bf16_all(const void *w, int d, int m, const void *x,
                                      PfStore st, hipStream_t s)
 {
     if (!prefill_forms_scores(1, T, d, m, n_cu)) st.fin_ctr = nullptr;
-    if (prefill_direct(d)) return launch_pm_all<kMode>(w, d, m, x, T, s2_part, n_cu, st, s);
+    if (prefill_direct(d)) return launch_pm_all<kMode>(w, d, m, x, T, s2_part, n_cu, st, kStreamPromptBytes, s);
     const int bm = prefill_token_tile(T, m, n_cu);
     const int n_tt = (T + bm - 1) / bm;
     const PfGeom g = prefill_geometry(m, n_tt, n_cu);
@@ -1211,7 +1210,7 @@ hipError_t launch_prefill_gateup_keep_bf16(const void *w, int d, int m, const vo
     if (by_channel) {
         if (!prefill_direct(d)) return hipErrorInvalidValue;
         if (!prefill_forms_scores(1, T, d, m, n_cu)) st.fin_ctr = nullptr;
-        return launch_pm_all<5>(w, d, m, x, T, s2_part, n_cu, st, s);
+        return launch_pm_all<5>(w, d, m, x, T, s2_part, n_cu, st, kStreamPromptBytes, s);
     }
     return launch_pf_bf16_all<2>(w, d, m, x, T, s2_part, n_cu, st, s);
 }
@@ -1234,10 +1233,10 @@ hipError_t launch_prefill_gateup(const void *w, int is_bf16, int d, int m, const
 // workgroup cuts the list up for itself.  Register-staged kernel: both tile forms are launched, each sized for the
 // longest possible list (m channels), and the one the length does not call for exits at once.
 hipError_t launch_gateup_list_bf16(const void *w, int d, int m, const void *x, int T, const int *list, const int *n_list,
-                                   const unsigned char *tmask, uint16_t *hc, int ldh, int n_cu, hipStream_t s)
+                                   const unsigned char *tmask, uint16_t *hc, int ldh, int n_cu, long long stream_from, hipStream_t s)
 {
     PfStore st{list, n_list, hc, ldh, tmask, n_cu};
-    if (prefill_direct(d)) return launch_pm_all<1>(w, d, m, x, T, nullptr, n_cu, st, s);
+    if (prefill_direct(d)) return launch_pm_all<1>(w, d, m, x, T, nullptr, n_cu, st, stream_from, s);
     const int bm = prefill_token_tile(T, m, n_cu);  // (the list's length is not known here: priced as all m channels)
     const int n_tt = (T + bm - 1) / bm;
     PfGeom g{};
@@ -1263,14 +1262,14 @@ int precise_max_tokens(int is_bf16, int d) { return is_bf16 ? (prefill_direct(d)
 // the same as without.)
 hipError_t launch_precise_gateup(const void *w, int is_bf16, int d, int m, const void *x, int T, const int *list,
                                  const int *n_list, float *h, float *s2_part, const PrefillScores *fin, int n_cu,
-                                 hipStream_t s)
+                                 long long stream_from, hipStream_t s)
 {
     PfStore st{list, n_list, nullptr, 0, nullptr, n_cu};
     st.h32 = h;
     if (fin && !list) st.fin_ctr = fin->chunk_ctr, st.nrm = fin->nrm, st.scores = fin->scores;
     if (!is_bf16) return launch_gateup_f32_any(w, d, m, x, T, list ? nullptr : s2_part, n_cu, st, s);
-    if (list) return launch_pm<1, 4>(w, d, m, x, T, PmTiles{}, nullptr, n_cu, st, s);
-    return launch_pm<1, 3>(w, d, m, x, T, pm_tiles(m, 1, 1, n_cu), s2_part, n_cu, st, s);
+    if (list) return launch_pm<1, 4>(w, d, m, x, T, PmTiles{}, nullptr, n_cu, st, stream_from, s);
+    return launch_pm<1, 3>(w, d, m, x, T, pm_tiles(m, 1, 1, n_cu), s2_part, n_cu, st, stream_from, s);
 }
 
 // scores[j] = nrm[j] * sqrt(sum over token tiles, in tile order, of s2_part[tile][j])   (Eq. 3)

@@ -93,3 +93,35 @@ def test_decode_step(layer, B):
     pop.pop_prefill_partition(h, x[:64], 64, n_ret, n_cand)
     got = _past_the_caches(lambda s: pop.pop_decode_step(h, x[:B], B, [n_cand // 2] * B, y[:B], F32, stream=s))
     assert got and all(got)
+
+
+# Gate and up rows that the same call reads again (input-side scores and the forward pass after them, an FFN of several passes) are left in the
+# cache up to layers of 240 MiB and 384 MiB; down rows, read once, follow the FFN's rule
+@pytest.mark.gpu
+@pytest.mark.parametrize("layer", [(4096, 8192), (4104, 8000)], indirect=True)
+@pytest.mark.parametrize("T", [4, 24, 40])
+def test_rows_read_again(layer, T):
+    pop, h, m, x, y = layer
+    by_64 = m == 8192  # (other widths have no direct loads: tokens eight at a time, or the register-staged kernels)
+    n_ret, n_cand = m // 2, m // 8
+
+    def forward(s):
+        pop.pop_prefill_forward(h, x[:T], T, n_ret, n_cand, n_cand // 2, y[:T], F32, stream=s)
+
+    pop.pop_layer_set_importance(h, pop.POP_IMPORTANCE_INPUT_SIDE)
+    scores, *ffn = _past_the_caches(forward)
+    assert not scores
+    if T >= 32:
+        # (the register-staged contraction over a list: a form for either tile, one of which has nothing to do)
+        assert ffn == ([False, True] if by_64 else [False, False, False])
+    else:
+        passes = 1 if by_64 else (T + 7) // 8
+        assert ffn == [False, passes == 1] * passes
+    mask = torch.ones((1, m), dtype=torch.uint8, device="cuda")
+    got = _past_the_caches(lambda s: pop.pop_pruned_ffn(h, x[:T], T, mask, 1, y[:T], F32, stream=s))
+    if T < 32 and not by_64:
+        assert got == [passes == 1] * 2 * passes
+    pop.pop_layer_set_importance(h, pop.POP_IMPORTANCE_OUTPUT_SIDE)
+    if T < 32 and not by_64:
+        scores, *ffn = _past_the_caches(forward)
+        assert not scores and ffn == [False, passes == 1] * passes
