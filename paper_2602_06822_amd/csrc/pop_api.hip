@@ -541,7 +541,7 @@ int pop_prefill_partition(pop_layer_t *L, const void *x, int T, int n_ret, int n
         POP_HIP(launch_fill_int((int *)L->scores, m, 0, s));
     } else if (L->input_side) {
         POP_HIP(launch_input_norms(x, L->is_bf16, T, L->d, L->in_part, L->in_s2, s));
-        POP_HIP(launch_input_side_scores(L->w, L->is_bf16, L->d, L->in_s2, 1, nullptr, m, L->scores, m, kStreamPromptBytes, s));
+        POP_HIP(launch_input_side_scores(L->w, L->is_bf16, L->d, L->in_s2, 1, nullptr, m, L->scores, m, kStreamPartBytes, s));
     } else {
         const PrefillScores fin{L->pf_ctr, L->nrm, L->scores};
         if (few)  // (the same launch as pop_prefill_forward's: the same scores, bit for bit)

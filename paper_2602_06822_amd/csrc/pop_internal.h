@@ -55,7 +55,8 @@ __host__ __device__ __forceinline__ constexpr int channel_gap(int nvec, int is_b
 //   a prompt's own forward pass (all of gate and up, most of down), three layers: of 86 MB 1.02-1.08 (4 to 40 tokens), of 113 MB
 //   .97-.99, of 138 MB .97, of 270 MB .92-.94
 //   a stand-alone FFN (two thirds of the layer), three layers: of 67 MB 1.04-1.14 (1 to 40 tokens), of 138 MB .99-1.03, of 157 MB .96-1.00, of
-//   270 MB .90-.97; its matrix-core contraction over the list (half the layer and less) from 200 MB on
+//   270 MB .90-.97; a prompt's partition the same (gate and up: of 138 MB 1.07 at 40 tokens, of 157 MB .92); the FFN's matrix-core contraction
+//   over the list from 192 MB on
 // Rows that the same call asks for again stay in the cache, as long as it holds them: gate and up rows that scores of the
 // input-side reading come from and the prompt's forward pass reads after them (three layers, 40 tokens: of 138 MB 1.05, of 201 MB 1.02-1.07, of
 // 270 MB .98-.99), and the rows of an FFN that takes its tokens in several passes, two thirds of a layer in each (24 tokens: of 74 MB 1.08, of

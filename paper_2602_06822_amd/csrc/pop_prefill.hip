@@ -730,13 +730,16 @@ __device__ __forceinline__ void pm_tile(const uint16_t *__restrict__ w, const ui
 
 // One workgroup per compute unit; each walks its share of the tiles of its XCD (the token tiles of a channel chunk are
 // neighbours there and meet in its L2).  prefill_stream_kernel: weight rows past the caches, for layers of stream_rows and up to
-// two token tiles per chunk, which ask for a row at the same time (512 tokens, d 4096, m 11008: 87.9 -> 81.3 us; 2048 tokens
-// no change); with the narrow chunks' deeper ring where it is used.  A list of channels reads part of the layer only: one token
-// tile, and layers half as large again (kStreamListBytes; 100 tokens, half of d 4096, m 5504: 42.0 without / 42.8 with; two tiles, 333 tokens at
-// the 13B shape 107.6 / 108.3).
+// two token tiles per chunk, which ask for a row at the same time (2048 tokens no change); with the narrow chunks' deeper ring where it is
+// used.  512 tokens, d 4096, m 11008, in turn on one card: 87.8 -> 84.4 us.  Two tiles from 240 MB of weights on; three layers in turn, past
+// the caches over ordinary, 128 and 256 tokens: partition, of 138 MB 1.08 and 1.04, of 157 MB 1.01, of 201 MB .96 and .97; forward pass .95-.98;
+// but 200 tokens 1.15, 1.14, 1.02, of 226 MB 1.05, of 251 MB .98, and forward 1.02-1.05 up to 226 MB.
+// A list of channels reads part of the layer only: one token tile, and layers of 192 MB (100 tokens, half of d 4096, m 5504: 42.0 without /
+// 42.8 with; two tiles, 333 tokens at the 13B shape 107.6 / 108.3).
 template <int kMode>
 inline bool pm_streams(int d, int m, int n_tt, long long stream_from)
 {
+    if (n_tt == 2 && stream_from < kStreamTwiceBytes) stream_from = kStreamTwiceBytes;
     return n_tt <= (kMode == 1 || kMode == 4 ? 1 : 2) && stream_rows(d, m, 1, stream_from);
 }
 constexpr bool pm_deep(int mf, int f, int mode) { return mf == kPmDeepMF && f <= kPmDeepF && (mode == 0 || mode == 2 || mode == 5); }
@@ -1186,7 +1189,7 @@ static hipError_t launch_pf_bf16_all(const void *w, int d, int m, const void *x,
                                      PfStore st, hipStream_t s)
 {
     if (!prefill_forms_scores(1, T, d, m, n_cu)) st.fin_ctr = nullptr;
-    if (prefill_direct(d)) return launch_pm_all<kMode>(w, d, m, x, T, s2_part, n_cu, st, kStreamPromptBytes, s);
+    if (prefill_direct(d)) return launch_pm_all<kMode>(w, d, m, x, T, s2_part, n_cu, st, kMode == 0 ? kStreamPartBytes : kStreamPromptBytes, s);
     const int bm = prefill_token_tile(T, m, n_cu);
     const int n_tt = (T + bm - 1) / bm;
     const PfGeom g = prefill_geometry(m, n_tt, n_cu);

@@ -56,7 +56,7 @@ def layer(request):
     from paper_2602_06822_amd import binding as pop
     d, m = request.param
     w = [torch.zeros(s, dtype=torch.bfloat16, device="cuda") for s in ((m, d), (m, d), (d, m))]
-    h = pop.pop_layer_create(d, m, BF16, *w, 512, 8)
+    h = pop.pop_layer_create(d, m, BF16, *w, 1024, 8)
     x = torch.zeros((512, d), dtype=torch.bfloat16, device="cuda")
     y = torch.empty((512, d), device="cuda")
     try:
@@ -125,3 +125,29 @@ def test_rows_read_again(layer, T):
     if T < 32 and not by_64:
         scores, *ffn = _past_the_caches(forward)
         assert not scores and ffn == [False, passes == 1] * passes
+
+
+# A partition reads gate and up alone: from 144 MiB of weights on (up to 31 tokens, as the forward pass, from 128), and where two token tiles
+# share a chunk of channels from 240
+@pytest.mark.gpu
+@pytest.mark.parametrize("layer,T,want", [
+    ((3200, 7200), 16, True), ((3200, 7200), 40, False), ((4096, 6400), 40, True), ((4096, 6400), 128, False),
+    ((4096, 8192), 240, False), ((4096, 10240), 240, True), ((4096, 10240), 1024, False)], indirect=["layer"])
+def test_prompt(layer, T, want):
+    pop, h, m, x, y = layer
+    x = torch.zeros((T, x.shape[1]), dtype=torch.bfloat16, device="cuda")
+    y = torch.empty(x.shape, device="cuda")
+    n_ret, n_cand = m // 2, m // 8
+    got = _past_the_caches(lambda s: pop.pop_prefill_partition(h, x, T, n_ret, n_cand, stream=s))
+    assert got == [want]
+    contraction, down = _past_the_caches(lambda s: pop.pop_prefill_forward(h, x, T, n_ret, n_cand, n_cand // 2, y, F32, stream=s))
+    # (all of gate and up and most of down: one token tile from 128 MiB on)
+    assert contraction == (want or T == 40) and down == (T <= 320)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("layer,want", [((3200, 7200), False), ((4096, 6400), True)], indirect=["layer"])
+def test_input_side_partition(layer, want):
+    pop, h, m, x, y = layer
+    pop.pop_layer_set_importance(h, pop.POP_IMPORTANCE_INPUT_SIDE)
+    assert _past_the_caches(lambda s: pop.pop_prefill_partition(h, x[:100], 100, m // 2, m // 8, stream=s)) == [want]
