@@ -733,14 +733,19 @@ __device__ __forceinline__ void pm_tile(const uint16_t *__restrict__ w, const ui
 // two token tiles per chunk, which ask for a row at the same time (2048 tokens no change); with the narrow chunks' deeper ring where it is
 // used.  512 tokens, d 4096, m 11008, in turn on one card: 87.8 -> 84.4 us.  Two tiles from 240 MB of weights on; three layers in turn, past
 // the caches over ordinary, 128 and 256 tokens: partition, of 138 MB 1.08 and 1.04, of 157 MB 1.01, of 201 MB .96 and .97; forward pass .95-.98;
-// but 200 tokens 1.15, 1.14, 1.02, of 226 MB 1.05, of 251 MB .98, and forward 1.02-1.05 up to 226 MB.
+// but 200 tokens 1.15, 1.14, 1.02, of 226 MB 1.05, of 251 MB .98, and forward 1.02-1.05 up to 226 MB.  The second tile has to be three quarters
+// full, half where a compute unit runs one tile: one with few tokens of its own has its other rows from the cache, runs ahead, and what it
+// asked for is gone when the first tile comes to it, a read of every row from memory by each.  13B shape (two tiles a compute unit),
+// partition, three layers, 70 tokens 242 / 311 us, 85 278 / 306, 100 289 / 295, 115 298 / 294; d 8192, m 28672, two layers, 70 tokens 464 / 632, 115
+// 514 / 493; 7B shape (one), 70 tokens 157 / 168, 85 164 / 169, 100 182 / 171.
 // A list of channels reads part of the layer only: one token tile, and layers of 192 MB (100 tokens, half of d 4096, m 5504: 42.0 without /
 // 42.8 with; two tiles, 333 tokens at the 13B shape 107.6 / 108.3).
-template <int kMode>
-inline bool pm_streams(int d, int m, int n_tt, long long stream_from)
+template <int MF, int kMode>
+inline bool pm_streams(int d, int m, int T, bool one_each, long long stream_from)
 {
-    if (n_tt == 2 && stream_from < kStreamTwiceBytes) stream_from = kStreamTwiceBytes;
-    return n_tt <= (kMode == 1 || kMode == 4 ? 1 : 2) && stream_rows(d, m, 1, stream_from);
+    if (T <= 64 * MF) return stream_rows(d, m, 1, stream_from);
+    if (kMode == 1 || kMode == 4 || T > 128 * MF || T < (one_each ? 96 : 112) * MF) return false;
+    return stream_rows(d, m, 1, stream_from < kStreamTwiceBytes ? kStreamTwiceBytes : stream_from);
 }
 constexpr bool pm_deep(int mf, int f, int mode) { return mf == kPmDeepMF && f <= kPmDeepF && (mode == 0 || mode == 2 || mode == 5); }
 template <int MF, int kMode, bool kStream>
@@ -1135,7 +1140,7 @@ static hipError_t launch_pm(const void *w, int d, int m, const void *x, int T, c
     void (*kernel)(const uint16_t *, const uint16_t *, int, int, int, int, PmTiles, float *, PfStore);
     const int n_tt = (T + 64 * MF - 1) / (64 * MF);
     // (the list form learns its F on the device; wider chunks do not leave the room)
-    const bool deep = pm_deep(MF, g.f, kMode), stream = pm_streams<kMode>(d, m, n_tt, stream_from);
+    const bool deep = pm_deep(MF, g.f, kMode), stream = pm_streams<MF, kMode>(d, m, T, g.total <= n_cu, stream_from);
     const size_t lds = deep ? PmDeepRing::kBytes : PmRing<MF>::kBytes;
     if constexpr (kMode == 5) {
         kernel = stream ? prefill_rows_kernel<MF, true> : prefill_rows_kernel<MF, false>;
