@@ -572,7 +572,7 @@ constexpr int kSkThreads = 512;
 constexpr int kSkList = 4096;      // channels of a slab whose numbers are in LDS at a time
 constexpr int kSkCols = 128;       // columns per workgroup
 constexpr int kSkPair = 68;        // floats between two pairs of tokens' h (64, and four banks)
-constexpr int kSkChunk = 256;      // channels staged at a time (two groups of tokens)
+constexpr int kSkChunk = 256;      // channels staged at a time (skinny_staged_kernel)
 constexpr int kSkLd = kSkChunk + 8;  // LDS row stride of the staged h planes (16-byte aligned, rows four banks apart)
 
 // f = hi + mid + lo exactly for finite f (24 significant bits in three bf16 values of 8; the rests are exact differences)
@@ -748,17 +748,16 @@ __global__ __launch_bounds__(kSkThreads) void skinny_down_kernel(const uint4 *__
     }
 }
 
-// 17 to 32 tokens, two groups of 16: the workgroup stages h for all its waves, as three bf16 planes of 256 channels.  (Eight waves
-// that each see to their own have no registers for two groups' sums and two steps of rows, and with four the float32 sums are twice as
-// long: 24 tokens 62.7 us instead of 63.3 for the whole call, at a fifth more error.)
-template <class V, bool kMask>
-__global__ __launch_bounds__(kSkThreads) void skinny_pair_kernel(const uint4 *__restrict__ w, int nvec,
+// TG groups of 16 tokens, two of 17 to 32 tokens: the workgroup stages h for all its waves, as three bf16 planes of 256 channels.  (Eight
+// waves that each see to their own have no registers for two groups' sums and two steps of rows, and with four the float32 sums are twice
+// as long: 24 tokens 62.7 us instead of 63.3 for the whole call, at a fifth more error.)
+template <class V, int TG, bool kMask>
+__global__ __launch_bounds__(kSkThreads) void skinny_staged_kernel(const uint4 *__restrict__ w, int nvec,
                                                                  const int *__restrict__ list, const int *__restrict__ n_dev,
                                                                  const float *__restrict__ h, int m,
                                                                  const unsigned char *__restrict__ mask, int mask_stride,
                                                                  int T, float *__restrict__ partial, int d)
 {
-    constexpr int TG = 2;
     typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
     typedef float f32x4_t __attribute__((ext_vector_type(4)));
     extern __shared__ __attribute__((aligned(16))) unsigned char sk_lds[];
@@ -920,13 +919,19 @@ static hipError_t launch_skinny_down_partials(const void *w, int d, int m, const
 #define POP_SKQ(TQ)                                                                          \
     POP_SK((mask ? skinny_down_kernel<V, TQ, true> : skinny_down_kernel<V, TQ, false>), \
            (size_t)kSkList * 4 + (size_t)8 * 8 * kSkPair * 4)
-    // (pairs of tokens are loaded whether they exist or not, h and mask byte of each channel: as many as that as rows)
+    // (pairs of tokens are loaded whether they exist or not, h and mask byte of each channel: as many as that as rows.  With the eight
+    // pairs of 9 to 16 tokens that is what a wave's own h costs, so there h is staged, except where a slab is a single group of every
+    // wave's or masks are loaded over a long list.  Whole FFN of 12 tokens, three layers in turn, waves on their own / staged: one mask, d 2048,
+    // m 5504 78.9 / 80.0 us, d 2560, m 6144 93.1 / 92.2, d 3072 102.1 / 100.2, d 4096, m 5504 118.0 / 116.5, m 11008 143.0 / 141.6; own
+    // masks, d 2048, m 5504 114.7 / 111.5, d 2560 128.4 / 125.0, d 4096, m 5504 151.9 / 151.6, m 8192 166.8 / 167.4, m 14336 238.7 / 244.5)
     if (T <= 4) POP_SKQ(2);
     else if (T <= 6) POP_SKQ(3);
     else if (T <= 8) POP_SKQ(4);
-    else if (T <= 16) POP_SKQ(8);
+    else if (T <= 16 && (mask ? m >= 8192 : m <= 384 * n_slabs)) POP_SKQ(8);
+    else if (T <= 16)
+        POP_SK((mask ? skinny_staged_kernel<V, 1, true> : skinny_staged_kernel<V, 1, false>), (size_t)3 * 16 * kSkLd * 2 + 2 * kSkChunk * 4);
     else
-        POP_SK((mask ? skinny_pair_kernel<V, true> : skinny_pair_kernel<V, false>), (size_t)3 * 32 * kSkLd * 2 + 2 * kSkChunk * 4);
+        POP_SK((mask ? skinny_staged_kernel<V, 2, true> : skinny_staged_kernel<V, 2, false>), (size_t)3 * 32 * kSkLd * 2 + 2 * kSkChunk * 4);
 #undef POP_SKQ
 #undef POP_SK
     return hipGetLastError();
