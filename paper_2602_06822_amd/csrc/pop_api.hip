@@ -208,7 +208,7 @@ int ffn_scratch(pop_layer *L, int T, bool keep_all, int *ldh, int *n_split, hipS
 // Whole-prompt pruned FFN (Sec. 3.4: forward pass under the pruning structure): active list from the mask(s),
 // gate/up over the listed channels with H written in compact bf16 form, then the K-gathered down-projection GEMM.
 int pruned_ffn_mfma(pop_layer *L, const void *x, int T, const unsigned char *mask, int mask_rows, void *y, int y_bf16,
-                    bool rows_read, hipStream_t s)
+                    hipStream_t s)
 {
     const int m = L->m, d = L->d;
     int ldh, n_split;
@@ -222,20 +222,19 @@ int pruned_ffn_mfma(pop_layer *L, const void *x, int T, const unsigned char *mas
         tmask = mask;
     }
     POP_HIP(launch_gateup_list_bf16(L->w, d, m, x, T, L->ulist, L->n_ulist, tmask, L->ffn_hc, ldh, L->n_cu,
-                                   rows_read ? kStreamTwiceBytes : kStreamListBytes, s));
+                                   kStreamFfnBytes, s));
     POP_HIP(launch_down_gemm_bf16(L->w, d, L->ulist, L->n_ulist, L->ffn_hc, ldh, T, n_split, L->n_cu, L->ffn_part, y, y_bf16, s,
                                   L->zero_row));
     return POP_OK;
 }
 
-// Pruned FFN of x under the given masks.  rows_read: the call has just read the layer's gate and up rows.
-int pruned_ffn(pop_layer *L, const void *x, int T, const unsigned char *mask, int mask_rows, void *y, int y_bf16, bool rows_read,
-               hipStream_t s)
+// Pruned FFN of x under the given masks.
+int pruned_ffn(pop_layer *L, const void *x, int T, const unsigned char *mask, int mask_rows, void *y, int y_bf16, hipStream_t s)
 {
     const int m = L->m, d = L->d, ysize = y_bf16 ? 2 : 4;
     L->has_step = false;  // the step scratch is reused below
     L->ulist_prefix_ok = false;
-    if (L->is_bf16 && T >= kFfnMfmaMinTokens) return pruned_ffn_mfma(L, x, T, mask, mask_rows, y, y_bf16, rows_read, s);
+    if (L->is_bf16 && T >= kFfnMfmaMinTokens) return pruned_ffn_mfma(L, x, T, mask, mask_rows, y, y_bf16, s);
     const int few = precise_max_tokens(L->is_bf16, d);
     if (few > 0 && T > 1 && (T > L->chunk || (long long)T * m >= kFewTokenChannels)) {
         // a few tokens (bf16 layers: all of them) per pass over the weights
@@ -248,25 +247,25 @@ int pruned_ffn(pop_layer *L, const void *x, int T, const unsigned char *mask, in
         for (int t0 = 0; t0 < T; t0 += few) {
             const int n = T - t0 < few ? T - t0 : few;
             POP_HIP(launch_precise_gateup(L->w, L->is_bf16, d, m, (const char *)x + (size_t)t0 * d * L->esize, n, L->ulist,
-                                          L->n_ulist, L->hs, nullptr, nullptr, L->n_cu, rows_read ? kStreamTwiceBytes : kStreamListBytes, s));
+                                          L->n_ulist, L->hs, nullptr, nullptr, L->n_cu, kStreamFfnBytes, s));
             POP_HIP(launch_skinny_down(L->w, L->is_bf16, d, m, L->ulist, L->n_ulist, L->hs,
                                        mask_rows > 1 ? mask + (size_t)t0 * m : nullptr, m, n, L->partial,
                                        skinny_down_slabs(L->is_bf16, d, m, L->n_cu),
-                                       (char *)y + (size_t)t0 * d * ysize, y_bf16, kStreamPartBytes, s));
+                                       (char *)y + (size_t)t0 * d * ysize, y_bf16, kStreamFfnBytes, s));
         }
         return POP_OK;
     }
     if (mask_rows == 1) POP_HIP(launch_mask_to_list(mask, 1, m, L->ulist, L->n_ulist, s));
-    const bool again = T > L->chunk;  // (every pass reads the same rows)
+    const long long stream_from = T > L->chunk ? kStreamAgainBytes : kStreamFfnBytes;  // (every pass reads the same rows)
     for (int t0 = 0; t0 < T; t0 += L->chunk) {
         const int Bc = (T - t0 < L->chunk) ? T - t0 : L->chunk;
         const unsigned char *mk = mask_rows == 1 ? nullptr : mask + (size_t)t0 * m;
         if (mk) POP_HIP(launch_mask_to_list(mk, Bc, m, L->ulist, L->n_ulist, s));
         const char *xc = (const char *)x + (size_t)t0 * d * L->esize;
         POP_HIP(launch_gateup(L->w, L->is_bf16, d, m, xc, Bc, L->ulist, m, L->n_ulist, L->h, nullptr, nullptr, 0, 0,
-                              L->n_cu, again ? kStreamAgainBytes : (rows_read ? kStreamTwiceBytes : kStreamPartBytes), s));
+                              L->n_cu, stream_from, s));
         POP_HIP(launch_down(L->w, L->is_bf16, d, m, L->ulist, L->n_ulist, 0, L->h, mk, m, Bc, L->partial, L->n_slabs,
-                            (char *)y + (size_t)t0 * d * ysize, y_bf16, again ? kStreamAgainBytes : kStreamPartBytes, s));
+                            (char *)y + (size_t)t0 * d * ysize, y_bf16, stream_from, s));
     }
     return POP_OK;
 }
@@ -631,7 +630,7 @@ int pop_prefill_forward(pop_layer_t *L, const void *x, int T, int n_ret, int n_c
                                    skinny_down_slabs(L->is_bf16, d, m, L->n_cu), y, ydtype == POP_BF16, kStreamPromptBytes, s));
         return POP_OK;
     }
-    return pruned_ffn(L, x, T, L->ffn_any, 1, y, ydtype == POP_BF16, true, s);
+    return pruned_ffn(L, x, T, L->ffn_any, 1, y, ydtype == POP_BF16, s);
 }
 
 // Pass 1 and the selection of a decode step; the results stay in the layer's state.
@@ -778,7 +777,7 @@ int pop_pruned_ffn(pop_layer_t *L, const void *x, int T, const unsigned char *ma
     if (!x || !aligned16(x)) return POP_EINVAL;
     if (T < 1) return POP_ESHAPE;
     if (mask_rows != 1 && mask_rows != T) return POP_ESHAPE;
-    return pruned_ffn(L, x, T, mask, mask_rows, y, y_bf16, false, s);
+    return pruned_ffn(L, x, T, mask, mask_rows, y, y_bf16, s);
 }
 
 int pop_partition_from_scores(const float *scores, int m, int n_ret, int n_cand, unsigned char *region, int *ret_idx,

@@ -781,7 +781,7 @@ static hipError_t launch_dd(const void *w, int d, const int *list, const int *n_
     const size_t lds = DdRing<MF>::kBytes;
     const int n_tt = (T + 64 * MF - 1) / (64 * MF), n_nt = d / kDgBN, per_xcd = (n_tt * n_nt * n_split + 7) / 8;
     // (ldh: the layer's channels rounded up to 64)
-    const bool stream = n_tt == 1 && stream_rows(d, ldh, 1, kStreamPartBytes);
+    const bool stream = n_tt == 1 && stream_rows(d, ldh, 1, kStreamFfnBytes);
     const auto kernel = stream ? down_gemm_stream_kernel<MF> : down_gemm_dma_kernel<MF>;
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
                                        (int)lds);

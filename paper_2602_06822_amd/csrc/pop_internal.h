@@ -50,19 +50,20 @@ __host__ __device__ __forceinline__ constexpr int channel_gap(int nvec, int is_b
 // them there.  A plain read of rows from memory: 5.7-6.0 TB/s with ordinary loads, 6.4 with these; but what they read does not stay in
 // the 256 MB last-level cache, so where it would have been there for the next pass they lose.  A call cannot know what runs before
 // the next one on its layer: the rule is the size of the layer's weights (3 d m, bf16), drawn where no call was slower
-// with several layers in turn.  Time of a call past the caches over its time with ordinary loads:
-//   decode steps, six layers in turn: of 50 MB 1.02-1.08, of 67 MB .97-.98, of 94 MB .94-.98, of 157 MB .93-.95, of 270 MB .90-.93
-//   a prompt's own forward pass (all of gate and up, most of down), three layers: of 86 MB 1.02-1.08 (4 to 40 tokens), of 113 MB
-//   .97-.99, of 138 MB .97, of 270 MB .92-.94
-//   a stand-alone FFN (two thirds of the layer), three layers: of 67 MB 1.04-1.14 (1 to 40 tokens), of 138 MB .99-1.03, of 157 MB .96-1.00, of
-//   270 MB .90-.97; a prompt's partition the same (gate and up: of 138 MB 1.07 at 40 tokens, of 157 MB .92); the FFN's matrix-core contraction
-//   over the list from 192 MB on
+// with several layers in turn and half of their channels active.  Time of a call past the caches over its time with ordinary loads:
+//   decode steps, six layers: of 50 MB 1.02-1.11 (half of the channels active; .65 of them 1.02-1.08), of 68 MB 1.01-1.07 (.97-.98), of 79 MB
+//   .98-1.01, of 86 MB .98-1.00 (.93-.97), of 113 MB .94-.97, of 270 MB .90-.93; twelve layers: of 50 MB .96-.98, of 86 MB .92-.94
+//   a prompt's own forward pass (all of gate and up), three layers, 4 to 60 tokens: of 94 MB 1.00-1.08, of 113 MB .98-1.00, of 138 MB
+//   .96-.98, of 270 MB .92-.94
+//   a prompt's partition (gate and up alone), three layers, 40 tokens: of 138 MB 1.07, of 157 MB .92
+//   a stand-alone FFN (what is active of the layer), three layers, 1 to 40 tokens: of 157 MB 1.01-1.04 (.65 active .96-1.00), of 201 MB 1.00-1.02
+//   (.93-.98), of 226 MB .96-1.02, of 251 MB .93-1.00, of 270 MB .92-.98 (.90-.97); three tenths active, of 270 MB still 1.04
 // Rows that the same call asks for again stay in the cache, as long as it holds them: gate and up rows that scores of the
 // input-side reading come from and the prompt's forward pass reads after them (three layers, 40 tokens: of 138 MB 1.05, of 201 MB 1.02-1.07, of
-// 270 MB .98-.99), and the rows of an FFN that takes its tokens in several passes, two thirds of a layer in each (24 tokens: of 74 MB 1.08, of
-// 197 MB 1.03-1.04, of 271 MB 1.02-1.04).
-constexpr long long kStreamStepBytes = 64ll << 20, kStreamPromptBytes = 128ll << 20, kStreamPartBytes = 144ll << 20;
-constexpr long long kStreamListBytes = 192ll << 20, kStreamTwiceBytes = 240ll << 20, kStreamAgainBytes = 384ll << 20;
+// 270 MB .98-.99), and the rows of an FFN that takes its tokens in several passes (24 tokens: of 74 MB 1.08, of 197 MB 1.03-1.04, of 271 MB
+// 1.02-1.04).
+constexpr long long kStreamStepBytes = 80ll << 20, kStreamPromptBytes = 128ll << 20, kStreamPartBytes = 144ll << 20;
+constexpr long long kStreamFfnBytes = 240ll << 20, kStreamTwiceBytes = 240ll << 20, kStreamAgainBytes = 384ll << 20;
 inline bool stream_rows(int d, int m, int is_bf16, long long limit) { return is_bf16 && 6ll * d * m >= limit; }
 
 // From one channel's weights to the next's.

@@ -738,8 +738,7 @@ __device__ __forceinline__ void pm_tile(const uint16_t *__restrict__ w, const ui
 // asked for is gone when the first tile comes to it, a read of every row from memory by each.  13B shape (two tiles a compute unit),
 // partition, three layers, 70 tokens 242 / 311 us, 85 278 / 306, 100 289 / 295, 115 298 / 294; d 8192, m 28672, two layers, 70 tokens 464 / 632, 115
 // 514 / 493; 7B shape (one), 70 tokens 157 / 168, 85 164 / 169, 100 182 / 171.
-// A list of channels reads part of the layer only: one token tile, and layers of 192 MB (100 tokens, half of d 4096, m 5504: 42.0 without /
-// 42.8 with; two tiles, 333 tokens at the 13B shape 107.6 / 108.3).
+// A list of channels: one token tile (two, 333 tokens at the 13B shape: 107.6 without / 108.3 with).
 template <int MF, int kMode>
 inline bool pm_streams(int d, int m, int T, bool one_each, long long stream_from)
 {

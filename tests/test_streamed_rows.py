@@ -56,7 +56,8 @@ def _hidden(x, wg, wu):
 # (d, channels of the smaller layer, what runs, rows of x): the larger layer has the first size that streams
 CASES = ([(2048, 5461, "step", b) for b in (1, 2, 3, 8)] +
          [(4096, 5461, "forward", t) for t in (24, 40, 300, 400)] + [(4096, 5461, "input_side", 40)] + [(4096, 10239, "forward", t) for t in (128, 512)] +
-         [(4096, 8191, "ffn", t) for t in (12, 40)] + [(4096, 6143, "ffn", t) for t in (2, 12, 40)])
+         [(4096, 8191, "ffn", t) for t in (12, 40)] + [(4096, 10239, "ffn", t) for t in (2, 12, 40)] +
+         [(2048, 6826, "step", b) for b in (1, 2, 3, 8)])
 
 
 @pytest.mark.gpu
