@@ -264,7 +264,7 @@ int pop_layer_step_kind(pop_layer_t *layer, int *workgroups);
 /* ---- measurement aids: bare reads of device memory (they compute nothing of the method) ----
  * The decode step (Sec. 3.3 "Decoding Stage", Sec. 3.4) is bound by the bytes it must stream; these two calls request
  * such bytes and nothing else, so that timing them (events on `stream`) gives the time the memory system itself needs:
- * the yardstick next to the published peak bandwidth.  sink: dev, one unsigned int the kernels may OR a bit into.
+ * the yardstick next to the published peak bandwidth.  They load as a decode step of a layer that size does.  sink: dev, one unsigned int the kernels may OR a bit into.
  *   pop_probe_read       contiguous read of `bytes` (rounded down to 16) of buf (dev, 16-byte aligned).
  *   pop_probe_step_read  the weight rows one decode step of the layer's current partition reads: gate and up rows of
  *                        all retained and candidate channels, down rows of the retained channels and of the first k

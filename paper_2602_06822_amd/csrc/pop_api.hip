@@ -869,7 +869,7 @@ int pop_probe_step_read(pop_layer_t *L, int k, int workgroups, unsigned int *sin
     if (k < 0 || k > L->n_cand || workgroups < 1 || workgroups > 65535) return POP_ESHAPE;
     if (L->n_ret + L->n_cand == 0) return POP_OK;
     POP_HIP(launch_probe_step_read(L->w, L->d / (L->is_bf16 ? 8 : 4), channel_vectors(L->d / (L->is_bf16 ? 8 : 4), L->is_bf16), L->rc_idx, L->n_ret + L->n_cand, L->ret_idx,
-                                   L->n_ret, L->cand_idx, k, workgroups, sink, as_stream(stream)));
+                                   L->n_ret, L->cand_idx, k, workgroups, sink, stream_rows(L->d, L->m, L->is_bf16, kStreamStepBytes), as_stream(stream)));
     return POP_OK;
 }
 

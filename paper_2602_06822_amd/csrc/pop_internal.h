@@ -293,7 +293,7 @@ hipError_t launch_fill_int(int *p, int n, int value, hipStream_t s);
 hipError_t launch_probe_read(const void *buf, size_t bytes, int workgroups, unsigned int *sink, hipStream_t s);
 hipError_t launch_probe_step_read(const void *w, int nvec, int chan, const int *gu_list, int n_gu, const int *dn_ret,
                                   int n_dn_ret, const int *dn_sel, int n_dn_sel, int workgroups, unsigned int *sink,
-                                  hipStream_t s);
+                                  bool stream, hipStream_t s);
 
 // ---- prefill (pop_prefill.hip) ----
 // s2_part[tile][j] = sum over the tile's tokens of H[t][j]^2, one row per token tile.

@@ -42,7 +42,7 @@ def _kernels(call):
 
 
 _PAST = re.compile(r"StreamBF16|prefill_stream_kernel|down_gemm_stream_kernel|(prefill|down_gemm)_rows_kernelILi\dELb1E")
-_ROWS = re.compile(r"decode_fused_kernel|gateup\w*_kernel|skinny_\w+_kernel|down_kernel|down_gemm_\w*(rows|dma|stream|bf16)_kernel|"
+_ROWS = re.compile(r"probe_(step_)?read_kernel|decode_fused_kernel|gateup\w*_kernel|skinny_\w+_kernel|down_kernel|down_gemm_\w*(rows|dma|stream|bf16)_kernel|"
                    r"prefill_(mma|deep|stream|rows|bf16)_kernel|input_side_scores_kernel")
 
 
@@ -152,3 +152,15 @@ def test_input_side_partition(layer, want):
     pop, h, m, x, y = layer
     pop.pop_layer_set_importance(h, pop.POP_IMPORTANCE_INPUT_SIDE)
     assert _past_the_caches(lambda s: pop.pop_prefill_partition(h, x[:100], 100, m // 2, m // 8, stream=s)) == [want]
+
+
+# The bare reads that a step is held against load as the step does
+@pytest.mark.gpu
+@pytest.mark.parametrize("layer,past", [((2048, 6826), False), ((2048, 6827), True)], indirect=["layer"])
+def test_probe_reads(layer, past):
+    pop, h, m, x, y = layer
+    sink = torch.zeros(1, dtype=torch.int32, device="cuda")
+    pop.pop_prefill_partition(h, x[:64], 64, m // 2, m // 8)
+    assert _past_the_caches(lambda s: pop.pop_probe_step_read(h, m // 16, 256, sink, stream=s)) == [past]
+    buf = torch.zeros(6 * 2048 * m, dtype=torch.uint8, device="cuda")
+    assert _past_the_caches(lambda s: pop.pop_probe_read(buf, buf.numel(), 256, sink, stream=s)) == [past]
