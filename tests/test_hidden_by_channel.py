@@ -6,7 +6,7 @@ import pytest
 import torch
 
 from test_asm_waits import counted_waits, loads_in_flight, most_left_in_flight, product_hazards
-from test_streamed_rows import BF16, F32, _hidden, _listing, needs_hipcc
+from test_streamed_rows import BF16, F32, _functions, _hidden, _listing, needs_hipcc
 
 
 @needs_hipcc
@@ -32,6 +32,28 @@ def test_waits_of_the_row_kernels(tmp_path):
             f = products // (2 * mf)
             na, nb = (3, 3) if mf == 4 and f <= 8 else (2 if mf >= 4 else (3 if mf >= 2 else 4), 3 if mf >= 3 else (4 if mf == 2 else 5))
             assert (before, after, left) == ((f + 1) // 2, 2 * mf, most_left_in_flight(na, nb, 2 * mf, (f + 1) // 2, False))
+
+
+def _m0_of_the_compiler(lines):
+    """Instructions outside inline assembly that name m0."""
+    inside, found = False, []
+    for line in lines:
+        if "ASMSTART" in line or "ASMEND" in line:
+            inside = "ASMSTART" in line
+        elif not inside and re.search(r"\bm0\b", line.split(";")[0]):
+            found.append(line.strip())
+    return found
+
+
+@needs_hipcc
+def test_row_kernels_have_m0_to_themselves():
+    """Their direct loads set m0 in inline assembly, which cannot tell the compiler so: it must have no use for it of its own."""
+    assert _m0_of_the_compiler(["\ts_mov_b32 m0, s3", ";ASMSTART", "\ts_mov_b32 m0, s4", ";ASMEND"]) == ["s_mov_b32 m0, s3"]
+    found = _functions("pop_down_gemm.hip", "down_gemm_rows_kernel")
+    assert len(found) == 10
+    for name, lines in found.items():
+        assert any("ASMSTART" in x for x in lines) and sum("m0" in x for x in lines) > 20, name
+        assert not _m0_of_the_compiler(lines), name
 
 
 # (d, m, active channels, prompts run one after the other on one layer: a longer one leaves its rows behind)

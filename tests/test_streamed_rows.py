@@ -1,9 +1,11 @@
 """Weight rows of large bf16 layers are loaded past the caches.  The rule is the size of the layer, so a layer just above it
 is the layer just below it plus one channel of zeros, which no score, selection or output may notice; against plain float64."""
+import functools
 import os
 import re
 import shutil
 import subprocess
+import tempfile
 
 import pytest
 import torch
@@ -14,13 +16,25 @@ BF16, F32 = 1, 0
 needs_hipcc = pytest.mark.skipif(shutil.which("hipcc") is None, reason="needs hipcc")
 
 
+@functools.lru_cache(maxsize=None)
+def _assembly(src):
+    with tempfile.TemporaryDirectory() as tmp:
+        out = os.path.join(tmp, src + ".s")
+        subprocess.run(["hipcc", "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Xclang", "-target-feature", "-Xclang",
+                        "-packed-fp32-ops", "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-S", "--cuda-device-only",
+                        os.path.join(CSRC, src), "-o", out], check=True, capture_output=True, timeout=900)
+        with open(out) as text:
+            return text.read()
+
+
+def _functions(src, kernel):
+    """Lines of every instantiation of a kernel."""
+    return {m.group(1): m.group(2).split("\n")[1:] for m in
+            re.finditer(r"^(_ZN3pop\d+" + kernel + r"I\w+):(.*?)^\.Lfunc_end", _assembly(src), re.M | re.S)}
+
+
 def _listing(tmp_path, src, kernel):
-    out = tmp_path / (src + ".s")
-    subprocess.run(["hipcc", "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Xclang", "-target-feature", "-Xclang",
-                    "-packed-fp32-ops", "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-S", "--cuda-device-only",
-                    os.path.join(CSRC, src), "-o", str(out)], check=True, capture_output=True, timeout=900)
-    return {m.group(1): parse(m.group(2).split("\n")[1:]) for m in
-            re.finditer(r"^(_ZN3pop\d+" + kernel + r"I\w+):(.*?)^\.Lfunc_end", out.read_text(), re.M | re.S)}
+    return {name: parse(lines) for name, lines in _functions(src, kernel).items()}
 
 
 @needs_hipcc
