@@ -241,7 +241,7 @@ def run(args):
         single = timed(r_main, max(1, args.steps // 2), 1)["decode_us_per_token"]
 
     # the prefilling stage with its output (pop_prefill_forward: contraction that keeps H, partition, prefill mask,
-    # gathered columns, down-projection GEMM over the active channels), rotated over the layers
+    # down-projection GEMM over the active channels), rotated over the layers
     forward = None
     if not args.quick or args.forward:
         yp = torch.empty((PROMPT, d), dtype=torch.int16, device="cuda")
@@ -262,7 +262,7 @@ def run(args):
         f_flop = 4.0 * PROMPT * m * d + 2.0 * PROMPT * (n_ret + k) * d
         forward = dict(us_per_layer=round(f_us, 2), flop=f_flop, TFLOPs=round(f_flop / f_us / 1e6, 1),
                        frac_of_bf16_mfma_peak=round(f_flop / f_us / 1e6 / 2500.0, 4),
-                       note="whole call: both GEMMs, partition, mask, gather and the small kernels between them")
+                       note="whole call: both GEMMs, partition, mask and the small kernels between them")
         del yp
 
     # configs[2]: a 32-layer stack of this layer shape, one token through all layers (each layer its own weights,

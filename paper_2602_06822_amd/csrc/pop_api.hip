@@ -87,7 +87,7 @@ struct pop_layer {
     // whole-prompt pruned FFN on the matrix cores (bf16 layers), allocated at its first use
     uint16_t *ffn_hc = nullptr;        // [tokens][ldh] bf16: H of the active channels, compact
     size_t ffn_hc_cap = 0;             // elements
-    uint16_t *ffn_hall = nullptr;      // [tokens][ldh] bf16: H of all channels, kept by pop_prefill_forward
+    uint16_t *ffn_hall = nullptr;      // [m][tokens, in 64s] or [tokens][ldh] bf16: H of all channels, kept by pop_prefill_forward
     size_t ffn_hall_cap = 0;           // elements
     float *ffn_part = nullptr;         // [splits][tokens][d]: partial outputs of the split contraction
     size_t ffn_part_cap = 0;           // elements
@@ -96,7 +96,7 @@ struct pop_layer {
     // pruned FFN of a few tokens
     int chunk = 0;                     // tokens the decode kernels take at a time
     float *hs = nullptr;               // [precise_max_tokens][m] float32
-    uint16_t *zero_row = nullptr;      // 256 bytes of zeros: stands in for weight rows beyond a channel list
+    uint16_t *zero_row = nullptr;      // kZeroRowBytes of zeros: stands in for rows beyond a channel list
 };
 
 namespace {
@@ -131,10 +131,11 @@ StepCopy step_copy(const pop_layer *L, int B, float *cand_scores, unsigned char 
 constexpr int kFfnMfmaMinTokens = 32;
 
 // A stand-alone FFN of a few tokens: one pass of the decode kernels over a list where T fits one and T x m is below this, else
-// the pass whose time hardly grows with T (bf16 / float32 matrix cores).  Whole call, decode / other, shared mask: 7B shape
-// (m 11008) 2 tokens 42.8 / 49.0 us, 5 tokens 46.5 / 48.3, 6 tokens 49.3 / 48.5, 8 tokens 53.9 / 48.7; d 2048, m 14336, 4
-// tokens 38.5 / 40.4, 5 tokens 40.6 / 40.3; d 2048, m 5632, 8 tokens 27.5 / 28.7; float32 d 2048, m 5632, 2 tokens 28.1 / 33.4,
-// 8 tokens 34.9 / 33.2.
+// the pass whose time hardly grows with T (bf16 / float32 matrix cores).  Whole call, layers in turn, decode / other, shared mask: 7B shape
+// (m 11008) 2 tokens 41.5 / 45.2 us, 5 tokens 45.7 / 45.9, 6 tokens 48.3 / 46.4, 8 tokens 50.8 / 46.7; d 2048, m 5632, 6 tokens 24.2 / 25.8, 8 tokens
+// 26.3 / 26.0; float32 d 2048, m 5632, 4 tokens 28.9 / 30.6, 8 tokens 32.0 / 31.0.  The line fits these; since waves see to their own channels in
+// the other pass it lies too high by up to a half elsewhere (d 2048, m 14336, 3 tokens 37.1 / 36.1, 4 tokens 38.3 / 36.8; 13B shape, 3 tokens
+// 63.6 / 62.8, 4 tokens 65.7 / 63.1; d 1024, m 4000, 5 tokens 18.9 / 18.7, 8 tokens 21.3 / 18.7).
 constexpr int kFewTokenChannels = 60000;
 
 // Per-token masks of up to this many bytes become a list in one launch; larger ones are combined by the whole chip first, two
@@ -142,11 +143,12 @@ constexpr int kFewTokenChannels = 60000;
 constexpr int kMaskListBytes = 24576;
 
 // From this many sequences on a bf16 layer's batched step takes the matrix cores for its down projection: the vector
-// kernel's multiply-adds grow with the batch, the matrix-core kernel's time does not.  Whole step, vector / matrix, weights
-// from memory: d 1024, m 2816: 3 sequences 24.9 / 21.8 us; d 4104, m 5000: 3 sequences 41.3 / 39.9; 7B shape: 3 sequences at
-// sparsity .35 52.7 / 51.4 and at .5 50.0 / 50.7, 4 sequences 54.4 / 52.4 and 52.5 / 51.8; 13B shape: 3 sequences 73.1 / 74.4
-// and 66.5 / 65.8, 4 sequences 74.7 / 73.9 and 68.3 / 67.4, 8 84.6 / 79.3; d 8192, m 28672, .35: 3 sequences 184.8 / 191.3, 5
-// 198.7 / 201.8, 8 229.0 / 224.5.
+// kernel's multiply-adds grow with the batch, the matrix-core kernel's time does not.  The line was drawn for a matrix-core kernel whose
+// workgroups staged h, which was behind below it (7B shape, 3 sequences 50.0 / 50.7 us; 13B 73.1 / 74.4; d 8192, m 28672, 5 sequences
+// 198.7 / 201.8).  Whole step, vector / matrix, weights from memory, with the waves on their own: d 1024, m 2816, 2 sequences 21.1 / 18.3, 3
+// 22.5 / 19.0; d 4104, m 5000, 2 36.2 / 33.8; 7B shape at sparsity .35 2 43.6 / 42.3, 3 45.6 / 43.5, 4 47.4 / 44.9, at .5 2 41.0 / 37.9, 3 41.3 / 38.6; 13B
+// shape 2 63.8 / 61.7 and 49.9 / 48.8, 3 66.6 / 63.5 and 52.3 / 50.3, 4 69.0 / 65.9 and 55.4 / 52.2, 8 82.6 / 77.9; d 8192, m 28672 2 163.5 / 162.8, 3 167.7 /
+// 168.3, 5 180.3 / 181.3, 8 207.7 / 206.5.  So it lies too high by now on all but the largest layers.
 int skinny_min_batch(int d, int m)
 {
     const long long weights = (long long)d * m;
@@ -175,7 +177,8 @@ int grow(void **p, size_t *cap, size_t need, size_t esize)
 }
 
 // Scratch of the prompt-sized forward pass for T tokens: compact H, split partials, the byte mask; with keep_all
-// also H of all channels.  Returns the row stride of the H buffers and the number of contraction splits.
+// also H of all channels.  (A forward pass with H by channel does not read compact H; a pruned FFN of as many tokens after it, captured
+// in a graph perhaps, finds its scratch there.)  Returns the row stride of the H buffers and the number of contraction splits.
 int ffn_scratch(pop_layer *L, int T, bool keep_all, int *ldh, int *n_split, hipStream_t s, bool shorter_too = false)
 {
     // rows are whole 64-channel k-steps long: the direct-load GEMM reads the columns between a list's end and the end

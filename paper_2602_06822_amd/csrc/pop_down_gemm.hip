@@ -226,8 +226,8 @@ __global__ __launch_bounds__(512) void down_gemm_bf16_kernel(const uint16_t *__r
 // pointed at a row of zeros (zero_row, 256 bytes), which makes it irrelevant what the Hc columns beyond a hold, as long as
 // it is finite (the buffer is cleared when it is allocated and only ever holds H values).  Needs d % 128 == 0 and
 // ldh >= a rounded up to 64.
-// What bounds it: the loads into LDS, which deliver 30 bytes a cycle and compute unit at any depth (measured with nothing else running):
-// the 48 KB of a k-step at MF = 4 are 1650 cycles of the 2060 it takes at 2048 tokens, its products 1024.  Without the
+// What bounds it: no one thing.  The 48 KB of a k-step's loads at MF = 4 and its 96 KB of fragment reads take the LDS 1430 cycles (850 for
+// the loads alone, 58 bytes a cycle from the L2; the two do not overlap) of the 2060 it takes at 2048 tokens, its products 1024.  Without the
 // products 2048 tokens take 94 us of 133, 333 tokens at the 13B shape 31 of 42, an expert's 256 tokens 30 of 32; with the channel
 // numbers counted up instead of read, or all rows from 64 channels, at most 2 us less in any of them.
 // With one wave per SIMD, whatever does not fit between two products (12 cycles) comes on top, so the permutes of a fragment

@@ -58,6 +58,7 @@ __host__ __device__ __forceinline__ constexpr int channel_gap(int nvec, int is_b
 //   a prompt's partition (gate and up alone), three layers, 40 tokens: of 138 MB 1.07, of 157 MB .92
 //   a stand-alone FFN (what is active of the layer), three layers, 1 to 40 tokens: of 157 MB 1.01-1.04 (.65 active .96-1.00), of 201 MB 1.00-1.02
 //   (.93-.98), of 226 MB .96-1.02, of 251 MB .93-1.00, of 270 MB .92-.98 (.90-.97); three tenths active, of 270 MB still 1.04
+// A layer run by itself, all of what a step reads in that cache, is slower: 7B shape 33.4 / 34.2 us, eight sequences 46.4 / 49.7, 13B shape, two 60.0 / 63.2.
 // Rows that the same call asks for again stay in the cache, as long as it holds them: gate and up rows that scores of the
 // input-side reading come from and the prompt's forward pass reads after them (three layers, 40 tokens: of 138 MB 1.05, of 201 MB 1.02-1.07, of
 // 270 MB .98-.99), and the rows of an FFN that takes its tokens in several passes (24 tokens: of 74 MB 1.08, of 197 MB 1.03-1.04, of 271 MB

@@ -414,10 +414,11 @@ __host__ __device__ inline PmTiles pm_tiles(int n_ch, int n_tt, int mf, int n_cu
     return best;
 }
 
-// Bound by the loads into LDS, the matrix pipe and the chip's power together.  Direct loads deliver 30 bytes a cycle and compute unit
-// at any depth (70 bytes/ns at 2.4 GHz, nothing else running): the 54 KB of a k-step at MF = 4, F = 11 are 1850 cycles of the 2040
-// it takes, its products 1390 (512 tokens: pipe busy for 68 % of the waves' time), and with the pipe that busy the clock
-// falls to about 2.0 GHz: without its products the launch takes 51 instead of 77 us, 2048 tokens 231 instead of 309.  An expert's
+// Bound by the LDS, the matrix pipe and the chip's power together.  Direct loads of lines that the L2 holds deliver 58 bytes a cycle and
+// compute unit (135 bytes/ns, nothing else running, any depth from 8 loads a wave on), but fragment reads, 128 bytes a cycle, do not overlap with
+// them: 48 KB of loads take 850 cycles, with 96 KB of reads 1430, with 120 KB 1750.  So the 54 KB and 120 KB of a k-step at MF = 4, F = 11 are about
+// 1850 cycles of the LDS next to 1390 of products, of the 2040 it takes (512 tokens: pipe busy for 61-68 % of the waves' time), and with the pipe that busy
+// the clock falls to about 2.0 GHz: without its products the launch takes 51 instead of 77 us, 2048 tokens 231 instead of 309.  An expert's
 // 256 tokens (F 7) leave the pipe idle for two thirds of the time, the clock near 2.4 GHz, and take as long without products (71
 // of 72 us: weights from memory).  So what counts is work per byte loaded and per product: 16x16x32 products move fewer accumulator bytes per flop than 32x32x16 ones (7 % faster here at
 // equal cycles), a wave keeps all 16 F rows against its 16 MF tokens (MF + F fragment reads of 1 KB for MF * F products
@@ -447,7 +448,8 @@ __device__ __forceinline__ void pm_tile(const uint16_t *__restrict__ w, const ui
     constexpr int NA = Ring::NA, NB = Ring::NB;
     constexpr bool kList = kMode == 1 || kMode == 4, kPrecise = kMode == 3 || kMode == 4, kRows = kMode == 5;
     // An odd F leaves 16 rows for the last pass: half a request of each wave (without: two waves' whole ones, and the other two ask for
-    // rows again that are there, 2 KB of the 48 to 56 of a k-step.  With: eight experts 1015 -> 1005 us; 512 and 24 tokens the same).
+    // rows again that are there, 2 KB of the 48 to 56 of a k-step.  With: eight experts 1015 -> 1005 us; 512 and 24 tokens the same).  Not in the
+    // kernels with ordinary loads that store no H by channel: twelve partitions and FFNs with F of 7 and 11 between 1 % faster and 1 % slower.
     constexpr bool kHalf = (kStream || kRows) && F % 2;
     constexpr int BM = 64 * MF, BC = 8 * F;             // tokens and channels of the tile
     constexpr int PA = BM / 32, PB = (F + 1) / 2;       // direct loads per wave and k-step (32 rows a pass)
