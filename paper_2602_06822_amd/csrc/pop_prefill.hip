@@ -735,17 +735,18 @@ __device__ __forceinline__ void pm_tile(const uint16_t *__restrict__ w, const ui
 // two token tiles per chunk, which ask for a row at the same time (2048 tokens no change); with the narrow chunks' deeper ring where it is
 // used.  512 tokens, d 4096, m 11008, in turn on one card: 87.8 -> 84.4 us.  Two tiles from 240 MB of weights on; three layers in turn, past
 // the caches over ordinary, 128 and 256 tokens: partition, of 138 MB 1.08 and 1.04, of 157 MB 1.01, of 201 MB .96 and .97; forward pass .95-.98;
-// but 200 tokens 1.15, 1.14, 1.02, of 226 MB 1.05, of 251 MB .98, and forward 1.02-1.05 up to 226 MB.  The second tile has to be three quarters
-// full, half where a compute unit runs one tile: one with few tokens of its own has its other rows from the cache, runs ahead, and what it
-// asked for is gone when the first tile comes to it, a read of every row from memory by each.  13B shape (two tiles a compute unit),
-// partition, three layers, 70 tokens 242 / 311 us, 85 278 / 306, 100 289 / 295, 115 298 / 294; d 8192, m 28672, two layers, 70 tokens 464 / 632, 115
-// 514 / 493; 7B shape (one), 70 tokens 157 / 168, 85 164 / 169, 100 182 / 171.
+// but 200 tokens 1.15, 1.14, 1.02, of 226 MB 1.05, of 251 MB .98, and forward 1.02-1.05 up to 226 MB.  The second tile has to be seven eighths
+// full, half on rows of up to 8 KB where a compute unit runs one tile: one with few tokens of its own has its other rows from the cache, runs
+// ahead, the further the longer the rows, and what it asked for is gone when the first tile comes to it, a read of every row from memory by each.
+// Partition, us of three or two layers, by how full the second tile is: 13B shape (two tiles a compute unit) .09 242 / 311, .33 278 / 306, .56 289 / 295,
+// .80 298 / 294; d 8192, m 28672 .09 464 / 632; one tile a compute unit, 7B shape .09 157 / 168, .33 164 / 169, .56 182 / 171; d 6144, m 8192 .56 156 /
+// 161, .75 161 / 161, .88 166 / 162; d 12288, m 6000 .56 218 / 255, .75 230 / 246, .88 235 / 237, 1.0 241 / 239.
 // A list of channels: one token tile (two, 333 tokens at the 13B shape: 107.6 without / 108.3 with).
 template <int MF, int kMode>
 inline bool pm_streams(int d, int m, int T, bool one_each, long long stream_from)
 {
     if (T <= 64 * MF) return stream_rows(d, m, 1, stream_from);
-    if (kMode == 1 || kMode == 4 || T > 128 * MF || T < (one_each ? 96 : 112) * MF) return false;
+    if (kMode == 1 || kMode == 4 || T > 128 * MF || T < (one_each && d <= 4096 ? 96 : 120) * MF) return false;
     return stream_rows(d, m, 1, stream_from < kStreamTwiceBytes ? kStreamTwiceBytes : stream_from);
 }
 constexpr bool pm_deep(int mf, int f, int mode) { return mf == kPmDeepMF && f <= kPmDeepF && (mode == 0 || mode == 2 || mode == 5); }

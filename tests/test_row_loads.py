@@ -131,9 +131,9 @@ def test_rows_read_again(layer, past, T):
 @pytest.mark.parametrize("layer,T,want", [
     ((3200, 7200), 16, True), ((3200, 7200), 40, False), ((4096, 6400), 40, True), ((4096, 6400), 128, False),
     ((4096, 8192), 240, False), ((4096, 10240), 240, True), ((4096, 10240), 1024, False),
-    # (the second tile three quarters full, half where a compute unit runs one tile)
-    ((5120, 13824), 64, True), ((5120, 13824), 65, False), ((5120, 13824), 111, False), ((5120, 13824), 112, True),
-    ((4096, 10240), 95, False), ((4096, 10240), 96, True), ((4096, 10240), 160, False)], indirect=["layer"])
+    # (the second tile seven eighths full, half on rows of up to 8 KB where a compute unit runs one tile)
+    ((5120, 13824), 64, True), ((5120, 13824), 65, False), ((5120, 13824), 119, False), ((5120, 13824), 120, True),
+    ((6144, 8192), 224, False), ((6144, 8192), 240, True), ((4096, 10240), 95, False), ((4096, 10240), 96, True), ((4096, 10240), 160, False)], indirect=["layer"])
 def test_prompt(layer, T, want):
     pop, h, m, x, y = layer
     x = torch.zeros((T, x.shape[1]), dtype=torch.bfloat16, device="cuda")
